@@ -75,3 +75,27 @@ def test_quantized_layer_runs_through_the_forward_pass():
     Y, _ = b.modulora_fwd(qw, Xd, None, None, 0.0)
     Yr, _ = oracle.fwd(q_ref, s_ref, z_ref, K, N, bits, group, X, None, None, 0.0)
     assert_bar("Y", f64(Y), Yr)
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+@pytest.mark.parametrize("K,N,group", [(32, 8, 32), (160, 72, 32), (192, 64, 64), (384, 136, 128), (256, 8, 256),
+                                       (768, 200, 256)])
+def test_one_pass_kernel_at_tile_edges_and_ties(bits, K, N, group):
+    """The one-pass kernel (groups of 32 .. 256) where its 64-row and 128- / 256-input tiles end
+    inside the matrix, on weights that make its shortcut around the division decide: quotients
+    that are exact half-integers, and their float32 neighbours on either side."""
+    rng = np.random.default_rng(100 * bits + K)
+    W = weight(N, K, seed=bits + K)
+    maxq = (1 << bits) - 1
+    half = rng.integers(0, 2 * maxq + 1, size=(N, K)).astype(np.float32) / 2 - maxq // 2
+    half.reshape(N, K // group, group)[:, :, :2] = [-(maxq // 2), maxq - maxq // 2]     # the whole range: scale = 2^-5
+    ties = (half * np.float32(2.0 ** -5)).astype(np.float32)
+    nudge = rng.integers(-1, 2, size=(N, K))
+    ties = np.where(nudge < 0, np.nextafter(ties, np.float32(-9)), np.where(nudge > 0, np.nextafter(ties, np.float32(9)), ties))
+    ties.reshape(N, K // group, group)[:, :, :2] = np.float32(2.0 ** -5) * np.array([-(maxq // 2), maxq - maxq // 2], np.float32)
+    W[N // 2:] = ties[N // 2:]
+    qw = b.modulora_quantize_rtn(torch.from_numpy(W).cuda(), bits, group)
+    q_ref, s_ref, z_ref = rtn.quantize_packed(W, bits, group)
+    assert np.array_equal(qw.scales.cpu().numpy().view(np.uint16), s_ref)
+    assert np.array_equal(qw.zeros.cpu().numpy(), z_ref)
+    assert np.array_equal(qw.qweight.cpu().numpy().view(np.uint32), q_ref)
