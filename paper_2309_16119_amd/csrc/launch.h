@@ -195,7 +195,7 @@ inline size_t lora_down_partial_bytes(int M, int K, int N, int r) {
 hipError_t launch_lora_down(const DownArgs &a, hipStream_t stream);
 
 // dA[k][j] (+)= lora_scale * sum_m X[m][k] dYBt[m][j]   and
-// dB[j][n] (+)= lora_scale * sum_m XA[m][j] dY[m][n],  in two launches (partials, reduce).
+// dB[j][n] (+)= lora_scale * sum_m XA[m][j] dY[m][n]  (a second launch adds row chunks, if any).
 struct GradPairArgs {
     const uint16_t *X, *dY;      // bf16 [M][K], [M][N]
     int M, K, N, r;              // r >= 1
@@ -207,10 +207,11 @@ struct GradPairArgs {
     int f16;                     // X, dY are binary16 instead of bfloat16 (the paper-literal path)
 };
 struct GradGeom {
-    int cpl;                     // columns per lane (2 or 4)
-    int cols_a, cols_b;          // column blocks (64 * cpl columns) of X and of dY
+    int rg;                      // groups of 16 adapter columns
+    int cpl;                     // columns per lane (4 or 8)
+    int cols_a, cols_b;          // column blocks (16 * cpl columns) of X and of dY
     int chunks, rows_per_block;  // row chunks (one partial each)
-    int passes;                  // rank passes of 32 (r > 32)
+    int nwaves;                  // waves per workgroup, which divide the rows of a chunk
     size_t partial_floats;
 };
 GradGeom grad_geom(int M, int K, int N, int r);

@@ -4,9 +4,8 @@
 // "extended contraction" operands with which the tile GEMM adds the adapter term
 // s (X A) B inside its MFMA loop.
 //
-// All of these are bound by one streaming pass over X or dY.  The projections run on the
-// matrix cores (the fp32 factor split into three bfloat16 terms); the gradients are plain
-// fp32 FMA with coalesced 4-byte loads per lane.
+// All of these are bound by one streaming pass over X or dY, and all run on the matrix cores, the
+// fp32 operand (the factor, or P) split exactly into three bfloat16 terms.
 #include "device_common.h"
 #include "launch.h"
 
@@ -274,178 +273,217 @@ hipError_t launch_lora_down(const DownArgs &a, hipStream_t stream) {
 }
 
 // ---------------------------------------------------------------------------
-// Adapter gradients (Section 3.1.1), both in one launch plus one reduction launch:
+// Adapter gradients (Section 3.1.1), both in one launch:
 //   dA[k][j] = s * sum_m X[m][k]  dYBt[m][j]      dB[j][n] = s * sum_m XA[m][j] dY[m][n]
-// Stage 1: a workgroup owns 128 or 256 columns of X (or dY) and a chunk of rows; each lane owns 2
-// or 4 adjacent columns (one 4- or 8-byte load per row), the 4 waves take rows round-robin, P[m][:] is
-// wave-uniform.  The 4 waves' sums meet in LDS and go out as one partial per row chunk, laid
-// out like the outputs ([chunk][dA | dB]).  Stage 2 adds the chunks, applies s and the
-// accumulate flag.  No atomics (device-scope fp32 atomics bypass the per-XCD L2 and are slow)
-// and no zero-fill of the outputs.
+// on the matrix cores: per 32 rows, P^T (16 adapter columns x 32 rows; P = dYBt or XA, its fp32
+// values split exactly into three bfloat16 parts) times a 32-row block of X or dY.
+//
+// Bound by the read of X and dY.  On the vector ALUs (64 multiply-adds per row and lane at r = 16)
+// it was bound by those instead: 30 + 4 us (the 4 a second launch that added row chunks) at
+// 2048 x (4096 + 11008), r = 16, 20 + 4 at 777 x (11008 + 4096), 96 + 7 at 2048 x 16384, r = 64; now 14,
+// 9.5 and 26 us.  247 MB at 4096 x (8192 + 22016), r = 8: 47 + 4 -> 47 us, 5.3 TB/s.
+//
+// A lane loads CPL adjacent columns of the eight rows that it holds of the contraction, so 16 lanes
+// read 32 CPL contiguous bytes of a row; column c + q of the eight rows is then gathered with four
+// byte permutes and is the MFMA's right operand as it stands -- no transposed load, no LDS.  The
+// waves of a workgroup take blocks of 32 rows in turn and add their sums in LDS at the end, so one
+// workgroup can own a block of columns over all rows and write the gradient itself.
+//   CPL   4 (128-byte pieces; twice the workgroups): the data of a few thousand rows come out of the
+//         last-level cache and what counts is the number of compute units that pull (6656 x 2, M = 1024:
+//         7.9 us against 9.4).  8 (256-byte pieces) from 128 MB on, where HBM does the work (247 MB:
+//         47 us against 55; r = 32: 55 against 72), for r <= 32; beyond that eight columns'
+//         accumulators leave too few waves (r = 64 at 2048 x 16384: 26 us against 43).
+//   rows  in chunks that leave partials for a reduction launch (4 us) only where the columns are too
+//         few to occupy the chip and at least 1024 rows remain to each: 256 + 256 columns, M = 4096:
+//         14.4 -> 6.4 + 4.1 us; 2048 + 2048: 16.3 -> 9.3 + 4.2; a chunk of 512 rows gains less than
+//         the launch costs (4096 + 11008, M = 2048: 14.4 -> 13.0 + 4.0).
+// No atomics (device-scope fp32 atomics bypass the per-XCD L2 and are slow), no zero-fill.
 // ---------------------------------------------------------------------------
-// Up to this many rows go in one chunk (measured per call: 5.9 - 6.5 against 7.9 - 8.1 us at 33 - 64
-// rows; at 128 rows the single launch is no quicker than the pair).
-constexpr int GRAD_ONE_CHUNK_ROWS = 64;
 GradGeom grad_geom(int M, int K, int N, int r) {
     GradGeom g;
-    g.cpl = r <= 16 ? 4 : 2;                        // columns per lane (8- or 4-byte loads)
-    const int wcols = 64 * g.cpl;                   // columns per workgroup
+    g.rg = r > 0 ? (r + 15) / 16 : 1;
+    g.cpl = g.rg <= 2 && (size_t)M * ((size_t)K + N) * 2 >= (size_t)128 << 20 ? 8 : 4;
+    const int wcols = 16 * g.cpl;
     g.cols_a = (K + wcols - 1) / wcols;
     g.cols_b = (N + wcols - 1) / wcols;
-    const int col_blocks = g.cols_a + g.cols_b;
-    // enough row chunks to give the chip ~1024 workgroups, at least 32 rows each
-    int chunks = (1024 + col_blocks - 1) / col_blocks;
-    const int max_chunks = (M + 31) / 32;
-    if (chunks > max_chunks) chunks = max_chunks;
+    int chunks = 256 / (g.cols_a + g.cols_b);
+    if (chunks > M / 1024) chunks = M / 1024;
     if (chunks < 1) chunks = 1;
-    if (M <= GRAD_ONE_CHUNK_ROWS) chunks = 1;       // few rows: one launch, no reduction launch behind it
-    int rows = (M + chunks - 1) / chunks;
-    rows = (rows + 3) / 4 * 4;
+    const int rows = ((M + chunks - 1) / chunks + 31) / 32 * 32;
     g.rows_per_block = rows;
     g.chunks = (M + rows - 1) / rows;
-    g.passes = r > 32 ? 2 : 1;
+    const int most = g.rg * g.cpl <= 8 ? 16 : 8;     // their sums meet in at most 64 KB of LDS
+    g.nwaves = 1;
+    while (g.nwaves < most && g.nwaves * 32 < rows) g.nwaves *= 2;
     g.partial_floats = (size_t)g.chunks * (size_t)(K + N) * (size_t)(r > 0 ? r : 0);
     return g;
 }
 
-// F16: the activations are binary16 (paper-literal path) instead of bfloat16.
-template <int RP, int CPL, bool F16>
-__global__ __launch_bounds__(256) void lora_grad_partial_kernel(GradPairArgs a, GradGeom g) {
-    // one LDS buffer, used first for pieces of P and then for the waves' sums
-    constexpr int PROWS = 128, RED_ROW = CPL * RP + 1;
-    constexpr int LDS_FLOATS = 3 * 64 * RED_ROW > PROWS * RP ? 3 * 64 * RED_ROW : PROWS * RP;
-    __shared__ __attribute__((aligned(16))) float lds_buf[LDS_FLOATS];
-    float (*red)[64][RED_ROW] = reinterpret_cast<float (*)[64][RED_ROW]>(lds_buf);
-    float (*Ps)[RP] = reinterpret_cast<float (*)[RP]>(lds_buf);
+// RG: groups of 16 adapter columns; CPL: adjacent columns of X / dY per lane; F16: the activations are
+// binary16 (paper-literal path) instead of bfloat16.
+template <int RG, int CPL, bool F16>
+__global__ __launch_bounds__(RG * CPL <= 8 ? 1024 : 512) void lora_grad_partial_kernel(GradPairArgs a, GradGeom g) {
+    extern __shared__ __attribute__((aligned(16))) float red[];   // [nwaves / 2][CPL * RG * 4][64]
+    typedef uint32_t words_t __attribute__((ext_vector_type(CPL / 2)));
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = uniform(threadIdx.x >> 6), nwaves = blockDim.x >> 6;
+    const int i = lane & 15, cs = lane >> 4;
     const bool is_a = (int)blockIdx.x < g.cols_a;
     const uint16_t *__restrict__ act = is_a ? a.X : a.dY;
-    const float *__restrict__ P = is_a ? a.dYBt : a.XA;   // [M][r]: a row is the same for every lane (scalar loads)
-    const int C = is_a ? a.K : a.N;
-    const int c = (is_a ? blockIdx.x : blockIdx.x - g.cols_a) * (64 * CPL) + CPL * lane;
-    const int r = a.r, j0 = blockIdx.z * RP;
+    const float *__restrict__ P = is_a ? a.dYBt : a.XA;   // [M][r]
+    const int C = is_a ? a.K : a.N, r = a.r;
+    const int c = (is_a ? blockIdx.x : blockIdx.x - g.cols_a) * (16 * CPL) + CPL * i;
+    const bool col_ok = c < C;                            // C is a multiple of 8: all CPL columns or none
     const int m_begin = blockIdx.y * g.rows_per_block;
-    int m_end = m_begin + g.rows_per_block;
-    if (m_end > a.M) m_end = a.M;
-    const bool col_ok = c < C;   // C is a multiple of 8 >= CPL, so c + CPL - 1 < C too
-
-    float acc[CPL][RP];
-#pragma unroll
-    for (int t = 0; t < CPL; ++t)
-#pragma unroll
-        for (int j = 0; j < RP; ++j) acc[t][j] = 0.f;
-
-    // The rows of P that the workgroup needs pass through LDS, a piece of PROWS rows at a time:
-    // every lane of a wave needs the same RP values of a row, and reading them from LDS (one
-    // address for the whole wave: a broadcast) costs RP / 4 instructions per row, where loads from
-    // global memory with a wave-uniform address would cost RP.
-    typedef uint32_t words_t __attribute__((ext_vector_type(CPL / 2)));
-    auto row_fma = [&](words_t v, int prow) {
-        float x[CPL];
-#pragma unroll
-        for (int q = 0; q < CPL / 2; ++q) {
-            uint32_t wq;
-            wq = v[q];
-            x[2 * q] = F16 ? half_bits_to_float((uint16_t)(wq & 0xFFFFu)) : __uint_as_float(wq << 16);
-            x[2 * q + 1] = F16 ? half_bits_to_float((uint16_t)(wq >> 16)) : __uint_as_float(wq & 0xFFFF0000u);
-        }
-#pragma unroll
-        for (int j = 0; j < RP; j += 4) {
-            const float4 pj = *reinterpret_cast<const float4 *>(&Ps[prow][j]);
-            const float pv[4] = {pj.x, pj.y, pj.z, pj.w};
-#pragma unroll
-            for (int z = 0; z < 4; ++z)
-#pragma unroll
-                for (int t = 0; t < CPL; ++t) acc[t][j + z] = __builtin_fmaf(x[t], pv[z], acc[t][j + z]);
-        }
-    };
+    const int m_end = m_begin + g.rows_per_block < a.M ? m_begin + g.rows_per_block : a.M;
     const uint16_t *col = act + (col_ok ? c : 0);
-    for (int mb = m_begin; mb < m_end; mb += PROWS) {
-        const int me = mb + PROWS < m_end ? mb + PROWS : m_end;
-        __syncthreads();                              // the previous piece has been consumed
-        for (int x = threadIdx.x; x < (me - mb) * RP; x += 256) {
-            const int prow = x / RP, j = x % RP;
-            Ps[prow][j] = j0 + j < r ? P[(size_t)(mb + prow) * r + j0 + j] : 0.f;
+
+    f32x4 acc[CPL][RG];
+#pragma unroll
+    for (int q = 0; q < CPL; ++q)
+#pragma unroll
+        for (int t = 0; t < RG; ++t) acc[q][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    for (int mb = m_begin + 32 * wave; mb < m_end; mb += 32 * nwaves) {
+        const int m8 = mb + 8 * cs;                       // this lane's eight rows of the contraction
+        words_t x[8];
+        float p[RG][8];
+        if (mb + 32 <= m_end) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = *reinterpret_cast<const words_t *>(col + (size_t)(m8 + e) * C);
+#pragma unroll
+            for (int t = 0; t < RG; ++t)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    p[t][e] = 0.f;
+                    if (16 * t + i < r) p[t][e] = P[(size_t)(m8 + e) * r + 16 * t + i];
+                }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                x[e] = words_t(0u);
+                if (m8 + e < m_end) x[e] = *reinterpret_cast<const words_t *>(col + (size_t)(m8 + e) * C);
+            }
+#pragma unroll
+            for (int t = 0; t < RG; ++t)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    p[t][e] = 0.f;
+                    if (16 * t + i < r && m8 + e < m_end) p[t][e] = P[(size_t)(m8 + e) * r + 16 * t + i];
+                }
+        }
+        bf16x8 ph[RG], pm[RG], pl[RG];
+#pragma unroll
+        for (int t = 0; t < RG; ++t) {
+            uint32_t hi[4], mid[4], lo[4];
+            split3(p[t], hi, mid, lo);
+            ph[t] = regs_to_bf16x8(hi);
+            pm[t] = regs_to_bf16x8(mid);
+            pl[t] = regs_to_bf16x8(lo);
+        }
+#pragma unroll
+        for (int q = 0; q < CPL; ++q) {
+            uint32_t b[4];                                // column c + q of the eight rows
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                b[e] = __builtin_amdgcn_perm(x[2 * e + 1][q / 2], x[2 * e][q / 2], q & 1 ? 0x07060302u : 0x05040100u);
+            if (F16) {
+                uint32_t bh[4], bl[4];
+                split_f16x8(b, bh, bl);
+                const bf16x8 oh = regs_to_bf16x8(bh), ol = regs_to_bf16x8(bl);
+#pragma unroll
+                for (int t = 0; t < RG; ++t) {
+                    acc[q][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph[t], oh, acc[q][t], 0, 0, 0);
+                    acc[q][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pm[t], oh, acc[q][t], 0, 0, 0);
+                    acc[q][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl[t], oh, acc[q][t], 0, 0, 0);
+                    acc[q][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph[t], ol, acc[q][t], 0, 0, 0);
+                    acc[q][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pm[t], ol, acc[q][t], 0, 0, 0);
+                    acc[q][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl[t], ol, acc[q][t], 0, 0, 0);
+                }
+            } else {
+                const bf16x8 o = regs_to_bf16x8(b);
+#pragma unroll
+                for (int t = 0; t < RG; ++t) {
+                    acc[q][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph[t], o, acc[q][t], 0, 0, 0);
+                    acc[q][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pm[t], o, acc[q][t], 0, 0, 0);
+                    acc[q][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl[t], o, acc[q][t], 0, 0, 0);
+                }
+            }
+        }
+    }
+
+    // the waves' sums meet in LDS, half of the waves handing theirs to the other half at a time
+    constexpr int FL = CPL * RG * 4;
+    for (int half = nwaves >> 1; half > 0; half >>= 1) {
+        if (wave >= half && wave < 2 * half) {
+#pragma unroll
+            for (int q = 0; q < CPL; ++q)
+#pragma unroll
+                for (int t = 0; t < RG; ++t)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) red[((wave - half) * FL + (q * RG + t) * 4 + v) * 64 + lane] = acc[q][t][v];
         }
         __syncthreads();
-        // groups of four rows per wave (rows m, m + 4, m + 8, m + 12); the loads of the next group
-        // are issued before the arithmetic of the current one, so a wave always has a group in flight
-        int m = mb + wave;
-        bool have = m + 12 < me;
-        words_t cur[4];
-        if (have) {
+        if (wave < half) {
 #pragma unroll
-            for (int u = 0; u < 4; ++u) cur[u] = *reinterpret_cast<const words_t *>(col + (size_t)(m + 4 * u) * C);
+            for (int q = 0; q < CPL; ++q)
+#pragma unroll
+                for (int t = 0; t < RG; ++t)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) acc[q][t][v] += red[(wave * FL + (q * RG + t) * 4 + v) * 64 + lane];
         }
-        while (have) {
-            const int mn = m + 16;
-            const bool have_next = mn + 12 < me;
-            words_t nxt[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) nxt[u] = cur[u];
-            if (have_next) {
-#pragma unroll
-                for (int u = 0; u < 4; ++u) nxt[u] = *reinterpret_cast<const words_t *>(col + (size_t)(mn + 4 * u) * C);
-            }
-#pragma unroll
-            for (int u = 0; u < 4; ++u) row_fma(cur[u], m + 4 * u - mb);
-#pragma unroll
-            for (int u = 0; u < 4; ++u) cur[u] = nxt[u];
-            m = mn;
-            have = have_next;
-        }
-        for (; m < me; m += 4) row_fma(*reinterpret_cast<const words_t *>(col + (size_t)m * C), m - mb);
+        __syncthreads();
     }
-    __syncthreads();                                  // every wave is done with the last piece of P
-
-    if (wave > 0) {
-#pragma unroll
-        for (int t = 0; t < CPL; ++t)
-#pragma unroll
-            for (int j = 0; j < RP; ++j) red[wave - 1][lane][t * RP + j] = acc[t][j];
-    }
-    __syncthreads();
     if (wave != 0 || !col_ok) return;
     // a single row chunk is the whole sum: finish here (scale, accumulate flag) in the outputs
-    // themselves, which have the layout of a partial, and skip stage 2
+    // themselves, which have the layout of a partial, and skip the reduction launch
     const bool direct = g.chunks == 1;
     float *part = a.partials + (size_t)blockIdx.y * ((size_t)(a.K + a.N) * r);
-    float *base_a = direct ? a.dA : part;
-    float *base_b = direct ? a.dB : part + (size_t)a.K * r;
     const bool add_old = direct && a.accumulate;
+    const float scale = direct ? a.lora_scale : 1.0f;
+    // accumulator register v of this lane: adapter column 16 t + 4 cs + v, activation column c + q
+    if (is_a) {
+        float *base = (direct ? a.dA : part) + (size_t)c * r;
 #pragma unroll
-    for (int t = 0; t < CPL; ++t) {
-        float v[RP];
+        for (int q = 0; q < CPL; ++q)
 #pragma unroll
-        for (int j = 0; j < RP; ++j) {
-            v[j] = acc[t][j] + red[0][lane][t * RP + j] + red[1][lane][t * RP + j] + red[2][lane][t * RP + j];
-            if (direct) v[j] *= a.lora_scale;
-        }
-        if (is_a) {
-            float *dst = base_a + (size_t)(c + t) * r + j0;
-            if ((r & 3) == 0) {
-#pragma unroll
-                for (int j = 0; j < RP; j += 4)
-                    if (j0 + j < r) {
-                        float4 o = make_float4(v[j], v[j + 1], v[j + 2], v[j + 3]);
+            for (int t = 0; t < RG; ++t) {
+                const int j = 16 * t + 4 * cs;
+                float *dst = base + (size_t)q * r + j;
+                if ((r & 3) == 0) {
+                    if (j < r) {
+                        float4 o = make_float4(scale * acc[q][t][0], scale * acc[q][t][1], scale * acc[q][t][2], scale * acc[q][t][3]);
                         if (add_old) {
-                            const float4 old = *reinterpret_cast<const float4 *>(dst + j);
+                            const float4 old = *reinterpret_cast<const float4 *>(dst);
                             o.x += old.x; o.y += old.y; o.z += old.z; o.w += old.w;
                         }
-                        *reinterpret_cast<float4 *>(dst + j) = o;
+                        *reinterpret_cast<float4 *>(dst) = o;
                     }
-            } else {
+                } else {
 #pragma unroll
-                for (int j = 0; j < RP; ++j)
-                    if (j0 + j < r) dst[j] = add_old ? dst[j] + v[j] : v[j];
+                    for (int v = 0; v < 4; ++v)
+                        if (j + v < r) dst[v] = add_old ? dst[v] + scale * acc[q][t][v] : scale * acc[q][t][v];
+                }
             }
-        } else {
-            float *dst = base_b + (size_t)j0 * a.N + (c + t);
+    } else {
+        float *base = (direct ? a.dB : part + (size_t)a.K * r) + c;
 #pragma unroll
-            for (int j = 0; j < RP; ++j)
-                if (j0 + j < r) dst[(size_t)j * a.N] = add_old ? dst[(size_t)j * a.N] + v[j] : v[j];
-        }
+        for (int t = 0; t < RG; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int j = 16 * t + 4 * cs + v;
+                if (j >= r) continue;
+#pragma unroll
+                for (int q = 0; q < CPL; q += 4) {
+                    float4 o = make_float4(scale * acc[q][t][v], scale * acc[q + 1][t][v], scale * acc[q + 2][t][v], scale * acc[q + 3][t][v]);
+                    float4 *dst = reinterpret_cast<float4 *>(base + (size_t)j * a.N + q);
+                    if (add_old) {
+                        const float4 old = *dst;
+                        o.x += old.x; o.y += old.y; o.z += old.z; o.w += old.w;
+                    }
+                    *dst = o;
+                }
+            }
     }
 }
 
@@ -478,23 +516,27 @@ __global__ __launch_bounds__(256) void lora_grad_reduce_kernel(GradPairArgs a, i
     *dst = o;
 }
 
-hipError_t launch_lora_grad_pair(const GradPairArgs &a, hipStream_t stream) {
-    const GradGeom g = grad_geom(a.M, a.K, a.N, a.r);
-    dim3 grid(g.cols_a + g.cols_b, g.chunks, g.passes);
-    if (a.f16) {
-        if (a.r <= 8) launch_kernel("lora_grad", lora_grad_partial_kernel<8, 4, true>, grid, 256, 0, stream, a, g);
-        else if (a.r <= 16) launch_kernel("lora_grad", lora_grad_partial_kernel<16, 4, true>, grid, 256, 0, stream, a, g);
-        else launch_kernel("lora_grad", lora_grad_partial_kernel<32, 2, true>, grid, 256, 0, stream, a, g);
-    } else {
-        if (a.r <= 8) launch_kernel("lora_grad", lora_grad_partial_kernel<8, 4, false>, grid, 256, 0, stream, a, g);
-        else if (a.r <= 16) launch_kernel("lora_grad", lora_grad_partial_kernel<16, 4, false>, grid, 256, 0, stream, a, g);
-        else launch_kernel("lora_grad", lora_grad_partial_kernel<32, 2, false>, grid, 256, 0, stream, a, g);
-    }
+template <int RG, int CPL>
+static hipError_t launch_grad(const GradPairArgs &a, const GradGeom &g, hipStream_t stream) {
+    const dim3 grid(g.cols_a + g.cols_b, g.chunks);
+    const size_t lds = (size_t)(g.nwaves / 2) * CPL * RG * 4 * 64 * sizeof(float);
+    if (a.f16) launch_kernel("lora_grad", lora_grad_partial_kernel<RG, CPL, true>, grid, g.nwaves * 64, lds, stream, a, g);
+    else launch_kernel("lora_grad", lora_grad_partial_kernel<RG, CPL, false>, grid, g.nwaves * 64, lds, stream, a, g);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || g.chunks == 1) return e;
     const size_t n = (size_t)(a.K + a.N) * a.r;
     launch_kernel("lora_grad_reduce", lora_grad_reduce_kernel, (unsigned)((n / 4 + 255) / 256), 256, 0, stream, a, g.chunks);
     return hipGetLastError();
+}
+
+hipError_t launch_lora_grad_pair(const GradPairArgs &a, hipStream_t stream) {
+    const GradGeom g = grad_geom(a.M, a.K, a.N, a.r);
+    switch (g.rg) {
+        case 1: return g.cpl == 8 ? launch_grad<1, 8>(a, g, stream) : launch_grad<1, 4>(a, g, stream);
+        case 2: return g.cpl == 8 ? launch_grad<2, 8>(a, g, stream) : launch_grad<2, 4>(a, g, stream);
+        case 3: return launch_grad<3, 4>(a, g, stream);
+        default: return launch_grad<4, 4>(a, g, stream);
+    }
 }
 
 }  // namespace mlr

@@ -1,0 +1,54 @@
+"""The adapter-gradient kernel where its tiles end: 32-row blocks, 64- and 128-column blocks, groups
+of 16 adapter columns, waves without rows, row chunks with the reduction launch; both activation
+types, with and without accumulation, against float64 products of the same operands."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2309_16119_amd import binding as b
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # K, N, M, r
+    (32, 8, 1, 1),
+    (64, 72, 31, 16),
+    (96, 136, 33, 17),
+    (128, 64, 64, 48),
+    (160, 200, 515, 33),           # 16 waves, most of them with one block more than the others
+    (96, 264, 300, 64),
+    (64, 40, 1030, 3),             # one row chunk: too few rows for two
+    (256, 264, 2051, 8),           # two row chunks and the reduction launch
+    (64, 128, 4200, 40),
+    (8192, 8456, 4100, 8),         # from 128 MB of activations on: eight columns per lane
+    (16384, 264, 4105, 20),
+]
+
+
+@pytest.mark.parametrize("f16", [False, True])
+@pytest.mark.parametrize("K,N,M,r", SHAPES)
+def test_adapter_gradients_at_tile_edges(K, N, M, r, f16):
+    gen = torch.Generator(device="cuda").manual_seed(K + 3 * N + M)
+    dtype = torch.float16 if f16 else torch.bfloat16
+    X = torch.randn((M, K), device="cuda", generator=gen).to(dtype)
+    dY = torch.randn((M, N), device="cuda", generator=gen).to(dtype)
+    XA = torch.randn((M, r), device="cuda", generator=gen)
+    T = torch.randn((M, r), device="cuda", generator=gen)
+    A, B = torch.zeros((K, r), device="cuda"), torch.zeros((r, N), device="cuda")
+    s = 0.75
+    call = b.modulora_f16_bwd_lora if f16 else b.modulora_bwd_lora
+    dA = torch.full((K, r), float("nan"), device="cuda")
+    dB = torch.full((r, N), float("nan"), device="cuda")
+    call(X, dY, A, B, s, XA=XA, dYBt=T, dA=dA, dB=dB)
+    dA0 = torch.randn((K, r), device="cuda", generator=gen)
+    dB0 = torch.randn((r, N), device="cuda", generator=gen)
+    dA2, dB2 = dA0.clone(), dB0.clone()
+    call(X, dY, A, B, s, XA=XA, dYBt=T, dA=dA2, dB=dB2, accumulate=True)
+    # fp32 sums of M exact products: the rounding errors of M additions, taken as independent, times 8
+    unit = 8 * np.sqrt(M) * 2.0 ** -24 * s
+    for got, got2, old, act, P, left in ((dA, dA2, dA0, X, T, True), (dB, dB2, dB0, dY, XA, False)):
+        a64, p64 = act.double(), P.double()
+        ref = s * (a64.T @ p64 if left else p64.T @ a64)
+        mag = a64.abs().T @ p64.abs() if left else p64.abs().T @ a64.abs()
+        assert bool(((got.double() - ref).abs() <= unit * mag + 1e-30).all())
+        assert bool(((got2.double() - ref - old.double()).abs() <= unit * mag + 2.0 ** -23 * (ref + old.double()).abs() + 1e-30).all())
