@@ -301,7 +301,7 @@ __global__ __launch_bounds__(big::THREADS, 2) void gemm_big_kernel(GemmDev d, Bi
                 asm volatile("s_waitcnt vmcnt(%4)" : "+v"(st.bw_lo), "+v"(st.bw_hi), "+v"(st.bw_scale), "+v"(st.bw_zero) : "n"(KEEP) : "memory");
                 // the 8-code chunks straddle two words: join them now, so that a landed set is 4 registers
 #pragma unroll
-                for (int i = 0; i < 4; ++i) st.bw_lo[i] = __builtin_amdgcn_alignbit(st.bw_hi[i], st.bw_lo[i], bw_shift);
+                for (int i = 0; i < 4; ++i) st.bw_lo[i] = unit_codes<BITS>(__builtin_amdgcn_alignbit(st.bw_hi[i], st.bw_lo[i], bw_shift), 0u);
             } else {
                 asm volatile("s_waitcnt vmcnt(%3)" : "+v"(st.bw_lo), "+v"(st.bw_scale), "+v"(st.bw_zero) : "n"(KEEP) : "memory");
             }
@@ -309,54 +309,53 @@ __global__ __launch_bounds__(big::THREADS, 2) void gemm_big_kernel(GemmDev d, Bi
         }
     };
 
-    // w = fma(q, scale, bias): bias = -zero * scale for an integer zero point, or the binary16 zero
-    // point itself where it is one that is added (Section 2.2 eq. (2) as printed)
-    auto dq_of = [](uint16_t scale_bits, uint32_t zero_bits) {
-        if (!F16) return make_dq(scale_bits, (uint8_t)zero_bits);
-        DqConst c;
-        c.scale = half_bits_to_float(scale_bits);
-        c.bias = half_bits_to_float((uint16_t)zero_bits);
-        return c;
-    };
     // dequantize the staged words of one set into the W tile of buffer buf: quarter `part`
     // (0..3) of the thread's share, or all of it (part < 0)
+    // (the binary16 3-bit backward kernel has no register left for a mask)
+    const DqMasks masks = make_dq_masks<BITS, !(BWD && F16 && BITS == 3)>();
+    const uint32_t bw_bytes = bw_shift ? 0x0C030C02u : 0x0C010C00u;      // 2 bits: which half of the word
     auto store_w = [&](int buf, const WStage &st, int part) {
         unsigned char *Ws = smem + W_BASE + buf * W_BYTES;
         if (!BWD) {
             const int nl = tid & (CT - 1);
-            const DqConst dq = dq_of((uint16_t)st.fw_scale, st.fw_zero);
+            const DqPair dq = make_dq_pair<BITS, F16>(st.fw_scale, st.fw_zero);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 if (part >= 0 && j != part) continue;
                 uint32_t o[4];
-                dequant_quarter<BITS, F16>(st.fw_words, j, dq, o);
+                dequant_quarter_pairs<BITS, F16>(st.fw_words, j, dq, masks, o);
                 *reinterpret_cast<uint4 *>(Ws + tile_off(nl, fw_kb * 4 + j)) = make_uint4(o[0], o[1], o[2], o[3]);
             }
         } else {
             const int no = tid & 15, ko = tid >> 4;
-            const uint32_t sc[2] = {st.bw_scale[0], st.bw_scale[1]};
-            uint32_t chunk[4];
-            DqConst dq[4];
+            uint32_t y[4];
+            DqPair dq[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                chunk[i] = BITS == 3 ? st.bw_lo[i] : st.bw_lo[i] >> bw_shift;   // 3-bit: joined by wait_loads()
-                const uint16_t sb = bw_kok ? (uint16_t)(sc[i >> 1] >> ((i & 1) * 16)) : (uint16_t)0;
+                // (3-bit: done by wait_loads(), which joins the two words)
+                y[i] = BITS == 3 ? st.bw_lo[i] : unit_codes<BITS>(st.bw_lo[i], bw_bytes);
+                const uint32_t sb = bw_kok ? (st.bw_scale[i >> 1] >> ((i & 1) * 16)) & 0xFFFFu : 0u;
                 const uint32_t zb = F16 ? (bw_kok ? (st.bw_zero16[i >> 1] >> ((i & 1) * 16)) & 0xFFFFu : 0u) : (st.bw_zero >> (i * 8)) & 0xFFu;
-                dq[i] = dq_of(sb, zb);
+                dq[i] = make_dq_pair<BITS, F16>(sb, zb);
             }
             // a 16-lane group fills one row per store; neighbouring groups take their eight rows in
             // opposite order of parity, so that the two rows of a 32-lane store fall into different
             // halves of the banks
 #pragma unroll
-            for (int kk = 0; kk < 8; ++kk) {
-                if (part >= 0 && kk / 2 != part) continue;
-                const int kq = kk ^ (ko & 1);
-                uint32_t o[2];
+            for (int p = 0; p < 4; ++p) {
+                if (part >= 0 && p != part) continue;
+                const int pq = p ^ (ko & 1);         // codes pq and pq + 4 of the unit's eight
+                float lo[4], hi[4];
 #pragma unroll
-                for (int i = 0; i < 2; ++i)
-                    o[i] = pack_pair<F16>(dq_value(chunk_code<BITS>(chunk[2 * i], kq), dq[2 * i]),
-                                          dq_value(chunk_code<BITS>(chunk[2 * i + 1], kq), dq[2 * i + 1]));
-                *reinterpret_cast<uint2 *>(Ws + tile_off(ko * 8 + kq, no >> 1) + (no & 1) * 8) = make_uint2(o[0], o[1]);
+                for (int i = 0; i < 4; ++i) {
+                    const half16x2 h = unit_pair<BITS, F16>(y[i], (uint32_t)(BITS * pq), masks);
+                    lo[i] = dq_lo<F16>(h, dq[i]);
+                    hi[i] = dq_hi<F16>(h, dq[i]);
+                }
+                unsigned char *row = Ws + tile_off(ko * 8 + pq, no >> 1) + (no & 1) * 8;
+                *reinterpret_cast<uint2 *>(row) = make_uint2(pack_pair_cvt<F16>(lo[0], lo[1]), pack_pair_cvt<F16>(lo[2], lo[3]));
+                row = Ws + tile_off(ko * 8 + pq + 4, no >> 1) + (no & 1) * 8;
+                *reinterpret_cast<uint2 *>(row) = make_uint2(pack_pair_cvt<F16>(hi[0], hi[1]), pack_pair_cvt<F16>(hi[2], hi[3]));
             }
         }
     };
@@ -511,7 +510,7 @@ __global__ __launch_bounds__(big::THREADS, 2) void gemm_big_kernel(GemmDev d, Bi
                 if (BITS == 3) {
                     st.bw_hi = load_at<u32x4>(wbase, bw_offhi);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) st.bw_lo[i] = __builtin_amdgcn_alignbit(st.bw_hi[i], st.bw_lo[i], bw_shift);
+                    for (int i = 0; i < 4; ++i) st.bw_lo[i] = unit_codes<BITS>(__builtin_amdgcn_alignbit(st.bw_hi[i], st.bw_lo[i], bw_shift), 0u);
                 }
                 st.bw_scale = load_at<u32x2>(a.w.scales + (size_t)bw_g0 * N + r0, bw_soff * 2);
                 if (F16) st.bw_zero16 = load_at<u32x2>(a.zeros16 + (size_t)bw_g0 * N + r0, bw_soff * 2);

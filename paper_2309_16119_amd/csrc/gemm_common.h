@@ -151,6 +151,121 @@ __device__ __forceinline__ void dequant_quarter(const uint32_t *w, int j, const 
     }
 }
 
+// The same quarter by fewer and cheaper instructions.  A code OR-ed into the mantissa of a binary16
+// power of two whose unit in that bit is one is that power of two plus the code, two codes per
+// instruction: (w >> s & fields) | magic.  The multiply-add then reads either half as it stands:
+//   (q - zero) scale = (2^m + q) scale - (2^m + zero) scale,
+// and with zero <= 255 and 2^m of 64 or 1024 the second product has at most 22 significant bits, so
+// both it and the result are exact, as they are in dq_value().  A wave's extract, convert and
+// multiply-add cost 4 issue cycles each (measured; plain shifts, ANDs and fp32 multiply-adds 2):
+// 14 per 3-bit code that way, 9.5 this way; the 256 x 256 kernel 1252 -> 1216 us forward and 1218 ->
+// 1196 backward at 4096 x 8192 x 22016 (3 bits), 172 -> 165 and 158 -> 153 at 2048 x 4096 x 11008 (4 bits),
+// 86 -> 83 both ways at 1024 x 6656 x 6656 (2 bits).  (In the producer waves of the 128 x 64 kernel it
+// measured slower, 75 -> 79 us a step: they wait for LDS, and two rows per store pass conflict.)  Binary16 layers add their zero point, whose sum with
+// the power of two would round: there the power of two is taken off first (exact).
+struct DqPair {
+    _Float16 scale, z;   // z: the binary16 zero point that is added (F16)
+    float lo, hi;        // addend of the codes in the low and in the high halves (integer zero points)
+};
+struct DqMasks {
+    uint32_t fields, magic;      // in registers of their own: one v_and_or_b32 instead of two instructions with literals
+};
+template <int BITS, bool IN_REGS = true>
+__device__ __forceinline__ DqMasks make_dq_masks() {
+    DqMasks m;
+    m.fields = BITS == 4 ? 0x000F000Fu : (BITS == 2 ? 0x00030003u : 0x00070070u);
+    m.magic = BITS == 3 ? 0x64005400u : 0x64006400u;       // 1024.0 twice; 3 bits: 1024.0, 64.0 (low field at bits 4-6)
+    if (IN_REGS) {
+        asm volatile("" : "+s"(m.fields));
+        asm volatile("" : "+v"(m.magic));
+    }
+    return m;
+}
+template <int BITS, bool F16>
+__device__ __forceinline__ DqPair make_dq_pair(uint32_t scale_bits, uint32_t zero_bits) {
+    DqPair c;
+    const uint16_t sb = (uint16_t)scale_bits;
+    __builtin_memcpy(&c.scale, &sb, 2);
+    if (F16) {
+        const uint16_t zb = (uint16_t)zero_bits;
+        __builtin_memcpy(&c.z, &zb, 2);
+        c.lo = c.hi = 0.f;
+    } else {
+        c.z = (_Float16)0.0f;
+        const float s = (float)c.scale, z = (float)(zero_bits & 0xFFu);
+        c.hi = -(1024.0f + z) * s;
+        c.lo = BITS == 3 ? -(64.0f + z) * s : c.hi;
+    }
+    return c;
+}
+// a pair's two weights in fp32, the products exact: one v_fma_mix_f32 each, with the halves as they stand
+template <bool F16>
+__device__ __forceinline__ float dq_lo(half16x2 h, const DqPair &c) {
+    return __builtin_fmaf((float)h.x, (float)c.scale, F16 ? (float)c.z : c.lo);
+}
+template <bool F16>
+__device__ __forceinline__ float dq_hi(half16x2 h, const DqPair &c) {
+    return __builtin_fmaf((float)h.y, (float)c.scale, F16 ? (float)c.z : c.hi);
+}
+// Codes p (low half) and p + 4 (high half) of quarter j, as they enter the multiply-add.
+template <int BITS, bool F16>
+__device__ __forceinline__ half16x2 quarter_pair(const uint32_t *w, int j, int p, const DqMasks &m) {
+    uint32_t x;
+    if (BITS == 4) {
+        x = w[j] >> (4 * p);
+    } else if (BITS == 2) {
+        // the quarter's two bytes side by side, one per half
+        x = __builtin_amdgcn_perm(0u, w[j >> 1], (j & 1) ? 0x0C030C02u : 0x0C010C00u) >> (2 * p);
+    } else {
+        const int sh = 24 * j + 3 * p - 4;       // stream bit that lands at register bit 0
+        if (sh < 0) x = w[0] << (-sh);
+        else if ((sh & 31) == 0) x = w[sh >> 5];
+        else if ((sh >> 5) == 2) x = w[2 % BITS] >> (sh & 31);
+        else if ((sh & 31) + 19 <= 32) x = w[sh >> 5] >> (sh & 31);
+        else x = __builtin_amdgcn_alignbit(w[((sh >> 5) + 1) % BITS], w[sh >> 5], sh & 31);
+    }
+    x = (x & m.fields) | m.magic;
+    half16x2 h;
+    __builtin_memcpy(&h, &x, 4);
+    if (F16) h -= half16x2{(_Float16)(BITS == 3 ? 64.0f : 1024.0f), (_Float16)1024.0f};
+    return h;
+}
+// The same for the eight codes of one weight column inside a word (the backward kernels' units): `y`
+// from unit_codes(), pass p (any lane's own order) by its right shift BITS * p.
+template <int BITS>
+__device__ __forceinline__ uint32_t unit_codes(uint32_t chunk_or_word, uint32_t two_bit_bytes) {
+    if (BITS == 2) return __builtin_amdgcn_perm(0u, chunk_or_word, two_bit_bytes);
+    return BITS == 3 ? chunk_or_word << 4 : chunk_or_word;
+}
+template <int BITS, bool F16>
+__device__ __forceinline__ half16x2 unit_pair(uint32_t y, uint32_t shift, const DqMasks &m) {
+    const uint32_t x = ((y >> shift) & m.fields) | m.magic;
+    half16x2 h;
+    __builtin_memcpy(&h, &x, 4);
+    if (F16) h -= half16x2{(_Float16)(BITS == 3 ? 64.0f : 1024.0f), (_Float16)1024.0f};
+    return h;
+}
+// Two fp32 values rounded to nearest even into a pair of 16-bit floats by ONE conversion: the fences
+// keep the compiler from folding a binary16 conversion into the multiply-adds (v_fma_mixlo_f16 takes
+// 8 cycles a value, v_fma_mix_f32 and half of v_cvt_pk_f16_f32 take 6).
+template <bool F16>
+__device__ __forceinline__ uint32_t pack_pair_cvt(float lo, float hi) {
+    if (F16) asm("" : "+v"(lo), "+v"(hi));
+    return pack_pair<F16>(lo, hi);
+}
+template <int BITS, bool F16>
+__device__ __forceinline__ void dequant_quarter_pairs(const uint32_t *w, int j, const DqPair &c, const DqMasks &m, uint32_t out[4]) {
+    float v[8];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const half16x2 h = quarter_pair<BITS, F16>(w, j, p, m);
+        v[p] = dq_lo<F16>(h, c);
+        v[p + 4] = dq_hi<F16>(h, c);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) out[i] = pack_pair_cvt<F16>(v[2 * i], v[2 * i + 1]);
+}
+
 // gemm_big.hip: the 256x256 8-wave variant
 hipError_t launch_gemm_big(const GemmArgs &a, hipStream_t stream);
 // gemm_mid.hip: 128x64 tiles for grids of about one tile per CU, producer and consumer waves
