@@ -5,6 +5,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cstdlib>
 #include <cstring>
 #include <mutex>
 #include <string>
@@ -64,7 +65,21 @@ mlr::LayerView view_of(const modulora_qweight *w) {
 struct WsLayout {
     size_t act_ext, w_ext, p0, p1, gpart, gemm_part, dpart, total;
     size_t gemm_part_bytes;      // size of the region at gemm_part
+    bool direct_fwd, direct_bwd; // gemm_direct.hip takes this direction unless a streaming kernel does
 };
+
+// Bytes that gemm_direct.hip needs at the start of the workspace for the directions it takes.
+size_t direct_bytes(int32_t K, int32_t N, int32_t M, int32_t r, bool fwd, bool bwd) {
+    const size_t f = fwd ? mlr::direct_plan(M, K, N, false).ws_bytes(M, N, r) : 0;
+    const size_t b = bwd ? mlr::direct_plan(M, N, K, true).ws_bytes(M, K, r) : 0;
+    return f > b ? f : b;
+}
+// 17 .. 32 tokens would take two passes of a streaming kernel: from 20 M weights on one direct pass is
+// quicker (8192 x 8192, 32 tokens: 33 / 31 us in two passes, 20 / 23 direct; smaller layers keep their
+// results of the streaming kernels).
+bool stream_takes(bool supported, int32_t K, int32_t N, int32_t M, bool direct) {
+    return supported && !(direct && M > mlr::SMALLM_ROWS && (size_t)K * N >= ((size_t)20 << 20));
+}
 
 WsLayout ws_layout(int32_t K, int32_t N, int32_t M, int32_t r) {
     WsLayout l{};
@@ -74,9 +89,13 @@ WsLayout ws_layout(int32_t K, int32_t N, int32_t M, int32_t r) {
     // fp32 partial tiles of the split contraction of the 256 x 256 kernel (also when r == 0)
     const size_t part = align256(mlr::gemm_partial_bytes(M, K, N));
     l.gemm_part_bytes = part;
+    l.direct_fwd = mlr::direct_wins(K, N, M, r, false);
+    l.direct_bwd = mlr::direct_wins(K, N, M, r, true);
+    const size_t dir = direct_bytes(K, N, M, r, l.direct_fwd, l.direct_bwd);
     if (r <= 0) {
         l.gemm_part = 0;
         l.total = small > part ? small : part;
+        if (dir > l.total) l.total = dir;
         return l;
     }
     const size_t RE = (size_t)mlr::lora_ext_len(r);
@@ -90,6 +109,7 @@ WsLayout ws_layout(int32_t K, int32_t N, int32_t M, int32_t r) {
     l.gemm_part = off; off += part;
     l.dpart = off;   off += align256(mlr::lora_down_partial_bytes(M, K, N, r));
     l.total = off > small ? off : small;
+    if (dir > l.total) l.total = dir;
     return l;
 }
 
@@ -99,8 +119,15 @@ WsLayout ws_layout(int32_t K, int32_t N, int32_t M, int32_t r) {
 // (without them the 256 x 256 kernel runs whole tiles).
 WsLayout ws_layout_fwd(const mlr::LayerView &v, int32_t M, int32_t r, size_t avail) {
     WsLayout l{};
-    if (mlr::smallm_fwd_supported(v, M)) {
+    l.direct_fwd = mlr::direct_wins(v.K, v.N, M, r, false);
+    const size_t dir = direct_bytes(v.K, v.N, M, r, l.direct_fwd, false);
+    if (dir > avail) l.direct_fwd = false;
+    if (stream_takes(mlr::smallm_fwd_supported(v, M), v.K, v.N, M, l.direct_fwd)) {
         l.total = mlr::smallm_fwd_ws_bytes(v, r);
+        return l;
+    }
+    if (l.direct_fwd) {
+        l.total = dir;
         return l;
     }
     size_t off = 0;
@@ -142,13 +169,14 @@ int check_fwd_args(const modulora_qweight *w, const uint16_t *X, int32_t M, cons
 
 int run_fwd(const modulora_qweight *w, const uint16_t *X, int32_t M, const float *A, const float *B, int32_t r,
             float lora_scale, uint16_t *Y, float *XA, char *ws, const WsLayout &l, hipStream_t st) {
-    if (mlr::smallm_fwd_supported(view_of(w), M)) {
+    const bool streams = stream_takes(mlr::smallm_fwd_supported(view_of(w), M), w->d_in, w->d_out, M, l.direct_fwd);
+    if (streams || l.direct_fwd) {
         mlr::SmallArgs sa{};
         sa.w = view_of(w);
         sa.act = X; sa.M = M; sa.out = Y;
         sa.A = A; sa.B = B; sa.r = r; sa.lora_scale = lora_scale;
         sa.P_out = XA; sa.ws = ws;
-        return hip_status(mlr::launch_smallm_fwd(sa, st));
+        return hip_status(streams ? mlr::launch_smallm_fwd(sa, st) : mlr::launch_direct(sa, false, st));
     }
     mlr::GemmArgs g{};
     g.w = view_of(w);
@@ -302,13 +330,14 @@ int modulora_bwd_input(const modulora_qweight *w, const uint16_t *dY, int32_t M,
 
     hipStream_t st = static_cast<hipStream_t>(stream);
     char *ws = static_cast<char *>(workspace);
-    if (mlr::smallm_bwd_supported(view_of(w), M)) {
+    const bool streams = stream_takes(mlr::smallm_bwd_supported(view_of(w), M), w->d_in, w->d_out, M, l.direct_bwd);
+    if (streams || l.direct_bwd) {
         mlr::SmallArgs sa{};
         sa.w = view_of(w);
         sa.act = dY; sa.M = M; sa.out = dX;
         sa.A = A; sa.B = B; sa.r = r; sa.lora_scale = lora_scale;
         sa.P_out = dYBt; sa.ws = ws;
-        return hip_status(mlr::launch_smallm_bwd(sa, st));
+        return hip_status(streams ? mlr::launch_smallm_bwd(sa, st) : mlr::launch_direct(sa, true, st));
     }
     mlr::GemmArgs g{};
     g.w = view_of(w);
@@ -398,6 +427,7 @@ mlr::F16Layer view_of(const modulora_qweight_f16 *w) {
 }
 struct F16Ws {
     size_t p0, p1, gpart, dpart, gemm_part, total;
+    bool direct_fwd, direct_bwd;
 };
 F16Ws f16_ws(int32_t K, int32_t N, int32_t M, int32_t r) {
     F16Ws l{};
@@ -415,6 +445,12 @@ F16Ws f16_ws(int32_t K, int32_t N, int32_t M, int32_t r) {
         const size_t small = mlr::smallm_ws_bytes(K, N, r);
         if (small > l.total) l.total = small;
     }
+    // MODULORA_F16_PLAIN (read once per process) keeps every shape on the plain kernel, for comparisons
+    static const bool force_plain = std::getenv("MODULORA_F16_PLAIN") != nullptr;
+    l.direct_fwd = !force_plain && mlr::direct_wins(K, N, M, r, false);
+    l.direct_bwd = !force_plain && mlr::direct_wins(K, N, M, r, true);
+    const size_t dir = direct_bytes(K, N, M, r, l.direct_fwd, l.direct_bwd);
+    if (dir > l.total) l.total = dir;
     return l;
 }
 // P = act F for binary16 activations (X A or dY B^T; fp32-exact products on the matrix cores): the
@@ -471,7 +507,8 @@ int modulora_f16_fwd(const modulora_qweight_f16 *w, const uint16_t *X, int32_t M
     const F16Ws l = f16_ws(w->d_in, w->d_out, M, r);
     if ((s = check_ws_f16(l, workspace, workspace_bytes)) != MODULORA_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (mlr::smallm_fwd_supported(stream_view_of(w), M)) {
+    const bool streams = stream_takes(mlr::smallm_fwd_supported(stream_view_of(w), M), w->d_in, w->d_out, M, l.direct_fwd);
+    if (streams || l.direct_fwd) {
         // a handful of tokens: the direct product with the quantized matrix (Section 3.1.2)
         mlr::SmallArgs sa{};
         sa.w = stream_view_of(w);
@@ -479,7 +516,7 @@ int modulora_f16_fwd(const modulora_qweight_f16 *w, const uint16_t *X, int32_t M
         sa.A = A; sa.B = B; sa.r = r; sa.lora_scale = lora_scale;
         sa.P_out = XA; sa.ws = workspace;
         sa.f16 = true; sa.zeros16 = w->zeros; sa.bias16 = w->bias;
-        return hip_status(mlr::launch_smallm_fwd(sa, st));
+        return hip_status(streams ? mlr::launch_smallm_fwd(sa, st) : mlr::launch_direct(sa, false, st));
     }
     float *P = nullptr;
     if (r > 0) {
@@ -502,14 +539,15 @@ int modulora_f16_bwd_input(const modulora_qweight_f16 *w, const uint16_t *dY, in
     const F16Ws l = f16_ws(w->d_in, w->d_out, M, r);
     if ((s = check_ws_f16(l, workspace, workspace_bytes)) != MODULORA_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (mlr::smallm_bwd_supported(stream_view_of(w), M)) {
+    const bool streams = stream_takes(mlr::smallm_bwd_supported(stream_view_of(w), M), w->d_in, w->d_out, M, l.direct_bwd);
+    if (streams || l.direct_bwd) {
         mlr::SmallArgs sa{};
         sa.w = stream_view_of(w);
         sa.act = dY; sa.M = M; sa.out = dX;
         sa.A = A; sa.B = B; sa.r = r; sa.lora_scale = lora_scale;
         sa.P_out = dYBt; sa.ws = workspace;
         sa.f16 = true; sa.zeros16 = w->zeros; sa.bias16 = nullptr;
-        return hip_status(mlr::launch_smallm_bwd(sa, st));
+        return hip_status(streams ? mlr::launch_smallm_bwd(sa, st) : mlr::launch_direct(sa, true, st));
     }
     float *P = nullptr;
     if (r > 0) {

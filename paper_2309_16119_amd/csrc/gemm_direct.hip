@@ -1,0 +1,667 @@
+// Dequantize-and-multiply for a few dozen to a thousand tokens: the weight goes from packed words to
+// matrix-core operands inside one wave and never through a weight tile that waves share.  Same
+// mathematics as gemm_tile.hip (ModuLoRA Figure 1: forward X What^T and backward dY What with What
+// re-materialized in 16 bits from the packed codes, plus the adapter term of eq. (3)), for both storage
+// conventions.
+//
+// Why another kernel: with 33 ... 128 tokens the tile kernels spend their time on everything but the
+// product -- four launches (projection, its sum, product, sum of slices), a weight tile stored to LDS
+// and read back by every wave, a barrier per 64 elements.  Here
+//   - a wave owns 32 output columns and all rows of a block (1 ... 4 tiles of 32), so a weight is
+//     dequantized once per row block and feeds 1 ... 4 MFMAs straight from registers.  Forward a lane holds
+//     the column's 32-code blocks as its operand needs them; backward it dequantizes the block of its
+//     weight column and the wave turns 64 x 32 weights round in 4 KB of LDS of its own, read back with
+//     the transposing LDS read (no barrier: LDS operations of one wave keep their order).
+//   - eight waves: four column groups x two halves of every 256-element chunk, so that a chunk of
+//     activations, fetched by direct global->LDS loads into a ring, is read by four waves only and a
+//     barrier falls due once per two 64-element steps.
+//   - the contraction is cut into slices to fill 256 compute units (direct_plan()); the slices' fp32
+//     results are added by the second launch, which also adds the projection's partial sums and applies
+//     the adapter term in fp32.  The projection itself is a side job of the product kernel's first
+//     microsecond, spread over its workgroups.  Two launches in all.
+// What bounds it (stamps of an instrumented build, 8192 x 8192, 3 bits): a chunk takes 1.35 us forward
+// at 64 rows -- 184 of the step's ~250 instructions per wave and step pair are the dequantization's, and
+// two waves a SIMD issue one 4-cycle operation per 2.1 ns -- and 1.9 us at 128 rows, where its 64 MFMAs
+// per SIMD need 1.05; start 2.6 us, end 1.5 ... 3 us (partial results).  Direct loads sent all at once at
+// the top of a chunk cost 0.1 us of it; plain instead of streaming stores of the results 1.5 us.
+#include <type_traits>
+
+#include "gemm_common.h"
+
+namespace mlr {
+
+namespace direct {
+typedef _Float16 half16x8 __attribute__((ext_vector_type(8)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+constexpr int THREADS = 512, NWAVES = 8;
+constexpr int CT = 128;                       // output columns of a workgroup: four waves of 32
+constexpr int CHUNK = 256;                    // contraction elements of one activation chunk
+constexpr int ROW_BYTES = CHUNK * 2;
+constexpr int SCRATCH = 32 * 1024;            // transposition buffers (backward) / projection sums
+constexpr int SETS = 4;                       // staged register sets of packed words
+template <int RT_>
+struct Geo {
+    static constexpr int RT = RT_, MT = 32 * RT;
+    static constexpr int SLOT = MT * ROW_BYTES;
+    static constexpr int SLOTS = RT <= 2 ? 4 : 2;
+    static constexpr int NA = MT / 16;                      // direct loads per thread and chunk
+    static constexpr int LDS_BYTES = SLOTS * SLOT + SCRATCH;
+    static constexpr int KEEP0 = (RT + 1) / 2;              // row tiles that the first half of the contraction's waves finish
+};
+}  // namespace direct
+
+struct DirectDev {
+    LayerView w;
+    const uint16_t *act;          // [M][C]
+    const uint16_t *zeros16;      // F16: binary16 zero points
+    const uint16_t *bias16;       // F16 forward: bias or NULL
+    int M, C, Cout;
+    int tiles_m, tiles_c, split, nch;
+    float *part;                  // [split][M][Cout]
+    int proj_parts;               // workgroups that share one row tile's projection over one slice
+    float *ppart;                 // [split * proj_parts][M][r]
+    const float *Fp;              // projection factor: forward A [C][r], backward B [r][C]
+    const float *Fo;              // output factor: forward B [r][Cout], backward A [Cout][r]
+    int r;
+    float lora_scale;
+    uint16_t *out;                // [M][Cout]
+    float *P_out;                 // [M][r] or NULL
+    // group of a 32-code block: (blk + plus) * magic / 2^32 (blk and the blocks per group < 2^15), with
+    // (0, 2^32 / d + 1) for d blocks per group and (1, 2^32 - 1) for d = 1
+    uint32_t group_plus, group_magic;
+    __device__ __forceinline__ uint32_t group_of_block(uint32_t blk) const { return __umulhi(blk + group_plus, group_magic); }
+};
+
+// The projection of 16 activation rows over contraction elements [k0, k1) (multiples of 8), all waves
+// of the workgroup together: P[row][j] = sum act[row][c] F(c, j) on the matrix cores, the fp32 factor
+// split exactly into three bfloat16 terms (binary16 activations into two).  `red`: NWAVES * RG * 256
+// floats of LDS.  Ends with every thread past its reads of `red`.
+template <bool F_IS_A, bool F16>
+__device__ __forceinline__ void direct_project(const DirectDev &d, int row0, int k0, int k1, float *dst, float *red) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+    const int i = lane & 15, cs = lane >> 4, r = d.r;
+    const int row = row0 + i < d.M ? row0 + i : d.M - 1;
+    const uint16_t *arow = d.act + (size_t)row * d.C;
+    const int steps = (k1 - k0 + 31) / 32;
+    const int s0 = steps * wave / direct::NWAVES, s1 = steps * (wave + 1) / direct::NWAVES;
+    const int RG = (r + 15) >> 4;
+    for (int g = 0; g < RG; ++g) {
+        const int j = g * 16 + i;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        constexpr int UNR = 4;
+        for (int st = s0; st < s1; st += UNR) {
+            uint4 av[UNR];
+            float f[UNR][8];
+#pragma unroll
+            for (int q = 0; q < UNR; ++q) {
+                const int c = k0 + (st + q) * 32 + cs * 8;
+                const bool ok = st + q < s1 && c < k1;
+                av[q] = make_uint4(0, 0, 0, 0);
+                if (ok) av[q] = *reinterpret_cast<const uint4 *>(arow + c);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) f[q][e] = 0.f;
+                if (ok && j < r) {
+                    if (F_IS_A) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) f[q][e] = d.Fp[(size_t)(c + e) * r + j];
+                    } else {
+                        const float4 q0 = *reinterpret_cast<const float4 *>(d.Fp + (size_t)j * d.C + c);
+                        const float4 q1 = *reinterpret_cast<const float4 *>(d.Fp + (size_t)j * d.C + c + 4);
+                        f[q][0] = q0.x; f[q][1] = q0.y; f[q][2] = q0.z; f[q][3] = q0.w;
+                        f[q][4] = q1.x; f[q][5] = q1.y; f[q][6] = q1.z; f[q][7] = q1.w;
+                    }
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < UNR; ++q) {
+                uint32_t p[3][4];
+                split3(f[q], p[0], p[1], p[2]);
+                const uint32_t ar[4] = {av[q].x, av[q].y, av[q].z, av[q].w};
+                uint32_t a2[2][4];
+                if (F16) split_f16x8(ar, a2[0], a2[1]);
+#pragma unroll
+                for (int h = 0; h < (F16 ? 2 : 1); ++h) {
+                    bf16x8 x, y;
+                    __builtin_memcpy(&x, F16 ? a2[h] : ar, 16);
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) {
+                        __builtin_memcpy(&y, p[t], 16);
+                        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, acc, 0, 0, 0);
+                    }
+                }
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) red[((wave * RG + g) * 4 + v) * 64 + lane] = acc[v];
+    }
+    __syncthreads();
+    for (int x = tid; x < RG * 256; x += direct::THREADS) {
+        const int g = x >> 8, v = (x >> 6) & 3, l = x & 63;
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < direct::NWAVES; ++w) sum += red[((w * RG + g) * 4 + v) * 64 + l];
+        const int prow = row0 + 4 * (l >> 4) + v, j = g * 16 + (l & 15);
+        if (prow < d.M && j < r) dst[(size_t)prow * r + j] = sum;
+    }
+    __syncthreads();
+}
+
+template <int BITS, bool BWD, bool F16, int RT>
+__global__ __launch_bounds__(direct::THREADS, 2) void gemm_direct_kernel(DirectDev d) {
+    using namespace direct;
+    using G = Geo<RT>;
+    constexpr int MT = G::MT, SLOT = G::SLOT, SLOTS = G::SLOTS, NA = G::NA;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+    const int cg = wave & 3, kg = wave >> 2;
+    const int N = d.w.N, C = d.C, Cout = d.Cout, M = d.M;
+
+    // linear item: row blocks fastest, then column blocks, then slices; a contiguous run per XCD
+    const int total = d.tiles_m * d.tiles_c * d.split, per_xcd = (total + 7) / 8;
+    const int item = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
+    if (item >= total) return;                 // grid padded to a multiple of 8
+    const int tm = item % d.tiles_m, rest = item / d.tiles_m;
+    const int tc = rest % d.tiles_c, slice = rest / d.tiles_c;
+    const int m0 = tm * MT, c0 = tc * CT;
+    const int ch0 = (int)((long)d.nch * slice / d.split), ch1 = (int)((long)d.nch * (slice + 1) / d.split);
+    const int ch1_full = ch1 < C / CHUNK ? ch1 : C / CHUNK;        // the last chunk of the contraction may be ragged
+    const int n_ch = ch1_full - ch0;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
+
+    // ---- activation chunks: direct loads -----------------------------------------
+    // 16-byte piece idx = i*512 + tid sits at byte 16*idx of the slot: row i*16 + tid/32, physical
+    // piece tid%32, which holds logical piece (tid%32) ^ (row & 15).
+    const int ar0 = tid >> 5, alc = (tid & 31) ^ ar0;
+    uint32_t a_voff[NA];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        int m = m0 + i * 16 + ar0;
+        if (m > M - 1) m = M - 1;
+        a_voff[i] = (uint32_t)(((size_t)(m - m0) * C + alc * 8) * 2);
+    }
+    const uint16_t *act0 = d.act + (size_t)m0 * C;
+    auto issue_a_part = [&](int c, int slot, int i) {      // c: a whole chunk of the contraction
+        load_to_lds_16(act0 + c * CHUNK, a_voff[i], lds0 + slot * SLOT + i * (THREADS * 16) + wave * 1024);
+    };
+    auto issue_a = [&](int c, int slot) {
+#pragma unroll
+        for (int i = 0; i < NA; ++i) issue_a_part(c, slot, i);
+    };
+
+    // ---- packed words of a 64-element unit p of the contraction ---------------------------------
+    // forward : lane l holds column c0 + 32 cg + l % 32, 32-code block 2 p + l / 32 of the 64 elements
+    // backward: lane l holds weight column n = 64 p + l, the 32-code block of this wave's outputs
+    const int half = lane >> 5;
+    uint32_t w_col = 0;                        // forward: the column; backward unused
+    int kb = 0;
+    uint32_t bw_g = 0;
+    if (!BWD) {
+        int n = c0 + cg * 32 + (lane & 31);
+        if (n > N - 1) n = N - 1;
+        w_col = (uint32_t)n;
+    } else {
+        kb = c0 / 32 + cg;
+        const int kb_last = Cout / 32 - 1;
+        if (kb > kb_last) kb = kb_last;
+        bw_g = d.group_of_block((uint32_t)kb);
+    }
+    struct WSet {
+        uint32_t w[BITS], sc, zp;
+    };
+    WSet ws[SETS];
+#pragma unroll
+    for (int i = 0; i < SETS; ++i) {
+#pragma unroll
+        for (int q = 0; q < BITS; ++q) ws[i].w[q] = 0;
+        ws[i].sc = ws[i].zp = 0;
+    }
+    const int last_ch = ch1_full - 1;
+    auto unit_of = [&](int t) {                // step t of this wave; past the last whole chunk that chunk's units again
+        const int c = ch0 + (t >> 1);
+        return (c < last_ch ? c : last_ch) * (CHUNK / 64) + kg * 2 + (t & 1);
+    };
+    // Addresses are a uniform base per word row (kept) plus one 32-bit offset per lane, so that a unit
+    // costs a handful of scalar operations: in a loop bound by issue those count too.  (Offsets stay
+    // below 2^32 bytes: direct_wins().)
+    const uint32_t *wrow[BITS];
+#pragma unroll
+    for (int q = 0; q < BITS; ++q) wrow[q] = d.w.qweight + (size_t)(BWD ? kb * BITS + q : q) * N;
+    const uint16_t *sbase = d.w.scales + (BWD ? (size_t)bw_g * N : (size_t)0), *zbase16 = d.zeros16 + (BWD ? (size_t)bw_g * N : (size_t)0);
+    const uint8_t *zbase8 = d.w.zeros + (BWD ? (size_t)bw_g * N : (size_t)0);
+    // ragged: the unit holds the end of the contraction (lanes past it repeat valid words)
+    auto load_w = [&](WSet &s, int p, auto ragged) {
+        constexpr bool RAGGED = decltype(ragged)::value;
+        uint32_t woff, soff;
+        if (!BWD) {
+            const bool both = !RAGGED || p * 64 + 32 < C;          // the upper block exists
+            woff = (uint32_t)p * (uint32_t)(2 * BITS * N * 4) + (both && half ? (uint32_t)(BITS * N) + w_col : w_col) * 4u;
+            const uint32_t g0 = d.group_of_block((uint32_t)p * 2u), g1 = both ? d.group_of_block((uint32_t)p * 2u + 1u) : g0;
+            soff = (half ? g1 * (uint32_t)N : g0 * (uint32_t)N) + w_col;
+        } else {
+            soff = (uint32_t)(p * 64 + lane);
+            if (RAGGED && soff > (uint32_t)(N - 1)) soff = (uint32_t)(N - 1);
+            woff = soff * 4;
+        }
+#pragma unroll
+        for (int q = 0; q < BITS; ++q) aload_b32(s.w[q], wrow[q], woff);
+        aload_u16(s.sc, sbase, soff * 2);
+        if (F16) aload_u16(s.zp, zbase16, soff * 2);
+        else aload_u8(s.zp, zbase8, soff);
+    };
+    constexpr int WL = BITS + 2;               // load instructions of one load_w()
+    auto tie_set = [&](WSet &s) {
+#pragma unroll
+        for (int q = 0; q < BITS; ++q) asm volatile("" : "+v"(s.w[q])::"memory");
+        asm volatile("" : "+v"(s.sc), "+v"(s.zp)::"memory");
+    };
+    auto wait_vm = [&](auto keep) {
+        constexpr int KEEP = decltype(keep)::value;
+        static_assert(KEEP < 64, "vmcnt is a 6-bit counter");
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(KEEP) : "memory");
+    };
+    const DqMasks masks = make_dq_masks<BITS>();
+
+    // ---- operands ------------------------------------------------------------------
+    struct BFrag {
+        uint32_t v[4][4];                      // four 16-deep MFMA steps
+    };
+    BFrag bq[2];
+    unsigned char *tbuf = smem + SLOTS * SLOT + wave * 4096;       // backward: 64 n x 32 k, private to the wave
+    const int t_wr = lane * 64, t_swz = (lane >> 2) & 3;
+    const int ti = lane & 15, tg = (lane >> 4) & 1;
+    int t_rd[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+        t_rd[e] = (8 * half + 4 * e + (ti >> 2)) * 64 + (((2 * tg + ((ti & 3) >> 1)) ^ ((2 * half + e) & 3)) << 4) + 8 * (ti & 1);
+    // quarter j of the staged block -> operand registers (forward) or the wave's transposition buffer
+    auto dequant_part = [&](BFrag &b, const WSet &s, const DqPair &dq, int j) {
+        uint32_t o[4];
+        dequant_quarter_pairs<BITS, F16>(s.w, j, dq, masks, o);
+        if (!BWD) {
+#pragma unroll
+            for (int x = 0; x < 4; ++x) {
+                asm volatile("" : "+v"(o[x]));       // computed here, between the MFMAs, not where it is used
+                b.v[j][x] = o[x];
+            }
+        } else {
+            *reinterpret_cast<uint4 *>(tbuf + t_wr + ((j ^ t_swz) << 4)) = make_uint4(o[0], o[1], o[2], o[3]);
+        }
+    };
+    auto transposed_read = [&](BFrag &b) {
+        // the wave's own stores above are read by other lanes of it: LDS operations of a wave keep their order
+        asm volatile("" ::: "memory");
+        typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+        typedef __attribute__((address_space(3))) unsigned char lds_byte;
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)((lds_byte *)(tbuf + t_rd[e] + s * 1024)));
+                __builtin_memcpy(&b.v[s][2 * e], &v, 8);
+            }
+        asm volatile("" ::: "memory");
+    };
+    f32x16 acc[RT];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][v] = 0.f;
+
+    // 16-byte piece of MFMA step j: forward 16 kg + 8 u + 4 half + j, backward 16 kg + 8 u + 2 j + half
+    const int a_lane = (lane & 31) * ROW_BYTES + kg * 256 + (((BWD ? half : 4 * half) ^ (lane & 15)) << 4);
+    struct AFrag {
+        bf16x8 f[RT];
+    };
+    auto load_a = [&](AFrag &f, int slot_off, int u, int j) {
+        const int off = slot_off + (a_lane ^ ((8 * u + (BWD ? 2 * j : j)) << 4));
+#pragma unroll
+        for (int i = 0; i < RT; ++i) f.f[i] = *reinterpret_cast<const bf16x8 *>(smem + off + i * 32 * ROW_BYTES);
+    };
+    auto mul = [&](const AFrag &a, const uint32_t *b) {
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {
+            if (F16) {
+                half16x8 x, y;
+                __builtin_memcpy(&x, &a.f[i], 16);
+                __builtin_memcpy(&y, b, 16);
+                acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x, y, acc[i], 0, 0, 0);
+            } else {
+                bf16x8 y;
+                __builtin_memcpy(&y, b, 16);
+                acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.f[i], y, acc[i], 0, 0, 0);
+            }
+        }
+    };
+
+    // ---- prologue --------------------------------------------------------------------
+    const std::integral_constant<bool, false> whole;
+    if (n_ch > 0) {
+        load_w(ws[0], unit_of(0), whole);
+        load_w(ws[1], unit_of(1), whole);
+        load_w(ws[2], unit_of(2), whole);
+#pragma unroll
+        for (int sl = 0; sl < SLOTS - 1; ++sl) issue_a(ch0 + sl < last_ch ? ch0 + sl : last_ch, sl);
+    }
+    if (d.r > 0) {
+        // this slice's share of the projection while the first chunks are on their way: 16-row tile
+        // q of the row block and part x of the slice by the workgroup of column block q + 2 RT x
+        const int k1 = ch1 * CHUNK < C ? ch1 * CHUNK : C;
+        const int steps = (k1 - ch0 * CHUNK + 31) / 32;
+        for (int q = tc; q < 2 * RT * d.proj_parts; q += d.tiles_c) {
+            const int row0 = m0 + 16 * (q % (2 * RT)), x = q / (2 * RT);
+            if (row0 >= M) continue;
+            const int ks = ch0 * CHUNK + 32 * (steps * x / d.proj_parts);
+            const int ke = x + 1 == d.proj_parts ? k1 : ch0 * CHUNK + 32 * (steps * (x + 1) / d.proj_parts);
+            direct_project<!BWD, F16>(d, row0, ks, ke, d.ppart + (size_t)(slice * d.proj_parts + x) * M * d.r,
+                                      reinterpret_cast<float *>(smem + SLOTS * SLOT));
+        }
+    }
+    if (n_ch > 0) {
+        wait_vm(std::integral_constant<int, 0>());
+        tie_set(ws[0]);
+        tie_set(ws[1]);
+        tie_set(ws[2]);
+        {
+            const DqPair dq = make_dq_pair<BITS, F16>(ws[0].sc, ws[0].zp);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) dequant_part(bq[0], ws[0], dq, j);
+            if (BWD) transposed_read(bq[0]);
+        }
+        load_w(ws[3], unit_of(3), whole);
+        load_w(ws[0], unit_of(4), whole);
+        __syncthreads();
+
+        // ---- steady state --------------------------------------------------------------
+        // Step t multiplies with the operands of unit t (registers bq[t & 1]), turns the words of unit
+        // t + 1 (set (t + 1) % 4) into the other operand registers and re-fills that set with unit t + 5.
+        // Loads return in order.  Younger than the words of unit t + 1 are those of t + 2 .. t + 4 and
+        // the activation chunks sent since (each during the first of a chunk's two steps, spread over
+        // it); younger than the chunk that the next step needs are the words and chunks issued since.
+        constexpr int A_KEEP = SLOTS == 2 ? 2 * WL : 6 * WL + 2 * NA;
+        int slot = 0;                              // ring slot of the current chunk
+        for (int cc = 0; cc < n_ch; cc += 2) {
+#pragma unroll
+            for (int uu = 0; uu < 2; ++uu) {
+                if (cc + uu < n_ch) {
+                    const int fill = ch0 + cc + uu + SLOTS - 1;
+                    const int fill_c = fill < last_ch ? fill : last_ch, fill_slot = (slot + SLOTS - 1) % SLOTS;
+                    const int slot_off = slot * SLOT;
+                    AFrag f[2];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        const int t = 2 * (cc + uu) + u;
+                        WSet &s = ws[(2 * uu + u + 1) & 3];
+                        if (u == 0) wait_vm(std::integral_constant<int, 3 * WL + NA>());
+                        else wait_vm(std::integral_constant<int, 3 * WL + 2 * NA>());
+                        tie_set(s);
+                        const DqPair dq = make_dq_pair<BITS, F16>(s.sc, s.zp);
+                        const BFrag &bc = bq[u];
+                        BFrag &bn = bq[u ^ 1];
+                        if (u == 0) load_a(f[0], slot_off, 0, 0);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            if (j < 3 || u == 0) load_a(f[(j + 1) & 1], slot_off, j < 3 ? u : 1, (j + 1) & 3);
+                            if (u == 0) {
+#pragma unroll
+                                for (int i = 0; i < NA; ++i)
+                                    if (i % 4 == j) issue_a_part(fill_c, fill_slot, i);
+                            }
+                            mul(f[j & 1], bc.v[j]);
+                            if (!BWD) {
+                                dequant_part(bn, s, dq, j);
+                            } else if (j < 3) {
+                                // all of the block is stored by the third MFMA step, read back under the fourth
+                                dequant_part(bn, s, dq, j);
+                                if (j == 2) dequant_part(bn, s, dq, 3);
+                            } else {
+                                transposed_read(bn);
+                            }
+                            if (BWD && j == 3) continue;
+                            // the LDS reads first, then the quarter's ~20 VALU operations spread over the MFMAs
+                            if (j < 3 || u == 0) __builtin_amdgcn_sched_group_barrier(0x100, RT, 0);
+#pragma unroll
+                            for (int i = 0; i < RT; ++i) {
+                                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                                __builtin_amdgcn_sched_group_barrier(0x002, 24 / RT, 0);
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        load_w(s, unit_of(t + 5), whole);
+                    }
+                    wait_vm(std::integral_constant<int, A_KEEP>());
+                    __syncthreads();
+                    slot = (slot + 1) % SLOTS;
+                }
+            }
+        }
+        // fetches past the end of the slice are still in flight, towards LDS and towards the sets
+        wait_vm(std::integral_constant<int, 0>());
+#pragma unroll
+        for (int i = 0; i < SETS; ++i) tie_set(ws[i]);
+        __syncthreads();
+    }
+    // ---- a ragged last chunk: activation pieces past the end are taken as zero ------------------
+    if (ch1 > ch1_full) {
+        const int k = ch1_full * CHUNK, over = k + alc * 8 - (C - 8);
+        const uint32_t back = over > 0 ? (uint32_t)over * 2u : 0u;      // such pieces re-read the last one of the row
+#pragma unroll
+        for (int i = 0; i < NA; ++i) load_to_lds_16(act0 + k, a_voff[i] - back, lds0 + i * (THREADS * 16) + wave * 1024);
+        wait_vm(std::integral_constant<int, 0>());
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int p = ch1_full * (CHUNK / 64) + kg * 2 + u, left = C - p * 64;      // wave-uniform
+            if (left > 0) {
+                load_w(ws[0], p, std::integral_constant<bool, true>());
+                wait_vm(std::integral_constant<int, 0>());
+                tie_set(ws[0]);
+                const DqPair dq = make_dq_pair<BITS, F16>(ws[0].sc, ws[0].zp);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) dequant_part(bq[0], ws[0], dq, j);
+                if (BWD) transposed_read(bq[0]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    AFrag f;
+                    load_a(f, 0, u, j);
+                    const bool ok = (BWD ? 16 * j + 8 * half : 32 * half + 8 * j) < left;
+                    const bf16x8 zero = {};
+#pragma unroll
+                    for (int i = 0; i < RT; ++i) f.f[i] = ok ? f.f[i] : zero;
+                    mul(f, bq[0].v[j]);
+                }
+            }
+        }
+        __syncthreads();
+    }
+
+    // ---- the two halves of the contraction meet in LDS: waves of half kg keep row tiles
+    // [0, KEEP0) or [KEEP0, RT) and hand the others to their partner
+    constexpr int KEEP0 = G::KEEP0;
+    float4 *red = reinterpret_cast<float4 *>(smem);
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        if ((i >= KEEP0) == (kg == 1)) continue;
+        const int dstw = wave ^ 4, x = i >= KEEP0 ? i - KEEP0 : i;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            red[((dstw * KEEP0 + x) * 4 + q) * 64 + lane] = make_float4(acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]);
+    }
+    __syncthreads();
+    const int col = c0 + cg * 32 + (lane & 31);
+    float *part = d.part + (size_t)slice * M * Cout + col;
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+        if ((i >= KEEP0) != (kg == 1)) continue;
+        const int x = i >= KEEP0 ? i - KEEP0 : i;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const float4 o = red[((wave * KEEP0 + x) * 4 + q) * 64 + lane];
+            const float o4[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = m0 + i * 32 + 8 * q + 4 * half + v;
+                if (row < M && col < Cout) __builtin_nontemporal_store(acc[i][4 * q + v] + o4[v], part + (size_t)row * Cout);
+            }
+        }
+    }
+}
+
+// Sum of the slices' partial results and of the projection's, the adapter term, the bias, one rounding.
+// A workgroup finishes 32 rows x 64 columns; a thread eight adjacent columns of one row.
+template <bool BWD, bool F16>
+__global__ __launch_bounds__(256) void gemm_direct_finish_kernel(DirectDev d) {
+    extern __shared__ __attribute__((aligned(16))) float fin_lds[];
+    const int tid = threadIdx.x, r = d.r, M = d.M, Cout = d.Cout;
+    float *Ps = fin_lds, *Fs = fin_lds + 32 * r;            // [32][r], [r][64]
+    const int m0 = blockIdx.y * 32, c0 = blockIdx.x * 64;
+    const int m = m0 + (tid >> 3), cl = (tid & 7) * 8, col = c0 + cl;
+    const bool mine = m < M && col < Cout;                  // Cout is a multiple of 8
+    const float *src = d.part + (mine ? (size_t)m * Cout + col : (size_t)0);
+    const size_t stride = (size_t)M * Cout;
+    constexpr int SB = 4;
+    float4 v0[SB], v1[SB];
+    auto load_slices = [&](int q0) {
+#pragma unroll
+        for (int u = 0; u < SB; ++u)
+            if (q0 + u < d.split) {
+                v0[u] = *reinterpret_cast<const float4 *>(src + (size_t)(q0 + u) * stride);
+                v1[u] = *reinterpret_cast<const float4 *>(src + (size_t)(q0 + u) * stride + 4);
+            }
+    };
+    float y[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    auto add_slices = [&](int q0) {
+#pragma unroll
+        for (int u = 0; u < SB; ++u)
+            if (q0 + u < d.split) {
+                y[0] += v0[u].x; y[1] += v0[u].y; y[2] += v0[u].z; y[3] += v0[u].w;
+                y[4] += v1[u].x; y[5] += v1[u].y; y[6] += v1[u].z; y[7] += v1[u].w;
+            }
+    };
+    load_slices(0);
+    if (r > 0) {
+        const int rows = M - m0 < 32 ? M - m0 : 32;
+        for (int x = tid; x < rows * r; x += 256) {
+            const float *p = d.ppart + (size_t)m0 * r + x;
+            float sum = 0.f;
+#pragma unroll 8
+            for (int s = 0; s < d.split * d.proj_parts; ++s) sum += p[(size_t)s * M * r];
+            Ps[x] = sum;
+            if (blockIdx.x == 0 && d.P_out != nullptr) d.P_out[(size_t)m0 * r + x] = sum;
+        }
+        const int cols = Cout - c0 < 64 ? Cout - c0 : 64;
+        if (!BWD) {
+            for (int x = tid; x < r * 64; x += 256) {
+                const int c = x & 63, j = x >> 6;
+                if (c < cols) Fs[x] = d.Fo[(size_t)j * Cout + c0 + c];
+            }
+        } else {
+            for (int x = tid; x < cols * r; x += 256) {
+                const int c = x / r, j = x - c * r;
+                Fs[j * 64 + c] = d.Fo[(size_t)c0 * r + x];
+            }
+        }
+        __syncthreads();
+    }
+    add_slices(0);
+    for (int q0 = SB; q0 < d.split; q0 += SB) { load_slices(q0); add_slices(q0); }
+    if (!mine) return;
+    float l[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < r; ++j) {
+        const float p = Ps[(tid >> 3) * r + j];
+        const float4 f0 = *reinterpret_cast<const float4 *>(Fs + j * 64 + cl), f1 = *reinterpret_cast<const float4 *>(Fs + j * 64 + cl + 4);
+        l[0] = __builtin_fmaf(p, f0.x, l[0]); l[1] = __builtin_fmaf(p, f0.y, l[1]);
+        l[2] = __builtin_fmaf(p, f0.z, l[2]); l[3] = __builtin_fmaf(p, f0.w, l[3]);
+        l[4] = __builtin_fmaf(p, f1.x, l[4]); l[5] = __builtin_fmaf(p, f1.y, l[5]);
+        l[6] = __builtin_fmaf(p, f1.z, l[6]); l[7] = __builtin_fmaf(p, f1.w, l[7]);
+    }
+    if (F16 && !BWD && d.bias16 != nullptr) {               // the frozen layer's bias: forward only
+        const uint4 bw = *reinterpret_cast<const uint4 *>(d.bias16 + col);
+        const uint32_t w4[4] = {bw.x, bw.y, bw.z, bw.w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            y[2 * q] += half_bits_to_float((uint16_t)(w4[q] & 0xFFFFu));
+            y[2 * q + 1] += half_bits_to_float((uint16_t)(w4[q] >> 16));
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 8; ++c) y[c] = __builtin_fmaf(d.lora_scale, l[c], y[c]);
+    const uint4 o = make_uint4(pack_pair<F16>(y[0], y[1]), pack_pair<F16>(y[2], y[3]), pack_pair<F16>(y[4], y[5]), pack_pair<F16>(y[6], y[7]));
+    *reinterpret_cast<uint4 *>(d.out + (size_t)m * Cout + col) = o;
+}
+
+namespace {
+template <int BITS, bool BWD, bool F16, int RT>
+hipError_t launch_direct_rt(const DirectDev &d, hipStream_t stream) {
+    auto kern = gemm_direct_kernel<BITS, BWD, F16, RT>;
+    constexpr size_t LDS = (size_t)direct::Geo<RT>::LDS_BYTES;
+    static bool configured[64] = {};
+    const hipError_t e = ensure_lds_limit(reinterpret_cast<const void *>(kern), LDS, configured);
+    if (e != hipSuccess) return e;
+    const int blocks = (d.tiles_m * d.tiles_c * d.split + 7) / 8 * 8;
+    launch_kernel(F16 ? (BWD ? "f16_gemm_bwd_direct" : "f16_gemm_fwd_direct") : (BWD ? "gemm_bwd_direct" : "gemm_fwd_direct"), kern, blocks,
+                  direct::THREADS, LDS, stream, d);
+    return hipGetLastError();
+}
+template <int BITS, bool BWD, bool F16>
+hipError_t launch_direct_bits(const DirectDev &d, int rt, hipStream_t stream) {
+    switch (rt) {
+        case 1: return launch_direct_rt<BITS, BWD, F16, 1>(d, stream);
+        case 2: return launch_direct_rt<BITS, BWD, F16, 2>(d, stream);
+        case 3: return launch_direct_rt<BITS, BWD, F16, 3>(d, stream);
+        default: return launch_direct_rt<BITS, BWD, F16, 4>(d, stream);
+    }
+}
+template <bool BWD, bool F16>
+hipError_t launch_direct_any(const DirectDev &d, int rt, hipStream_t stream) {
+    hipError_t e;
+    switch (d.w.bits) {
+        case 2: e = launch_direct_bits<2, BWD, F16>(d, rt, stream); break;
+        case 3: e = launch_direct_bits<3, BWD, F16>(d, rt, stream); break;
+        default: e = launch_direct_bits<4, BWD, F16>(d, rt, stream); break;
+    }
+    if (e != hipSuccess) return e;
+    const size_t lds = (size_t)(32 + 64) * d.r * sizeof(float);          // at most 24 KB
+    launch_kernel(F16 ? (BWD ? "f16_gemm_bwd_direct_fixup" : "f16_gemm_fwd_direct_fixup")
+                      : (BWD ? "gemm_bwd_direct_fixup" : "gemm_fwd_direct_fixup"),
+                  gemm_direct_finish_kernel<BWD, F16>, dim3((d.Cout + 63) / 64, (d.M + 31) / 32), 256, lds, stream, d);
+    return hipGetLastError();
+}
+}  // namespace
+
+bool direct_wins(int K, int N, int M, int r, bool backward) {
+    const size_t elements = (size_t)K * N;
+    if (M > 1024 || elements < ((size_t)1 << 23) || elements > ((size_t)1 << 32)) return false;
+    const int C = backward ? N : K, Cout = backward ? K : N;
+    double us;
+    const DirectPlan p = direct_plan(M, C, Cout, backward, &us);
+    const bool one_round = (long)p.tiles_m * p.tiles_c * p.split <= 256;
+    const double margin = one_round ? 1.1 : (M <= 128 ? 1.2 : 1.3);
+    return us * margin < gemm_tile_us(M, C, Cout) + (r > 0 ? 9.0 : 0.0);
+}
+
+hipError_t launch_direct(const SmallArgs &a, bool backward, hipStream_t stream) {
+    const int C = backward ? a.w.N : a.w.K, Cout = backward ? a.w.K : a.w.N;
+    const DirectPlan p = direct_plan(a.M, C, Cout, backward);
+    DirectDev d;
+    d.w = a.w;
+    d.act = a.act;
+    d.zeros16 = a.zeros16;
+    d.bias16 = a.bias16;
+    d.M = a.M; d.C = C; d.Cout = Cout;
+    d.tiles_m = p.tiles_m; d.tiles_c = p.tiles_c; d.split = p.split; d.nch = p.chunks; d.proj_parts = p.proj_parts;
+    d.part = static_cast<float *>(a.ws);
+    d.ppart = reinterpret_cast<float *>(static_cast<char *>(a.ws) + p.partial_bytes(a.M, Cout));
+    d.Fp = backward ? a.B : a.A;
+    d.Fo = backward ? a.A : a.B;
+    d.r = a.r;
+    d.lora_scale = a.lora_scale;
+    d.out = a.out;
+    d.P_out = a.P_out;
+    const uint32_t bpg = (uint32_t)(a.w.group / 32);
+    d.group_plus = bpg > 1 ? 0u : 1u;
+    d.group_magic = bpg > 1 ? (uint32_t)((1ull << 32) / bpg) + 1u : 0xFFFFFFFFu;
+    if (a.f16) return backward ? launch_direct_any<true, true>(d, p.rt, stream) : launch_direct_any<false, true>(d, p.rt, stream);
+    return backward ? launch_direct_any<true, false>(d, p.rt, stream) : launch_direct_any<false, false>(d, p.rt, stream);
+}
+
+}  // namespace mlr

@@ -653,37 +653,44 @@ static TilePick forced_pick() {
     return (TilePick)cached;
 }
 
+// Estimated time of the whole grid in microseconds, from measured times of one 64-deep
+// contraction step of each variant: alone on a CU (t1) and sharing it with a second
+// workgroup (t2), times how often the 256 CUs (x occupancy) are refilled.  The 256 x 256
+// kernel cuts the tiles of its last, partial round into slices of the contraction
+// (BigPlan); that round then costs 1/split of a round plus the traffic of the partial
+// tiles (written once, read once) and one more launch.
+// (any token count: a 32-row tile kernel for M <= 32 measured 1.2 us per step, more than any of these)
+static TilePick cheapest_pick(int M, int C, int Cout, double *us) {
+    struct Variant { TilePick pick; int mt, ct, occ; double t1, t2; };
+    const Variant vs[5] = {{PICK_MID, 256, 128, 2, 1.46, 1.95},
+                           {PICK_M128, 128, 128, 2, 0.97, 1.40},
+                           {PICK_M64, 64, 128, 2, 0.75, 1.10},
+                           {PICK_M64K, 64, 128, 1, 0.62, 0.62},
+                           {PICK_T128S, 128, 64, 1, 0.48, 0.48}};   // gemm_mid.hip
+    const double steps = (double)C / 64.0;
+    const BigPlan bp = big_plan(M, C, Cout);
+    double best = ((double)(bp.full / 256) + (bp.tail ? 1.0 / bp.split : 0.0)) * (bp.mt == 128 ? 1.0 : 1.83) * steps;
+    if (bp.split > 1) best += (bp.mt == 128 ? 12.0 : 9.0) + (double)bp.partial_bytes() / 4.0e6;
+    TilePick pick = PICK_BIG;
+    for (const Variant &v : vs) {
+        const long tiles = (long)((M + v.mt - 1) / v.mt) * ((Cout + v.ct - 1) / v.ct);
+        const double cost = steps * (tiles <= 256 ? v.t1 : (double)((tiles + 256 * v.occ - 1) / (256 * v.occ)) * v.t2);
+        if (cost < best) { best = cost; pick = v.pick; }
+    }
+    if (us) *us = best;
+    return pick;
+}
+double gemm_tile_us(int M, int C, int Cout) {
+    if (forced_pick() != PICK_AUTO) return 0.0;      // a forced tile kernel is always the cheapest way
+    double us;
+    cheapest_pick(M, C, Cout, &us);
+    return us;
+}
+
 template <int BITS, bool BWD>
 static hipError_t launch_bits_dir(const GemmArgs &a, hipStream_t stream) {
-    const int Cout = BWD ? a.w.K : a.w.N;
     TilePick pick = forced_pick();
-    if (pick == PICK_AUTO) {
-        {   // (any token count: a 32-row tile kernel for M <= 32 measured 1.2 us per step, more than any of these)
-            // Estimated time of the whole grid in microseconds, from measured times of one 64-deep
-            // contraction step of each variant: alone on a CU (t1) and sharing it with a second
-            // workgroup (t2), times how often the 256 CUs (x occupancy) are refilled.  The 256 x 256
-            // kernel cuts the tiles of its last, partial round into slices of the contraction
-            // (BigPlan); that round then costs 1/split of a round plus the traffic of the partial
-            // tiles (written once, read once) and one more launch.
-            struct Variant { TilePick pick; int mt, ct, occ; double t1, t2; };
-            const Variant vs[5] = {{PICK_MID, 256, 128, 2, 1.46, 1.95},
-                                   {PICK_M128, 128, 128, 2, 0.97, 1.40},
-                                   {PICK_M64, 64, 128, 2, 0.75, 1.10},
-                                   {PICK_M64K, 64, 128, 1, 0.62, 0.62},
-                                   {PICK_T128S, 128, 64, 1, 0.48, 0.48}};   // gemm_mid.hip
-            const int C = BWD ? a.w.N : a.w.K;
-            const double steps = (double)C / 64.0;
-            const BigPlan bp = big_plan(a.M, C, Cout);
-            double best = ((double)(bp.full / 256) + (bp.tail ? 1.0 / bp.split : 0.0)) * (bp.mt == 128 ? 1.0 : 1.83) * steps;
-            if (bp.split > 1) best += (bp.mt == 128 ? 12.0 : 9.0) + (double)bp.partial_bytes() / 4.0e6;
-            pick = PICK_BIG;
-            for (const Variant &v : vs) {
-                const long tiles = (long)((a.M + v.mt - 1) / v.mt) * ((Cout + v.ct - 1) / v.ct);
-                const double cost = steps * (tiles <= 256 ? v.t1 : (double)((tiles + 256 * v.occ - 1) / (256 * v.occ)) * v.t2);
-                if (cost < best) { best = cost; pick = v.pick; }
-            }
-        }
-    }
+    if (pick == PICK_AUTO) pick = cheapest_pick(a.M, BWD ? a.w.N : a.w.K, BWD ? a.w.K : a.w.N, nullptr);
     switch (pick) {
         case PICK_MID:
             return launch_variant<BITS, BWD, 256, 256, 128, 128, 64, 2, 0>(

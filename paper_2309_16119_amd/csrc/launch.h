@@ -285,4 +285,56 @@ size_t smallm_fwd_ws_bytes(const LayerView &w, int r);    // what launch_smallm_
 hipError_t launch_smallm_fwd(const SmallArgs &a, hipStream_t stream);
 hipError_t launch_smallm_bwd(const SmallArgs &a, hipStream_t stream);
 
+// ---- gemm_direct.hip: a few dozen to a few hundred tokens -------------------------
+struct DirectPlan {
+    int rt, tiles_m, tiles_c, chunks, split;   // row tiles of 32 per row block, grid, chunks of 256 of the contraction, slices
+    int proj_parts;  // workgroups that share the projection of 16 rows over one slice
+    // fp32 results of the slices, then the projection's
+    size_t partial_bytes(int M, int Cout) const { return ((size_t)split * M * Cout * 4 + 255) & ~(size_t)255; }
+    size_t ws_bytes(int M, int Cout, int r) const { return partial_bytes(M, Cout) + (((size_t)split * proj_parts * M * r * 4 + 255) & ~(size_t)255); }
+};
+// The split of the contraction with the smallest estimated time, in microseconds (`us`).  The model and
+// its constants are a least-squares fit (6 % rms) to 1080 timed calls: six layers of 4096 x 4096 to
+// 8192 x 22016, 12 ... 768 tokens, both directions, 1 ... 16 slices; over them the slice count it picks
+// is on average 0.5 % and at most 10 % slower than the best one.  A round of 256 workgroups costs
+// `chunk` per chunk of 256 elements of the longest slice (by row tiles and direction: issue-bound up to
+// 64 rows, matrix cores and issue beyond; backward also transposes) plus its start; the slices' fp32
+// results are written and read once at 4 TB/s; 9.5 is both launches and the sum.
+inline DirectPlan direct_plan(int M, int C, int Cout, bool backward, double *us = nullptr) {
+    DirectPlan p;
+    p.tiles_m = (M + 127) / 128;
+    p.rt = ((M + p.tiles_m - 1) / p.tiles_m + 31) / 32;
+    p.tiles_m = (M + 32 * p.rt - 1) / (32 * p.rt);
+    p.tiles_c = (Cout + 127) / 128;
+    p.chunks = (C + 255) / 256;
+    const double chunk[2][4] = {{0.91, 1.15, 1.33, 1.72}, {1.23, 1.49, 1.76, 2.10}}, start[4] = {2.0, 1.2, 0.6, 0.0};
+    const long tiles = (long)p.tiles_m * p.tiles_c;
+    p.split = 1;
+    double best = 1e30;
+    for (int s = 1; s <= 16 && (s == 1 || p.chunks / s >= 2); ++s) {
+        const double rounds = (double)((tiles * s + 255) / 256);
+        const double cost = 9.5 + rounds * ((p.chunks + s - 1) / s * chunk[backward][p.rt - 1] + start[p.rt - 1]) +
+                            (double)s * M * Cout * (8.0 / 4.0e6);
+        if (cost < best) { best = cost; p.split = s; }
+    }
+    if (us) *us = best;
+    p.proj_parts = p.tiles_c / (2 * p.rt);
+    if (p.proj_parts > 32 / p.split) p.proj_parts = 32 / p.split;
+    if (p.proj_parts < 1) p.proj_parts = 1;
+    return p;
+}
+// Whether gemm_direct.hip is the quicker way for this shape and direction, by its own estimate against
+// that of the tile kernels (gemm_tile_us()) plus 9 us for their projection launches, where there is an
+// adapter.  The margins (1.1 where every workgroup runs at once, 1.2 and 1.3 beyond: the estimates
+// drift apart as many rounds lower the clock) lose 0.35 % on average to always taking the quicker side,
+// over eight layers of 2048 x 4096 to 8192 x 22016 and 33 ... 1024 tokens (192 timed pairs), and never
+// take the direct kernel where it is more than 5 % the slower one.  Measured, us a call forward /
+// backward, r = 8: 8192 x 8192, 48 tokens 42 / 43 -> 23 / 26, 128 tokens 42 / 42 -> 30 / 33; 4096 x 4096,
+// 512 tokens 37 / 36 -> 30 / 33; beyond the line 8192 x 22016, 512 tokens: 193 with tiles, 225 direct.
+// Layers under 2^23 weights keep the tile kernels (a few us either way); over 2^32 the kernel's 32-bit
+// offsets would overflow.
+bool direct_wins(int K, int N, int M, int r, bool backward);
+double gemm_tile_us(int M, int C, int Cout);      // gemm_tile.hip: estimated time of the cheapest tile kernel
+hipError_t launch_direct(const SmallArgs &a, bool backward, hipStream_t stream);
+
 }  // namespace mlr

@@ -1,0 +1,132 @@
+"""The kernel for a few dozen to a thousand tokens (gemm_direct.hip) where it can go wrong: row blocks of
+one to four tiles of 32 rows and more than one block, outputs that end inside a column block, contractions
+that end inside a chunk of 256, a step of 64 or a half of one, groups of one 32-code block up to the whole
+row, every rank class, slices; both directions, both storage conventions, against the two oracles."""
+import os
+import re
+import subprocess
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from oracle import paper_literal as pl
+from paper_2309_16119_amd import binding as b
+from paper_2309_16119_amd import build, synth
+
+from test_kernel_resources import _hipcc
+
+# bits, d_in, d_out, tokens, rank, group
+SHAPES = [
+    (3, 4096, 2056, 33, 8, 128),        # two row tiles; backward contraction ends 8 elements into a chunk
+    (4, 4256, 4104, 65, 17, 224),       # three row tiles; forward contraction ends in half a step
+    (2, 2080, 4104, 100, 5, 32),        # four row tiles; a group per 32-code block
+    (3, 4160, 2568, 129, 64, 4160),     # two row blocks; one group per row
+    (4, 4128, 2304, 256, 16, 96),       # odd number of blocks per group
+    (2, 4128, 8200, 100, 0, 32),        # no adapter
+    (3, 4096, 4096, 512, 8, 128),       # four row blocks
+    (3, 8192, 2624, 20, 8, 128),        # one row tile, instead of two passes of a streaming kernel
+    (4, 4096, 2104, 7, 33, 128),        # a handful of tokens that the backward streaming kernel does not take
+    (3, 288, 32768, 40, 8, 288),        # an output of little more than two column blocks (backward only)
+]
+
+
+def _ran(call, conv, direction):
+    b.modulora_profile_begin()
+    out = call()
+    torch.cuda.synchronize()
+    names = set(b.modulora_profile_end())
+    return out, (("f16_gemm_" if conv == "f16" else "gemm_") + direction + "_direct") in names
+
+
+def _close(got, ref, rel, n_sum):
+    got = got.float().cpu().numpy().astype(np.float64)
+    tol = rel * np.abs(ref) + (4e-7 * np.sqrt(n_sum) + 2e-5) * np.abs(ref).max()
+    assert np.all(np.abs(got - ref) <= tol), float(np.abs(got - ref).max())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("conv", ["bf16", "f16"])
+@pytest.mark.parametrize("bits,K,N,M,r,group", SHAPES)
+def test_against_the_oracle(bits, K, N, M, r, group, conv):
+    cfg = synth.LayerConfig("t", K, N, bits, group, M, r, seed=77)
+    s, f16 = 2.0, conv == "f16"
+    if f16:
+        L = synth.make_layer_f16(cfg)
+        w = b.QWeightF16.from_numpy(L["qweight"], L["scales"], L["zeros_f16"], L["bias"], K, N, bits, group)
+        act = lambda x: torch.from_numpy(np.ascontiguousarray(x).view(np.int16)).cuda().view(torch.float16)
+        oa = (L["qweight"], L["scales"], L["zeros_f16"], K, N, bits, group)
+        fwd, bwd, rel = b.modulora_f16_fwd, b.modulora_f16_bwd_input, 2.0 ** -10
+    else:
+        L = synth.make_layer(cfg)
+        w = b.QWeight.from_numpy(L["qweight"], L["scales"], L["zeros"], K, N, bits, group)
+        act = lambda x: torch.from_numpy(np.ascontiguousarray(x).view(np.int16)).cuda().view(torch.bfloat16)
+        oa = (L["qweight"], L["scales"], L["zeros"], K, N, bits, group)
+        fwd, bwd, rel = b.modulora_fwd, b.modulora_bwd_input, 2.0 ** -8
+    A, B = (L["A"], L["B"]) if r else (None, None)
+    Ad, Bd = (torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()) if r else (None, None)
+    X, dY = act(L["X"]), act(L["dY"])
+    nan = lambda cols: torch.full((M, cols), float("nan"), dtype=X.dtype, device="cuda")
+    (Y, XA), ran_fwd = _ran(lambda: fwd(w, X, Ad, Bd, s, nan(N)), conv, "fwd")
+    (dX, T), ran_bwd = _ran(lambda: bwd(w, dY, Ad, Bd, s, nan(K)), conv, "bwd")
+    assert ran_bwd and (ran_fwd or M < 16 or K < 512), (ran_fwd, ran_bwd)
+    if f16:
+        Yr, Ur = pl.fwd(*oa, L["X"], A, B, s, L["bias"])
+        dXr, Tr = pl.bwd_input(*oa, L["dY"], A, B, s)
+    else:
+        Yr, Ur = oracle.fwd(*oa, L["X"], A, B, s)
+        dXr, Tr = oracle.bwd_input(*oa, L["dY"], A, B, s)
+    if ran_fwd:
+        _close(Y, Yr, rel, K + r)
+    _close(dX, dXr, rel, N + r)
+    if r:
+        _close(XA, Ur, 2.0 ** -20, K)
+        _close(T, Tr, 2.0 ** -20, N)
+    # no atomics: a second run gives the same bits
+    assert torch.equal(dX.view(torch.int16), bwd(w, dY, Ad, Bd, s)[0].view(torch.int16))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("conv", ["bf16", "f16"])
+@pytest.mark.parametrize("bits", [2, 3, 4])
+def test_picks_out_single_weights_bit_for_bit(bits, conv):
+    """One-hot rows: an output is one materialized weight, in every lane and register position."""
+    K, N, group, M = 4160, 4104, 32, 96
+    f16 = conv == "f16"
+    cfg = synth.LayerConfig("t", K, N, bits, group, 1, 0, seed=5)
+    if f16:
+        L = synth.make_layer_f16(cfg, with_bias=False)
+        w = b.QWeightF16.from_numpy(L["qweight"], L["scales"], L["zeros_f16"], None, K, N, bits, group)
+        What = b.modulora_f16_dequant(w)
+        fwd, bwd, dtype = b.modulora_f16_fwd, b.modulora_f16_bwd_input, torch.float16
+    else:
+        L = synth.make_layer(cfg)
+        w = b.QWeight.from_numpy(L["qweight"], L["scales"], L["zeros"], K, N, bits, group)
+        What = b.modulora_dequant(w)            # [N][K], bit-exact against the oracle (test_gpu_parity.py)
+        fwd, bwd, dtype = b.modulora_fwd, b.modulora_bwd_input, torch.bfloat16
+    for lo in (0, K // 2 - 48, K - M):
+        rows = torch.zeros((M, K), dtype=dtype, device="cuda")
+        rows[torch.arange(M), lo + torch.arange(M)] = 1.0
+        (Y, _), ran = _ran(lambda: fwd(w, rows, None, None, 1.0), conv, "fwd")
+        assert ran and torch.equal(Y.view(torch.int16), What.t()[lo:lo + M].contiguous().view(torch.int16))
+    for lo in (0, N // 2 - 52, N - M):
+        rows = torch.zeros((M, N), dtype=dtype, device="cuda")
+        rows[torch.arange(M), lo + torch.arange(M)] = 1.0
+        (dX, _), ran = _ran(lambda: bwd(w, rows, None, None, 1.0), conv, "bwd")
+        assert ran and torch.equal(dX.view(torch.int16), What[lo:lo + M].contiguous().view(torch.int16))
+
+
+@pytest.mark.skipif(_hipcc() is None, reason="hipcc not available")
+def test_kernels_do_not_spill(tmp_path):
+    """The kernel counts its assembly-issued loads and keeps registers untouched while they are in flight."""
+    out = tmp_path / "gemm_direct.s"
+    cmd = [_hipcc(), *build.HIPCC_FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, "gemm_direct.hip"), "-o", str(out)]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    text = out.read_text()
+    names = re.findall(r"^\s*\.name:\s+(\S+)", text, flags=re.M)
+    assert sum("gemm_direct_kernel" in n for n in names) == 48     # 3 bit widths x 2 directions x 2 conventions x 4 row tiles
+    spills = re.findall(r"^\s*\.[vs]gpr_spill_count:\s+(\d+)", text, flags=re.M)
+    assert len(spills) == 2 * len(names) and all(int(s) == 0 for s in spills)
+    assert "scratch_load" not in text and "scratch_store" not in text
