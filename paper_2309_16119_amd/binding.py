@@ -103,15 +103,24 @@ lib = _load()
 
 
 # ----------------------------------------------------------------------------- helpers
-def _ptr(t: Optional[torch.Tensor]) -> ctypes.c_void_p:
+# A call on a small layer costs more on the host than on the GPU (256 x 256, 16 tokens, one forward call:
+# 19 us of Python against 11 us of kernels), so pointers and streams travel as plain integers, which the
+# declared argument types convert, and streams are read from torch's C layer without a Stream object.
+_raw_stream = torch._C._cuda_getCurrentRawStream
+_current_device = torch._C._cuda_getDevice
+
+
+def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     if t is None:
-        return ctypes.c_void_p(0)
+        return None
     assert t.is_contiguous(), "tensors must be contiguous"
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream() -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+def _stream() -> int:
+    if not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream      # initialises, or says why it cannot
+    return _raw_stream(_current_device())
 
 
 class QWeight:
@@ -156,8 +165,14 @@ def _workspace(device, nbytes: int) -> Optional[torch.Tensor]:
     Callers that capture graphs can size the buffer first with reserve_workspace()."""
     if nbytes == 0:
         return None
-    key = (torch.device(device), torch.cuda.current_stream(device).cuda_stream)
-    held = _workspaces.setdefault(key, [])
+    device = torch.device(device)
+    index = device.index
+    if device.type != "cuda" or index is None:
+        index = torch.cuda.current_stream(device).device_index      # refuses what is not a GPU
+    key = (index, _raw_stream(index))
+    held = _workspaces.get(key)
+    if held is None:
+        held = _workspaces.setdefault(key, [])
     if not held or held[-1].numel() < nbytes:
         held.append(torch.empty(nbytes, dtype=torch.uint8, device=device))
     return held[-1]
@@ -202,15 +217,15 @@ def modulora_fwd(w: QWeight, X: torch.Tensor, A: Optional[torch.Tensor], B: Opti
     r = 0 if A is None else A.shape[1]
     if r:
         assert A.dtype == torch.float32 and B.dtype == torch.float32
-        assert tuple(A.shape) == (w.d_in, r) and tuple(B.shape) == (r, w.d_out)
+        assert A.shape == (w.d_in, r) and B.shape == (r, w.d_out)
     if Y is None:
         Y = torch.empty((M, w.d_out), dtype=torch.bfloat16, device=X.device)
     if XA is None and want_XA and r:
         XA = torch.empty((M, r), dtype=torch.float32, device=X.device)
-    nbytes = modulora_workspace_bytes(w, M, r)
+    st = ctypes.byref(w.c_struct())
+    nbytes = lib.modulora_workspace_bytes(st, M, r)
     ws = _workspace(X.device, nbytes)
-    st = w.c_struct()
-    _check(lib.modulora_fwd(ctypes.byref(st), _ptr(X), M, _ptr(A), _ptr(B), r, float(lora_scale),
+    _check(lib.modulora_fwd(st, _ptr(X), M, _ptr(A), _ptr(B), r, float(lora_scale),
                             _ptr(Y), _ptr(XA), _ptr(ws), nbytes, _stream()), "modulora_fwd")
     return Y, XA
 
@@ -241,15 +256,15 @@ def modulora_bwd_input(w: QWeight, dY: torch.Tensor, A: Optional[torch.Tensor], 
     r = 0 if A is None else A.shape[1]
     if r:
         assert A.dtype == torch.float32 and B.dtype == torch.float32
-        assert tuple(A.shape) == (w.d_in, r) and tuple(B.shape) == (r, w.d_out)
+        assert A.shape == (w.d_in, r) and B.shape == (r, w.d_out)
     if dX is None:
         dX = torch.empty((M, w.d_in), dtype=torch.bfloat16, device=dY.device)
     if dYBt is None and want_dYBt and r:
         dYBt = torch.empty((M, r), dtype=torch.float32, device=dY.device)
-    nbytes = modulora_workspace_bytes(w, M, r)
+    st = ctypes.byref(w.c_struct())
+    nbytes = lib.modulora_workspace_bytes(st, M, r)
     ws = _workspace(dY.device, nbytes)
-    st = w.c_struct()
-    _check(lib.modulora_bwd_input(ctypes.byref(st), _ptr(dY), M, _ptr(A), _ptr(B), r, float(lora_scale),
+    _check(lib.modulora_bwd_input(st, _ptr(dY), M, _ptr(A), _ptr(B), r, float(lora_scale),
                                   _ptr(dX), _ptr(dYBt), _ptr(ws), nbytes, _stream()), "modulora_bwd_input")
     return dX, dYBt
 
@@ -263,7 +278,7 @@ def modulora_bwd_lora(X: torch.Tensor, dY: torch.Tensor, A: torch.Tensor, B: tor
     d_out = dY.shape[1]
     r = A.shape[1]
     assert X.dtype == torch.bfloat16 and dY.dtype == torch.bfloat16 and dY.shape[0] == M
-    assert tuple(A.shape) == (d_in, r) and tuple(B.shape) == (r, d_out)
+    assert A.shape == (d_in, r) and B.shape == (r, d_out)
     if dA is None:
         assert not accumulate
         dA = torch.empty((d_in, r), dtype=torch.float32, device=X.device)
@@ -330,15 +345,15 @@ def _f16_call(fn, name, w: QWeightF16, act: torch.Tensor, width_in: int, width_o
     r = 0 if A is None else A.shape[1]
     if r:
         assert A.dtype == torch.float32 and B.dtype == torch.float32
-        assert tuple(A.shape) == (w.d_in, r) and tuple(B.shape) == (r, w.d_out)
+        assert A.shape == (w.d_in, r) and B.shape == (r, w.d_out)
     if out is None:
         out = torch.empty((M, width_out), dtype=torch.float16, device=act.device)
     if P is None and want_P and r:
         P = torch.empty((M, r), dtype=torch.float32, device=act.device)
-    nbytes = modulora_f16_workspace_bytes(w, M, r)
+    st = ctypes.byref(w.c_struct())
+    nbytes = lib.modulora_f16_workspace_bytes(st, M, r)
     ws = _workspace(act.device, nbytes)
-    st = w.c_struct()
-    _check(fn(ctypes.byref(st), _ptr(act), M, _ptr(A), _ptr(B), r, float(lora_scale), _ptr(out), _ptr(P), _ptr(ws), nbytes,
+    _check(fn(st, _ptr(act), M, _ptr(A), _ptr(B), r, float(lora_scale), _ptr(out), _ptr(P), _ptr(ws), nbytes,
               _stream()), name)
     return out, P
 
@@ -362,7 +377,7 @@ def modulora_f16_bwd_lora(X: torch.Tensor, dY: torch.Tensor, A: torch.Tensor, B:
     d_out = dY.shape[1]
     r = A.shape[1]
     assert X.dtype == torch.float16 and dY.dtype == torch.float16 and dY.shape[0] == M
-    assert tuple(A.shape) == (d_in, r) and tuple(B.shape) == (r, d_out)
+    assert A.shape == (d_in, r) and B.shape == (r, d_out)
     if dA is None:
         assert not accumulate
         dA = torch.empty((d_in, r), dtype=torch.float32, device=X.device)
