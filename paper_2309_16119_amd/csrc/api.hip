@@ -74,13 +74,6 @@ size_t direct_bytes(int32_t K, int32_t N, int32_t M, int32_t r, bool fwd, bool b
     const size_t b = bwd ? mlr::direct_plan(M, N, K, true).ws_bytes(M, K, r) : 0;
     return f > b ? f : b;
 }
-// 17 .. 32 tokens would take two passes of a streaming kernel: from 20 M weights on one direct pass is
-// quicker (8192 x 8192, 32 tokens: 33 / 31 us in two passes, 20 / 23 direct; smaller layers keep their
-// results of the streaming kernels).
-bool stream_takes(bool supported, int32_t K, int32_t N, int32_t M, bool direct) {
-    return supported && !(direct && M > mlr::SMALLM_ROWS && (size_t)K * N >= ((size_t)20 << 20));
-}
-
 WsLayout ws_layout(int32_t K, int32_t N, int32_t M, int32_t r) {
     WsLayout l{};
     // the streaming kernels for a handful of tokens keep the slices' partial tiles and the
@@ -122,7 +115,7 @@ WsLayout ws_layout_fwd(const mlr::LayerView &v, int32_t M, int32_t r, size_t ava
     l.direct_fwd = mlr::direct_wins(v.K, v.N, M, r, false);
     const size_t dir = direct_bytes(v.K, v.N, M, r, l.direct_fwd, false);
     if (dir > avail) l.direct_fwd = false;
-    if (stream_takes(mlr::smallm_fwd_supported(v, M), v.K, v.N, M, l.direct_fwd)) {
+    if (mlr::smallm_fwd_supported(v, M)) {
         l.total = mlr::smallm_fwd_ws_bytes(v, r);
         return l;
     }
@@ -169,7 +162,7 @@ int check_fwd_args(const modulora_qweight *w, const uint16_t *X, int32_t M, cons
 
 int run_fwd(const modulora_qweight *w, const uint16_t *X, int32_t M, const float *A, const float *B, int32_t r,
             float lora_scale, uint16_t *Y, float *XA, char *ws, const WsLayout &l, hipStream_t st) {
-    const bool streams = stream_takes(mlr::smallm_fwd_supported(view_of(w), M), w->d_in, w->d_out, M, l.direct_fwd);
+    const bool streams = mlr::smallm_fwd_supported(view_of(w), M);
     if (streams || l.direct_fwd) {
         mlr::SmallArgs sa{};
         sa.w = view_of(w);
@@ -330,7 +323,7 @@ int modulora_bwd_input(const modulora_qweight *w, const uint16_t *dY, int32_t M,
 
     hipStream_t st = static_cast<hipStream_t>(stream);
     char *ws = static_cast<char *>(workspace);
-    const bool streams = stream_takes(mlr::smallm_bwd_supported(view_of(w), M), w->d_in, w->d_out, M, l.direct_bwd);
+    const bool streams = mlr::smallm_bwd_supported(view_of(w), M);
     if (streams || l.direct_bwd) {
         mlr::SmallArgs sa{};
         sa.w = view_of(w);
@@ -507,7 +500,7 @@ int modulora_f16_fwd(const modulora_qweight_f16 *w, const uint16_t *X, int32_t M
     const F16Ws l = f16_ws(w->d_in, w->d_out, M, r);
     if ((s = check_ws_f16(l, workspace, workspace_bytes)) != MODULORA_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const bool streams = stream_takes(mlr::smallm_fwd_supported(stream_view_of(w), M), w->d_in, w->d_out, M, l.direct_fwd);
+    const bool streams = mlr::smallm_fwd_supported(stream_view_of(w), M);
     if (streams || l.direct_fwd) {
         // a handful of tokens: the direct product with the quantized matrix (Section 3.1.2)
         mlr::SmallArgs sa{};
@@ -539,7 +532,7 @@ int modulora_f16_bwd_input(const modulora_qweight_f16 *w, const uint16_t *dY, in
     const F16Ws l = f16_ws(w->d_in, w->d_out, M, r);
     if ((s = check_ws_f16(l, workspace, workspace_bytes)) != MODULORA_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const bool streams = stream_takes(mlr::smallm_bwd_supported(stream_view_of(w), M), w->d_in, w->d_out, M, l.direct_bwd);
+    const bool streams = mlr::smallm_bwd_supported(stream_view_of(w), M);
     if (streams || l.direct_bwd) {
         mlr::SmallArgs sa{};
         sa.w = stream_view_of(w);

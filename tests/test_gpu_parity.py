@@ -246,6 +246,51 @@ def test_second_streaming_pass_picks_out_the_right_rows():
     assert np.all(np.abs(f64(dX) - Wf[hot]) <= 2.0 ** -7 * np.abs(Wf[hot]))
 
 
+@pytest.mark.parametrize("f16", [False, True])
+@pytest.mark.parametrize("bits,K,N,M", [(2, 8192, 2816, 17), (3, 8192, 8192, 24), (4, 5120, 6656, 32)])
+def test_up_to_32_tokens_multiply_the_unrounded_weight(bits, K, N, M, f16):
+    """17 .. 32 tokens, layers of 20 M weights and more among them: both directions are two passes of the
+    streaming kernels, whose weight is the code times the scale and never rounded to 16 bits.  Against that
+    weight in 64 bits the forward result carries the rounding of the output alone (standard deviation
+    2^-7 / sqrt(12) of a value's power of two in bfloat16, 1.65e-3 of normally distributed values in the
+    2-norm); a weight rounded first adds about as much again (2.33e-3).  In binary16 both are an eighth, and
+    the fp32 sums of products with 1024 + code (2^-14 of a code each) come up to the difference: there the
+    kernels that ran are the check."""
+    gen = torch.Generator(device="cuda").manual_seed(bits)
+    W = torch.randn((N, K), device="cuda", generator=gen) * 0.02
+    q = b.modulora_quantize_rtn(W, bits, 128)
+    words = (q.qweight.long() & 0xFFFFFFFF).view(K // 32, bits, N)
+    code = []
+    for pos in range(0, 32 * bits, bits):               # the 32 codes of a block, two of which may straddle words
+        v = words[:, pos // 32] >> (pos % 32)
+        if pos % 32 + bits > 32:
+            v = v | (words[:, pos // 32 + 1] << (32 - pos % 32))
+        code.append(v & ((1 << bits) - 1))
+    codes = torch.stack(code, dim=1).reshape(K, N).t().double()
+    s = q.scales.double().t().repeat_interleave(128, dim=1)
+    dtype = torch.float16 if f16 else torch.bfloat16
+    if f16:
+        zeros16 = (-q.zeros.float() * q.scales.float()).half()
+        w = b.QWeightF16(q.qweight, q.scales, zeros16, None, K, N, bits, 128)
+        exact = codes * s + zeros16.double().t().repeat_interleave(128, dim=1)
+        fwd, bwd, prefix = b.modulora_f16_fwd, b.modulora_f16_bwd_input, "f16_"
+    else:
+        w = q
+        exact = (codes - q.zeros.double().t().repeat_interleave(128, dim=1)) * s
+        fwd, bwd, prefix = b.modulora_fwd, b.modulora_bwd_input, ""
+    X = torch.randn((M, K), device="cuda", generator=gen).to(dtype)
+    dY = torch.randn((M, N), device="cuda", generator=gen).to(dtype)
+    b.modulora_profile_begin()
+    Y, _ = fwd(w, X, None, None, 1.0)
+    bwd(w, dY, None, None, 1.0)
+    torch.cuda.synchronize()
+    prof = b.modulora_profile_end()
+    assert {k: v[0] for k, v in prof.items()} == {prefix + k: 2 for k in ("stream_fwd", "stream_fwd_finish", "stream_bwd", "stream_bwd_finish")}
+    ref = X.double() @ exact.t()
+    err = float((Y.double() - ref).norm() / ref.norm())
+    assert f16 or err <= 1.9e-3, err
+
+
 @pytest.mark.parametrize("bits", [2, 3, 4])
 def test_adapter_term_dominant(bits):
     """Large adapters (the LoRA term is most of the output): a dropped, mis-scaled or
