@@ -98,7 +98,7 @@ WsLayout ws_layout(int32_t K, int32_t N, int32_t M, int32_t r) {
     l.w_ext = off;   off += align256(maxdim * RE * 2);
     l.p0 = off;      off += align256((size_t)M * r * 4);
     l.p1 = off;      off += align256((size_t)M * r * 4);
-    l.gpart = off;   off += align256(mlr::grad_geom(M, K, N, r).partial_floats * 4);
+    l.gpart = off;   off += align256(mlr::grad_geom(M, K, N, r, false).partial_floats * 4);
     l.gemm_part = off; off += part;
     l.dpart = off;   off += align256(mlr::lora_down_partial_bytes(M, K, N, r));
     l.total = off > small ? off : small;
@@ -428,7 +428,7 @@ F16Ws f16_ws(int32_t K, int32_t N, int32_t M, int32_t r) {
     if (r > 0) {
         l.p0 = off;    off += align256((size_t)M * r * 4);
         l.p1 = off;    off += align256((size_t)M * r * 4);
-        l.gpart = off; off += align256(mlr::grad_geom(M, K, N, r).partial_floats * 4);
+        l.gpart = off; off += align256(mlr::grad_geom(M, K, N, r, true).partial_floats * 4);
         l.dpart = off; off += align256(mlr::lora_down_partial_bytes(M, K, N, r));   // slices of the rank-r projection
     }
     l.gemm_part = off; off += align256(mlr::gemm_partial_bytes(M, K, N));   // partial tiles of the 256 x 256 kernel

@@ -214,7 +214,7 @@ struct GradGeom {
     int nwaves;                  // waves per workgroup, which divide the rows of a chunk
     size_t partial_floats;
 };
-GradGeom grad_geom(int M, int K, int N, int r);
+GradGeom grad_geom(int M, int K, int N, int r, bool f16);
 hipError_t launch_lora_grad_pair(const GradPairArgs &a, hipStream_t stream);
 
 // ---- f16_path.hip: the layer in the paper's own storage convention ---------------------

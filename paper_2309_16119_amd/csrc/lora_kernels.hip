@@ -293,22 +293,49 @@ hipError_t launch_lora_down(const DownArgs &a, hipStream_t stream) {
 //         7.9 us against 9.4).  8 (256-byte pieces) from 128 MB on, where HBM does the work (247 MB:
 //         47 us against 55; r = 32: 55 against 72), for r <= 32; beyond that eight columns'
 //         accumulators leave too few waves (r = 64 at 2048 x 16384: 26 us against 43).
-//   rows  in chunks that leave partials for a reduction launch (4 us) only where the columns are too
+//         Registers let two workgroups share a compute unit only at CPL 4, r <= 16, bfloat16; the others
+//         run 256 workgroups at a time, and 257 ... 512 blocks of 64 columns as two rounds: there 8 goes
+//         from the first row on (binary16, r = 8, 8192 + 8320 columns: M = 1536 21.8 -> 18.0 us, 3000 39.1 ->
+//         30.5; not binary16 with r > 16, where it is even to 4 % the slower).  So it does where 129 ... 170
+//         blocks of 64 columns allow one chunk of rows, but half as many of 128 three (binary16,
+//         4096 + 4224 columns, M = 4096: 25.0 -> 21.1).
+//   rows  in chunks that leave partials for a reduction launch (4 us) where the columns are too
 //         few to occupy the chip and at least 1024 rows remain to each: 256 + 256 columns, M = 4096:
 //         14.4 -> 6.4 + 4.1 us; 2048 + 2048: 16.3 -> 9.3 + 4.2; a chunk of 512 rows gains less than
 //         the launch costs (4096 + 11008, M = 2048: 14.4 -> 13.0 + 4.0).
+//         Where the blocks leave compute units idle in the last round of 256: up to five chunks where the
+//         rounds that they save, at 4.5 TB/s, outweigh the second launch and its partials and enough rows
+//         remain.  8192 + 8320 columns (129 blocks), M = 8192: one chunk 53.0 us, three 48.1; binary16 72.4,
+//         five 59.6; M = 16384: 135 and 152, five 104 and 113; r = 64 at M = 4096: 75.8, three 65.0; r = 8,
+//         too few rows: 26.7, three 28.5.  6144 + 6144 columns, M = 16384: two chunks 84.7, five 80.0.
+//         Over 656 timed shapes of 4096 ... 44032 columns and 1536 ... 16384 rows the choice is on average
+//         3 % slower than the best of the eight or sixteen timed (one or two widths, one to eight chunks).
 // No atomics (device-scope fp32 atomics bypass the per-XCD L2 and are slow), no zero-fill.
 // ---------------------------------------------------------------------------
-GradGeom grad_geom(int M, int K, int N, int r) {
+GradGeom grad_geom(int M, int K, int N, int r, bool f16) {
     GradGeom g;
     g.rg = r > 0 ? (r + 15) / 16 : 1;
-    g.cpl = g.rg <= 2 && (size_t)M * ((size_t)K + N) * 2 >= (size_t)128 << 20 ? 8 : 4;
+    const bool pair = !f16 && g.rg == 1;             // two workgroups of CPL 4 share a compute unit
+    const int blocks4 = (K + 63) / 64 + (N + 63) / 64;
+    const bool wide = (size_t)M * ((size_t)K + N) * 2 >= (size_t)128 << 20 ||
+                      (!pair && ((blocks4 > 256 && !(f16 && g.rg == 2)) || (blocks4 > 128 && blocks4 <= 170 && M >= 3 * 960)));
+    g.cpl = g.rg <= 2 && wide ? 8 : 4;
     const int wcols = 16 * g.cpl;
     g.cols_a = (K + wcols - 1) / wcols;
     g.cols_b = (N + wcols - 1) / wcols;
-    int chunks = 256 / (g.cols_a + g.cols_b);
-    if (chunks > M / 1024) chunks = M / 1024;
+    const int blocks = g.cols_a + g.cols_b, fewest = !pair && g.cpl == 8 ? 960 : 1024;
+    int chunks = 256 / blocks;
+    if (chunks > M / fewest) chunks = M / fewest;
     if (chunks < 1) chunks = 1;
+    if (!(pair && g.cpl == 4)) {
+        const double bytes = (double)M * ((double)K + N) * 2.0;
+        const auto us = [&](int c) {                 // rounds of 256 workgroups, and what a second launch adds
+            const long n = (long)blocks * c;
+            return bytes / 4.5e6 * (double)((n + 255) / 256 * 256) / (double)n + (c > 1 ? 4.0 + c * ((double)K + N) * r * 8.0 / 4.0e6 : 0.0);
+        };
+        for (int c = chunks + 1; c <= 5 && M / c >= (pair ? 2048 : 1365); ++c)
+            if (us(c) < us(chunks)) chunks = c;
+    }
     const int rows = ((M + chunks - 1) / chunks + 31) / 32 * 32;
     g.rows_per_block = rows;
     g.chunks = (M + rows - 1) / rows;
@@ -530,7 +557,7 @@ static hipError_t launch_grad(const GradPairArgs &a, const GradGeom &g, hipStrea
 }
 
 hipError_t launch_lora_grad_pair(const GradPairArgs &a, hipStream_t stream) {
-    const GradGeom g = grad_geom(a.M, a.K, a.N, a.r);
+    const GradGeom g = grad_geom(a.M, a.K, a.N, a.r, a.f16 != 0);
     switch (g.rg) {
         case 1: return g.cpl == 8 ? launch_grad<1, 8>(a, g, stream) : launch_grad<1, 4>(a, g, stream);
         case 2: return g.cpl == 8 ? launch_grad<2, 8>(a, g, stream) : launch_grad<2, 4>(a, g, stream);

@@ -22,6 +22,10 @@ SHAPES = [
     (64, 128, 4200, 40),
     (8192, 8456, 4100, 8),         # from 128 MB of activations on: eight columns per lane
     (16384, 264, 4105, 20),
+    (4096, 4232, 2900, 8),         # binary16: eight columns per lane, three chunks
+    (8192, 8456, 1100, 16),        # binary16: eight columns per lane below 128 MB
+    (8192, 8456, 6200, 3),         # three or more chunks of 131 column blocks
+    (4096, 4232, 4100, 40),        # the same at 131 blocks of 64 columns
 ]
 
 
@@ -52,3 +56,16 @@ def test_adapter_gradients_at_tile_edges(K, N, M, r, f16):
         mag = a64.abs().T @ p64.abs() if left else p64.abs().T @ a64.abs()
         assert bool(((got.double() - ref).abs() <= unit * mag + 1e-30).all())
         assert bool(((got2.double() - ref - old.double()).abs() <= unit * mag + 2.0 ** -23 * (ref + old.double()).abs() + 1e-30).all())
+
+
+@pytest.mark.parametrize("K,N,M,r,f16", [(8192, 8320, 8192, 8, False), (8192, 8320, 4096, 8, True), (4096, 4232, 4100, 64, False)])
+def test_rows_are_cut_where_column_blocks_fill_half_the_chip(K, N, M, r, f16):
+    """129 ... 131 column blocks on 256 compute units: one chunk of rows would leave half of them idle."""
+    dtype = torch.float16 if f16 else torch.bfloat16
+    X, dY = torch.zeros((M, K), dtype=dtype, device="cuda"), torch.zeros((M, N), dtype=dtype, device="cuda")
+    P = torch.zeros((M, r), device="cuda")
+    A, B = torch.zeros((K, r), device="cuda"), torch.zeros((r, N), device="cuda")
+    b.modulora_profile_begin()
+    (b.modulora_f16_bwd_lora if f16 else b.modulora_bwd_lora)(X, dY, A, B, 1.0, XA=P, dYBt=P)
+    torch.cuda.synchronize()
+    assert {k: v[0] for k, v in b.modulora_profile_end().items()} == {"lora_grad": 1, "lora_grad_reduce": 1}
