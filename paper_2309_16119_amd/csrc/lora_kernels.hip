@@ -439,6 +439,38 @@ __global__ __launch_bounds__(RG * CPL <= 8 ? 1024 : 512) void lora_grad_partial_
         }
     }
 
+    // An infinity has no exact split (inf - inf is NaN) and meets the zero parts of the other operand
+    // (inf * 0).  A wave that finds a NaN among its sums adds its rows again with fp32 multiply-adds, which
+    // give what the definition does (every dY NaN, 4096 x (8192 + 22016), r = 8: 161 us a call instead of 42).
+    float sum = 0.f;
+#pragma unroll
+    for (int q = 0; q < CPL; ++q)
+#pragma unroll
+        for (int t = 0; t < RG; ++t) sum += (acc[q][t][0] + acc[q][t][1]) + (acc[q][t][2] + acc[q][t][3]);
+    if (__builtin_expect(__any(sum != sum), 0)) {
+#pragma unroll
+        for (int q = 0; q < CPL; ++q)
+#pragma unroll
+            for (int t = 0; t < RG; ++t) acc[q][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int mb = m_begin + 32 * wave; mb < m_end; mb += 32 * nwaves)
+            for (int m = mb; m < mb + 32 && m < m_end; ++m) {
+                const words_t x = *reinterpret_cast<const words_t *>(col + (size_t)m * C);
+#pragma unroll
+                for (int t = 0; t < RG; ++t)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int j = 16 * t + 4 * cs + v;       // the layout of the sums, see below
+                        const float p = j < r ? P[(size_t)m * r + j] : 0.f;
+#pragma unroll
+                        for (int q = 0; q < CPL; ++q) {
+                            const uint32_t bits = q & 1 ? x[q / 2] >> 16 : x[q / 2] & 0xFFFFu;
+                            const float xq = F16 ? half_bits_to_float((uint16_t)bits) : __uint_as_float(bits << 16);
+                            acc[q][t][v] = __builtin_fmaf(xq, p, acc[q][t][v]);
+                        }
+                    }
+            }
+    }
+
     // the waves' sums meet in LDS, half of the waves handing theirs to the other half at a time
     constexpr int FL = CPL * RG * 4;
     for (int half = nwaves >> 1; half > 0; half >>= 1) {

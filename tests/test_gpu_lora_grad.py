@@ -69,3 +69,29 @@ def test_rows_are_cut_where_column_blocks_fill_half_the_chip(K, N, M, r, f16):
     (b.modulora_f16_bwd_lora if f16 else b.modulora_bwd_lora)(X, dY, A, B, 1.0, XA=P, dYBt=P)
     torch.cuda.synchronize()
     assert {k: v[0] for k, v in b.modulora_profile_end().items()} == {"lora_grad": 1, "lora_grad_reduce": 1}
+
+
+@pytest.mark.parametrize("f16", [False, True])
+@pytest.mark.parametrize("K,N,M,r", [(64, 72, 31, 16), (96, 136, 600, 17), (160, 264, 70, 64), (8192, 8264, 70, 8)])
+def test_infinities_stay_infinities(K, N, M, r, f16):
+    """Overflowed activations or hand-offs (common in binary16): an infinite factor gives +-inf in the sums
+    that it enters and NaN only where it meets zero or an opposite infinity, and leaves the others alone."""
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    dtype = torch.float16 if f16 else torch.bfloat16
+    X, dY = (torch.randn((M, c), device="cuda", generator=gen).to(dtype) for c in (K, N))
+    XA, T = (torch.randint(1, 9, (M, r), device="cuda", generator=gen).float() / 4 for _ in range(2))   # exact in bfloat16
+    X[M // 2, 3], X[M - 1, K - 1], X[0, 8] = float("inf"), float("-inf"), float("nan")
+    dY[M // 3, 5] = float("-inf")
+    dY[0, 11] = dY[M - 1, 11] = float("inf")
+    T[M // 4, r // 2], XA[1, 0] = float("inf"), float("-inf")
+    X[M // 4, 9], dY[1, 7] = 0.0, 0.0
+    A, B = torch.zeros((K, r), device="cuda"), torch.zeros((r, N), device="cuda")
+    dA, dB = (b.modulora_f16_bwd_lora if f16 else b.modulora_bwd_lora)(X, dY, A, B, 0.5, XA=XA, dYBt=T)
+    for got, act, P, left in ((dA, X, T, True), (dB, dY, XA, False)):
+        for j in range(r):
+            terms = 0.5 * act.double() * P[:, j:j + 1].double()
+            ref, mag = terms.sum(0), terms.abs().sum(0)
+            g = (got[:, j] if left else got[j]).double()
+            assert torch.equal(g.isnan(), ref.isnan()) and torch.equal(g.isposinf(), ref.isposinf()) and torch.equal(g.isneginf(), ref.isneginf())
+            ok = ref.isfinite()
+            assert bool(((g - ref).abs()[ok] <= (8 * np.sqrt(M) * 2.0 ** -24 * mag + 1e-30)[ok]).all())
