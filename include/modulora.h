@@ -130,14 +130,20 @@ int modulora_fwd(const modulora_qweight *w, const uint16_t *X, int32_t M,
 /*
  * modulora_fwd for callers that cannot provide scratch memory or allocate any: code that runs
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
- * arguments, results (bit for bit) and error codes as modulora_fwd, minus the workspace: the
- * scratch is a static device array of MODULORA_STATIC_SCRATCH_BYTES inside the library (each GPU
+ * arguments and error codes as modulora_fwd, minus the workspace: the
+ * scratch is a static device array of MODULORA_STATIC_SCRATCH_BYTES (with 4 MiB more behind it for the
+ * kernel for up to 1024 tokens alone) inside the library (each GPU
  * the library runs on holds its own copy from the first call on that GPU until the process
  * ends).  The call allocates and frees nothing, on the host side of the GPU or through any
  * library.  A layer / M / r whose forward pass needs more scratch than that returns
  * MODULORA_ERR_WORKSPACE (the streaming passes for a handful of tokens need < 8 MiB at every benchmark layer; the
- * tile kernels need about 2 (M + d_out) (3 r + 16) bytes; partial tiles of a split last round of
- * 256 x 256 tiles are used only when they also fit, otherwise those tiles run whole).
+ * tile kernels need about 2 (M + d_out) (3 r + 16) bytes).
+ * Results are those of modulora_fwd bit for bit, except where that call adds up more fp32 partial
+ * results of a split contraction than the array holds.  Partial tiles of a split last round of
+ * 256 x 256 tiles that do not fit are done without (those tiles run whole); where the kernel for up to 1024
+ * tokens needs more than the array and the 4 MiB (never while its at most sixteen slices of
+ * 4 M d_out bytes fit the array) the tile kernels run instead.  The fp32 sums then have another
+ * order; everything stated at modulora_fwd holds.
  * All calls on one GPU share that GPU's array and it keeps the last call's contents (nothing in
  * it needs clearing: every region is written before it is read): two calls that overlap in
  * time on one GPU -- different streams, or different host threads -- race; order them on one

@@ -109,19 +109,18 @@ WsLayout ws_layout(int32_t K, int32_t N, int32_t M, int32_t r) {
 // What modulora_fwd alone touches for this layer (no backward, no adapter-gradient regions), for
 // a scratch buffer of `avail` bytes: the M <= 16 stream's exact need, or the adapter operands of
 // the tile kernels plus -- only if they still fit -- the partial tiles of a split contraction
-// (without them the 256 x 256 kernel runs whole tiles).
-WsLayout ws_layout_fwd(const mlr::LayerView &v, int32_t M, int32_t r, size_t avail) {
+// (without them the 256 x 256 kernel runs whole tiles).  gemm_direct.hip runs where its slices' results
+// and projection sums fit `avail_direct` bytes.
+WsLayout ws_layout_fwd(const mlr::LayerView &v, int32_t M, int32_t r, size_t avail, size_t avail_direct) {
     WsLayout l{};
-    l.direct_fwd = mlr::direct_wins(v.K, v.N, M, r, false);
-    const size_t dir = direct_bytes(v.K, v.N, M, r, l.direct_fwd, false);
-    if (dir > avail) l.direct_fwd = false;
     if (mlr::smallm_fwd_supported(v, M)) {
         l.total = mlr::smallm_fwd_ws_bytes(v, r);
         return l;
     }
-    if (l.direct_fwd) {
-        l.total = dir;
-        return l;
+    if (mlr::direct_wins(v.K, v.N, M, r, false)) {
+        l.total = direct_bytes(v.K, v.N, M, r, true, false);
+        l.direct_fwd = l.total <= avail_direct;
+        if (l.direct_fwd) return l;
     }
     size_t off = 0;
     if (r > 0) {
@@ -203,14 +202,19 @@ int run_fwd(const modulora_qweight *w, const uint16_t *X, int32_t M, const float
 // One array per GPU, in that GPU's memory from the moment the code object is loaded there until
 // the process ends.  In host code the array's name is only a handle: the device address comes
 // from hipGetSymbolAddress, once per device, and only that pointer is ever given to kernels.
+// Behind the public size lie 4 MiB for gemm_direct.hip alone.  Its slices' results come to exactly 16 MiB at
+// many common sizes (4096 x 4096 at 256, 512 and 1024 tokens, 8192 x 8192 at 128 ... 512), and its projection
+// sums lie behind them: beside slices that fit 16 MiB at most r / 256 of those bytes, or with one part for each
+// of sixteen slices 16 * 1024 * 64 * 4 = 4 MiB.  So every call whose slices fit runs it, as modulora_fwd does.
 constexpr size_t kStaticScratchBytes = MODULORA_STATIC_SCRATCH_BYTES;
+constexpr size_t kStaticDirectBytes = kStaticScratchBytes + ((size_t)4 << 20);
 constexpr int kMaxDevices = 64;
 void *g_scratch_ptr[kMaxDevices] = {};
 std::mutex g_scratch_mutex;
 
 }  // namespace
 
-static __device__ __align__(256) unsigned char scratch[MODULORA_STATIC_SCRATCH_BYTES];
+static __device__ __align__(256) unsigned char scratch[MODULORA_STATIC_SCRATCH_BYTES + (4u << 20)];
 
 namespace {
 
@@ -302,8 +306,8 @@ int modulora_fwd_static(const modulora_qweight *w, const uint16_t *X, int32_t M,
                         int32_t r, float lora_scale, uint16_t *Y, float *XA, void *stream) {
     int s = check_fwd_args(w, X, M, A, B, r, Y, XA);
     if (s != MODULORA_OK) return s;
-    const WsLayout l = ws_layout_fwd(view_of(w), M, r, kStaticScratchBytes);
-    if (l.total > kStaticScratchBytes) return MODULORA_ERR_WORKSPACE;     // beyond the library's scratch
+    const WsLayout l = ws_layout_fwd(view_of(w), M, r, kStaticScratchBytes, kStaticDirectBytes);
+    if (!l.direct_fwd && l.total > kStaticScratchBytes) return MODULORA_ERR_WORKSPACE;     // beyond the library's scratch
     char *ws = nullptr;
     if ((s = static_scratch(&ws)) != MODULORA_OK) return s;
     return run_fwd(w, X, M, A, B, r, lora_scale, Y, XA, ws, l, static_cast<hipStream_t>(stream));

@@ -54,6 +54,9 @@ _both.first = True      # the first call on the GPU loads the array's address (a
     # 256 x 256 kernel with a split contraction whose partial tiles (4 MB) fit the scratch, then a
     # layer without adapter whose only scratch is partial tiles
     ((3, 8224, 328, 200, 8, 32), (2, 8192, 512, 256, 0, 128)),
+    # the kernel for up to 1024 tokens: slices of exactly 16 MiB with projection sums behind them, and less
+    ((3, 4096, 4096, 512, 8, 128), (3, 8192, 8192, 128, 64, 128)),
+    ((3, 4096, 4096, 256, 64, 128), (4, 4096, 2056, 33, 0, 128)),
 ])
 def test_static_scratch_forward_equals_workspace_forward(first, second):
     for shape in (first, second):
@@ -61,18 +64,40 @@ def test_static_scratch_forward_equals_workspace_forward(first, second):
         _both(_layer(bits, K, N, M, r, group, seed=51))
 
 
-def test_partial_tiles_that_do_not_fit_are_done_without():
-    """A shape whose split contraction would need 64 MB of partial tiles: the static entry point
-    runs those tiles whole instead (a different summation order inside fp32 accumulation, so the
-    comparison with the workspace path is at the oracle's bar, not bit for bit)."""
-    L = _layer(3, 8192, 8192, 300, 8, 128, seed=52)        # 64 tiles x 4 slices x 256 KB
+def _ran(call):
+    b.modulora_profile_begin()
+    call()
+    torch.cuda.synchronize()
+    return {name for name in b.modulora_profile_end() if not name.startswith("lora_")}
+
+
+@pytest.mark.parametrize("shape,static,workspace", [
+    # 50 tiles x 5 slices x 256 KB of partial tiles
+    ((3, 2816, 2456, 1100, 8, 128), {"gemm_fwd_256x256"}, {"gemm_fwd_256x256", "gemm_fwd_256x256_fixup"}),
+    # 42 MB of slices in the kernel for up to 1024 tokens
+    ((2, 6656, 6656, 777, 8, 64), {"gemm_fwd_256x256"}, {"gemm_fwd_direct", "gemm_fwd_direct_fixup"}),
+    # 16 MiB of slices and 0.1 MiB of projection sums: fit
+    ((3, 4096, 4096, 512, 8, 128), {"gemm_fwd_direct", "gemm_fwd_direct_fixup"}, {"gemm_fwd_direct", "gemm_fwd_direct_fixup"}),
+    # 16.2 MiB in all, and 9.5 MiB: fit
+    ((3, 8192, 22016, 48, 8, 128), {"gemm_fwd_direct", "gemm_fwd_direct_fixup"}, {"gemm_fwd_direct", "gemm_fwd_direct_fixup"}),
+    ((3, 8192, 8192, 300, 8, 128), {"gemm_fwd_direct", "gemm_fwd_direct_fixup"}, {"gemm_fwd_direct", "gemm_fwd_direct_fixup"}),
+])
+def test_partial_tiles_that_do_not_fit_are_done_without(shape, static, workspace):
+    """Partial results of a split contraction within and beyond the static scratch: beyond it the static
+    entry point runs whole tiles (a different summation order inside fp32 accumulation, so the comparison
+    with the workspace path is at the oracle's bar, not bit for bit)."""
+    bits, K, N, M, r, group = shape
+    L = _layer(bits, K, N, M, r, group, seed=52)
     D = to_device(L)
     s = L["lora_scale"]
-    Y = torch.full((300, 8192), float("nan"), dtype=torch.bfloat16, device="cuda")
-    b.modulora_fwd_static(D["w"], D["Xd"], D["Ad"], D["Bd"], s, Y, None)
-    rows = np.array([0, 17, 128, 255, 256, 299])
+    Y = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    Y_ref = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda")
+    assert _ran(lambda: b.modulora_fwd_static(D["w"], D["Xd"], D["Ad"], D["Bd"], s, Y, None)) == static
+    assert _ran(lambda: b.modulora_fwd(D["w"], D["Xd"], D["Ad"], D["Bd"], s, Y_ref)) == workspace
+    rows = np.unique(np.array([0, 17, M // 2 - 1, M // 2, M - 2, M - 1]))
     Yr, _ = oracle.fwd(*oracle_args(L), np.ascontiguousarray(L["X"][rows]), L["A"], L["B"], s)
     assert_bar("Y", f64(Y)[rows], Yr)
-    Y_ref, _ = b.modulora_fwd(D["w"], D["Xd"], D["Ad"], D["Bd"], s)
     assert not torch.isnan(Y.float()).any()
+    if static == workspace:
+        assert torch.equal(Y.view(torch.int16), Y_ref.view(torch.int16))
     assert float((Y.float() - Y_ref.float()).abs().max()) <= 2.0 ** -7 * float(Y_ref.float().abs().max())
