@@ -105,9 +105,11 @@ lib = _load()
 # ----------------------------------------------------------------------------- helpers
 # A call on a small layer costs more on the host than on the GPU (256 x 256, 16 tokens, one forward call:
 # 19 us of Python against 11 us of kernels), so pointers and streams travel as plain integers, which the
-# declared argument types convert, and streams are read from torch's C layer without a Stream object.
-_raw_stream = torch._C._cuda_getCurrentRawStream
-_current_device = torch._C._cuda_getDevice
+# declared argument types convert, and streams are read from torch's C layer without a Stream object.  Both
+# functions are private to torch: a build without them (one for CPUs, say) imports this module all the same
+# and goes through torch.cuda, which says at the first call what it lacks.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda index: torch.cuda.current_stream(index).cuda_stream)
+_current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:

@@ -2,10 +2,13 @@
 declares, and rejects bad arguments on the host before any HIP call is made.
 No kernel is launched here."""
 import ctypes
+import importlib.util
 import os
 import re
+import types
 
 import pytest
+import torch
 
 from paper_2309_16119_amd import binding as b
 
@@ -217,3 +220,17 @@ def test_static_scratch_forward_rejections():
     # 30000 tokens at rank 64 need about 19 MB of adapter operands: more than the 16 MiB array
     assert f(qw(), M=30000, r=64) == 7
     assert b.STATIC_SCRATCH_BYTES == 16 << 20
+
+
+def test_binding_without_the_private_torch_functions(monkeypatch):
+    """A torch build that lacks the two private functions behind the stream lookup: the module imports and
+    takes the public way."""
+    monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    monkeypatch.delattr(torch._C, "_cuda_getDevice", raising=False)
+    spec = importlib.util.spec_from_file_location("paper_2309_16119_amd.binding_again", b.__file__)
+    again = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(again)
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(again, "_current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda index: types.SimpleNamespace(cuda_stream=4096 + index))
+    assert again._stream() == 4099 and again._raw_stream(1) == 4097
