@@ -26,6 +26,8 @@ SHAPES = [
     (4, 4128, 2304, 256, 16, 96),       # odd number of blocks per group
     (2, 4128, 8200, 100, 0, 32),        # no adapter
     (3, 4096, 4096, 512, 8, 128),       # four row blocks
+    (4, 4096, 2568, 777, 8, 128),       # seven row blocks, the last ragged, whole contractions
+    (2, 3104, 2824, 1000, 33, 3104),    # eight
     (3, 8224, 2624, 20, 8, 32),         # one row tile: a shape that no streaming kernel takes
     (4, 4096, 2104, 7, 33, 128),        # a handful of tokens that the backward streaming kernel does not take
     (3, 288, 32768, 40, 8, 288),        # an output of little more than two column blocks (backward only)

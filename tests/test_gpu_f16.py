@@ -68,7 +68,8 @@ SHAPES = [
     (3, 2816, 2456, 1100, 8, 128, True),
     (4, 2816, 2456, 1100, 0, 64, False),
     # a hundred-odd tokens (or that many past a multiple of 256) against a weight of 4096 x 4096 or more:
-    # the 256-column kernel with 128-row tiles, split contraction and second launch (ragged M, N, last step)
+    # the kernel for up to 1024 tokens (ragged M, N, last step); the 256-column kernel with 128-row tiles,
+    # which takes such token counts where that one does not, has a test of its own below
     (3, 4096, 4104, 100, 8, 128, True),
     (4, 4128, 4096, 128, 16, 32, False),
     (2, 4096, 4224, 300, 40, 64, True),
@@ -269,6 +270,43 @@ def test_large_shape_on_sampled_rows_and_one_hot(bits):
     eyeN = torch.eye(N, dtype=torch.float16, device="cuda")
     dX1, _ = b.modulora_f16_bwd_input(E["w"], eyeN[:M].contiguous(), None, None, 1.0)
     assert np.array_equal(dX1.view(torch.int16).cpu().numpy().view(np.uint16), What[:M])
+
+
+@pytest.mark.parametrize("bits", [2, 3, 4])
+def test_half_row_tiles_of_the_256_column_kernel(bits):
+    """Token counts whose last block of 256 rows is at most half full, past what the kernel for up to 1024
+    tokens takes: the 128-row instantiation of the 256-column kernel (the producer / consumer and the plain
+    kernel have no second launch, and 256-row tiles are not chosen at five blocks of 128 rows), ragged in
+    rows, columns and the last step of both contractions; sampled rows, and one-hot rows bit for bit."""
+    K, N, M, r, group = 4128, 4104, 520, 16, 96
+    D = layer(bits, K, N, M, r, group, seed=15)
+    s = D["lora_scale"]
+    b.modulora_profile_begin()
+    Y, XA = b.modulora_f16_fwd(D["w"], D["Xd"], D["Ad"], D["Bd"], s)
+    dX, T = b.modulora_f16_bwd_input(D["w"], D["dYd"], D["Ad"], D["Bd"], s)
+    torch.cuda.synchronize()
+    names = {k for k in b.modulora_profile_end() if not k.startswith("lora_")}
+    assert names == {"f16_gemm_fwd", "f16_gemm_fwd_fixup", "f16_gemm_bwd", "f16_gemm_bwd_fixup"}, names
+    rows = np.unique(np.concatenate(([0, 127, 128, 383, 511, 512, M - 1], np.random.default_rng(3).integers(0, M, 40))))
+    Yr, XAr = pl.fwd(*oargs(D), np.ascontiguousarray(D["X"][rows]), D["A"], D["B"], s, D["bias"])
+    dXr, Tr = pl.bwd_input(*oargs(D), np.ascontiguousarray(D["dY"][rows]), D["A"], D["B"], s)
+    tight("Y", f64(Y)[rows], Yr, K + r)
+    tight("dX", f64(dX)[rows], dXr, N + r)
+    tight("XA", f64(XA)[rows], XAr, K, out_f16=False)
+    tight("dYBt", f64(T)[rows], Tr, N, out_f16=False)
+
+    E = layer(bits, K, N, 1, 0, group, seed=15, with_bias=False)
+    What = b.modulora_f16_dequant(E["w"])            # [N][K], bit-exact against the oracle (above)
+    for lo in (0, K - M):
+        X = torch.zeros((M, K), dtype=torch.float16, device="cuda")
+        X[torch.arange(M), lo + torch.arange(M)] = 1.0
+        Y1, _ = b.modulora_f16_fwd(E["w"], X, None, None, 1.0)
+        assert torch.equal(Y1.view(torch.int16), What.t()[lo:lo + M].contiguous().view(torch.int16))
+    for lo in (0, N - M):
+        dY = torch.zeros((M, N), dtype=torch.float16, device="cuda")
+        dY[torch.arange(M), lo + torch.arange(M)] = 1.0
+        dX1, _ = b.modulora_f16_bwd_input(E["w"], dY, None, None, 1.0)
+        assert torch.equal(dX1.view(torch.int16), What[lo:lo + M].contiguous().view(torch.int16))
 
 
 def test_outputs_do_not_depend_on_stale_memory():

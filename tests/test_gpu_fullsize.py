@@ -22,31 +22,32 @@ from gpu_util import assert_bar, assert_tight, f64
 
 pytestmark = pytest.mark.gpu
 
+# configuration, tokens (None: the configuration's own), kernel of the forward and of the backward product
 CASES = [
-    ("c2_7b_attn", None),
-    ("c3_7b_gate_up", None),
-    ("c3_7b_down", None),
-    ("c4_30b_attn", None),
-    ("c5_65b_attn", 16),
-    ("c5_65b_attn", 1),
-    ("c5_65b_attn", 256),
-    ("c5_65b_attn", 4096),
-    ("c5_65b_up", 16),
-    ("c5_65b_down", 16),
-    ("c5_65b_down", 1),
-    ("c4_30b_up", None),
-    ("c4_30b_down", None),
-    ("c5_65b_up", 1),
-    ("c5_65b_up", 256),
-    ("c5_65b_up", 4096),
-    ("c5_65b_down", 256),
-    ("c5_65b_down", 4096),
-    # the decoder layer of the benchmark at 128 tokens: the 128-row instantiation of the large tile kernel
-    ("c5_65b_attn", 32),      # two passes of the streaming kernels
-    ("c5_65b_up", 24),
-    ("c5_65b_attn", 128),
-    ("c5_65b_up", 128),
-    ("c5_65b_down", 128),
+    ("c2_7b_attn", None, "direct", "direct"),
+    ("c3_7b_gate_up", None, "256x256", "256x256"),
+    ("c3_7b_down", None, "256x256", "256x256"),
+    ("c4_30b_attn", None, "256x256", "256x256"),
+    ("c5_65b_attn", 16, "stream", "stream"),
+    ("c5_65b_attn", 1, "stream", "stream"),
+    ("c5_65b_attn", 256, "direct", "direct"),
+    ("c5_65b_attn", 4096, "256x256", "256x256"),
+    ("c5_65b_up", 16, "stream", "stream"),
+    ("c5_65b_down", 16, "stream", "stream"),
+    ("c5_65b_down", 1, "stream", "stream"),
+    ("c4_30b_up", None, "256x256", "256x256"),
+    ("c4_30b_down", None, "256x256", "256x256"),
+    ("c5_65b_up", 1, "stream", "stream"),
+    ("c5_65b_up", 256, "256x256", "256x256"),
+    ("c5_65b_up", 4096, "256x256", "256x256"),
+    ("c5_65b_down", 256, "direct", "256x256"),
+    ("c5_65b_down", 4096, "256x256", "256x256"),
+    ("c5_65b_attn", 32, "stream", "stream"),      # two passes
+    ("c5_65b_up", 24, "stream", "stream"),
+    ("c5_65b_attn", 128, "direct", "direct"),
+    ("c5_65b_up", 128, "direct", "direct"),
+    ("c5_65b_down", 128, "direct", "direct"),
+    ("c5_65b_up", 300, "128x256", "128x256"),     # the 128-row instantiation of the large tile kernel
 ]
 
 
@@ -68,16 +69,23 @@ def sample_rows(M):
     return np.unique(rows[rows < M])
 
 
-@pytest.mark.parametrize("name,M", CASES)
-def test_full_size_layer_against_oracle(name, M):
+def kernel_name(direction, kernel):
+    return "stream_" + direction if kernel == "stream" else "gemm_%s_%s" % (direction, kernel)
+
+
+@pytest.mark.parametrize("name,M,fwd_kernel,bwd_kernel", CASES)
+def test_full_size_layer_against_oracle(name, M, fwd_kernel, bwd_kernel):
     cfg = synth.CONFIGS[name] if M is None else synth.CONFIGS[name].with_M(M)
     L = synth.make_layer_torch(cfg, "cuda", seed=11)
     K, N, M, r, s = cfg.K, cfg.N, cfg.M, cfg.r, cfg.lora_scale
     w = b.QWeight(L["qweight"], L["scales"], L["zeros"], K, N, cfg.bits, cfg.group)
+    b.modulora_profile_begin()
     Y, XA = b.modulora_fwd(w, L["X"], L["A"], L["B"], s)
     dX, T = b.modulora_bwd_input(w, L["dY"], L["A"], L["B"], s)
     dA, dB = b.modulora_bwd_lora(L["X"], L["dY"], L["A"], L["B"], s, XA=XA, dYBt=T)
     torch.cuda.synchronize()
+    names = set(b.modulora_profile_end())
+    assert {kernel_name("fwd", fwd_kernel), kernel_name("bwd", bwd_kernel)} <= names, names
 
     # host copies for the oracle
     qw = L["qweight"].cpu().numpy().view(np.uint32)
@@ -92,10 +100,11 @@ def test_full_size_layer_against_oracle(name, M):
     dXr, Tr = oracle.bwd_input(*wargs, np.ascontiguousarray(dYh[rows]), Ah, Bh, s)
 
     extra_Y = extra_dX = 0.0
-    if M <= 32:   # code-domain arithmetic of the streaming kernels (see test_gpu_parity.py)
+    fwd_codes, bwd_codes = fwd_kernel == "stream", bwd_kernel == "stream"
+    if fwd_codes or bwd_codes:   # code-domain arithmetic of the streaming kernels (see test_gpu_parity.py)
         Wabs = np.abs(oracle.dequant_f32(*wargs).astype(np.float64))
-        extra_Y = 2.0 ** -8 * (np.abs(synth.bf16_bits_to_f64(Xh[rows])) @ Wabs.T)
-        extra_dX = 2.0 ** -7 * (np.abs(synth.bf16_bits_to_f64(dYh[rows])) @ Wabs)
+        extra_Y = fwd_codes * 2.0 ** -8 * (np.abs(synth.bf16_bits_to_f64(Xh[rows])) @ Wabs.T)
+        extra_dX = bwd_codes * 2.0 ** -7 * (np.abs(synth.bf16_bits_to_f64(dYh[rows])) @ Wabs)
     Yg, dXg = f64(Y)[rows], f64(dX)[rows]
     assert_bar("Y", Yg, Yr)
     assert_tight("Y", Yg, Yr, True, K, extra_Y)
@@ -118,8 +127,8 @@ def test_full_size_layer_against_oracle(name, M):
     rows_t = torch.from_numpy(rows).cuda()
     torch.backends.cuda.matmul.allow_tf32 = False
     for oname, act, out, P, F_up, ref_rows, Ksum, code_tol in (
-            ("Y", L["X"], Y, XA, L["B"], Yr, K, 2.0 ** -8 if M <= 32 else 0.0),
-            ("dX", L["dY"], dX, T, L["A"].t(), dXr, N, 2.0 ** -7 if M <= 32 else 0.0)):
+            ("Y", L["X"], Y, XA, L["B"], Yr, K, 2.0 ** -8 if fwd_codes else 0.0),
+            ("dX", L["dY"], dX, T, L["A"].t(), dXr, N, 2.0 ** -7 if bwd_codes else 0.0)):
         Wm = Wf.t() if oname == "Y" else Wf
         ref = act.float() @ Wm + s * (P @ F_up)
         scale = float(ref.abs().max())
@@ -137,13 +146,13 @@ def test_full_size_layer_against_oracle(name, M):
     # Each side carries one bfloat16 rounding per output element (uniform within half an ulp:
     # standard deviation 2^-9 / sqrt(3) relative, independent signs), so the two sums differ by
     # about 2^-9 / sqrt(3) * sqrt(sum (dY Y)^2 + sum (dX X)^2); eight standard deviations are
-    # allowed.  At M <= 32 the code-domain kernels add per-weight terms of the same size (the
+    # allowed.  The code-domain kernels (M <= 32) add per-weight terms of the same size (the
     # skipped rounding of the weight, the rounded scaled activation): three times as much.
     lhs_terms = L["dY"].double() * Y.double()
     rhs_terms = dX.double() * L["X"].double()
     lhs, rhs = float(lhs_terms.sum()), float(rhs_terms.sum())
     sigma = 2.0 ** -9 / np.sqrt(3.0) * float(torch.sqrt((lhs_terms ** 2).sum() + (rhs_terms ** 2).sum()))
-    assert abs(lhs - rhs) <= (24.0 if M <= 32 else 8.0) * sigma, (lhs, rhs, sigma)
+    assert abs(lhs - rhs) <= (24.0 if fwd_codes or bwd_codes else 8.0) * sigma, (lhs, rhs, sigma)
 
 
 def test_operands_beyond_four_gib():

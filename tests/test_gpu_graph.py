@@ -5,7 +5,7 @@ atomics, so results do not depend on timing), with the program's own eager work 
 synchronizations between the replays and new inputs written into the captured buffers each time.
 The shapes cover the launch configurations: the 128 x 64 producer / consumer kernel, the
 streaming kernels (M <= 16, one and two quantization groups per backward tile; two passes for 24
-tokens), the 256 x 256 kernel and its 128-row instantiation with a split contraction and the second launch, and the projection kernel's two forms
+tokens), the kernel for up to 1024 tokens, the 256 x 256 kernel and its 128-row instantiation with a split contraction and the second launch, and the projection kernel's two forms
 (one row tile per workgroup; four that share the factor, with its finish launch), each with the
 adapter-gradient launches."""
 import pytest
@@ -27,6 +27,7 @@ pytestmark = pytest.mark.gpu
     (2, 6400, 520, 1100, 8, 64),      # projection with four row tiles per workgroup, slices of the contraction + finish
     (3, 4096, 1024, 128, 8, 128),     # 128-row instantiation of the 256-column kernel, split contraction + fix-up
     (3, 4096, 4096, 24, 8, 128),      # two passes of the streaming kernels that share the scratch
+    (3, 4096, 2600, 100, 8, 128),     # the kernel for up to 1024 tokens, slices of the contraction + second launch
 ])
 def test_graph_replays_equal_eager_steps(bits, K, N, M, r, group):
     L = layer(bits, K, N, M, r, group, seed=4)
