@@ -293,12 +293,13 @@ hipError_t launch_lora_down(const DownArgs &a, hipStream_t stream) {
 //         7.9 us against 9.4).  8 (256-byte pieces) from 128 MB on, where HBM does the work (247 MB:
 //         47 us against 55; r = 32: 55 against 72), for r <= 32; beyond that eight columns'
 //         accumulators leave too few waves (r = 64 at 2048 x 16384: 26 us against 43).
-//         Registers let two workgroups share a compute unit only at CPL 4, r <= 16, bfloat16; the others
-//         run 256 workgroups at a time, and 257 ... 512 blocks of 64 columns as two rounds: there 8 goes
-//         from the first row on (binary16, r = 8, 8192 + 8320 columns: M = 1536 21.8 -> 18.0 us, 3000 39.1 ->
-//         30.5; not binary16 with r > 16, where it is even to 4 % the slower).  So it does where 129 ... 170
-//         blocks of 64 columns allow one chunk of rows, but half as many of 128 three (binary16,
-//         4096 + 4224 columns, M = 4096: 25.0 -> 21.1).
+//         From 257 rows on (16 waves) registers let two workgroups share a compute unit only at CPL 4, r <= 16,
+//         bfloat16; the others run 256 workgroups at a time, and 257 ... 512 blocks of 64 columns as two
+//         rounds: there 8 goes from the first row past 256 on (binary16, r = 8, 8192 + 8320 columns: M = 256 5.6
+//         against 6.1 us, 400 10.4 -> 8.3, 1536 21.8 -> 18.0, 3000 39.1 -> 30.5; 8192 + 22016: M = 256 5.9 against 6.5,
+//         1024 17.6 -> 16.2; more blocks, 22016 x 2: M = 1024 25.1 against 27.3; not binary16 with r > 16, where
+//         it is up to 7 % the slower from 1280 rows on).  So it does where 129 ... 170 blocks of 64 columns allow
+//         one chunk of rows, but half as many of 128 three (binary16, 4096 + 4224 columns, M = 4096: 25.0 -> 21.1).
 //   rows  in chunks that leave partials for a reduction launch (4 us) where the columns are too
 //         few to occupy the chip and at least 1024 rows remain to each: 256 + 256 columns, M = 4096:
 //         14.4 -> 6.4 + 4.1 us; 2048 + 2048: 16.3 -> 9.3 + 4.2; a chunk of 512 rows gains less than
@@ -318,7 +319,7 @@ GradGeom grad_geom(int M, int K, int N, int r, bool f16) {
     const bool pair = !f16 && g.rg == 1;             // two workgroups of CPL 4 share a compute unit
     const int blocks4 = (K + 63) / 64 + (N + 63) / 64;
     const bool wide = (size_t)M * ((size_t)K + N) * 2 >= (size_t)128 << 20 ||
-                      (!pair && ((blocks4 > 256 && !(f16 && g.rg == 2)) || (blocks4 > 128 && blocks4 <= 170 && M >= 3 * 960)));
+                      (!pair && ((blocks4 > 256 && blocks4 <= 512 && M > 256 && !(f16 && g.rg == 2)) || (blocks4 > 128 && blocks4 <= 170 && M >= 3 * 960)));
     g.cpl = g.rg <= 2 && wide ? 8 : 4;
     const int wcols = 16 * g.cpl;
     g.cols_a = (K + wcols - 1) / wcols;

@@ -23,7 +23,8 @@ SHAPES = [
     (8192, 8456, 4100, 8),         # from 128 MB of activations on: eight columns per lane
     (16384, 264, 4105, 20),
     (4096, 4232, 2900, 8),         # binary16: eight columns per lane, three chunks
-    (8192, 8456, 1100, 16),        # binary16: eight columns per lane below 128 MB
+    (8192, 8456, 300, 16),         # binary16: eight columns per lane below 128 MB
+    (8192, 8456, 256, 16),         # four
     (8192, 8456, 6200, 3),         # three or more chunks of 131 column blocks
     (4096, 4232, 4100, 40),        # the same at 131 blocks of 64 columns
 ]
@@ -72,7 +73,7 @@ def test_rows_are_cut_where_column_blocks_fill_half_the_chip(K, N, M, r, f16):
 
 
 @pytest.mark.parametrize("f16", [False, True])
-@pytest.mark.parametrize("K,N,M,r", [(64, 72, 31, 16), (96, 136, 600, 17), (160, 264, 70, 64), (8192, 8264, 70, 8)])
+@pytest.mark.parametrize("K,N,M,r", [(64, 72, 31, 16), (96, 136, 600, 17), (160, 264, 70, 64), (8192, 8264, 300, 8)])
 def test_infinities_stay_infinities(K, N, M, r, f16):
     """Overflowed activations or hand-offs (common in binary16): an infinite factor gives +-inf in the sums
     that it enters and NaN only where it meets zero or an opposite infinity, and leaves the others alone."""
