@@ -443,19 +443,23 @@ __global__ __launch_bounds__(RG * CPL <= 8 ? 1024 : 512) void lora_grad_partial_
     // An infinity has no exact split (inf - inf is NaN) and meets the zero parts of the other operand
     // (inf * 0).  A wave that finds a NaN among its sums adds its rows again with fp32 multiply-adds, which
     // give what the definition does (every dY NaN, 4096 x (8192 + 22016), r = 8: 161 us a call instead of 42).
-    float sum = 0.f;
+    bool nan = false;
 #pragma unroll
     for (int q = 0; q < CPL; ++q)
 #pragma unroll
-        for (int t = 0; t < RG; ++t) sum += (acc[q][t][0] + acc[q][t][1]) + (acc[q][t][2] + acc[q][t][3]);
-    if (__builtin_expect(__any(sum != sum), 0)) {
+        for (int t = 0; t < RG; ++t)             // a compare tells of two sums whether either is NaN
+            nan |= __builtin_isunordered(acc[q][t][0], acc[q][t][1]) | __builtin_isunordered(acc[q][t][2], acc[q][t][3]);
+    if (__builtin_expect(__any(nan), 0)) {
 #pragma unroll
         for (int q = 0; q < CPL; ++q)
 #pragma unroll
             for (int t = 0; t < RG; ++t) acc[q][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        int c_again = c;
+        asm("" : "+v"(c_again));                         // addresses of its own: none stays alive for it in the loop above
+        const uint16_t *col_again = act + (c_again < C ? c_again : 0);
         for (int mb = m_begin + 32 * wave; mb < m_end; mb += 32 * nwaves)
             for (int m = mb; m < mb + 32 && m < m_end; ++m) {
-                const words_t x = *reinterpret_cast<const words_t *>(col + (size_t)m * C);
+                const words_t x = *reinterpret_cast<const words_t *>(col_again + (size_t)m * C);
 #pragma unroll
                 for (int t = 0; t < RG; ++t)
 #pragma unroll
