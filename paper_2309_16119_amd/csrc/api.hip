@@ -82,8 +82,8 @@ WsLayout ws_layout(int32_t K, int32_t N, int32_t M, int32_t r) {
     // fp32 partial tiles of the split contraction of the 256 x 256 kernel (also when r == 0)
     const size_t part = align256(mlr::gemm_partial_bytes(M, K, N));
     l.gemm_part_bytes = part;
-    l.direct_fwd = mlr::direct_wins(K, N, M, r, false);
-    l.direct_bwd = mlr::direct_wins(K, N, M, r, true);
+    l.direct_fwd = mlr::direct_wins(K, N, M, r, false, false);
+    l.direct_bwd = mlr::direct_wins(K, N, M, r, true, false);
     const size_t dir = direct_bytes(K, N, M, r, l.direct_fwd, l.direct_bwd);
     if (r <= 0) {
         l.gemm_part = 0;
@@ -117,7 +117,7 @@ WsLayout ws_layout_fwd(const mlr::LayerView &v, int32_t M, int32_t r, size_t ava
         l.total = mlr::smallm_fwd_ws_bytes(v, r);
         return l;
     }
-    if (mlr::direct_wins(v.K, v.N, M, r, false)) {
+    if (mlr::direct_wins(v.K, v.N, M, r, false, false)) {
         l.total = direct_bytes(v.K, v.N, M, r, true, false);
         l.direct_fwd = l.total <= avail_direct;
         if (l.direct_fwd) return l;
@@ -444,8 +444,8 @@ F16Ws f16_ws(int32_t K, int32_t N, int32_t M, int32_t r) {
     }
     // MODULORA_F16_PLAIN (read once per process) keeps every shape on the plain kernel, for comparisons
     static const bool force_plain = std::getenv("MODULORA_F16_PLAIN") != nullptr;
-    l.direct_fwd = !force_plain && mlr::direct_wins(K, N, M, r, false);
-    l.direct_bwd = !force_plain && mlr::direct_wins(K, N, M, r, true);
+    l.direct_fwd = !force_plain && mlr::direct_wins(K, N, M, r, false, true);
+    l.direct_bwd = !force_plain && mlr::direct_wins(K, N, M, r, true, true);
     const size_t dir = direct_bytes(K, N, M, r, l.direct_fwd, l.direct_bwd);
     if (dir > l.total) l.total = dir;
     return l;

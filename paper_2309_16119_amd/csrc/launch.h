@@ -325,15 +325,24 @@ inline DirectPlan direct_plan(int M, int C, int Cout, bool backward, double *us 
 }
 // Whether gemm_direct.hip is the quicker way for this shape and direction, by its own estimate against
 // that of the tile kernels (gemm_tile_us()) plus 9 us for their projection launches, where there is an
-// adapter.  The margins (1.1 where every workgroup runs at once, 1.2 and 1.3 beyond: the estimates
-// drift apart as many rounds lower the clock) lose 0.35 % on average to always taking the quicker side,
-// over eight layers of 2048 x 4096 to 8192 x 22016 and 33 ... 1024 tokens (192 timed pairs), and never
-// take the direct kernel where it is more than 5 % the slower one.  Measured, us a call forward /
+// adapter.  The margins are 1.1 where every workgroup runs at once and 1.2 or 1.3 beyond, because many
+// rounds lower the clock.  They are 1.5 for long calls of three rounds and more against whole 256-row tiles,
+// whose steps then take 1.5 us and not the 1.83 of their estimate (6656 x 17920, r = 8: 392 tokens 137 us with
+// tiles, 156 direct; binary16, 407 tokens 147 and 170).
+// In bfloat16 a rank beyond 16 costs the direct kernel more than the tiles.  For each further 16 columns a turn of
+// the projection takes 3.2 us in the product kernel.  The second launch adds the projection's parts in trips of
+// eight loads, 0.5 us each, and multiplies.  The tiles pay 2 ... 6 us per 16 columns, and with the rank's share of the
+// projection, which reads B^T slowly (1024 x 8832 forward, 38 tokens: r = 8 18.2 us with tiles, 16.3 direct, r = 32
+// 18.4 and 21.9, r = 64 23.7 and 31.6).  In binary16 the tiles' epilogue pays for a rank as well: no such term.
+// Over 2295 timed pairs (33 ... 1024 tokens, 2^23 to 2^28 weights, r = 0 to 64, both conventions, wherever the
+// margins 1.1 to 1.3 alone take the direct kernel) the choice is on average 0.5 % (bfloat16) and 0.1 % (binary16)
+// slower than the quicker way.  It is over 3 % slower with the direct kernel in 1.2 % of them (at most 13 %); without the
+// last two rules it was in 7 % (at most 41 %).  Measured, us a call forward /
 // backward, r = 8: 8192 x 8192, 48 tokens 42 / 43 -> 23 / 26, 128 tokens 42 / 42 -> 30 / 33; 4096 x 4096,
 // 512 tokens 37 / 36 -> 30 / 33; beyond the line 8192 x 22016, 512 tokens: 193 with tiles, 225 direct.
 // Layers under 2^23 weights keep the tile kernels (a few us either way); over 2^32 the kernel's 32-bit
 // offsets would overflow.
-bool direct_wins(int K, int N, int M, int r, bool backward);
+bool direct_wins(int K, int N, int M, int r, bool backward, bool f16);
 double gemm_tile_us(int M, int C, int Cout);      // gemm_tile.hip: estimated time of the cheapest tile kernel
 hipError_t launch_direct(const SmallArgs &a, bool backward, hipStream_t stream);
 

@@ -22,12 +22,12 @@ SHAPES = [
     (3, 4096, 2056, 33, 8, 128),        # two row tiles; backward contraction ends 8 elements into a chunk
     (4, 4256, 4104, 65, 17, 224),       # three row tiles; forward contraction ends in half a step
     (2, 2080, 4104, 100, 5, 32),        # four row tiles; a group per 32-code block
-    (3, 4160, 2568, 129, 64, 4160),     # two row blocks; one group per row
+    (3, 4160, 4104, 129, 64, 4160),     # two row blocks; one group per row
     (4, 4128, 2304, 256, 16, 96),       # odd number of blocks per group
     (2, 4128, 8200, 100, 0, 32),        # no adapter
     (3, 4096, 4096, 512, 8, 128),       # four row blocks
     (4, 4096, 2568, 777, 8, 128),       # seven row blocks, the last ragged, whole contractions
-    (2, 3104, 2824, 1000, 33, 3104),    # eight
+    (2, 4000, 3336, 1000, 33, 4000),    # eight
     (3, 8224, 2624, 20, 8, 32),         # one row tile: a shape that no streaming kernel takes
     (4, 4096, 2104, 7, 33, 128),        # a handful of tokens that the backward streaming kernel does not take
     (3, 288, 32768, 40, 8, 288),        # an output of little more than two column blocks (backward only)
@@ -87,6 +87,36 @@ def test_against_the_oracle(bits, K, N, M, r, group, conv):
         _close(T, Tr, 2.0 ** -20, N)
     # no atomics: a second run gives the same bits
     assert torch.equal(dX.view(torch.int16), bwd(w, dY, Ad, Bd, s)[0].view(torch.int16))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("conv,direction,K,N,M,r,direct", [
+    # the rank's price: an output of 69 column blocks, whose 32 projection parts the second launch adds in a row
+    ("bf16", "fwd", 1024, 8832, 38, 8, True),
+    ("bf16", "fwd", 1024, 8832, 38, 64, False),
+    ("bf16", "bwd", 9728, 1536, 288, 16, True),
+    ("bf16", "bwd", 9728, 1536, 288, 32, False),
+    # the tile kernels of binary16 pay for a rank as well
+    ("f16", "fwd", 3072, 3072, 245, 64, True),
+    ("bf16", "fwd", 4096, 4096, 129, 64, True),
+    # five rounds of workgroups against whole 256-row tiles, three against 128-row ones (a last block of 88 rows)
+    ("bf16", "fwd", 6656, 17920, 392, 8, False),
+    ("f16", "fwd", 6656, 17920, 407, 8, False),
+    ("bf16", "fwd", 22016, 8192, 600, 8, True),
+    ("bf16", "fwd", 6656, 6656, 777, 8, True),
+])
+def test_runs_where_it_is_the_quicker_way(conv, direction, K, N, M, r, direct):
+    cfg = synth.LayerConfig("t", K, N, 3, 128, M, r)
+    L = synth.make_layer_torch(cfg, device="cuda", seed=9)
+    act = L["X"] if direction == "fwd" else L["dY"]
+    if conv == "f16":
+        w = b.QWeightF16(L["qweight"], L["scales"], -L["scales"], None, K, N, 3, 128)
+        call = b.modulora_f16_fwd if direction == "fwd" else b.modulora_f16_bwd_input
+        act = act.to(torch.float16)
+    else:
+        w = b.QWeight(L["qweight"], L["scales"], L["zeros"], K, N, 3, 128)
+        call = b.modulora_fwd if direction == "fwd" else b.modulora_bwd_input
+    assert _ran(lambda: call(w, act, L["A"], L["B"], 2.0), conv, direction)[1] == direct
 
 
 @pytest.mark.gpu
