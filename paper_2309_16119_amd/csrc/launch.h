@@ -340,8 +340,10 @@ inline DirectPlan direct_plan(int M, int C, int Cout, bool backward, double *us 
 // last two rules it was in 7 % (at most 41 %).  Measured, us a call forward /
 // backward, r = 8: 8192 x 8192, 48 tokens 42 / 43 -> 23 / 26, 128 tokens 42 / 42 -> 30 / 33; 4096 x 4096,
 // 512 tokens 37 / 36 -> 30 / 33; beyond the line 8192 x 22016, 512 tokens: 193 with tiles, 225 direct.
-// Layers under 2^23 weights keep the tile kernels (a few us either way); over 2^32 the kernel's 32-bit
-// offsets would overflow.
+// Layers under 2^23 weights keep the tile kernels, whose tests choose such sizes; that line is not where the times
+// cross.  Timed below it with the rule alone (188 pairs, 1024 x 1024 to 2048 x 4000, 33 ... 512 tokens, r = 8, us a
+// call with tiles / direct, forward): 2048 x 2048, 64 tokens 24.4 / 15.2, binary16 42.2 / 15.9; 1024 x 1024, 64 tokens 17.3 / 15.0,
+// 512 tokens 17.2 / 17.1.  Over 2^32 weights the kernel's 32-bit offsets would overflow.
 bool direct_wins(int K, int N, int M, int r, bool backward, bool f16);
 double gemm_tile_us(int M, int C, int Cout);      // gemm_tile.hip: estimated time of the cheapest tile kernel
 hipError_t launch_direct(const SmallArgs &a, bool backward, hipStream_t stream);

@@ -35,7 +35,8 @@ __device__ __forceinline__ float f16_bits_to_float(uint16_t bits) { return __hal
 // A workgroup takes 64 rows x TK inputs (TK = 128, or 256 for groups of 256): a thread holds 8 (16)
 // float4, whose loads are all issued first; a group is 8, 16, 32 or 64 adjacent lanes of one load, so
 // its range is a cross-lane reduction.  The tile's rows are wide enough (512 bytes) for the memory
-// and the tile few enough registers for eight workgroups on a compute unit.
+// and 128 inputs few enough registers (52) for eight workgroups on a compute unit.  256 inputs take 86, which
+// leaves five, and reach almost the same rate: 137 us at that size with groups of 256 (421 in two passes).
 //
 // The quotient w / s is not divided out per element (ten instructions each): with inv = 1 / s off
 // by an ulp, t = w inv is within 2^-22 + 2^-23 (relative) of the rounded quotient, and
