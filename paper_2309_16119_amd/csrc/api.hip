@@ -186,6 +186,7 @@ int run_fwd(const modulora_qweight *w, const uint16_t *X, int32_t M, const float
         d.lora_scale = lora_scale;
         d.act_ext = reinterpret_cast<uint16_t *>(ws + l.act_ext);
         d.RE = mlr::lora_ext_len(r);
+        d.segments = mlr::lora_ext_segments(false);
         d.w_ext = reinterpret_cast<uint16_t *>(ws + l.w_ext);
         d.Wsrc = B; d.w_from_A = false; d.Cw = w->d_out;
         d.partials = reinterpret_cast<float *>(ws + l.dpart);
@@ -352,6 +353,7 @@ int modulora_bwd_input(const modulora_qweight *w, const uint16_t *dY, int32_t M,
         d.lora_scale = lora_scale;
         d.act_ext = reinterpret_cast<uint16_t *>(ws + l.act_ext);
         d.RE = mlr::lora_ext_len(r);
+        d.segments = mlr::lora_ext_segments(false);
         d.w_ext = reinterpret_cast<uint16_t *>(ws + l.w_ext);
         d.Wsrc = A; d.w_from_A = true; d.Cw = w->d_in;
         d.partials = reinterpret_cast<float *>(ws + l.dpart);
@@ -423,13 +425,16 @@ mlr::F16Layer view_of(const modulora_qweight_f16 *w) {
     return mlr::F16Layer{w->d_in, w->d_out, w->bits, w->group_size, w->qweight, w->scales, w->zeros, w->bias};
 }
 struct F16Ws {
-    size_t p0, p1, gpart, dpart, gemm_part, total;
+    size_t act_ext, w_ext, p0, p1, gpart, dpart, gemm_part, total;
     bool direct_fwd, direct_bwd;
 };
 F16Ws f16_ws(int32_t K, int32_t N, int32_t M, int32_t r) {
     F16Ws l{};
     size_t off = 0;
     if (r > 0) {
+        const size_t RE = (size_t)mlr::lora_ext_len(r, true);
+        l.act_ext = off; off += align256((size_t)M * RE * 2);
+        l.w_ext = off;   off += align256((size_t)(K > N ? K : N) * RE * 2);
         l.p0 = off;    off += align256((size_t)M * r * 4);
         l.p1 = off;    off += align256((size_t)M * r * 4);
         l.gpart = off; off += align256(mlr::grad_geom(M, K, N, r, true).partial_floats * 4);
@@ -442,26 +447,48 @@ F16Ws f16_ws(int32_t K, int32_t N, int32_t M, int32_t r) {
         const size_t small = mlr::smallm_ws_bytes(K, N, r);
         if (small > l.total) l.total = small;
     }
-    // MODULORA_F16_PLAIN (read once per process) keeps every shape on the plain kernel, for comparisons
-    static const bool force_plain = std::getenv("MODULORA_F16_PLAIN") != nullptr;
-    l.direct_fwd = !force_plain && mlr::direct_wins(K, N, M, r, false, true);
-    l.direct_bwd = !force_plain && mlr::direct_wins(K, N, M, r, true, true);
+    l.direct_fwd = !mlr::f16_plain_forced() && mlr::direct_wins(K, N, M, r, false, true);
+    l.direct_bwd = !mlr::f16_plain_forced() && mlr::direct_wins(K, N, M, r, true, true);
     const size_t dir = direct_bytes(K, N, M, r, l.direct_fwd, l.direct_bwd);
     if (dir > l.total) l.total = dir;
     return l;
 }
 // P = act F for binary16 activations (X A or dY B^T; fp32-exact products on the matrix cores): the
-// projection kernel of the bfloat16 path with each activation split into two bfloat16 operands.  No
-// extended-contraction operands here: this path adds the adapter term in the product kernel's epilogue.
+// projection kernel of the bfloat16 path with each activation split into two bfloat16 operands.
 int f16_project(const uint16_t *act, int32_t M, int32_t C, const float *F, bool f_is_A, int32_t r, float *P, char *ws,
                 const F16Ws &l, hipStream_t st) {
     mlr::DownArgs d{};
     d.act = act; d.act_f16 = true; d.M = M; d.C = C; d.r = r;
     d.Fm = F; d.f_is_A = f_is_A;
     d.P = P; d.lora_scale = 1.0f;
-    d.act_ext = nullptr; d.RE = 0; d.w_ext = nullptr; d.Wsrc = nullptr; d.w_from_A = false; d.Cw = 0;
     d.partials = reinterpret_cast<float *>(ws + l.dpart);
     return hip_status(mlr::launch_lora_down(d, st));
+}
+// One direction through the tile kernels: the projection (with the extended operands of the tuned
+// kernels, which the plain one has no use for), then the product.
+int f16_tiles(const modulora_qweight_f16 *w, bool backward, const uint16_t *act, int32_t M, const float *A, const float *B, int32_t r,
+              float lora_scale, uint16_t *out, float *P_out, char *ws, const F16Ws &l, hipStream_t st) {
+    mlr::F16Adapter ad{};
+    if (r > 0) {
+        mlr::DownArgs d{};
+        d.act = act; d.act_f16 = true; d.M = M; d.C = backward ? w->d_out : w->d_in; d.r = r;
+        d.Fm = backward ? B : A; d.f_is_A = !backward;
+        d.P = P_out ? P_out : reinterpret_cast<float *>(ws + l.p0);
+        d.lora_scale = lora_scale;
+        d.partials = reinterpret_cast<float *>(ws + l.dpart);
+        if (!mlr::f16_plain_forced()) {
+            d.RE = mlr::lora_ext_len(r, true);
+            d.segments = mlr::lora_ext_segments(true);
+            d.act_ext = reinterpret_cast<uint16_t *>(ws + l.act_ext);
+            d.w_ext = reinterpret_cast<uint16_t *>(ws + l.w_ext);
+            d.Wsrc = backward ? A : B; d.w_from_A = backward; d.Cw = backward ? w->d_in : w->d_out;
+        }
+        const int s = hip_status(mlr::launch_lora_down(d, st));
+        if (s != MODULORA_OK) return s;
+        ad = mlr::F16Adapter{d.P, d.Wsrc ? d.Wsrc : (backward ? A : B), r, lora_scale, d.act_ext, d.w_ext, d.RE};
+    }
+    float *parts = l.total > 0 ? reinterpret_cast<float *>(ws + l.gemm_part) : nullptr;
+    return hip_status(mlr::launch_f16_gemm(view_of(w), backward, act, M, out, ad, parts, st));
 }
 
 // the codes and scales of the layer as the streaming kernels take them (zero points travel separately)
@@ -515,13 +542,7 @@ int modulora_f16_fwd(const modulora_qweight_f16 *w, const uint16_t *X, int32_t M
         sa.f16 = true; sa.zeros16 = w->zeros; sa.bias16 = w->bias;
         return hip_status(streams ? mlr::launch_smallm_fwd(sa, st) : mlr::launch_direct(sa, false, st));
     }
-    float *P = nullptr;
-    if (r > 0) {
-        P = XA ? XA : reinterpret_cast<float *>(static_cast<char *>(workspace) + l.p0);
-        if ((s = f16_project(X, M, w->d_in, A, true, r, P, static_cast<char *>(workspace), l, st)) != MODULORA_OK) return s;
-    }
-    float *parts = l.total > 0 ? reinterpret_cast<float *>(static_cast<char *>(workspace) + l.gemm_part) : nullptr;
-    return hip_status(mlr::launch_f16_gemm(view_of(w), false, X, M, Y, P, B, r, lora_scale, parts, st));
+    return f16_tiles(w, false, X, M, A, B, r, lora_scale, Y, XA, static_cast<char *>(workspace), l, st);
 }
 
 int modulora_f16_bwd_input(const modulora_qweight_f16 *w, const uint16_t *dY, int32_t M, const float *A, const float *B,
@@ -546,13 +567,7 @@ int modulora_f16_bwd_input(const modulora_qweight_f16 *w, const uint16_t *dY, in
         sa.f16 = true; sa.zeros16 = w->zeros; sa.bias16 = nullptr;
         return hip_status(streams ? mlr::launch_smallm_bwd(sa, st) : mlr::launch_direct(sa, true, st));
     }
-    float *P = nullptr;
-    if (r > 0) {
-        P = dYBt ? dYBt : reinterpret_cast<float *>(static_cast<char *>(workspace) + l.p0);
-        if ((s = f16_project(dY, M, w->d_out, B, false, r, P, static_cast<char *>(workspace), l, st)) != MODULORA_OK) return s;
-    }
-    float *parts = l.total > 0 ? reinterpret_cast<float *>(static_cast<char *>(workspace) + l.gemm_part) : nullptr;
-    return hip_status(mlr::launch_f16_gemm(view_of(w), true, dY, M, dX, P, A, r, lora_scale, parts, st));
+    return f16_tiles(w, true, dY, M, A, B, r, lora_scale, dX, dYBt, static_cast<char *>(workspace), l, st);
 }
 
 int modulora_f16_bwd_lora(int32_t d_in, int32_t d_out, int32_t M, int32_t r, float lora_scale, const uint16_t *X,

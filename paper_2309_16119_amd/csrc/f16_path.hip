@@ -9,9 +9,17 @@
 // the same LSB-first bitstream as in the bfloat16 path.  What is materialized tile by tile in
 // LDS and consumed by v_mfma_f32_32x32x16_f16; it never reaches HBM.
 //
-// This path has its own, plainer kernels (one tile shape, adapter term in the epilogue):
+// The products run on the binary16 instantiations of the tuned kernels: gemm_big.hip and gemm_mid.hip by
+// the estimate of gemm_tile.hip, the adapter term carried as six bfloat16 segments of the contraction.
+// (Its term s P F in their epilogues, fp32 on the vector ALUs, cost 4 us per 8 columns of rank in a 256 x 256
+// tile and 8 ... 60 us in the second launch, whose single waves waited for it: 924 tokens x 6272 x 8192, r = 16,
+// 93 + 44 and 97 + 39 us a product, now 98 + 13 and 104 + 11; 450 x 4608 x 15744, r = 32, 70 + 69 and 199, now
+// 76 + 13 and 79 + 11.)  Its own kernels, plainer ones:
 //   f16_dequant_kernel   test-only materialization of What
-//   f16_gemm_kernel      the two products with What, adapter term and bias in the epilogue
+//   f16_gemm_kernel      the two products with What, adapter term and bias in the epilogue; only where
+//                        MODULORA_F16_PLAIN asks for it: up to six times slower on every shape timed (31 tokens
+//                        x 14464 x 512: 190 us against 30 + 4; 318 x 10624 x 384: 144 against 24 + 4; 80 x 256 x
+//                        512: 11 and 16 against 7 and 8)
 // The projections P = act F (X A or dY B^T) reuse lora_down_kernel, each binary16 activation split
 // exactly into two bfloat16 operands; the adapter gradients reuse lora_grad_partial_kernel with a
 // binary16 element conversion.
@@ -388,40 +396,26 @@ static hipError_t launch_f16_gemm_bits(F16GemmArgs &a, bool backward, hipStream_
     return small ? launch_f16_gemm_variant<BITS, false, 64>(a, stream) : launch_f16_gemm_variant<BITS, false, 128>(a, stream);
 }
 
-hipError_t launch_f16_gemm(const F16Layer &w, bool backward, const uint16_t *act, int M, uint16_t *out, const float *P,
-                           const float *Fm, int r, float lora_scale, float *partials, hipStream_t stream) {
-    // About one 128 x 64 tile per compute unit (half a round to a round and a quarter of the 256):
-    // the producer / consumer kernel of the bfloat16 path, instantiated for this storage convention
-    // (its loads, LDS layout and wave roles are the same; dequantization, MFMA type and epilogue
-    // differ).  Measured: 33 against 64-69 us at 512 x 4096 x 4096; with many rounds of such small
-    // tiles (4096 x 8192 x 8192) the kernel below is the faster one, 826 against 1197 us.
-    {
-        const int Cout = backward ? w.K : w.N;
-        const long tiles = (long)((M + 127) / 128) * ((Cout + 63) / 64);
-        const long tiles256 = (long)((M + 255) / 256) * ((Cout + 255) / 256);
-        // a hundred-odd tokens (the last block of 256 rows at most half full) against a large weight: the
-        // 256-column kernel with 128-row tiles, as on the bfloat16 path (27 + 7 against 49 us at 128 x 8192 x 8192)
-        const bool half_rows = big_plan(M, backward ? w.N : w.K, Cout).mt == 128 && (long)w.K * w.N >= 4096L * 4096L;
-        const bool use_mid = !half_rows && tiles >= 128 && tiles <= 320;
-        // a few dozen 256 x 256 tiles or more: that kernel (the tiles of a partial last round are cut
-        // into slices of the contraction, as on the bfloat16 path)
-        const bool use_big = half_rows || (!use_mid && tiles256 >= 24);
-        // MODULORA_F16_PLAIN (read once per process) keeps every shape on the plain kernel, for comparisons
-        static const bool force_plain = std::getenv("MODULORA_F16_PLAIN") != nullptr;
-        if (M > 32 && (use_mid || use_big) && !force_plain) {
-            GemmArgs g{};
-            g.w.K = w.K; g.w.N = w.N; g.w.bits = w.bits; g.w.group = w.group;
-            g.w.qweight = w.qweight; g.w.scales = w.scales; g.w.zeros = nullptr;
-            g.backward = backward; g.act = act; g.M = M; g.out = out;
-            g.zeros16 = w.zeros; g.bias16 = w.bias;
-            g.ep_P = r > 0 ? P : nullptr; g.ep_F = Fm; g.ep_r = r; g.ep_scale = lora_scale;
-            g.partials = partials;
-            g.partials_bytes = partials ? gemm_partial_bytes(M, w.K, w.N) : 0;
-            return use_mid ? launch_gemm_mid_f16(g, stream) : launch_gemm_big_f16(g, stream);
-        }
+bool f16_plain_forced() {
+    static const bool forced = std::getenv("MODULORA_F16_PLAIN") != nullptr;      // read once per process
+    return forced;
+}
+
+hipError_t launch_f16_gemm(const F16Layer &w, bool backward, const uint16_t *act, int M, uint16_t *out,
+                           const F16Adapter &ad, float *partials, hipStream_t stream) {
+    if (!f16_plain_forced()) {
+        GemmArgs g{};
+        g.w.K = w.K; g.w.N = w.N; g.w.bits = w.bits; g.w.group = w.group;
+        g.w.qweight = w.qweight; g.w.scales = w.scales; g.w.zeros = nullptr;
+        g.backward = backward; g.act = act; g.M = M; g.out = out;
+        g.zeros16 = w.zeros; g.bias16 = w.bias;
+        g.act_ext = ad.act_ext; g.w_ext = ad.w_ext; g.RE = ad.RE;
+        g.partials = partials;
+        g.partials_bytes = partials ? gemm_partial_bytes(M, w.K, w.N) : 0;
+        return launch_gemm_f16(g, stream);
     }
     F16GemmArgs a;
-    a.w = w; a.act = act; a.M = M; a.out = out; a.P = P; a.Fm = Fm; a.r = r; a.lora_scale = lora_scale;
+    a.w = w; a.act = act; a.M = M; a.out = out; a.P = ad.P; a.Fm = ad.Fm; a.r = ad.r; a.lora_scale = ad.lora_scale;
     a.tiles_m = a.tiles_c = 0;
     switch (w.bits) {
         case 2: return launch_f16_gemm_bits<2>(a, backward, stream);

@@ -105,11 +105,10 @@ __device__ __forceinline__ BigItem big_item_of_block(int bid, const BigPlan &p) 
 
 // Epilogue of one wave for its i-th block of 32 rows: one RNE to bfloat16 (binary16); the
 // 32 x 64 patch goes through LDS so that the global stores are 16 bytes per lane and 128
-// contiguous bytes per row.  F16 (the layer in the paper's own storage convention): the adapter
-// term s P F and the bias join here, before the rounding (Figure 1 / eq. (3); the bias belongs
-// to the frozen layer and enters the forward pass only); P's 32 rows pass through LDS behind
-// the patches.
-// `slot`: which of the per-wave LDS areas (patch, rows of P) this wave uses.
+// contiguous bytes per row.  F16 (the layer in the paper's own storage convention): the bias joins
+// here, before the rounding (Figure 1 / eq. (3); it belongs to the frozen layer and enters the
+// forward pass only).
+// `slot`: which of the per-wave LDS patches this wave uses.
 template <bool F16, int WM>
 __device__ __forceinline__ void big_epilogue_rows(f32x16 (&acc_i)[big::TJ], int i, unsigned char *smem, const GemmArgs &a, int Cout,
                                                   int m0, int c0, int wave, int lane, int slot) {
@@ -117,24 +116,13 @@ __device__ __forceinline__ void big_epilogue_rows(f32x16 (&acc_i)[big::TJ], int 
     const int wm = wave >> 2, wn = wave & 3;
     uint16_t *out = a.out;
     const int M = a.M;
-    if (F16) {
-        const int r = a.ep_r, N = a.w.N;
-        const bool bwd = a.backward;
-        float *Ps = reinterpret_cast<float *>(smem + 40960) + slot * (32 * 64);   // [jj][32 rows]
-        int cc[TJ];
-        float lora[TJ][16];
+    if (F16 && !a.backward && a.bias16 != nullptr) {
 #pragma unroll
         for (int j = 0; j < TJ; ++j) {
             const int col = c0 + wn * WN + j * 32 + (lane & 31);
-            cc[j] = col < Cout ? col : Cout - 1;
-        }
-        adapter_term_32rows<TJ>(a.ep_P, a.ep_F, r, N, bwd, m0 + wm * WM + i * 32, M, cc, Ps, lane, lora);
+            const float bias = half_bits_to_float(a.bias16[col < Cout ? col : Cout - 1]);
 #pragma unroll
-        for (int j = 0; j < TJ; ++j) {
-            float bias = 0.f;
-            if (!bwd && a.bias16 != nullptr) bias = half_bits_to_float(a.bias16[cc[j]]);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc_i[j][v] = __builtin_fmaf(a.ep_scale, lora[j][v], acc_i[j][v] + bias);
+            for (int v = 0; v < 16; ++v) acc_i[j][v] += bias;
         }
     }
     uint16_t *patch = reinterpret_cast<uint16_t *>(smem) + slot * (32 * PATCH_ROW);
@@ -389,12 +377,13 @@ __global__ __launch_bounds__(big::THREADS, 2) void gemm_big_kernel(GemmDev d, Bi
         for (int j = 0; j < TJ; ++j)
             f.bf[j] = *reinterpret_cast<const bf16x8 *>(smem + (offW0 ^ (ks << 5)) + wbuf * W_BYTES + j * 32 * ROW_BYTES);
     };
-    auto mfma_frags = [&](const Frags &f) {
+    auto mfma_frags = [&](const Frags &f, auto extension) {
+        constexpr bool EXT = decltype(extension)::value;      // bfloat16 operands in either convention
 #pragma unroll
         for (int i = 0; i < TI; ++i)
 #pragma unroll
             for (int j = 0; j < TJ; ++j)
-                if (F16) {
+                if (F16 && !EXT) {
                     half16x8 x, y;
                     __builtin_memcpy(&x, &f.af[i], sizeof x);
                     __builtin_memcpy(&y, &f.bf[j], sizeof y);
@@ -437,7 +426,7 @@ __global__ __launch_bounds__(big::THREADS, 2) void gemm_big_kernel(GemmDev d, Bi
                     for (int ks = 0; ks < RT / 16; ++ks) {
                         if (ks % G::A_EVERY == 0) issue_a_part(ta, a_fill, ks / G::A_EVERY);
                         if (ks + 1 < RT / 16) load_frags(f[(ks + 1) & 1], oa, u, ks + 1);
-                        mfma_frags(f[ks & 1]);
+                        mfma_frags(f[ks & 1], std::false_type());
                         store_w(u ^ 1, wst[u ^ 1], ks);
                         __builtin_amdgcn_sched_barrier(0);
                     }
@@ -457,8 +446,8 @@ __global__ __launch_bounds__(big::THREADS, 2) void gemm_big_kernel(GemmDev d, Bi
 
     // ---- tail: ragged last main tile and the adapter extension, one at a time, through
     // registers into buffer 0 (predicated; a handful of tiles at most) ---------------
-    for (int t = takes_tail ? n_full : n_tiles; t < n_tiles; ++t) {
-        const bool ext = t >= n_main;
+    auto tail_tile = [&](int t, auto extension) {
+        constexpr bool ext = decltype(extension)::value;
         const int r0 = ext ? (t - n_main) * RT : t * RT;
         const int ld = ext ? a.RE : C;
         const uint16_t *abase = (ext ? a.act_ext + (size_t)m0 * ld : act_rowblock) + r0;
@@ -473,7 +462,7 @@ __global__ __launch_bounds__(big::THREADS, 2) void gemm_big_kernel(GemmDev d, Bi
             if (r0 + ch * 8 < ld) v = load_at<uint4>(abase, (uint32_t)(((size_t)(m - m0) * ld + ch * 8) * 2));
             *reinterpret_cast<uint4 *>(As + tile_off(row, ch)) = v;
         }
-        if (ext) {
+        if constexpr (ext) {
 #pragma unroll
             for (int i = 0; i < W_CH; ++i) {
                 const int idx = i * THREADS + tid;
@@ -527,9 +516,14 @@ __global__ __launch_bounds__(big::THREADS, 2) void gemm_big_kernel(GemmDev d, Bi
         for (int ks = 0; ks < ksteps; ++ks) {
             Frags f;
             load_frags(f, offA0, 0, ks);
-            mfma_frags(f);
+            mfma_frags(f, extension);
         }
         __syncthreads();
+    };
+    // (one loop after the other: a choice between the two kinds of tile inside one spills registers)
+    if (takes_tail) {
+        if (n_main > n_full) tail_tile(n_full, std::false_type());
+        for (int t = n_main; t < n_tiles; ++t) tail_tile(t, std::true_type());
     }
 
     if (item.slice >= 0) {
@@ -613,12 +607,8 @@ static hipError_t launch_big_mt(const GemmArgs &a, BigPlan plan, hipStream_t str
     launch_kernel(name, kern, blocks, big::THREADS, lds_bytes, stream, d, plan);
     hipError_t err = hipGetLastError();
     if (err != hipSuccess || plan.split <= 1) return err;
-    // one wave's patch, and (F16, at the offset the epilogue expects) its 32 rows of P
-    constexpr size_t FIXUP_LDS = F16 ? 40960 + 32 * 64 * 4 : 32 * big::PATCH_ROW * 2;
+    constexpr size_t FIXUP_LDS = 32 * big::PATCH_ROW * 2;      // one wave's patch
     auto fix = gemm_big_fixup_kernel<F16, MT>;
-    static bool fix_configured[64] = {};
-    const hipError_t e2 = ensure_lds_limit(reinterpret_cast<const void *>(fix), FIXUP_LDS, fix_configured);
-    if (e2 != hipSuccess) return e2;
     const char *fix_name = F16 ? (BWD ? "f16_gemm_bwd_fixup" : "f16_gemm_fwd_fixup")
                                : MT == 256 ? (BWD ? "gemm_bwd_256x256_fixup" : "gemm_fwd_256x256_fixup")
                                            : (BWD ? "gemm_bwd_128x256_fixup" : "gemm_fwd_128x256_fixup");

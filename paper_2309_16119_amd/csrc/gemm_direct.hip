@@ -634,7 +634,7 @@ bool direct_wins(int K, int N, int M, int r, bool backward, bool f16) {
     const int C = backward ? N : K, Cout = backward ? K : N;
     double us;
     const DirectPlan p = direct_plan(M, C, Cout, backward, &us);
-    double tiles = gemm_tile_us(M, C, Cout) + (r > 0 ? 9.0 : 0.0);
+    double tiles = gemm_tile_us(M, C, Cout, false) + (r > 0 ? 9.0 : 0.0);
     const long rounds = ((long)p.tiles_m * p.tiles_c * p.split + 255) / 256;
     double margin = rounds == 1 ? 1.1 : (M <= 128 ? 1.2 : 1.3);
     if (rounds >= 3 && M > 256 && us > 110.0 && big_plan(M, C, Cout).mt == 256) margin = 1.5;

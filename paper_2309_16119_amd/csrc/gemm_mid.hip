@@ -4,7 +4,8 @@
 // re-materialized from the packed codes, plus the adapter term of eq. (3) as an extended
 // contraction).  A second instantiation (F16) serves the layer in the paper's own storage
 // convention: binary16 activations and outputs, What = binary16(fma(q, scale, z)) with a binary16
-// zero point that is added, f16 MFMAs, and the adapter term and the bias added in the epilogue.
+// zero point that is added, f16 MFMAs (bfloat16 ones for the extension), and the bias added in the
+// epilogue.
 //
 // With one small tile per CU every 128-deep step holds only 16 MFMAs per SIMD, and in a
 // kernel where every wave fetches, dequantizes, stores, synchronizes and multiplies in
@@ -426,12 +427,13 @@ __global__ __launch_bounds__(mid::THREADS, 3) void gemm_mid_kernel(GemmDev d) {
         for (int j = 0; j < TJ; ++j)
             f.bf[j] = *reinterpret_cast<const bf16x8 *>(smem + wbuf * W_BYTES + (offW0 ^ (sidx << 5)) + j * 32 * ROW_BYTES);
     };
-    auto mfma_frags = [&](const Frags &f) {
+    auto mfma_frags = [&](const Frags &f, auto extension) {
+        constexpr bool EXT = decltype(extension)::value;      // bfloat16 operands in either convention
 #pragma unroll
         for (int i = 0; i < TI; ++i)
 #pragma unroll
             for (int j = 0; j < TJ; ++j)
-                if (F16) {
+                if (F16 && !EXT) {
                     half16x8 x, y;
                     __builtin_memcpy(&x, &f.af[i], sizeof x);
                     __builtin_memcpy(&y, &f.bf[j], sizeof y);
@@ -452,7 +454,7 @@ __global__ __launch_bounds__(mid::THREADS, 3) void gemm_mid_kernel(GemmDev d) {
 #pragma unroll
                     for (int sidx = 0; sidx < KS; ++sidx) load_frags(f[sidx], a_cur, u, sidx);
 #pragma unroll
-                    for (int sidx = 0; sidx < KS; ++sidx) mfma_frags(f[sidx]);
+                    for (int sidx = 0; sidx < KS; ++sidx) mfma_frags(f[sidx], std::false_type());
                     __syncthreads();
                     a_cur = a_cur == 3 * A_BYTES ? 0 : a_cur + A_BYTES;
                 }
@@ -460,7 +462,7 @@ __global__ __launch_bounds__(mid::THREADS, 3) void gemm_mid_kernel(GemmDev d) {
         }
         __syncthreads();
     }
-    for (int t = n_full; t < n_tiles; ++t) {
+    auto tail_tile = [&](int t, auto extension) {
         bool ext;
         int r0, ksteps;
         tail_geometry(t, ext, r0, ksteps);
@@ -471,11 +473,14 @@ __global__ __launch_bounds__(mid::THREADS, 3) void gemm_mid_kernel(GemmDev d) {
             if (KS * kg + sidx < ksteps) {
                 Frags f;
                 load_frags(f, 0, 0, sidx);
-                mfma_frags(f);
+                mfma_frags(f, extension);
             }
         }
         __syncthreads();
-    }
+    };
+    // (one loop after the other: a choice between the two kinds of MFMA inside one spills registers)
+    for (int t = n_full; t < n_main; ++t) tail_tile(t, std::false_type());
+    for (int t = n_main; t < n_tiles; ++t) tail_tile(t, std::true_type());
 
     // ---- the two halves of the contraction meet in LDS: of its 64 rows a consumer keeps block kg
     // (32 rows) and hands the other block to its partner
@@ -505,25 +510,15 @@ __global__ __launch_bounds__(mid::THREADS, 3) void gemm_mid_kernel(GemmDev d) {
     }
     __syncthreads();
 
-    // ---- F16: the adapter term s P F and the bias join here, before the one rounding
-    // (Figure 1 / eq. (3); the bias belongs to the frozen layer and enters the forward pass only) ----
-    if (F16) {
-        const int r = a.ep_r;
-        float *Ps = reinterpret_cast<float *>(smem + 32768) + wave * (32 * 64);   // this wave's 32 rows of P, [jj][32 rows]
-        int cc[TJ];
-        float lora[TJ][16];
+    // ---- F16: the bias joins here, before the one rounding (Figure 1 / eq. (3); it belongs to the
+    // frozen layer and enters the forward pass only) ----
+    if (F16 && !BWD && a.bias16 != nullptr) {
 #pragma unroll
         for (int j = 0; j < TJ; ++j) {
             const int col = c0 + j * 32 + (lane & 31);
-            cc[j] = col < Cout ? col : Cout - 1;
-        }
-        adapter_term_32rows<TJ>(a.ep_P, a.ep_F, r, N, BWD, m0 + wm * 64 + kg * 32, a.M, cc, Ps, lane, lora);
+            const float bias = half_bits_to_float(a.bias16[col < Cout ? col : Cout - 1]);
 #pragma unroll
-        for (int j = 0; j < TJ; ++j) {
-            float bias = 0.f;
-            if (!BWD && a.bias16 != nullptr) bias = half_bits_to_float(a.bias16[cc[j]]);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) fin[j][v] = __builtin_fmaf(a.ep_scale, lora[j][v], fin[j][v] + bias);
+            for (int v = 0; v < 16; ++v) fin[j][v] += bias;
         }
     }
 

@@ -660,7 +660,8 @@ static TilePick forced_pick() {
 // (BigPlan); that round then costs 1/split of a round plus the traffic of the partial
 // tiles (written once, read once) and one more launch.
 // (any token count: a 32-row tile kernel for M <= 32 measured 1.2 us per step, more than any of these)
-static TilePick cheapest_pick(int M, int C, int Cout, double *us) {
+// `tuned_only`: of the 256 x 256 and the 128 x 64 kernel, the two that exist for binary16.
+static TilePick cheapest_pick(int M, int C, int Cout, bool tuned_only, double *us) {
     struct Variant { TilePick pick; int mt, ct, occ; double t1, t2; };
     const Variant vs[5] = {{PICK_MID, 256, 128, 2, 1.46, 1.95},
                            {PICK_M128, 128, 128, 2, 0.97, 1.40},
@@ -673,6 +674,7 @@ static TilePick cheapest_pick(int M, int C, int Cout, double *us) {
     if (bp.split > 1) best += (bp.mt == 128 ? 12.0 : 9.0) + (double)bp.partial_bytes() / 4.0e6;
     TilePick pick = PICK_BIG;
     for (const Variant &v : vs) {
+        if (tuned_only && v.pick != PICK_T128S) continue;
         const long tiles = (long)((M + v.mt - 1) / v.mt) * ((Cout + v.ct - 1) / v.ct);
         const double cost = steps * (tiles <= 256 ? v.t1 : (double)((tiles + 256 * v.occ - 1) / (256 * v.occ)) * v.t2);
         if (cost < best) { best = cost; pick = v.pick; }
@@ -680,17 +682,17 @@ static TilePick cheapest_pick(int M, int C, int Cout, double *us) {
     if (us) *us = best;
     return pick;
 }
-double gemm_tile_us(int M, int C, int Cout) {
+double gemm_tile_us(int M, int C, int Cout, bool f16) {
     if (forced_pick() != PICK_AUTO) return 0.0;      // a forced tile kernel is always the cheapest way
     double us;
-    cheapest_pick(M, C, Cout, &us);
+    cheapest_pick(M, C, Cout, f16, &us);
     return us;
 }
 
 template <int BITS, bool BWD>
 static hipError_t launch_bits_dir(const GemmArgs &a, hipStream_t stream) {
     TilePick pick = forced_pick();
-    if (pick == PICK_AUTO) pick = cheapest_pick(a.M, BWD ? a.w.N : a.w.K, BWD ? a.w.K : a.w.N, nullptr);
+    if (pick == PICK_AUTO) pick = cheapest_pick(a.M, BWD ? a.w.N : a.w.K, BWD ? a.w.K : a.w.N, false, nullptr);
     switch (pick) {
         case PICK_MID:
             return launch_variant<BITS, BWD, 256, 256, 128, 128, 64, 2, 0>(
@@ -709,6 +711,11 @@ static hipError_t launch_bits_dir(const GemmArgs &a, hipStream_t stream) {
         default:
             return launch_gemm_big(a, stream);
     }
+}
+
+hipError_t launch_gemm_f16(const GemmArgs &a, hipStream_t stream) {
+    const int C = a.backward ? a.w.N : a.w.K, Cout = a.backward ? a.w.K : a.w.N;
+    return cheapest_pick(a.M, C, Cout, true, nullptr) == PICK_T128S ? launch_gemm_mid_f16(a, stream) : launch_gemm_big_f16(a, stream);
 }
 
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t stream) {

@@ -16,9 +16,11 @@ struct LayerView {
 };
 
 // Length of the extended contraction that carries the rank-r adapter through the
-// MFMA pipeline: three bfloat16 segments of r (hi*hi, hi*lo, lo*hi), padded to
-// the MFMA K-step of 16.
-inline int lora_ext_len(int r) { return r > 0 ? ((3 * r + 15) / 16) * 16 : 0; }
+// MFMA pipeline: bfloat16 segments of r, padded to the MFMA K-step of 16.  Three
+// (hi*hi, hi*lo, lo*hi: 2^-16 relative) where the output is bfloat16; six of a
+// three-way split (what is dropped is below 2^-23) where it is binary16.
+inline int lora_ext_segments(bool f16) { return f16 ? 6 : 3; }
+inline int lora_ext_len(int r, bool f16 = false) { return r > 0 ? ((lora_ext_segments(f16) * r + 15) / 16) * 16 : 0; }
 
 // ---- kernel launches and the profiling hook (api.hip owns the state) ---------------
 // While modulora_profile_begin() is active, prof_events() hands out a fresh pair of events
@@ -56,18 +58,14 @@ struct GemmArgs {
     int RE;                   // multiple of 16
     float *partials;          // scratch for the partial tiles of a split contraction, or NULL
     size_t partials_bytes;    // its size: a plan that needs more runs whole tiles only
-    // The layer in the paper's own storage convention (launch_gemm_mid_f16 only): binary16
-    // activations and outputs, binary16 zero points that are added (w.zeros unused), an optional
-    // binary16 bias (forward), and the adapter term s P F in the epilogue instead of the extended
-    // contraction (act_ext, w_ext, RE unused).
+    // The layer in the paper's own storage convention (the _f16 launches only): binary16
+    // activations and outputs, binary16 zero points that are added (w.zeros unused) and an optional
+    // binary16 bias (forward).  The extended operands are bfloat16 all the same.
     const uint16_t *zeros16;  // binary16 [K/group][N]
     const uint16_t *bias16;   // binary16 [N] or NULL
-    const float *ep_P;        // fp32 [M][ep_r] or NULL
-    const float *ep_F;        // forward B [r][N], backward A [K][r]
-    int ep_r;
-    float ep_scale;
 };
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t stream);
+hipError_t launch_gemm_f16(const GemmArgs &a, hipStream_t stream);      // the paper's own storage convention
 // gemm_mid.hip, binary16 instantiation: the 128 x 64 producer / consumer kernel for the layer in
 // the paper's own storage convention (GemmArgs::zeros16, bias16, ep_*).
 hipError_t launch_gemm_mid_f16(const GemmArgs &a, hipStream_t stream);
@@ -130,7 +128,7 @@ struct DownArgs {
     float *P;             // fp32 [M][r]
     float lora_scale;
     uint16_t *act_ext;    // may be NULL
-    int RE;
+    int RE, segments;     // lora_ext_len(), lora_ext_segments()
     uint16_t *w_ext;      // may be NULL
     const float *Wsrc;
     bool w_from_A;
@@ -229,9 +227,18 @@ struct F16Layer {
 hipError_t launch_f16_dequant(const F16Layer &w, uint16_t *What, hipStream_t stream);
 // P[M][r] = act[M][C] F, F = A [C][r] (f_is_A) or B^T with B [r][C]
 // forward: out[M][N] = act What^T + bias + s P B; backward: out[M][K] = act What + s P A^T
+// P and Fm are what the plain kernel adds the adapter term from, the extended operands what the tuned ones do.
 // partials: scratch of gemm_partial_bytes(M, K, N) bytes for the 256 x 256 kernel's split contraction, or NULL
-hipError_t launch_f16_gemm(const F16Layer &w, bool backward, const uint16_t *act, int M, uint16_t *out, const float *P,
-                           const float *Fm, int r, float lora_scale, float *partials, hipStream_t stream);
+struct F16Adapter {
+    const float *P, *Fm;          // NULL without an adapter
+    int r;
+    float lora_scale;
+    const uint16_t *act_ext, *w_ext;
+    int RE;
+};
+bool f16_plain_forced();          // MODULORA_F16_PLAIN: every shape on the plain kernel, for comparisons
+hipError_t launch_f16_gemm(const F16Layer &w, bool backward, const uint16_t *act, int M, uint16_t *out,
+                           const F16Adapter &ad, float *partials, hipStream_t stream);
 
 // ---- quantize.hip: round-to-nearest group quantizer + packer -------------------------
 struct QuantArgs {
@@ -345,7 +352,7 @@ inline DirectPlan direct_plan(int M, int C, int Cout, bool backward, double *us 
 // call with tiles / direct, forward): 2048 x 2048, 64 tokens 24.4 / 15.2, binary16 42.2 / 15.9; 1024 x 1024, 64 tokens 17.3 / 15.0,
 // 512 tokens 17.2 / 17.1.  Over 2^32 weights the kernel's 32-bit offsets would overflow.
 bool direct_wins(int K, int N, int M, int r, bool backward, bool f16);
-double gemm_tile_us(int M, int C, int Cout);      // gemm_tile.hip: estimated time of the cheapest tile kernel
+double gemm_tile_us(int M, int C, int Cout, bool f16);      // gemm_tile.hip: estimated time of the cheapest tile kernel
 hipError_t launch_direct(const SmallArgs &a, bool backward, hipStream_t stream);
 
 }  // namespace mlr

@@ -11,14 +11,26 @@
 
 namespace mlr {
 
-// value of extended-operand element e (0 <= e < RE) given the fp32 source values:
-// segments [0,r) [r,2r) [2r,3r) hold (hi,hi,lo) for the activation side and
-// (hi,lo,hi) for the weight side, so that the dot product over the three segments
-// is  hi*hi + hi*lo + lo*hi  ~=  (hi+lo)*(hi+lo)  to about 2^-16 relative.
-__device__ __forceinline__ uint16_t split_part(float v, bool want_lo) {
-    const uint16_t hi = float_to_bf16_bits(v);
-    if (!want_lo) return hi;
-    return float_to_bf16_bits(v - bf16_bits_to_float(hi));
+// Extended operands, segments of r elements.  Three segments (bfloat16 outputs): (hi,hi,lo) on the
+// activation side and (hi,lo,hi) on the weight side of a two-way split, so that the dot product is
+// hi*hi + hi*lo + lo*hi ~= (hi+lo)*(hi+lo) to about 2^-16 relative.  Six segments (binary16 outputs):
+// the products of a three-way split down to 2^-16 of the first, (0,0,1,1,0,2) against (0,1,0,1,2,0); the
+// three parts carry all 24 bits and what is left out is below 2^-23.  There the parts are truncations
+// and an infinity or NaN stands in the first segment only: an infinite factor or projection then gives
+// the infinity that the definition gives, not the NaN of inf - inf or inf * 0.
+__device__ __forceinline__ uint16_t ext_part(float v, int segment, int segments, bool weight_side) {
+    if (segments == 3) {
+        const uint16_t hi = float_to_bf16_bits(v);
+        if (segment != (weight_side ? 1 : 2)) return hi;
+        return float_to_bf16_bits(v - bf16_bits_to_float(hi));
+    }
+    const int part = ((weight_side ? 0x021010 : 0x201100) >> (4 * segment)) & 15;
+    const uint32_t b0 = __float_as_uint(v) & 0xFFFF0000u;
+    if ((b0 & 0x7F800000u) == 0x7F800000u) return segment ? (uint16_t)0 : (uint16_t)((b0 >> 16) | ((__float_as_uint(v) & 0xFFFFu) ? 1u : 0u));
+    const float r1 = v - __uint_as_float(b0);
+    const uint32_t b1 = __float_as_uint(r1) & 0xFFFF0000u;
+    const float r2 = r1 - __uint_as_float(b1);
+    return (uint16_t)((part == 0 ? b0 : part == 1 ? b1 : __float_as_uint(r2)) >> 16);
 }
 
 // ---------------------------------------------------------------------------
@@ -36,7 +48,7 @@ __device__ __forceinline__ bf16x8 regs_to_bf16x8(const uint32_t r[4]) {
 }
 
 // Eight consecutive elements (one 16-byte store) of the weight-side extension w_ext [Cw][RE]:
-// row c holds the segments (hi, lo, hi) of the r factor values of that row and zero padding.
+// row c holds the segments of the r factor values of that row (ext_part()) and zero padding.
 // Unit u = c * (RE / 8) + chunk, consecutive threads take consecutive units: the stores are
 // contiguous, and the loads of a wave touch a few dozen adjacent rows c (from B [r][Cw]: runs of
 // adjacent floats in up to eight rows j; from A [Cw][r]: adjacent floats of a row).
@@ -50,13 +62,13 @@ __device__ __forceinline__ void write_w_ext_unit(const DownArgs &a, size_t u) {
         const int e = e0 + q;
         seg[q] = e / r;
         const int j = e - seg[q] * r;
-        src[q] = seg[q] < 3 ? (a.w_from_A ? a.Wsrc[(size_t)c * r + j] : a.Wsrc[(size_t)j * a.Cw + c]) : 0.f;
+        src[q] = seg[q] < a.segments ? (a.w_from_A ? a.Wsrc[(size_t)c * r + j] : a.Wsrc[(size_t)j * a.Cw + c]) : 0.f;
     }
     uint32_t o[4];
 #pragma unroll
     for (int q = 0; q < 8; q += 2) {
-        const uint32_t lo16 = seg[q] < 3 ? split_part(src[q], seg[q] == 1) : 0u;
-        const uint32_t hi16 = seg[q + 1] < 3 ? split_part(src[q + 1], seg[q + 1] == 1) : 0u;
+        const uint32_t lo16 = seg[q] < a.segments ? ext_part(src[q], seg[q], a.segments, true) : 0u;
+        const uint32_t hi16 = seg[q + 1] < a.segments ? ext_part(src[q + 1], seg[q + 1], a.segments, true) : 0u;
         o[q >> 1] = lo16 | (hi16 << 16);
     }
     *reinterpret_cast<uint4 *>(a.w_ext + u * 8) = make_uint4(o[0], o[1], o[2], o[3]);
@@ -190,9 +202,9 @@ __global__ __launch_bounds__(1024) void lora_down_kernel(DownArgs a, int row_blo
         const int pr = x / a.RE, e = x % a.RE;
         if (m0 + pr >= a.M) continue;
         uint16_t v = 0;
-        if (e < 3 * r) {
+        if (e < a.segments * r) {
             const int seg = e / r, j = e % r;
-            v = split_part(a.lora_scale * Ps[pr * (16 * RG) + j], seg == 2);
+            v = ext_part(a.lora_scale * Ps[pr * (16 * RG) + j], seg, a.segments, false);
         }
         a.act_ext[(size_t)(m0 + pr) * a.RE + e] = v;
     }
@@ -228,9 +240,9 @@ __global__ __launch_bounds__(256) void lora_down_finish_kernel(DownArgs a, int r
         const int pr = x / a.RE, e = x % a.RE;
         if (m0 + pr >= a.M) continue;
         uint16_t v = 0;
-        if (e < 3 * r) {
+        if (e < a.segments * r) {
             const int seg = e / r, j = e % r;
-            v = split_part(a.lora_scale * Ps[pr * (16 * RG) + j], seg == 2);
+            v = ext_part(a.lora_scale * Ps[pr * (16 * RG) + j], seg, a.segments, false);
         }
         a.act_ext[(size_t)(m0 + pr) * a.RE + e] = v;
     }

@@ -367,3 +367,35 @@ def test_operands_beyond_four_gib():
     assert_bar("dB", f64(dB), dBr)
     tight("dA", f64(dA), dAr, n_live * N, out_f16=False)
     tight("dB", f64(dB), dBr, n_live * K, out_f16=False)
+
+
+@pytest.mark.parametrize("K,N,M,r,bits", [
+    (544, 264, 17, 3, 3),            # one ragged tile, an extension that ends inside a step
+    (1120, 2056, 130, 64, 4),        # 128 x 64 tiles, three steps of 128 and more for the extension
+    (2816, 2456, 1100, 33, 2),       # 256 x 256 tiles cut into slices, the last of which takes the extension
+    (96, 4104, 2100, 16, 3),         # whole 256 x 256 tiles whose extension is as long as the contraction
+])
+def test_adapter_term_through_the_extended_contraction(K, N, M, r, bits):
+    """An adapter term thirty times the base product, whose six-segment split has to carry what fp32 does:
+    the error against float64 stays within the output's rounding (2^-11) plus that of fp32 sums.  An
+    infinite factor gives the infinities of the definition and NaN nowhere else."""
+    D = layer(bits, K, N, M, r, 32, seed=21)
+    A, B, s = D["A"] * np.float32(30), D["B"] * np.float32(30), D["lora_scale"]
+    Ad, Bd = torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda()
+    rows = np.unique(np.concatenate(([0, M - 1, M // 2], np.random.default_rng(2).integers(0, M, 20))))
+    Y, _ = b.modulora_f16_fwd(D["w"], D["Xd"], Ad, Bd, s)
+    dX, _ = b.modulora_f16_bwd_input(D["w"], D["dYd"], Ad, Bd, s)
+    Yr, _ = pl.fwd(*oargs(D), np.ascontiguousarray(D["X"][rows]), A, B, s, D["bias"])
+    dXr, _ = pl.bwd_input(*oargs(D), np.ascontiguousarray(D["dY"][rows]), A, B, s)
+    for got, ref, n in ((f64(Y)[rows], Yr, K + r), (f64(dX)[rows], dXr, N + r)):
+        assert np.all(np.abs(got - ref) <= 2.0 ** -11 * np.abs(ref) + 6e-8 * np.sqrt(n) * np.abs(ref).max() + 2.0 ** -25)
+    Bi = Bd.clone()
+    Bi[r - 1, 5] = float("inf")
+    Ai = Ad.clone()
+    Ai[7, r - 1] = -float("inf")
+    Y2, _ = b.modulora_f16_fwd(D["w"], D["Xd"], Ad, Bi, s)
+    dX2, _ = b.modulora_f16_bwd_input(D["w"], D["dYd"], Ai, Bd, s)
+    for got, was, col in ((Y2, Y, 5), (dX2, dX, 7)):
+        assert bool(torch.isinf(got[:, col]).all())
+        keep = torch.arange(got.shape[1], device="cuda") != col
+        assert torch.equal(got[:, keep].view(torch.int16), was[:, keep].view(torch.int16))
