@@ -65,6 +65,7 @@ mlr::LayerView view_of(const modulora_qweight *w) {
 struct WsLayout {
     size_t act_ext, w_ext, p0, p1, gpart, gemm_part, dpart, total;
     size_t gemm_part_bytes;      // size of the region at gemm_part
+    size_t dpart_bytes;          // size of the region at dpart
     bool direct_fwd, direct_bwd; // gemm_direct.hip takes this direction unless a streaming kernel does
 };
 
@@ -100,7 +101,8 @@ WsLayout ws_layout(int32_t K, int32_t N, int32_t M, int32_t r) {
     l.p1 = off;      off += align256((size_t)M * r * 4);
     l.gpart = off;   off += align256(mlr::grad_geom(M, K, N, r, false).partial_floats * 4);
     l.gemm_part = off; off += part;
-    l.dpart = off;   off += align256(mlr::lora_down_partial_bytes(M, K, N, r));
+    l.dpart_bytes = align256(mlr::lora_down_partial_bytes(M, K, N, r));
+    l.dpart = off;   off += l.dpart_bytes;
     l.total = off > small ? off : small;
     if (dir > l.total) l.total = dir;
     return l;
@@ -123,14 +125,17 @@ WsLayout ws_layout_fwd(const mlr::LayerView &v, int32_t M, int32_t r, size_t ava
         if (l.direct_fwd) return l;
     }
     size_t off = 0;
+    const size_t part = align256(mlr::big_plan(M, v.K, v.N).partial_bytes());
     if (r > 0) {
         const size_t RE = (size_t)mlr::lora_ext_len(r);
         l.act_ext = off; off += align256((size_t)M * RE * 2);
         l.w_ext = off;   off += align256((size_t)v.N * RE * 2);
         l.p0 = off;      off += align256((size_t)M * r * 4);
-        l.dpart = off;   off += align256(mlr::lora_down_partial_bytes(M, v.K, v.N, r));
+        // (the projection by tiles where its slices fit beside everything else)
+        l.dpart_bytes = align256(mlr::lora_down_partial_bytes(M, v.K, v.N, r));
+        if (off + l.dpart_bytes + part > avail) l.dpart_bytes = align256(mlr::lora_down_row_bytes(M, v.K, v.N, r));
+        l.dpart = off;   off += l.dpart_bytes;
     }
-    const size_t part = align256(mlr::big_plan(M, v.K, v.N).partial_bytes());
     l.gemm_part = off;
     if (off + part <= avail) {
         l.gemm_part_bytes = part;
@@ -190,6 +195,7 @@ int run_fwd(const modulora_qweight *w, const uint16_t *X, int32_t M, const float
         d.w_ext = reinterpret_cast<uint16_t *>(ws + l.w_ext);
         d.Wsrc = B; d.w_from_A = false; d.Cw = w->d_out;
         d.partials = reinterpret_cast<float *>(ws + l.dpart);
+        d.partials_bytes = l.dpart_bytes;
         const int s = hip_status(mlr::launch_lora_down(d, st));
         if (s != MODULORA_OK) return s;
         g.act_ext = d.act_ext;
@@ -357,6 +363,7 @@ int modulora_bwd_input(const modulora_qweight *w, const uint16_t *dY, int32_t M,
         d.w_ext = reinterpret_cast<uint16_t *>(ws + l.w_ext);
         d.Wsrc = A; d.w_from_A = true; d.Cw = w->d_in;
         d.partials = reinterpret_cast<float *>(ws + l.dpart);
+        d.partials_bytes = l.dpart_bytes;
         if ((s = hip_status(mlr::launch_lora_down(d, st))) != MODULORA_OK) return s;
         g.act_ext = d.act_ext;
         g.w_ext = d.w_ext;
@@ -389,6 +396,7 @@ int modulora_bwd_lora(int32_t d_in, int32_t d_out, int32_t M, int32_t r, float l
         d.P = reinterpret_cast<float *>(ws + l.p0);
         d.lora_scale = lora_scale;
         d.partials = reinterpret_cast<float *>(ws + l.dpart);
+        d.partials_bytes = l.dpart_bytes;
         if ((s = hip_status(mlr::launch_lora_down(d, st))) != MODULORA_OK) return s;
         XA = d.P;
     }
@@ -398,6 +406,7 @@ int modulora_bwd_lora(int32_t d_in, int32_t d_out, int32_t M, int32_t r, float l
         d.P = reinterpret_cast<float *>(ws + l.p1);
         d.lora_scale = lora_scale;
         d.partials = reinterpret_cast<float *>(ws + l.dpart);
+        d.partials_bytes = l.dpart_bytes;
         if ((s = hip_status(mlr::launch_lora_down(d, st))) != MODULORA_OK) return s;
         dYBt = d.P;
     }
@@ -425,7 +434,7 @@ mlr::F16Layer view_of(const modulora_qweight_f16 *w) {
     return mlr::F16Layer{w->d_in, w->d_out, w->bits, w->group_size, w->qweight, w->scales, w->zeros, w->bias};
 }
 struct F16Ws {
-    size_t act_ext, w_ext, p0, p1, gpart, dpart, gemm_part, total;
+    size_t act_ext, w_ext, p0, p1, gpart, dpart, dpart_bytes, gemm_part, total;
     bool direct_fwd, direct_bwd;
 };
 F16Ws f16_ws(int32_t K, int32_t N, int32_t M, int32_t r) {
@@ -438,7 +447,8 @@ F16Ws f16_ws(int32_t K, int32_t N, int32_t M, int32_t r) {
         l.p0 = off;    off += align256((size_t)M * r * 4);
         l.p1 = off;    off += align256((size_t)M * r * 4);
         l.gpart = off; off += align256(mlr::grad_geom(M, K, N, r, true).partial_floats * 4);
-        l.dpart = off; off += align256(mlr::lora_down_partial_bytes(M, K, N, r));   // slices of the rank-r projection
+        l.dpart_bytes = align256(mlr::lora_down_partial_bytes(M, K, N, r));
+        l.dpart = off; off += l.dpart_bytes;                                        // slices of the rank-r projection
     }
     l.gemm_part = off; off += align256(mlr::gemm_partial_bytes(M, K, N));   // partial tiles of the 256 x 256 kernel
     l.total = off;
@@ -462,6 +472,7 @@ int f16_project(const uint16_t *act, int32_t M, int32_t C, const float *F, bool 
     d.Fm = F; d.f_is_A = f_is_A;
     d.P = P; d.lora_scale = 1.0f;
     d.partials = reinterpret_cast<float *>(ws + l.dpart);
+    d.partials_bytes = l.dpart_bytes;
     return hip_status(mlr::launch_lora_down(d, st));
 }
 // One direction through the tile kernels: the projection (with the extended operands of the tuned
@@ -476,6 +487,7 @@ int f16_tiles(const modulora_qweight_f16 *w, bool backward, const uint16_t *act,
         d.P = P_out ? P_out : reinterpret_cast<float *>(ws + l.p0);
         d.lora_scale = lora_scale;
         d.partials = reinterpret_cast<float *>(ws + l.dpart);
+        d.partials_bytes = l.dpart_bytes;
         if (!mlr::f16_plain_forced()) {
             d.RE = mlr::lora_ext_len(r, true);
             d.segments = mlr::lora_ext_segments(true);

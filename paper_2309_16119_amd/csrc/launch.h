@@ -133,20 +133,25 @@ struct DownArgs {
     const float *Wsrc;
     bool w_from_A;
     int Cw;
-    float *partials;      // scratch of lora_down_partial_bytes() bytes (split contraction)
+    float *partials;      // scratch for the slices of a split contraction
+    size_t partials_bytes;   // at least down_plan_bytes(lora_down_row_plan(), ...)
 };
-// How launch_lora_down covers act [M][C]: a workgroup of `nwaves` waves owns `rowt` tiles of 16 rows
+// How launch_lora_down covers act [M][C].
+// By rows (lora_down_kernel): a workgroup of `nwaves` waves owns `rowt` tiles of 16 rows
 // (they share every factor operand: the fp32 factor is fetched and split once per workgroup and
 // step, not once per 16 rows) and one of `split` slices of the contraction, which its waves
 // divide again.  With split > 1 the slices leave partial tiles that a second small kernel adds.
 // Many tokens take rowt = 4 and as many slices as give the chip about two workgroups per compute
 // unit; few tokens keep one tile per workgroup and split only a deep contraction.
+// By tiles (lora_down_tile_kernel): see lora_down_plan().
 struct DownPlan {
     int rowt, nwaves, split;
+    bool tiles;
 };
-inline DownPlan lora_down_plan(int M, int C, int r) {
+inline DownPlan lora_down_row_plan(int M, int C, int r) {
     DownPlan p;
     const int rg = (r + 15) / 16;
+    p.tiles = false;
     const int tiles16 = (M + 15) / 16;
     // (a contraction under ~6000 is too short to split further: there one tile per workgroup and no
     // second launch is quicker)
@@ -177,18 +182,45 @@ inline DownPlan lora_down_plan(int M, int C, int r) {
     }
     return p;
 }
+// By tiles where the row kernel's waves, each splitting the factor for itself with one or two steps' loads
+// in flight (registers: 16 columns of rank are 16 floats a step), wait for memory: every rank over 32, from 4 M
+// activations on a rank over 16, and long deep calls of any rank.  Measured, us with the second launch,
+// by rows / by tiles: r = 64: 280 x 2048 14.0 / 12, 1024 x 4096 28 / 13.6, 2048 x 11008 67 / 28 (B^T: 85 / 29),
+// 4096 x 11008 69 / 42; r = 32: 1500 x 4096 15 / 12 (B^T 20 / 12), 4096 x 6656 27 / 21; r = 16: 1024 x 6656
+// 11.2 / 10.5, 3200 x 11008 25 / 21; on the other side r = 64, 2048 x 1152 11 / 13; r = 32, 600 x 2048 9.5 / 9.5,
+// 2048 x 2048 9.7 / 11; r = 16, 2048 x 4096 9.7 / 9.9, 4096 x 4096 11.4 / 13.0.
+// Slices: as many workgroups as fit the chip at once, at most 24 slices (their sums are read back), two chunks
+// of 128 at least, and no more than the longest slice's number of chunks asks for.
+inline DownPlan lora_down_plan(int M, int C, int r) {
+    const int rg = (r + 15) / 16;
+    const long work = (long)M * C;
+    const bool tiles = rg >= 3 ? M >= 256 && C >= 2048 : rg == 2 ? M >= 512 && C >= 4096 && work >= 4000000L : M >= 1024 && C >= 6144;
+    if (!tiles) return lora_down_row_plan(M, C, r);
+    DownPlan p;
+    p.tiles = true;
+    p.rowt = p.nwaves = 4;
+    const int row_blocks = (M + 63) / 64, chunks = (C + 127) / 128;
+    int most = (rg >= 3 ? 512 : 1024) / row_blocks;
+    if (most > 24) most = 24;
+    if (most > chunks / 2) most = chunks / 2;
+    if (most < 1) most = 1;
+    const int longest = (chunks + most - 1) / most;
+    p.split = (chunks + longest - 1) / longest;
+    return p;
+}
+inline size_t down_plan_bytes(const DownPlan &p, int M, int r) {
+    if (r <= 0 || p.split <= 1) return 0;
+    const size_t row_blocks = (size_t)(((M + 15) / 16) + p.rowt - 1) / p.rowt;
+    return (size_t)p.split * row_blocks * (size_t)p.rowt * 256u * (size_t)((r + 15) / 16) * sizeof(float);
+}
 inline size_t lora_down_partial_bytes(int M, int K, int N, int r) {
-    if (r <= 0) return 0;
-    size_t most = 0;
-    for (int C : {K, N}) {
-        const DownPlan p = lora_down_plan(M, C, r);
-        if (p.split <= 1) continue;
-        const size_t rg = (size_t)(r + 15) / 16;
-        const size_t row_blocks = (size_t)(((M + 15) / 16) + p.rowt - 1) / p.rowt;
-        const size_t b = (size_t)p.split * row_blocks * (size_t)p.rowt * 256u * rg * sizeof(float);
-        if (b > most) most = b;
-    }
-    return most;
+    const size_t k = down_plan_bytes(lora_down_plan(M, K, r), M, r), n = down_plan_bytes(lora_down_plan(M, N, r), M, r);
+    return k > n ? k : n;
+}
+// What the row plans alone need: a caller with little scratch keeps to them.
+inline size_t lora_down_row_bytes(int M, int K, int N, int r) {
+    const size_t k = down_plan_bytes(lora_down_row_plan(M, K, r), M, r), n = down_plan_bytes(lora_down_row_plan(M, N, r), M, r);
+    return k > n ? k : n;
 }
 hipError_t launch_lora_down(const DownArgs &a, hipStream_t stream);
 

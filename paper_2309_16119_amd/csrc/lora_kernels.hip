@@ -74,12 +74,27 @@ __device__ __forceinline__ void write_w_ext_unit(const DownArgs &a, size_t u) {
     *reinterpret_cast<uint4 *>(a.w_ext + u * 8) = make_uint4(o[0], o[1], o[2], o[3]);
 }
 
+// One element of a projection (column j, 0 .. 15 at least): P and, where it is asked for, its place in
+// every segment of the activation-side extension; the threads past the rank write the zeros that pad it.
+__device__ __forceinline__ void store_projection(const DownArgs &a, int m, int j, float p) {
+    const int r = a.r;
+    if (j < r) a.P[(size_t)m * r + j] = p;
+    if (a.act_ext == nullptr) return;
+    uint16_t *ext = a.act_ext + (size_t)m * a.RE;
+    if (j < r) {
+        const float v = a.lora_scale * p;
+        for (int seg = 0; seg < a.segments; ++seg) ext[seg * r + j] = ext_part(v, seg, a.segments, false);
+    }
+    // (at most 15 zeros: RE is the segments' length rounded up to 16)
+    if (j < 16 && a.segments * r + j < a.RE) ext[a.segments * r + j] = 0;
+}
+
 // ROWT: 16-row tiles per workgroup (they share every factor operand); UNR: steps whose loads
 // are issued together before any of them is used.
 // ACT_F16: the activations are binary16; each operand is split exactly into two bfloat16 ones.
 template <int RG, int ROWT, bool F_IS_A, bool ACT_F16>
 __global__ __launch_bounds__(1024) void lora_down_kernel(DownArgs a, int row_blocks, int split) {
-    extern __shared__ __attribute__((aligned(16))) float lds_f[];   // [waves][ROWT][RG][256] partial tiles, then Ps
+    extern __shared__ __attribute__((aligned(16))) float lds_f[];   // [waves][ROWT][RG][256] partial tiles
     constexpr int UNR = ROWT > 1 ? 2 : (RG == 1 ? 4 : (RG == 2 ? 2 : 1));
     constexpr int ROWS = 16 * ROWT;
     const int tid = threadIdx.x, nthreads = blockDim.x;
@@ -184,67 +199,175 @@ __global__ __launch_bounds__(1024) void lora_down_kernel(DownArgs a, int row_blo
 #pragma unroll
             for (int v = 0; v < 4; ++v) lds_f[((wave * TILES + t * RG + g) * 4 + v) * 64 + lane] = acc[t][g][v];
     __syncthreads();
-    float *Ps = lds_f + nwaves * TILES * 256;               // [ROWS][16 * RG]
     for (int x = tid; x < TILES * 256; x += nthreads) {
-        const int tile = x >> 8, v = (x >> 6) & 3, l = x & 63;
+        const int tile = x >> 8, prow = 16 * (tile / RG) + ((x >> 4) & 15), j = (tile % RG) * 16 + (x & 15);
+        const int v = (x >> 4) & 3, l = 16 * ((x >> 6) & 3) + (x & 15);      // where the tile's element stands in LDS
         float sum = 0.f;
         for (int w = 0; w < nwaves; ++w) sum += lds_f[((w * TILES + tile) * 4 + v) * 64 + l];
-        const int prow = 16 * (tile / RG) + 4 * (l >> 4) + v, j = (tile % RG) * 16 + (l & 15);
-        Ps[prow * (16 * RG) + j] = sum;
         if (split > 1)   // a slice of the contraction: leave the tile for lora_down_finish_kernel
             a.partials[((size_t)blockIdx.y * row_blocks + blockIdx.x) * (TILES * 256) + prow * (16 * RG) + j] = sum;
-        else if (m0 + prow < a.M && j < r)
-            a.P[(size_t)(m0 + prow) * r + j] = sum;
+        else if (m0 + prow < a.M)
+            store_projection(a, m0 + prow, j, sum);
     }
-    if (a.act_ext == nullptr || split > 1) return;
-    __syncthreads();
-    for (int x = tid; x < ROWS * a.RE; x += nthreads) {
-        const int pr = x / a.RE, e = x % a.RE;
-        if (m0 + pr >= a.M) continue;
-        uint16_t v = 0;
-        if (e < a.segments * r) {
-            const int seg = e / r, j = e % r;
-            v = ext_part(a.lora_scale * Ps[pr * (16 * RG) + j], seg, a.segments, false);
+}
+
+// The same projection for many rows or a large rank (lora_down_plan()): a workgroup owns 64 rows (a tile of
+// 16 per wave) and one of `split` slices of the contraction, which it walks in chunks of 128.  The factor's
+// chunk is split into its three parts once per workgroup, into LDS, and every wave multiplies from there;
+// the activations and factor values of two further chunks are on their way to registers meanwhile.
+// Bound by a chunk's chain of split, barrier, LDS reads and MFMAs -- 1.05 us for a workgroup alone on its compute
+// unit at r <= 16, 1.6 at 32, 2.3 at 64 -- into which the unit's other workgroups fall; workgroups of eight
+// waves were no quicker anywhere.
+constexpr int DOWN_WAVES = 4;
+template <int RG, bool F_IS_A, bool ACT_F16>
+__global__ __launch_bounds__(DOWN_WAVES * 64) void lora_down_tile_kernel(DownArgs a, int row_blocks, int split) {
+    constexpr int NW = DOWN_WAVES;
+    constexpr int KC = 128, ROW = KC * 2 + 16;           // bytes of an LDS row: 16 lanes of a 16-byte read meet 64 banks
+    constexpr int COLS = 16 * RG, PLANE = COLS * ROW;
+    constexpr int UNITS = (COLS * (KC / 8) + NW * 64 - 1) / (NW * 64);   // (column, eight elements) units per thread
+    __shared__ __attribute__((aligned(16))) unsigned char planes[3 * PLANE];
+    const int tid = threadIdx.x, r = a.r, C = a.C;
+    if ((int)blockIdx.x >= row_blocks) {
+        if (blockIdx.y != 0) return;
+        const size_t u = (size_t)(blockIdx.x - row_blocks) * (NW * 64) + tid;
+        if (u < (size_t)a.Cw * (a.RE >> 3)) write_w_ext_unit(a, u);
+        return;
+    }
+    const int lane = tid & 63, wave = uniform(tid >> 6), i = lane & 15, cs = lane >> 4;
+    const int m0 = (blockIdx.x * NW + wave) * 16;
+    const uint16_t *arow = a.act + (size_t)(m0 + i < a.M ? m0 + i : a.M - 1) * C + 8 * cs;
+    const int chunks = (C + KC - 1) / KC;
+    const int ch0 = (int)((long)chunks * blockIdx.y / split), ch1 = (int)((long)chunks * (blockIdx.y + 1) / split);
+
+    struct Chunk {
+        uint4 x[KC / 32];
+        float f[UNITS][8];
+    };
+    // column and octet of a unit: neighbouring lanes read neighbouring floats of the factor
+    auto unit_at = [&](int q, int &j, int &o) {
+        const int u = q * (NW * 64) + tid;
+        j = F_IS_A ? u % COLS : u / (KC / 8);
+        o = F_IS_A ? u / COLS : u % (KC / 8);
+        return COLS * (KC / 8) % (NW * 64) == 0 || u < COLS * (KC / 8);
+    };
+    auto load = [&](Chunk &k, int ch) {
+#pragma unroll
+        for (int s = 0; s < KC / 32; ++s) {
+            const int c = ch * KC + 32 * s;              // C is a multiple of 8: a lane's eight are all in or all out
+            k.x[s] = make_uint4(0, 0, 0, 0);
+            if (c + 8 * cs < C) k.x[s] = *reinterpret_cast<const uint4 *>(arow + c);
         }
-        a.act_ext[(size_t)(m0 + pr) * a.RE + e] = v;
+#pragma unroll
+        for (int q = 0; q < UNITS; ++q) {
+            int j, o;
+            const bool mine = unit_at(q, j, o);
+            const int c = ch * KC + 8 * o;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) k.f[q][e] = 0.f;
+            if (mine && j < r && c < C) {
+                if (F_IS_A) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) k.f[q][e] = a.Fm[(size_t)(c + e) * r + j];
+                } else {
+                    const float4 q0 = *reinterpret_cast<const float4 *>(a.Fm + (size_t)j * C + c);
+                    const float4 q1 = *reinterpret_cast<const float4 *>(a.Fm + (size_t)j * C + c + 4);
+                    k.f[q][0] = q0.x; k.f[q][1] = q0.y; k.f[q][2] = q0.z; k.f[q][3] = q0.w;
+                    k.f[q][4] = q1.x; k.f[q][5] = q1.y; k.f[q][6] = q1.z; k.f[q][7] = q1.w;
+                }
+            }
+        }
+    };
+    f32x4 acc[RG];
+#pragma unroll
+    for (int g = 0; g < RG; ++g) acc[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+    Chunk set[2];                                        // two chunks on their way: a trip to memory is longer than a chunk
+    load(set[0], ch0);
+    load(set[1], ch0 + 1 < ch1 ? ch0 + 1 : ch0);
+    for (int c2 = ch0; c2 < ch1; c2 += 2) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int ch = c2 + h;
+            if (ch >= ch1) break;
+            Chunk &k = set[h];
+            if (ch > ch0) __syncthreads();               // every wave has read the chunk before
+#pragma unroll
+            for (int q = 0; q < UNITS; ++q) {
+                int j, o;
+                if (!unit_at(q, j, o)) continue;
+                uint32_t p[3][4];
+                split3(k.f[q], p[0], p[1], p[2]);
+#pragma unroll
+                for (int t = 0; t < 3; ++t)
+                    *reinterpret_cast<uint4 *>(planes + t * PLANE + j * ROW + o * 16) = make_uint4(p[t][0], p[t][1], p[t][2], p[t][3]);
+            }
+            uint4 x[KC / 32];
+#pragma unroll
+            for (int s = 0; s < KC / 32; ++s) x[s] = k.x[s];
+            if (ch + 2 < ch1) load(k, ch + 2);
+            __syncthreads();
+#pragma unroll
+            for (int s = 0; s < KC / 32; ++s) {
+                const uint32_t ar[4] = {x[s].x, x[s].y, x[s].z, x[s].w};
+                uint32_t ah[4], al[4];
+                if (ACT_F16) split_f16x8(ar, ah, al);
+                const bf16x8 hi = regs_to_bf16x8(ACT_F16 ? ah : ar), lo = regs_to_bf16x8(ACT_F16 ? al : ar);
+#pragma unroll
+                for (int g = 0; g < RG; ++g)
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) {
+                        const bf16x8 b = *reinterpret_cast<const bf16x8 *>(planes + t * PLANE + (16 * g + i) * ROW + s * 64 + cs * 16);
+                        acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi, b, acc[g], 0, 0, 0);
+                        if (ACT_F16) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(lo, b, acc[g], 0, 0, 0);
+                    }
+            }
+        }
     }
+    // D register v of lane (i, cs): row 4 cs + v, column 16 g + i
+    if (split > 1) {
+        float *part = a.partials + (((size_t)blockIdx.y * row_blocks + blockIdx.x) * NW + wave) * (256 * RG);
+#pragma unroll
+        for (int g = 0; g < RG; ++g)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) part[(4 * cs + v) * COLS + 16 * g + i] = acc[g][v];
+        return;
+    }
+#pragma unroll
+    for (int g = 0; g < RG; ++g)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (m0 + 4 * cs + v < a.M) store_projection(a, m0 + 4 * cs + v, 16 * g + i, acc[g][v]);
 }
 
 // Second stage when the contraction was split over workgroups: add the slices' tiles of 16 rows
 // in slice order, write P and the activation-side extension.  One workgroup per 16 rows; the
-// partials of a first-stage workgroup hold its ROWT tiles one after the other.
+// partials of a first-stage workgroup hold its ROWT tiles one after the other.  Bound by its chain of
+// loads: every element of a thread is summed side by side, eight slices at a time.
 template <int RG>
 __global__ __launch_bounds__(256) void lora_down_finish_kernel(DownArgs a, int row_blocks, int split, int rowt) {
-    __shared__ float Ps[16 * 16 * RG];
-    const int tid = threadIdx.x, r = a.r, m0 = blockIdx.x * 16;
+    const int tid = threadIdx.x, m0 = blockIdx.x * 16;
     const int rb = blockIdx.x / rowt, tile = blockIdx.x % rowt;
-    const size_t wg_floats = (size_t)rowt * 256 * RG;
-    for (int x = tid; x < 256 * RG; x += 256) {
-        const float *src = a.partials + (size_t)rb * wg_floats + (size_t)tile * (256 * RG) + x;
-        float sum = 0.f;
-        int y = 0;
-        for (; y + 4 <= split; y += 4) {      // four slices' loads in flight
-            float v[4];
+    const size_t wg_floats = (size_t)rowt * 256 * RG, stride = (size_t)row_blocks * wg_floats;
+    const float *src = a.partials + (size_t)rb * wg_floats + (size_t)tile * (256 * RG) + tid;
+    constexpr int SB = 8;
+    float sum[RG];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = src[(size_t)(y + u) * row_blocks * wg_floats];
-            sum += v[0]; sum += v[1]; sum += v[2]; sum += v[3];
-        }
-        for (; y < split; ++y) sum += src[(size_t)y * row_blocks * wg_floats];
-        Ps[x] = sum;
-        const int prow = x / (16 * RG), j = x % (16 * RG);
-        if (m0 + prow < a.M && j < r) a.P[(size_t)(m0 + prow) * r + j] = sum;
+    for (int q = 0; q < RG; ++q) sum[q] = 0.f;
+    for (int y = 0; y < split; y += SB) {
+        float v[SB][RG];
+#pragma unroll
+        for (int u = 0; u < SB; ++u)
+#pragma unroll
+            for (int q = 0; q < RG; ++q) v[u][q] = y + u < split ? src[(size_t)(y + u) * stride + 256 * q] : 0.f;
+#pragma unroll
+        for (int u = 0; u < SB; ++u)
+#pragma unroll
+            for (int q = 0; q < RG; ++q)
+                if (y + u < split) sum[q] += v[u][q];
     }
-    if (a.act_ext == nullptr) return;
-    __syncthreads();
-    for (int x = tid; x < 16 * a.RE; x += 256) {
-        const int pr = x / a.RE, e = x % a.RE;
-        if (m0 + pr >= a.M) continue;
-        uint16_t v = 0;
-        if (e < a.segments * r) {
-            const int seg = e / r, j = e % r;
-            v = ext_part(a.lora_scale * Ps[pr * (16 * RG) + j], seg, a.segments, false);
-        }
-        a.act_ext[(size_t)(m0 + pr) * a.RE + e] = v;
+#pragma unroll
+    for (int q = 0; q < RG; ++q) {
+        const int x = tid + 256 * q, prow = x / (16 * RG), j = x % (16 * RG);
+        if (m0 + prow < a.M) store_projection(a, m0 + prow, j, sum[q]);
     }
 }
 
@@ -254,7 +377,7 @@ static hipError_t launch_down_rg(const DownArgs &a, const DownPlan &plan, hipStr
     const int row_blocks = (a.M + ROWS - 1) / ROWS;
     const int nwaves = plan.nwaves, nthreads = nwaves * 64, split = plan.split;
     const int w_blocks = a.w_ext ? (int)(((size_t)a.Cw * (a.RE / 8) + nthreads - 1) / nthreads) : 0;
-    const size_t lds = (size_t)(nwaves * RG * ROWT * 256 + ROWS * 16 * RG) * sizeof(float);
+    const size_t lds = (size_t)(nwaves * RG * ROWT * 256) * sizeof(float);
     const dim3 grid(row_blocks + w_blocks, split);
     if (a.act_f16) {
         if (a.f_is_A)
@@ -272,8 +395,36 @@ static hipError_t launch_down_rg(const DownArgs &a, const DownPlan &plan, hipStr
     return hipGetLastError();
 }
 
+template <int RG>
+static hipError_t launch_down_tiles(const DownArgs &a, const DownPlan &plan, hipStream_t stream) {
+    const int row_blocks = (a.M + 16 * DOWN_WAVES - 1) / (16 * DOWN_WAVES), split = plan.split;
+    const int w_blocks = a.w_ext ? (int)(((size_t)a.Cw * (a.RE / 8) + DOWN_WAVES * 64 - 1) / (DOWN_WAVES * 64)) : 0;
+    const dim3 grid(row_blocks + w_blocks, split);
+    if (a.act_f16) {
+        if (a.f_is_A) launch_kernel("lora_down", lora_down_tile_kernel<RG, true, true>, grid, DOWN_WAVES * 64, 0, stream, a, row_blocks, split);
+        else launch_kernel("lora_down", lora_down_tile_kernel<RG, false, true>, grid, DOWN_WAVES * 64, 0, stream, a, row_blocks, split);
+    } else if (a.f_is_A) {
+        launch_kernel("lora_down", lora_down_tile_kernel<RG, true, false>, grid, DOWN_WAVES * 64, 0, stream, a, row_blocks, split);
+    } else {
+        launch_kernel("lora_down", lora_down_tile_kernel<RG, false, false>, grid, DOWN_WAVES * 64, 0, stream, a, row_blocks, split);
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || split <= 1) return e;
+    launch_kernel("lora_down_finish", lora_down_finish_kernel<RG>, (a.M + 15) / 16, 256, 0, stream, a, row_blocks, split, DOWN_WAVES);
+    return hipGetLastError();
+}
+
 hipError_t launch_lora_down(const DownArgs &a, hipStream_t stream) {
-    const DownPlan plan = lora_down_plan(a.M, a.C, a.r);
+    DownPlan plan = lora_down_plan(a.M, a.C, a.r);
+    if (down_plan_bytes(plan, a.M, a.r) > a.partials_bytes) plan = lora_down_row_plan(a.M, a.C, a.r);
+    if (plan.tiles) {
+        switch ((a.r + 15) / 16) {
+            case 1: return launch_down_tiles<1>(a, plan, stream);
+            case 2: return launch_down_tiles<2>(a, plan, stream);
+            case 3: return launch_down_tiles<3>(a, plan, stream);
+            default: return launch_down_tiles<4>(a, plan, stream);
+        }
+    }
     if (plan.rowt == 4) {
         if (a.r <= 16) return launch_down_rg<1, 4>(a, plan, stream);
         return launch_down_rg<2, 4>(a, plan, stream);

@@ -96,3 +96,44 @@ def test_infinities_stay_infinities(K, N, M, r, f16):
             assert torch.equal(g.isnan(), ref.isnan()) and torch.equal(g.isposinf(), ref.isposinf()) and torch.equal(g.isneginf(), ref.isneginf())
             ok = ref.isfinite()
             assert bool(((g - ref).abs()[ok] <= (8 * np.sqrt(M) * 2.0 ** -24 * mag + 1e-30)[ok]).all())
+
+
+@pytest.mark.parametrize("f16", [False, True])
+@pytest.mark.parametrize("M,K,N,r", [
+    (256, 2048, 2056, 33),      # the smallest by tiles; B^T: the last chunk of 128 holds eight elements
+    (321, 2144, 4104, 64),      # a wave with one row, contractions that end inside a chunk
+    (1029, 4128, 6152, 17),     # rank over 16
+    (1025, 6176, 6280, 5),      # a rank that is no multiple of four, one row past the last block
+])
+def test_projections_by_tiles(M, K, N, r, f16):
+    """X A and dY B^T of the forward and backward calls by tiles (rows and ranks past lora_down_plan()'s line),
+    against float64: fp32 products (the split is exact) summed in fp32; and the adapter term that is
+    built from them, through the outputs of a layer whose weight is zero."""
+    gen = torch.Generator(device="cuda").manual_seed(M)
+    dtype = torch.float16 if f16 else torch.bfloat16
+    X = torch.randn((M, K), device="cuda", generator=gen).to(dtype)
+    dY = torch.randn((M, N), device="cuda", generator=gen).to(dtype)
+    A = torch.randn((K, r), device="cuda", generator=gen) * 0.02
+    B = torch.randn((r, N), device="cuda", generator=gen) * 0.02
+    words = torch.zeros((K * 3 // 32, N), dtype=torch.int32, device="cuda")
+    scales = torch.ones((K // 32, N), dtype=torch.float16, device="cuda")
+    if f16:
+        w = b.QWeightF16(words, scales, torch.zeros_like(scales), None, K, N, 3, 32)
+        fwd, bwd, rounding = b.modulora_f16_fwd, b.modulora_f16_bwd_input, 2.0 ** -11
+    else:
+        w = b.QWeight(words, scales, torch.zeros((K // 32, N), dtype=torch.uint8, device="cuda"), K, N, 3, 32)
+        fwd, bwd, rounding = b.modulora_fwd, b.modulora_bwd_input, 2.0 ** -8
+    Y, XA = fwd(w, X, A, B, 2.0)
+    dX, T = bwd(w, dY, A, B, 2.0)
+    P, Q = X.double() @ A.double(), dY.double() @ B.double().t()
+    # 32 units of 2^-24 of the sum of absolute products: fp32 sums of up to 64 steps per slice, then the slices
+    errs = []
+    for got, ref, act, F in ((XA, P, X, A), (T, Q, dY, B.t())):
+        bound = (act.double().abs() @ F.double().abs()) * 2.0 ** -24 * 32 + 2.0 ** -20 * ref.abs()
+        assert bool(((got.double() - ref).abs() <= bound).all()), float((got.double() - ref).abs().max())
+        errs.append(bound)
+    # the projection's error times the other factor, the split of the extended contraction, one rounding
+    for got, proj, err, F in ((Y, P, errs[0], B.double()), (dX, Q, errs[1], A.double().t())):
+        ref = 2.0 * proj @ F
+        bound = rounding * ref.abs() + 2.0 * (err + (2.0 ** -20 if f16 else 2.0 ** -15) * proj.abs()) @ F.abs() + 2.0 ** -25
+        assert bool(((got.double() - ref).abs() <= bound).all()), float((got.double() - ref).abs().max())
