@@ -54,18 +54,14 @@ struct DirectDev {
     LayerView w;
     const uint16_t *act;          // [M][C]
     const uint16_t *zeros16;      // F16: binary16 zero points
-    const uint16_t *bias16;       // F16 forward: bias or NULL
     int M, C, Cout;
     int tiles_m, tiles_c, split, nch;
     float *part;                  // [split][M][Cout]
     int proj_parts;               // workgroups that share one row tile's projection over one slice
-    float *ppart;                 // [split * proj_parts][M][r]
+    float *ppart;                 // [split * proj_parts], part_stride apart: [M][r]
+    int part_stride;
     const float *Fp;              // projection factor: forward A [C][r], backward B [r][C]
-    const float *Fo;              // output factor: forward B [r][Cout], backward A [Cout][r]
     int r;
-    float lora_scale;
-    uint16_t *out;                // [M][Cout]
-    float *P_out;                 // [M][r] or NULL
     // group of a 32-code block: (blk + plus) * magic / 2^32 (blk and the blocks per group < 2^15), with
     // (0, 2^32 / d + 1) for d blocks per group and (1, 2^32 - 1) for d = 1
     uint32_t group_plus, group_magic;
@@ -352,7 +348,7 @@ __global__ __launch_bounds__(direct::THREADS, 2) void gemm_direct_kernel(DirectD
             if (row0 >= M) continue;
             const int ks = ch0 * CHUNK + 32 * (steps * x / d.proj_parts);
             const int ke = x + 1 == d.proj_parts ? k1 : ch0 * CHUNK + 32 * (steps * (x + 1) / d.proj_parts);
-            direct_project<!BWD, F16>(d, row0, ks, ke, d.ppart + (size_t)(slice * d.proj_parts + x) * M * d.r,
+            direct_project<!BWD, F16>(d, row0, ks, ke, d.ppart + (size_t)(slice * d.proj_parts + x) * d.part_stride,
                                       reinterpret_cast<float *>(smem + SLOTS * SLOT));
         }
     }
@@ -506,89 +502,6 @@ __global__ __launch_bounds__(direct::THREADS, 2) void gemm_direct_kernel(DirectD
     }
 }
 
-// Sum of the slices' partial results and of the projection's, the adapter term, the bias, one rounding.
-// A workgroup finishes 32 rows x 64 columns; a thread eight adjacent columns of one row.
-template <bool BWD, bool F16>
-__global__ __launch_bounds__(256) void gemm_direct_finish_kernel(DirectDev d) {
-    extern __shared__ __attribute__((aligned(16))) float fin_lds[];
-    const int tid = threadIdx.x, r = d.r, M = d.M, Cout = d.Cout;
-    float *Ps = fin_lds, *Fs = fin_lds + 32 * r;            // [32][r], [r][64]
-    const int m0 = blockIdx.y * 32, c0 = blockIdx.x * 64;
-    const int m = m0 + (tid >> 3), cl = (tid & 7) * 8, col = c0 + cl;
-    const bool mine = m < M && col < Cout;                  // Cout is a multiple of 8
-    const float *src = d.part + (mine ? (size_t)m * Cout + col : (size_t)0);
-    const size_t stride = (size_t)M * Cout;
-    constexpr int SB = 4;
-    float4 v0[SB], v1[SB];
-    auto load_slices = [&](int q0) {
-#pragma unroll
-        for (int u = 0; u < SB; ++u)
-            if (q0 + u < d.split) {
-                v0[u] = *reinterpret_cast<const float4 *>(src + (size_t)(q0 + u) * stride);
-                v1[u] = *reinterpret_cast<const float4 *>(src + (size_t)(q0 + u) * stride + 4);
-            }
-    };
-    float y[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    auto add_slices = [&](int q0) {
-#pragma unroll
-        for (int u = 0; u < SB; ++u)
-            if (q0 + u < d.split) {
-                y[0] += v0[u].x; y[1] += v0[u].y; y[2] += v0[u].z; y[3] += v0[u].w;
-                y[4] += v1[u].x; y[5] += v1[u].y; y[6] += v1[u].z; y[7] += v1[u].w;
-            }
-    };
-    load_slices(0);
-    if (r > 0) {
-        const int rows = M - m0 < 32 ? M - m0 : 32;
-        for (int x = tid; x < rows * r; x += 256) {
-            const float *p = d.ppart + (size_t)m0 * r + x;
-            float sum = 0.f;
-#pragma unroll 8
-            for (int s = 0; s < d.split * d.proj_parts; ++s) sum += p[(size_t)s * M * r];
-            Ps[x] = sum;
-            if (blockIdx.x == 0 && d.P_out != nullptr) d.P_out[(size_t)m0 * r + x] = sum;
-        }
-        const int cols = Cout - c0 < 64 ? Cout - c0 : 64;
-        if (!BWD) {
-            for (int x = tid; x < r * 64; x += 256) {
-                const int c = x & 63, j = x >> 6;
-                if (c < cols) Fs[x] = d.Fo[(size_t)j * Cout + c0 + c];
-            }
-        } else {
-            for (int x = tid; x < cols * r; x += 256) {
-                const int c = x / r, j = x - c * r;
-                Fs[j * 64 + c] = d.Fo[(size_t)c0 * r + x];
-            }
-        }
-        __syncthreads();
-    }
-    add_slices(0);
-    for (int q0 = SB; q0 < d.split; q0 += SB) { load_slices(q0); add_slices(q0); }
-    if (!mine) return;
-    float l[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int j = 0; j < r; ++j) {
-        const float p = Ps[(tid >> 3) * r + j];
-        const float4 f0 = *reinterpret_cast<const float4 *>(Fs + j * 64 + cl), f1 = *reinterpret_cast<const float4 *>(Fs + j * 64 + cl + 4);
-        l[0] = __builtin_fmaf(p, f0.x, l[0]); l[1] = __builtin_fmaf(p, f0.y, l[1]);
-        l[2] = __builtin_fmaf(p, f0.z, l[2]); l[3] = __builtin_fmaf(p, f0.w, l[3]);
-        l[4] = __builtin_fmaf(p, f1.x, l[4]); l[5] = __builtin_fmaf(p, f1.y, l[5]);
-        l[6] = __builtin_fmaf(p, f1.z, l[6]); l[7] = __builtin_fmaf(p, f1.w, l[7]);
-    }
-    if (F16 && !BWD && d.bias16 != nullptr) {               // the frozen layer's bias: forward only
-        const uint4 bw = *reinterpret_cast<const uint4 *>(d.bias16 + col);
-        const uint32_t w4[4] = {bw.x, bw.y, bw.z, bw.w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            y[2 * q] += half_bits_to_float((uint16_t)(w4[q] & 0xFFFFu));
-            y[2 * q + 1] += half_bits_to_float((uint16_t)(w4[q] >> 16));
-        }
-    }
-#pragma unroll
-    for (int c = 0; c < 8; ++c) y[c] = __builtin_fmaf(d.lora_scale, l[c], y[c]);
-    const uint4 o = make_uint4(pack_pair<F16>(y[0], y[1]), pack_pair<F16>(y[2], y[3]), pack_pair<F16>(y[4], y[5]), pack_pair<F16>(y[6], y[7]));
-    *reinterpret_cast<uint4 *>(d.out + (size_t)m * Cout + col) = o;
-}
-
 namespace {
 template <int BITS, bool BWD, bool F16, int RT>
 hipError_t launch_direct_rt(const DirectDev &d, hipStream_t stream) {
@@ -619,12 +532,7 @@ hipError_t launch_direct_any(const DirectDev &d, int rt, hipStream_t stream) {
         case 3: e = launch_direct_bits<3, BWD, F16>(d, rt, stream); break;
         default: e = launch_direct_bits<4, BWD, F16>(d, rt, stream); break;
     }
-    if (e != hipSuccess) return e;
-    const size_t lds = (size_t)(32 + 64) * d.r * sizeof(float);          // at most 24 KB
-    launch_kernel(F16 ? (BWD ? "f16_gemm_bwd_direct_fixup" : "f16_gemm_fwd_direct_fixup")
-                      : (BWD ? "gemm_bwd_direct_fixup" : "gemm_fwd_direct_fixup"),
-                  gemm_direct_finish_kernel<BWD, F16>, dim3((d.Cout + 63) / 64, (d.M + 31) / 32), 256, lds, stream, d);
-    return hipGetLastError();
+    return e;
 }
 }  // namespace
 
@@ -656,22 +564,26 @@ hipError_t launch_direct(const SmallArgs &a, bool backward, hipStream_t stream) 
     d.w = a.w;
     d.act = a.act;
     d.zeros16 = a.zeros16;
-    d.bias16 = a.bias16;
     d.M = a.M; d.C = C; d.Cout = Cout;
     d.tiles_m = p.tiles_m; d.tiles_c = p.tiles_c; d.split = p.split; d.nch = p.chunks; d.proj_parts = p.proj_parts;
     d.part = static_cast<float *>(a.ws);
     d.ppart = reinterpret_cast<float *>(static_cast<char *>(a.ws) + p.partial_bytes(a.M, Cout));
     d.Fp = backward ? a.B : a.A;
-    d.Fo = backward ? a.A : a.B;
+    d.part_stride = DirectPlan::part_stride(a.M, a.r);
     d.r = a.r;
-    d.lora_scale = a.lora_scale;
-    d.out = a.out;
-    d.P_out = a.P_out;
     const uint32_t bpg = (uint32_t)(a.w.group / 32);
     d.group_plus = bpg > 1 ? 0u : 1u;
     d.group_magic = bpg > 1 ? (uint32_t)((1ull << 32) / bpg) + 1u : 0xFFFFFFFFu;
-    if (a.f16) return backward ? launch_direct_any<true, true>(d, p.rt, stream) : launch_direct_any<false, true>(d, p.rt, stream);
-    return backward ? launch_direct_any<true, false>(d, p.rt, stream) : launch_direct_any<false, false>(d, p.rt, stream);
+    hipError_t e;
+    if (a.f16) e = backward ? launch_direct_any<true, true>(d, p.rt, stream) : launch_direct_any<false, true>(d, p.rt, stream);
+    else e = backward ? launch_direct_any<true, false>(d, p.rt, stream) : launch_direct_any<false, false>(d, p.rt, stream);
+    if (e != hipSuccess) return e;
+    FinishArgs f{};
+    f.slices = d.part; f.slice_stride = (size_t)a.M * Cout; f.split = p.split; f.M = a.M; f.Cout = Cout;
+    f.ppart = d.ppart; f.part_stride = d.part_stride; f.parts = p.split * p.proj_parts; f.r = a.r;
+    f.F = backward ? a.A : a.B; f.bias16 = a.bias16; f.lora_scale = a.lora_scale; f.out = a.out; f.P_out = a.P_out;
+    return launch_finish(a.f16 ? (backward ? "f16_gemm_bwd_direct_fixup" : "f16_gemm_fwd_direct_fixup")
+                               : (backward ? "gemm_bwd_direct_fixup" : "gemm_fwd_direct_fixup"), f, backward, a.f16, stream);
 }
 
 }  // namespace mlr

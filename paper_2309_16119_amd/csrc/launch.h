@@ -324,13 +324,31 @@ size_t smallm_fwd_ws_bytes(const LayerView &w, int r);    // what launch_smallm_
 hipError_t launch_smallm_fwd(const SmallArgs &a, hipStream_t stream);
 hipError_t launch_smallm_bwd(const SmallArgs &a, hipStream_t stream);
 
+// ---- finish.hip: sum of a split contraction's slices, adapter term, bias, one rounding ----
+struct FinishArgs {
+    const float *slices;      // [split], `slice_stride` floats apart: fp32 [M][Cout]
+    size_t slice_stride;
+    int split, M, Cout;
+    const float *ppart;       // [parts], `part_stride` floats apart (a multiple of 4): the projection's fp32 [M][r]
+    int part_stride, parts;
+    int r;
+    const float *F;           // forward B [r][Cout], backward A [Cout][r]
+    const uint16_t *bias16;   // binary16 forward: [Cout] or NULL
+    float lora_scale;
+    uint16_t *out;            // [M][Cout]
+    float *P_out;             // [M][r] or NULL
+    uint32_t r_magic;         // set by launch_finish()
+};
+hipError_t launch_finish(const char *name, FinishArgs d, bool backward, bool f16, hipStream_t stream);
+
 // ---- gemm_direct.hip: a few dozen to a few hundred tokens -------------------------
 struct DirectPlan {
     int rt, tiles_m, tiles_c, chunks, split;   // row tiles of 32 per row block, grid, chunks of 256 of the contraction, slices
     int proj_parts;  // workgroups that share the projection of 16 rows over one slice
-    // fp32 results of the slices, then the projection's
+    // fp32 results of the slices, then the projection's, each part padded to whole float4
     size_t partial_bytes(int M, int Cout) const { return ((size_t)split * M * Cout * 4 + 255) & ~(size_t)255; }
-    size_t ws_bytes(int M, int Cout, int r) const { return partial_bytes(M, Cout) + (((size_t)split * proj_parts * M * r * 4 + 255) & ~(size_t)255); }
+    static int part_stride(int M, int r) { return (M * r + 3) & ~3; }
+    size_t ws_bytes(int M, int Cout, int r) const { return partial_bytes(M, Cout) + (((size_t)split * proj_parts * part_stride(M, r) * 4 + 255) & ~(size_t)255); }
 };
 // The split of the contraction with the smallest estimated time, in microseconds (`us`).  The model and
 // its constants are a least-squares fit (6 % rms) to 1080 timed calls: six layers of 4096 x 4096 to

@@ -293,11 +293,12 @@ __device__ __forceinline__ void smallm_project_f16(const uint16_t *act, int M, i
     }
 }
 
-// Sum of the projection workgroups' partials into Us (16 x r floats in LDS).
-template <int EPT>
+constexpr int STREAM_FINISH_RANK = 8;      // largest rank of the finish kernels in this file
+// Sum of the projection workgroups' partials into Us (16 x r floats in LDS, r at most STREAM_FINISH_RANK).
 __device__ __forceinline__ void smallm_sum_parts(const float *parts, int n_parts, int r, float *Us) {
-    // EPT elements per thread and up to sixteen workgroups' partials of each in flight together
-    // (n_parts <= 32), so that a small workgroup and a large rank still wait for few round trips
+    // two elements per thread (all of them in a single-wave workgroup) and up to sixteen workgroups'
+    // partials of each in flight together (n_parts <= 32)
+    constexpr int EPT = 2;
     const int n = 16 * r, stride = blockDim.x;
     for (int t0 = threadIdx.x; t0 < n; t0 += EPT * stride) {
         float sum[EPT];
@@ -438,16 +439,18 @@ constexpr int BCOLS = FWD_WAVES * WCOLS;  // columns per workgroup
 constexpr int MAX_RANGE = 2048;           // contraction elements of one K slice (64 KB of LDS)
 }  // namespace sm
 
-// The eight rows jj0 .. jj0 + 7 of B at columns col .. col + 7, all loads issued together (rows
-// past r come back as zeros).
-constexpr int FIN_BROWS = 8;
-__device__ __forceinline__ void smallm_load_b8x8(const SmallFwdDev &d, int jj0, int col, float4 b[FIN_BROWS][2]) {
+// The finish kernels below serve a rank of at most eight, whose factor rows fit one batch of loads; finish.hip
+// takes larger ones (16 rows, us here / there: r = 8 4096 wide 5.8 / 5.6, 11008 wide 4.5 / 5.2, 22016 wide 4.2 / 4.8;
+// r = 16 7.1 / 5.9, 5.2 / 5.0, 5.3 / 5.1; r = 64 13.0 / 6.8, 12.0 / 6.1, 12.0 / 6.8).
+constexpr int FIN_BROWS = STREAM_FINISH_RANK;
+// The rows of B at columns col .. col + 7, all loads issued together (rows past r come back as zeros).
+__device__ __forceinline__ void smallm_load_b8x8(const SmallFwdDev &d, int col, float4 b[FIN_BROWS][2]) {
 #pragma unroll
     for (int q = 0; q < FIN_BROWS; ++q) {
         b[q][0] = make_float4(0.f, 0.f, 0.f, 0.f);
         b[q][1] = b[q][0];
-        if (jj0 + q < d.r) {
-            const float *src = d.B + (size_t)(jj0 + q) * d.w.N + col;
+        if (q < d.r) {
+            const float *src = d.B + (size_t)q * d.w.N + col;
             b[q][0] = *reinterpret_cast<const float4 *>(src);
             b[q][1] = *reinterpret_cast<const float4 *>(src + 4);
         }
@@ -455,27 +458,18 @@ __device__ __forceinline__ void smallm_load_b8x8(const SmallFwdDev &d, int jj0, 
 }
 
 // Adds the adapter term (and, F16, the bias) to the eight adjacent outputs y[0..7] of row m, columns
-// col .. col + 7 (col a multiple of 8, col + 7 < N) and stores them as 16-bit floats.  `b0`: rows
-// 0 .. 7 of B for these columns, loaded by the caller ahead of time.
+// col .. col + 7 (col a multiple of 8, col + 7 < N) and stores them as 16-bit floats.  `b`: the rows
+// of B for these columns, loaded by the caller ahead of time.
 template <bool F16>
-__device__ __forceinline__ void smallm_fwd_store8(const SmallFwdDev &d, const float *Us, int m, int col, const float y[8], const float4 b0[FIN_BROWS][2]) {
+__device__ __forceinline__ void smallm_fwd_store8(const SmallFwdDev &d, const float *Us, int m, int col, const float y[8], const float4 b[FIN_BROWS][2]) {
     float l[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int jj0 = 0; jj0 < d.r; jj0 += FIN_BROWS) {
-        float4 b[FIN_BROWS][2];
-        if (jj0 == 0) {
 #pragma unroll
-            for (int q = 0; q < FIN_BROWS; ++q) { b[q][0] = b0[q][0]; b[q][1] = b0[q][1]; }
-        } else {
-            smallm_load_b8x8(d, jj0, col, b);
-        }
-#pragma unroll
-        for (int q = 0; q < FIN_BROWS; ++q) {
-            const float u = jj0 + q < d.r ? Us[m * d.r + jj0 + q] : 0.f;
-            l[0] = __builtin_fmaf(u, b[q][0].x, l[0]); l[1] = __builtin_fmaf(u, b[q][0].y, l[1]);
-            l[2] = __builtin_fmaf(u, b[q][0].z, l[2]); l[3] = __builtin_fmaf(u, b[q][0].w, l[3]);
-            l[4] = __builtin_fmaf(u, b[q][1].x, l[4]); l[5] = __builtin_fmaf(u, b[q][1].y, l[5]);
-            l[6] = __builtin_fmaf(u, b[q][1].z, l[6]); l[7] = __builtin_fmaf(u, b[q][1].w, l[7]);
-        }
+    for (int q = 0; q < FIN_BROWS; ++q) {
+        const float u = q < d.r ? Us[m * d.r + q] : 0.f;
+        l[0] = __builtin_fmaf(u, b[q][0].x, l[0]); l[1] = __builtin_fmaf(u, b[q][0].y, l[1]);
+        l[2] = __builtin_fmaf(u, b[q][0].z, l[2]); l[3] = __builtin_fmaf(u, b[q][0].w, l[3]);
+        l[4] = __builtin_fmaf(u, b[q][1].x, l[4]); l[5] = __builtin_fmaf(u, b[q][1].y, l[5]);
+        l[6] = __builtin_fmaf(u, b[q][1].z, l[6]); l[7] = __builtin_fmaf(u, b[q][1].w, l[7]);
     }
     float bias[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     if (F16 && d.bias16 != nullptr) {          // the bias of Figure 1 / eq. (3): part of the frozen layer
@@ -757,7 +751,7 @@ __global__ __launch_bounds__(sm::FWD_THREADS, 4) void smallm_fwd_kernel(SmallFwd
 constexpr int FIN_COLS = 32, FIN_SLICES = 16;
 template <bool F16>
 __global__ __launch_bounds__(64) void smallm_fwd_finish_kernel(SmallFwdDev d) {
-    __shared__ float Us[16 * 64];
+    __shared__ float Us[16 * STREAM_FINISH_RANK];
     const int tid = threadIdx.x, N = d.w.N;
     const int m = tid >> 2, col = blockIdx.x * FIN_COLS + 8 * (tid & 3);
     const bool mine = m < d.M && col < N;          // N is a multiple of 8: all eight columns or none
@@ -765,7 +759,7 @@ __global__ __launch_bounds__(64) void smallm_fwd_finish_kernel(SmallFwdDev d) {
     float4 b0[FIN_BROWS][2];
 #pragma unroll
     for (int q = 0; q < FIN_BROWS; ++q) { b0[q][0] = make_float4(0.f, 0.f, 0.f, 0.f); b0[q][1] = b0[q][0]; }
-    if (mine) smallm_load_b8x8(d, 0, col, b0);
+    if (mine) smallm_load_b8x8(d, col, b0);
     // (lanes with nothing to do read row 0, columns 0 .. 7; slices past the last one re-read the last
     // and are not added: no predicate per load)
     const float *base = d.Yacc + (mine ? (size_t)m * N + col : (size_t)0);
@@ -808,8 +802,7 @@ __global__ __launch_bounds__(64) void smallm_fwd_finish_kernel(SmallFwdDev d) {
         }
     };
     load_slices(0);
-    if (d.r <= 8) smallm_sum_parts<2>(d.Upart, d.n_proj, d.r, Us);     // 16 r elements over 64 lanes: no more loads than needed
-    else smallm_sum_parts<4>(d.Upart, d.n_proj, d.r, Us);
+    smallm_sum_parts(d.Upart, d.n_proj, d.r, Us);
     add_slices(0);
     for (int q0 = FIN_SLICES; q0 < d.ksplit; q0 += FIN_SLICES) { load_slices(q0); add_slices(q0); }
     if (blockIdx.x == 0 && d.XA != nullptr)
@@ -856,17 +849,17 @@ constexpr int NSTEP = 32;    // contraction elements per step (8 per lane group)
 constexpr int RED_BYTES = sm::WG_WAVES * 32 * 64 * 4;   // the waves' tiles meeting in LDS
 }
 
-// A[k0 + c][jj0 .. jj0 + 7] for the eight adjacent rows c, all loads issued together (columns past
+// A[k0 + c][0 .. 7] for the eight adjacent rows c, all loads issued together (columns past
 // r come back as zeros): 16-byte loads when the rows are 16-byte aligned (r a multiple of 4).
-__device__ __forceinline__ void smallm_load_a8(const SmallBwdDev &d, int k0, int jj0, float4 a[8][2]) {
+__device__ __forceinline__ void smallm_load_a8(const SmallBwdDev &d, int k0, float4 a[8][2]) {
     const int r = d.r;
 #pragma unroll
     for (int c = 0; c < 8; ++c) {
-        const float *src = d.A + (size_t)(k0 + c) * r + jj0;
+        const float *src = d.A + (size_t)(k0 + c) * r;
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             a[c][h] = make_float4(0.f, 0.f, 0.f, 0.f);
-            const int j = jj0 + 4 * h;
+            const int j = 4 * h;
             if ((r & 3) == 0) {
                 if (j < r) a[c][h] = *reinterpret_cast<const float4 *>(src + 4 * h);
             } else {
@@ -879,33 +872,23 @@ __device__ __forceinline__ void smallm_load_a8(const SmallBwdDev &d, int k0, int
     }
 }
 
-// Adapter term and 16-bit store of 8 adjacent outputs dX[m][k0 .. k0+7].  `a0`: columns 0 .. 7 of
+// Adapter term and 16-bit store of 8 adjacent outputs dX[m][k0 .. k0+7].  `a`: columns 0 .. 7 of
 // the eight rows of A, loaded by the caller ahead of time.
 template <bool F16>
-__device__ __forceinline__ void smallm_bwd_store8(const SmallBwdDev &d, const float *Ts, int m, int k0, const float y[8], const float4 a0[8][2]) {
-    float l[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int jj0 = 0; jj0 < d.r; jj0 += 8) {
-        float4 a[8][2];
-        if (jj0 == 0) {
+__device__ __forceinline__ void smallm_bwd_store8(const SmallBwdDev &d, const float *Ts, int m, int k0, const float y[8], const float4 a[8][2]) {
+    float l[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, t[STREAM_FINISH_RANK];
 #pragma unroll
-            for (int c = 0; c < 8; ++c) { a[c][0] = a0[c][0]; a[c][1] = a0[c][1]; }
-        } else {
-            smallm_load_a8(d, k0, jj0, a);
-        }
-        float t[8];
+    for (int q = 0; q < STREAM_FINISH_RANK; ++q) t[q] = q < d.r ? Ts[m * d.r + q] : 0.f;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) t[q] = jj0 + q < d.r ? Ts[m * d.r + jj0 + q] : 0.f;
-#pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            l[c] = __builtin_fmaf(t[0], a[c][0].x, l[c]);
-            l[c] = __builtin_fmaf(t[1], a[c][0].y, l[c]);
-            l[c] = __builtin_fmaf(t[2], a[c][0].z, l[c]);
-            l[c] = __builtin_fmaf(t[3], a[c][0].w, l[c]);
-            l[c] = __builtin_fmaf(t[4], a[c][1].x, l[c]);
-            l[c] = __builtin_fmaf(t[5], a[c][1].y, l[c]);
-            l[c] = __builtin_fmaf(t[6], a[c][1].z, l[c]);
-            l[c] = __builtin_fmaf(t[7], a[c][1].w, l[c]);
-        }
+    for (int c = 0; c < 8; ++c) {
+        l[c] = __builtin_fmaf(t[0], a[c][0].x, l[c]);
+        l[c] = __builtin_fmaf(t[1], a[c][0].y, l[c]);
+        l[c] = __builtin_fmaf(t[2], a[c][0].z, l[c]);
+        l[c] = __builtin_fmaf(t[3], a[c][0].w, l[c]);
+        l[c] = __builtin_fmaf(t[4], a[c][1].x, l[c]);
+        l[c] = __builtin_fmaf(t[5], a[c][1].y, l[c]);
+        l[c] = __builtin_fmaf(t[6], a[c][1].z, l[c]);
+        l[c] = __builtin_fmaf(t[7], a[c][1].w, l[c]);
     }
     float o[8];
 #pragma unroll
@@ -1241,7 +1224,7 @@ __global__ __launch_bounds__(sm::WG_THREADS, 2) void smallm_bwd_kernel(SmallBwdD
 // chain of loads): lane l owns row l / 4, columns 8 (l % 4) .. + 7.
 template <bool F16>
 __global__ __launch_bounds__(64) void smallm_bwd_finish_kernel(SmallBwdDev d) {
-    __shared__ float Ts[16 * 64];
+    __shared__ float Ts[16 * STREAM_FINISH_RANK];
     const int tid = threadIdx.x, K = d.w.K;
     const int m = tid >> 2, k0 = blockIdx.x * FIN_COLS + 8 * (tid & 3);
     float y[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
@@ -1249,7 +1232,7 @@ __global__ __launch_bounds__(64) void smallm_bwd_finish_kernel(SmallBwdDev d) {
     float4 a0[8][2];
 #pragma unroll
     for (int c = 0; c < 8; ++c) { a0[c][0] = make_float4(0.f, 0.f, 0.f, 0.f); a0[c][1] = a0[c][0]; }
-    if (m < d.M && d.r > 0) smallm_load_a8(d, k0, 0, a0);
+    if (m < d.M && d.r > 0) smallm_load_a8(d, k0, a0);
     // sixteen slices' loads (two 16-byte loads each) in flight at a time; the first sixteen are issued
     // before the projection partials are summed and consumed after
     constexpr int SB = FIN_SLICES;
@@ -1290,8 +1273,7 @@ __global__ __launch_bounds__(64) void smallm_bwd_finish_kernel(SmallBwdDev d) {
         }
     };
     load_slices(0);
-    if (d.r <= 8) smallm_sum_parts<2>(d.Tpart, d.n_proj, d.r, Ts);     // 16 r elements over 64 lanes: no more loads than needed
-    else smallm_sum_parts<4>(d.Tpart, d.n_proj, d.r, Ts);
+    smallm_sum_parts(d.Tpart, d.n_proj, d.r, Ts);
     add_slices(0);
     for (int q0 = SB; q0 < d.nsplit; q0 += SB) { load_slices(q0); add_slices(q0); }
     if (blockIdx.x == 0 && d.T_out != nullptr)
@@ -1488,6 +1470,13 @@ hipError_t launch_smallm_fwd(const SmallArgs &a, hipStream_t stream) {
     e = a.f16 ? launch_fwd_any<true>(d, a.w.bits, spg1, col_blocks, lds_bytes, stream)
               : launch_fwd_any<false>(d, a.w.bits, spg1, col_blocks, lds_bytes, stream);
     if (e != hipSuccess) return e;
+    if (a.r > STREAM_FINISH_RANK) {
+        FinishArgs f{};
+        f.slices = d.Yacc; f.slice_stride = (size_t)16 * N; f.split = d.ksplit; f.M = a.M; f.Cout = N;
+        f.ppart = d.Upart; f.part_stride = 16 * a.r; f.parts = d.n_proj; f.r = a.r;
+        f.F = a.B; f.bias16 = d.bias16; f.lora_scale = a.lora_scale; f.out = a.out; f.P_out = a.P_out;
+        return launch_finish(a.f16 ? "f16_stream_fwd_finish" : "stream_fwd_finish", f, false, a.f16, stream);
+    }
     if (a.f16) launch_kernel("f16_stream_fwd_finish", smallm_fwd_finish_kernel<true>, (N + FIN_COLS - 1) / FIN_COLS, 64, 0, stream, d);
     else launch_kernel("stream_fwd_finish", smallm_fwd_finish_kernel<false>, (N + FIN_COLS - 1) / FIN_COLS, 64, 0, stream, d);
     return hipGetLastError();
@@ -1547,6 +1536,13 @@ hipError_t launch_smallm_bwd(const SmallArgs &a, hipStream_t stream) {
     d.zeros16 = a.zeros16;
     e = a.f16 ? launch_bwd_any<true>(d, a.w.bits, k_blocks, stream) : launch_bwd_any<false>(d, a.w.bits, k_blocks, stream);
     if (e != hipSuccess) return e;
+    if (a.r > STREAM_FINISH_RANK) {
+        FinishArgs f{};
+        f.slices = d.acc; f.slice_stride = (size_t)16 * K; f.split = d.nsplit; f.M = a.M; f.Cout = K;
+        f.ppart = d.Tpart; f.part_stride = 16 * a.r; f.parts = d.n_proj; f.r = a.r;
+        f.F = a.A; f.bias16 = nullptr; f.lora_scale = a.lora_scale; f.out = a.out; f.P_out = a.P_out;
+        return launch_finish(a.f16 ? "f16_stream_bwd_finish" : "stream_bwd_finish", f, true, a.f16, stream);
+    }
     if (a.f16) launch_kernel("f16_stream_bwd_finish", smallm_bwd_finish_kernel<true>, K / FIN_COLS, 64, 0, stream, d);
     else launch_kernel("stream_bwd_finish", smallm_bwd_finish_kernel<false>, K / FIN_COLS, 64, 0, stream, d);
     return hipGetLastError();

@@ -90,6 +90,62 @@ def test_against_the_oracle(bits, K, N, M, r, group, conv):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("conv", ["bf16", "f16"])
+@pytest.mark.parametrize("bits,K,N,M,r,group", [
+    # second launches of up to 16 rows behind the streaming kernels: 32, 64 and 128 columns a workgroup, ranks that
+    # fill a group of 16 or not, that are no multiple of four, one row, sixteen, two passes
+    (4, 512, 640, 1, 9, 128),
+    (3, 2560, 384, 16, 64, 128),
+    (2, 768, 16512, 5, 17, 64),
+    (4, 512, 32896, 3, 33, 128),
+    (3, 4096, 4096, 29, 16, 128),
+    # and of 32 rows behind the direct kernel, deep and not: one row past a tile, a rank of 1, 2, 47 and 64
+    (3, 4096, 2056, 33, 1, 128),
+    (2, 4096, 4104, 65, 2, 32),
+    (4, 4128, 2304, 63, 47, 96),
+    (3, 4096, 4096, 700, 64, 128),
+    (3, 4096, 4096, 545, 15, 128),
+])
+def test_second_launch_adds_slices_and_adapter(bits, K, N, M, r, group, conv):
+    """An adapter term that is most of the output (factors times thirty), so that a part, a slice or a column of
+    the second launch that went missing or to the wrong place cannot hide."""
+    cfg = synth.LayerConfig("t", K, N, bits, group, M, r, seed=78)
+    s, f16 = 2.0, conv == "f16"
+    if f16:
+        L = synth.make_layer_f16(cfg)
+        w = b.QWeightF16.from_numpy(L["qweight"], L["scales"], L["zeros_f16"], L["bias"], K, N, bits, group)
+        What, dtype = b.modulora_f16_dequant(w), torch.float16
+        fwd, bwd, rel = b.modulora_f16_fwd, b.modulora_f16_bwd_input, 2.0 ** -10
+    else:
+        L = synth.make_layer(cfg)
+        w = b.QWeight.from_numpy(L["qweight"], L["scales"], L["zeros"], K, N, bits, group)
+        What, dtype = b.modulora_dequant(w), torch.bfloat16
+        fwd, bwd, rel = b.modulora_fwd, b.modulora_bwd_input, 2.0 ** -8
+    act = lambda x: torch.from_numpy(np.ascontiguousarray(x).view(np.int16)).cuda().view(dtype)
+    X, dY, W = act(L["X"]), act(L["dY"]), What.double()
+    A, B = torch.from_numpy(L["A"]).cuda() * 30, torch.from_numpy(L["B"]).cuda() * 30
+    nan = lambda cols, t: torch.full((M, cols), float("nan"), dtype=t, device="cuda")
+    Y, XA = fwd(w, X, A, B, s, nan(N, dtype), nan(r, torch.float32))
+    dX, T = bwd(w, dY, A, B, s, nan(K, dtype), nan(r, torch.float32))
+    XAr, Tr = X.double() @ A.double(), dY.double() @ B.double().t()
+    Yr = X.double() @ W.t() + s * XAr @ B.double()
+    if f16:
+        Yr = Yr + act(L["bias"]).double()
+    dXr = dY.double() @ W + s * Tr @ A.double().t()
+    # what multiplying by the codes instead of the rounded weight may change (up to 32 tokens)
+    extra_Y = extra_dX = 0.0
+    if M <= 32:
+        unit = (2.0 ** -11 if f16 else 2.0 ** -8)
+        extra_Y = (unit * X.double().abs() @ W.abs().t()).cpu().numpy()
+        extra_dX = (2 * unit * dY.double().abs() @ W.abs()).cpu().numpy() + (2.0 ** -25 * 15 * N if f16 else 0.0)
+    for got, ref, n, extra in ((Y, Yr, K + r, extra_Y), (dX, dXr, N + r, extra_dX)):
+        got, ref = got.double().cpu().numpy(), ref.cpu().numpy()
+        assert np.all(np.abs(got - ref) <= rel * np.abs(ref) + (4e-7 * np.sqrt(n) + 2e-5) * np.abs(ref).max() + extra)
+    _close(XA, XAr.cpu().numpy(), 2.0 ** -20, K)
+    _close(T, Tr.cpu().numpy(), 2.0 ** -20, N)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("conv,direction,K,N,M,r,direct", [
     # the rank's price: an output of 69 column blocks, whose 32 projection parts the second launch adds in a row
     ("bf16", "fwd", 1024, 8832, 38, 8, True),
