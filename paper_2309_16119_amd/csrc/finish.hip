@@ -11,18 +11,18 @@
 
 namespace mlr {
 
-// RG: sixteens of rank that there is room for (0, 1, 2, 4).  ROWS x COLS outputs, eight of a row per thread, in SG
+// R: columns of rank that there is room for (0, 8, 16, 32, 64).  ROWS x COLS outputs, eight of a row per thread, in SG
 // groups of threads that share the slices and the rank and meet in LDS.
 // DEEP: everything in flight at once, at two waves a SIMD.
-template <bool BWD, bool F16, int RG, int ROWS, int SG, bool DEEP>
-__global__ __launch_bounds__(256, DEEP ? 2 : (RG <= 1 ? 6 : 4)) void finish_kernel(FinishArgs d) {
-    constexpr int COLS = 2048 / ROWS / SG, R = 16 * RG, PS = R + 4;
-    constexpr int F4 = RG > 0 ? (R * COLS / 4 + 255) / 256 : 1;       // float4 of the factor's tile per thread
-    constexpr int P_SLOTS = RG > 0 ? ROWS * R / 4 : 1;                // float4 of the projection's rows
+template <bool BWD, bool F16, int R, int ROWS, int SG, bool DEEP>
+__global__ __launch_bounds__(256, DEEP ? 2 : (R <= 16 ? 6 : 4)) void finish_kernel(FinishArgs d) {
+    constexpr int COLS = 2048 / ROWS / SG, PS = R + 4;
+    constexpr int F4 = R > 0 ? (R * COLS / 4 + 255) / 256 : 1;       // float4 of the factor's tile per thread
+    constexpr int P_SLOTS = R > 0 ? ROWS * R / 4 : 1;                // float4 of the projection's rows
     constexpr int P4 = (P_SLOTS + 255) / 256, GROUPS = P_SLOTS < 256 ? 256 / P_SLOTS : 1;
-    constexpr int PB = (DEEP ? 16 : RG <= 1 ? 4 : 8) / P4, SB = DEEP ? 8 : 4;      // in flight: parts per slot, slices
-    __shared__ __attribute__((aligned(16))) float Fs[RG > 0 ? R * COLS : 4], Ps[RG > 0 ? ROWS * PS : 4];
-    __shared__ __attribute__((aligned(16))) float4 Gs[GROUPS > 1 ? 256 : 1], Ys[SG > 1 ? (SG - 1) * 2 * (256 / SG) : 1];
+    constexpr int PB = (DEEP ? 16 : R <= 16 ? 4 : 8) / P4, SB = DEEP ? 8 : 4;      // in flight: parts per slot, slices
+    __shared__ __attribute__((aligned(16))) float Fs[R > 0 ? R * COLS + COLS / 2 : 4], Ps[R > 0 ? GROUPS * ROWS * PS : 4];      // [group of parts][row]
+    __shared__ __attribute__((aligned(16))) float4 Ys[SG > 1 ? (SG - 1) * 2 * (256 / SG) : 1];
     const int tid = threadIdx.x, r = d.r, M = d.M, Cout = d.Cout;
     const int m0 = blockIdx.y * ROWS, c0 = blockIdx.x * COLS;
     const int sg = uniform(tid / (256 / SG)), row = tid % (256 / SG) / (COLS / 8), cl = tid % (COLS / 8) * 8, m = m0 + row, col = c0 + cl;
@@ -35,9 +35,20 @@ __global__ __launch_bounds__(256, DEEP ? 2 : (RG <= 1 ? 6 : 4)) void finish_kern
         j = x - q * r;
     };
 
+    const float *src = d.slices + (mine ? (size_t)m * Cout + col : (size_t)0);
+    float4 v0[SB], v1[SB];
+    auto load_slices = [&](int q0) {
+#pragma unroll
+        for (int u = 0; u < SB; ++u)
+            if ((q0 + u) * SG + sg < d.split) {
+                v0[u] = *reinterpret_cast<const float4 *>(src + (size_t)((q0 + u) * SG + sg) * d.slice_stride);
+                v1[u] = *reinterpret_cast<const float4 *>(src + (size_t)((q0 + u) * SG + sg) * d.slice_stride + 4);
+            }
+    };
+    load_slices(0);
     // forward: F [r][Cout], its tile [j][COLS]; backward: F [Cout][r], whose tile is one run of floats
     float4 f[F4];
-    if (RG > 0) {
+    if (R > 0) {
 #pragma unroll
         for (int q = 0; q < F4; ++q) {
             const int x = q * 256 + tid;
@@ -50,7 +61,6 @@ __global__ __launch_bounds__(256, DEEP ? 2 : (RG <= 1 ? 6 : 4)) void finish_kern
             }
         }
     }
-    const float *src = d.slices + (mine ? (size_t)m * Cout + col : (size_t)0);
     // the projection's rows m0 ... as one run of floats per part (parts are padded to whole float4)
     const int p_slot = tid % P_SLOTS, p_group = tid / P_SLOTS;
     const float *psrc = d.ppart + (size_t)m0 * r;
@@ -65,16 +75,7 @@ __global__ __launch_bounds__(256, DEEP ? 2 : (RG <= 1 ? 6 : 4)) void finish_kern
                 if (x < rows * r && s < d.parts) p[t][u] = *reinterpret_cast<const float4 *>(psrc + (size_t)s * d.part_stride + x);
             }
     };
-    if (RG > 0) load_parts(0);
-    float4 v0[SB], v1[SB];
-    auto load_slices = [&](int q0) {
-#pragma unroll
-        for (int u = 0; u < SB; ++u)
-            if ((q0 + u) * SG + sg < d.split) {
-                v0[u] = *reinterpret_cast<const float4 *>(src + (size_t)((q0 + u) * SG + sg) * d.slice_stride);
-                v1[u] = *reinterpret_cast<const float4 *>(src + (size_t)((q0 + u) * SG + sg) * d.slice_stride + 4);
-            }
-    };
+    if (R > 0) load_parts(0);
     float y[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     auto add_slices = [&](int q0) {
 #pragma unroll
@@ -84,12 +85,11 @@ __global__ __launch_bounds__(256, DEEP ? 2 : (RG <= 1 ? 6 : 4)) void finish_kern
                 y[4] += v1[u].x; y[5] += v1[u].y; y[6] += v1[u].z; y[7] += v1[u].w;
             }
     };
-    load_slices(0);
     float l[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (RG > 0) {
-        // backward: a column's r values side by side, its quads at 4 (quad ^ column / 8) so that the threads of a
+    if (R > 0) {
+        // backward: a column's r values side by side, four floats after every eighth column so that the threads of a
         // row, eight columns apart, meet different banks
-        auto bwd_at = [&](int c, int quad) { return c * R + 4 * ((quad ^ (c >> 3)) & (R / 4 - 1)); };
+        auto bwd_at = [&](int c, int quad) { return (c >> 3) * (8 * R + 4) + (c & 7) * R + 4 * quad; };
 #pragma unroll
         for (int q = 0; q < F4; ++q) {
             const int x = q * 256 + tid;
@@ -113,7 +113,7 @@ __global__ __launch_bounds__(256, DEEP ? 2 : (RG <= 1 ? 6 : 4)) void finish_kern
         if (!quads) {                                                 // zeros that fill up the last quad
             for (int x = tid; x < COLS * 4; x += 256)
                 if (BWD && (r & 3) + (x & 3) < 4) Fs[bwd_at(x >> 2, r >> 2) + (r & 3) + (x & 3)] = 0.f;
-            for (int x = tid; x < ROWS * 4; x += 256)
+            for (int x = tid; x < GROUPS * ROWS * 4; x += 256)
                 if ((r & 3) + (x & 3) < 4) Ps[(x >> 2) * PS + r + (x & 3)] = 0.f;
         }
         float4 sum[P4];
@@ -126,36 +126,41 @@ __global__ __launch_bounds__(256, DEEP ? 2 : (RG <= 1 ? 6 : 4)) void finish_kern
 #pragma unroll
                 for (int u = 0; u < PB; ++u) { sum[t].x += p[t][u].x; sum[t].y += p[t][u].y; sum[t].z += p[t][u].z; sum[t].w += p[t][u].w; }
         }
-        if (GROUPS > 1) {
-            Gs[tid] = sum[0];
-            __syncthreads();
-            if (tid < P_SLOTS) {
-#pragma unroll
-                for (int g = 1; g < GROUPS; ++g) {
-                    const float4 o = Gs[g * P_SLOTS + tid];
-                    sum[0].x += o.x; sum[0].y += o.y; sum[0].z += o.z; sum[0].w += o.w;
-                }
-            }
-        }
 #pragma unroll
         for (int t = 0; t < P4; ++t) {
             const int x = 4 * (p_slot + 256 * t);
-            if (p_group > 0 || x >= rows * r) continue;
+            if (x >= rows * r) continue;
             const float s4[4] = {sum[t].x, sum[t].y, sum[t].z, sum[t].w};
             int q, j;
             split_index(x, q, j);
+            float *dst = Ps + p_group * (ROWS * PS);
+            if (quads) {
+                *reinterpret_cast<float4 *>(dst + q * PS + j) = sum[t];
+            } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (x + e < rows * r) {
-                    Ps[q * PS + j] = s4[e];
-                    if (blockIdx.x == 0 && d.P_out != nullptr) d.P_out[(size_t)m0 * r + x + e] = s4[e];
+                for (int e = 0; e < 4; ++e) {
+                    if (x + e < rows * r) dst[q * PS + j] = s4[e];
+                    if (++j == r) { j = 0; ++q; }
                 }
-                if (++j == r) { j = 0; ++q; }
             }
         }
         __syncthreads();
+        if (blockIdx.x == 0 && d.P_out != nullptr)
+            for (int x = tid; x < rows * r; x += 256) {
+                int q, j;
+                split_index(x, q, j);
+                float o = Ps[q * PS + j];
+#pragma unroll
+                for (int g = 1; g < GROUPS; ++g) o += Ps[(g * ROWS + q) * PS + j];
+                d.P_out[(size_t)m0 * r + x] = o;
+            }
         for (int j = 4 * sg; j < r; j += 4 * SG) {
-            const float4 pj = *reinterpret_cast<const float4 *>(Ps + row * PS + j);
+            float4 pj = *reinterpret_cast<const float4 *>(Ps + row * PS + j);
+#pragma unroll
+            for (int g = 1; g < GROUPS; ++g) {
+                const float4 o = *reinterpret_cast<const float4 *>(Ps + (g * ROWS + row) * PS + j);
+                pj.x += o.x; pj.y += o.y; pj.z += o.z; pj.w += o.w;
+            }
             const float p4[4] = {pj.x, pj.y, pj.z, pj.w};
             if (!BWD) {
 #pragma unroll
@@ -221,12 +226,11 @@ template <bool BWD, bool F16, int ROWS, int SG, bool DEEP>
 hipError_t launch_finish_rows(const char *name, const FinishArgs &d, hipStream_t stream) {
     constexpr int COLS = 2048 / ROWS / SG;
     const dim3 grid((d.Cout + COLS - 1) / COLS, (d.M + ROWS - 1) / ROWS);
-    switch ((d.r + 15) / 16) {
-        case 0: launch_kernel(name, finish_kernel<BWD, F16, 0, ROWS, SG, DEEP>, grid, 256, 0, stream, d); break;
-        case 1: launch_kernel(name, finish_kernel<BWD, F16, 1, ROWS, SG, DEEP>, grid, 256, 0, stream, d); break;
-        case 2: launch_kernel(name, finish_kernel<BWD, F16, 2, ROWS, SG, DEEP>, grid, 256, 0, stream, d); break;
-        default: launch_kernel(name, finish_kernel<BWD, F16, 4, ROWS, SG, DEEP>, grid, 256, 0, stream, d); break;
-    }
+    if (d.r == 0) launch_kernel(name, finish_kernel<BWD, F16, 0, ROWS, SG, DEEP>, grid, 256, 0, stream, d);
+    else if (d.r <= 8) launch_kernel(name, finish_kernel<BWD, F16, 8, ROWS, SG, DEEP>, grid, 256, 0, stream, d);
+    else if (d.r <= 16) launch_kernel(name, finish_kernel<BWD, F16, 16, ROWS, SG, DEEP>, grid, 256, 0, stream, d);
+    else if (d.r <= 32) launch_kernel(name, finish_kernel<BWD, F16, 32, ROWS, SG, DEEP>, grid, 256, 0, stream, d);
+    else launch_kernel(name, finish_kernel<BWD, F16, 64, ROWS, SG, DEEP>, grid, 256, 0, stream, d);
     return hipGetLastError();
 }
 template <int ROWS, int SG, bool DEEP>
