@@ -341,7 +341,7 @@ struct FinishArgs {
 };
 hipError_t launch_finish(const char *name, FinishArgs d, bool backward, bool f16, hipStream_t stream);
 
-// ---- gemm_direct.hip: a few dozen to a few hundred tokens -------------------------
+// ---- gemm_direct.hip: a few dozen to a thousand tokens -------------------------
 struct DirectPlan {
     int rt, tiles_m, tiles_c, chunks, split;   // row tiles of 32 per row block, grid, chunks of 256 of the contraction, slices
     int proj_parts;  // workgroups that share the projection of 16 rows over one slice
@@ -397,10 +397,15 @@ inline DirectPlan direct_plan(int M, int C, int Cout, bool backward, double *us 
 // last two rules it was in 7 % (at most 41 %).  Measured, us a call forward /
 // backward, r = 8: 8192 x 8192, 48 tokens 42 / 43 -> 23 / 26, 128 tokens 42 / 42 -> 30 / 33; 4096 x 4096,
 // 512 tokens 37 / 36 -> 30 / 33; beyond the line 8192 x 22016, 512 tokens: 193 with tiles, 225 direct.
-// Layers under 2^23 weights keep the tile kernels, whose tests choose such sizes; that line is not where the times
-// cross.  Timed below it with the rule alone (188 pairs, 1024 x 1024 to 2048 x 4000, 33 ... 512 tokens, r = 8, us a
-// call with tiles / direct, forward): 2048 x 2048, 64 tokens 24.4 / 15.2, binary16 42.2 / 15.9; 1024 x 1024, 64 tokens 17.3 / 15.0,
-// 512 tokens 17.2 / 17.1.  Over 2^32 weights the kernel's 32-bit offsets would overflow.
+// Layers under 2^23 weights take it by the same estimate where their output is a whole number of its column blocks
+// of 128 (other sizes below that line stay with the tile kernels, for whose tests such sizes were chosen, though the
+// times do not cross there: 1056 x 4104 backward, 100 tokens 31 us with tiles, 18 direct).  A narrow output leaves
+// the projection to few workgroups: 3.2 us for each turn after the first (1024 x 256 backward, 464 tokens, r = 16:
+// 16 us with tiles, 24 direct).  Over 276 timed pairs (17 ... 1024 tokens, 256 to 22016 wide, both conventions, r = 0 to 64)
+// the choice is 0.7 % slower than the quicker way on average and 17 % quicker than tiles alone, us a call with tiles / direct:
+// 3840 x 1024, 30 tokens 29 / 13; 2560 x 2176 binary16, 35 tokens 31 / 15; 2304 x 2304, 58 tokens 30 / 15; 512 x 11136
+// backward, 143 tokens 47 / 23; 21248 x 256, 230 tokens, r = 0 55 / 20; 1024 x 1024, 64 tokens 17.3 / 15.0.
+// Over 2^32 weights the kernel's 32-bit offsets would overflow.
 bool direct_wins(int K, int N, int M, int r, bool backward, bool f16);
 double gemm_tile_us(int M, int C, int Cout, bool f16);      // gemm_tile.hip: estimated time of the cheapest tile kernel
 hipError_t launch_direct(const SmallArgs &a, bool backward, hipStream_t stream);

@@ -31,6 +31,13 @@ SHAPES = [
     (3, 8224, 2624, 20, 8, 32),         # one row tile: a shape that no streaming kernel takes
     (4, 4096, 2104, 7, 33, 128),        # a handful of tokens that the backward streaming kernel does not take
     (3, 288, 32768, 40, 8, 288),        # an output of little more than two column blocks (backward only)
+    # under 2^23 weights, an output of whole column blocks in both directions
+    (3, 1152, 2048, 64, 8, 128),
+    (4, 2048, 1024, 33, 16, 32),
+    (2, 1536, 4224, 150, 3, 64),
+    (3, 3840, 896, 5, 8, 32),           # a handful of tokens, groups of 32 at three bits: no streaming kernel
+    (2, 2048, 2176, 257, 33, 2048),     # three row blocks, one group per row
+    (4, 3200, 2560, 20, 0, 128),        # no adapter, a weight too small for two streaming passes
 ]
 
 
@@ -160,6 +167,13 @@ def test_second_launch_adds_slices_and_adapter(bits, K, N, M, r, group, conv):
     ("f16", "fwd", 6656, 17920, 407, 8, False),
     ("bf16", "fwd", 22016, 8192, 600, 8, True),
     ("bf16", "fwd", 6656, 6656, 777, 8, True),
+    # under 2^23 weights: by the estimate where the output is a whole number of column blocks
+    ("bf16", "fwd", 3840, 1024, 40, 8, True),
+    ("f16", "fwd", 2560, 2176, 35, 8, True),
+    ("bf16", "bwd", 512, 11136, 143, 8, True),
+    ("bf16", "fwd", 4096, 1064, 100, 8, False),
+    ("bf16", "bwd", 1024, 256, 464, 16, False),     # few workgroups share the projection
+    ("bf16", "fwd", 256, 1024, 64, 8, False),       # a contraction of one chunk
 ])
 def test_runs_where_it_is_the_quicker_way(conv, direction, K, N, M, r, direct):
     cfg = synth.LayerConfig("t", K, N, 3, 128, M, r)
