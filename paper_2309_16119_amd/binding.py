@@ -112,6 +112,18 @@ _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (lambda in
 _current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
 
 
+# The same calls in C++ (csrc/marshal.cpp) for plain contiguous GPU tensors, which it answers in half the time;
+# it returns None for everything else, and the code below, which defines the checks and the errors, does the call.
+# A torch build that it was not compiled for goes through Python for every call.
+try:
+    from . import _marshal
+except ImportError:
+    _marshal = None
+if _marshal is not None:
+    _marshal.use(*(ctypes.cast(getattr(lib, "modulora_" + kind + name), ctypes.c_void_p).value
+                   for kind in ("", "f16_") for name in ("fwd", "bwd_input", "bwd_lora", "workspace_bytes")))
+
+
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:
     if t is None:
         return None
@@ -156,7 +168,14 @@ class QWeight:
         return self.qweight.device
 
 
-_workspaces: dict = {}
+class _Held(dict):
+    def clear(self):
+        super().clear()
+        if _marshal is not None:
+            _marshal.forget_workspaces()
+
+
+_workspaces = _Held()        # without _marshal, which keeps its own
 
 
 def _workspace(device, nbytes: int) -> Optional[torch.Tensor]:
@@ -172,6 +191,8 @@ def _workspace(device, nbytes: int) -> Optional[torch.Tensor]:
     if device.type != "cuda" or index is None:
         index = torch.cuda.current_stream(device).device_index      # refuses what is not a GPU
     key = (index, _raw_stream(index))
+    if _marshal is not None:
+        return _marshal.workspace(index, key[1], nbytes)
     held = _workspaces.get(key)
     if held is None:
         held = _workspaces.setdefault(key, [])
@@ -189,6 +210,13 @@ def reserve_workspace(device, nbytes: int) -> None:
 def _check(status: int, where: str):
     if status != OK:
         raise ModuloraError(status, where)
+
+
+def _answer(got, where: str):
+    """What a call of _marshal returned: its results, or a status to be named."""
+    if got.__class__ is not tuple:
+        _check(got, where)
+    return got
 
 
 # ----------------------------------------------------------------------------- entry points
@@ -214,6 +242,10 @@ def modulora_fwd(w: QWeight, X: torch.Tensor, A: Optional[torch.Tensor], B: Opti
                  lora_scale: float, Y: Optional[torch.Tensor] = None, XA: Optional[torch.Tensor] = None,
                  want_XA: bool = True):
     """Y = X What^T + lora_scale (X A) B.  Returns (Y bf16 [M][d_out], XA fp32 [M][r] or None)."""
+    if _marshal is not None and Y is None and XA is None and w.__class__ is QWeight:
+        got = _marshal.product(False, False, w, X, A, B, lora_scale, want_XA)
+        if got is not None:
+            return _answer(got, "modulora_fwd")
     assert X.dtype == torch.bfloat16 and X.dim() == 2 and X.shape[1] == w.d_in
     M = X.shape[0]
     r = 0 if A is None else A.shape[1]
@@ -253,6 +285,10 @@ def modulora_bwd_input(w: QWeight, dY: torch.Tensor, A: Optional[torch.Tensor], 
                        lora_scale: float, dX: Optional[torch.Tensor] = None,
                        dYBt: Optional[torch.Tensor] = None, want_dYBt: bool = True):
     """dX = dY What + lora_scale (dY B^T) A^T.  Returns (dX bf16 [M][d_in], dYBt fp32 [M][r] or None)."""
+    if _marshal is not None and dX is None and dYBt is None and w.__class__ is QWeight:
+        got = _marshal.product(False, True, w, dY, A, B, lora_scale, want_dYBt)
+        if got is not None:
+            return _answer(got, "modulora_bwd_input")
     assert dY.dtype == torch.bfloat16 and dY.dim() == 2 and dY.shape[1] == w.d_out
     M = dY.shape[0]
     r = 0 if A is None else A.shape[1]
@@ -276,6 +312,10 @@ def modulora_bwd_lora(X: torch.Tensor, dY: torch.Tensor, A: torch.Tensor, B: tor
                       dA: Optional[torch.Tensor] = None, dB: Optional[torch.Tensor] = None,
                       accumulate: bool = False):
     """dA = s X^T (dY B^T), dB = s (X A)^T dY.  Returns (dA fp32 [d_in][r], dB fp32 [r][d_out])."""
+    if _marshal is not None and dA is None and dB is None and not accumulate:
+        got = _marshal.gradients(False, X, dY, A, B, lora_scale, XA, dYBt)
+        if got is not None:
+            return _answer(got, "modulora_bwd_lora")
     M, d_in = X.shape
     d_out = dY.shape[1]
     r = A.shape[1]
@@ -342,6 +382,10 @@ def modulora_f16_dequant(w: QWeightF16, out: Optional[torch.Tensor] = None) -> t
 
 
 def _f16_call(fn, name, w: QWeightF16, act: torch.Tensor, width_in: int, width_out: int, A, B, lora_scale, out, P, want_P):
+    if _marshal is not None and out is None and P is None and w.__class__ is QWeightF16:
+        got = _marshal.product(True, fn is lib.modulora_f16_bwd_input, w, act, A, B, lora_scale, want_P)
+        if got is not None:
+            return _answer(got, name)
     assert act.dtype == torch.float16 and act.dim() == 2 and act.shape[1] == width_in
     M = act.shape[0]
     r = 0 if A is None else A.shape[1]
@@ -375,6 +419,10 @@ def modulora_f16_bwd_lora(X: torch.Tensor, dY: torch.Tensor, A: torch.Tensor, B:
                           XA: Optional[torch.Tensor] = None, dYBt: Optional[torch.Tensor] = None,
                           dA: Optional[torch.Tensor] = None, dB: Optional[torch.Tensor] = None, accumulate: bool = False):
     """dA = s X^T (dY B^T), dB = s (X A)^T dY from float16 X, dY."""
+    if _marshal is not None and dA is None and dB is None and not accumulate:
+        got = _marshal.gradients(True, X, dY, A, B, lora_scale, XA, dYBt)
+        if got is not None:
+            return _answer(got, "modulora_f16_bwd_lora")
     M, d_in = X.shape
     d_out = dY.shape[1]
     r = A.shape[1]

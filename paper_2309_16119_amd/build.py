@@ -1,4 +1,4 @@
-"""Build libmodulora.so (HIP, gfx950 only) in-tree with hipcc.
+"""Build libmodulora.so (HIP, gfx950 only) and the host-side module _marshal.so in-tree with hipcc.
 
     python -m paper_2309_16119_amd.build          # compile every source, link
 
@@ -7,9 +7,11 @@ tree; nothing is installed into site-packages and there is no JIT cache.
 """
 from __future__ import annotations
 
+import importlib.util
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
@@ -17,6 +19,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libmodulora.so")
+MARSHAL = os.path.join(PKG, "_marshal.so")
 
 SOURCES = ["api.hip", "dequant_kernel.hip", "gemm_tile.hip", "gemm_big.hip", "gemm_mid.hip", "gemm_direct.hip", "finish.hip", "lora_kernels.hip", "smallm.hip", "optim.hip", "quantize.hip", "f16_path.hip", "bench_hooks.hip"]
 
@@ -45,12 +48,30 @@ def _compile(src: str, extra: list[str]) -> str:
     return obj
 
 
+def _build_marshal() -> None:
+    """The module that hands tensors to the library: host code against torch's headers."""
+    torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
+    inc = [os.path.join(ROOT, "include"), "/opt/rocm/include", os.path.join(torch_dir, "include"),
+           os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"]]
+    libs = os.path.join(torch_dir, "lib")
+    tmp = MARSHAL + ".tmp.%d" % os.getpid()
+    cmd = [_hipcc(), "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           *("-I" + d for d in inc), os.path.join(CSRC, "marshal.cpp"), "-o", tmp, "-L" + libs, "-ltorch_python", "-ltorch", "-ltorch_cpu",
+           "-lc10", "-lc10_hip"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("hipcc failed for marshal.cpp:\n%s\n%s" % (res.stdout, res.stderr))
+    os.replace(tmp, MARSHAL)
+
+
 def build_library(extra_flags: list[str] | None = None, verbose: bool = False) -> str:
-    """Compile every HIP source for gfx950 and link the shared library.  Always rebuilds."""
+    """Compile every HIP source for gfx950, link the shared library and build the host module.  Always rebuilds."""
     os.makedirs(OBJ, exist_ok=True)
     extra = list(extra_flags or [])
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=8) as ex:
+        marshal = ex.submit(_build_marshal)
         objs = list(ex.map(lambda s: _compile(s, extra), SOURCES))
+        marshal.result()
     tmp = LIB + ".tmp.%d" % os.getpid()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]
     res = subprocess.run(cmd, capture_output=True, text=True)

@@ -74,7 +74,13 @@ class ModuLoRALinear(torch.nn.Module):
             self.register_parameter("B", None)
 
     def forward(self, x: torch.Tensor) -> torch.Tensor:
-        return LPLoRAFunction.apply(x, self.A, self.B, self.w, self.lora_scale)
+        A, B, w = self.A, self.B, self.w
+        if b._marshal is not None and w.__class__ in (b.QWeight, b.QWeightF16):
+            # the same function in C++, for plain tensors outside of torch's transforms; None: not one of those
+            y = b._marshal.layer(w.__class__ is b.QWeightF16, x, A, B, w, self.lora_scale)
+            if y is not None:
+                return y
+        return LPLoRAFunction.apply(x, A, B, w, self.lora_scale)
 
     def reserve_workspace(self, tokens: int) -> None:
         """Size the binding's cached scratch buffer of the current stream for `tokens` rows now, so
