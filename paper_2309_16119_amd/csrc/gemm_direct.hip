@@ -536,28 +536,31 @@ hipError_t launch_direct_any(const DirectDev &d, int rt, hipStream_t stream) {
 }
 }  // namespace
 
+double direct_us(const DirectPlan &p, int M, int Cout, int r, bool backward, bool f16) {
+    const double chunk[2][4] = {{1.06, 1.23, 1.42, 1.67}, {1.34, 1.53, 1.71, 1.97}};
+    const double rounds = (double)(((long)p.tiles_m * p.tiles_c * p.split + 255) / 256);
+    double us = 4.5 + rounds * ((p.chunks + p.split - 1) / p.split * chunk[backward][p.rt - 1] + (p.rt == 1 ? 3.0 : 4.9)) +
+                1.85e-6 * p.split * M * (double)Cout;
+    if (r > 0) {
+        // turns of the projection of 16 rows that the busiest workgroup takes (8 steps of 32 to a chunk, 32 to a turn)
+        const int steps = ((p.chunks + p.split - 1) / p.split * 8 + p.proj_parts - 1) / p.proj_parts;
+        const double turns = (double)((2 * p.rt * p.proj_parts + p.tiles_c - 1) / p.tiles_c * ((steps + 31) / 32));
+        const double more = (double)((r - 1) / 16), outputs = (double)((M + 31) / 32) * ((Cout + 63) / 64);
+        us += 2.2 * turns + 1.69 * more * turns + (r > 16 ? 1.55e-4 * (r - 16) * outputs : 0.0);
+        if (f16) us += (0.64 + 0.53 * more) * turns;
+    }
+    return us;
+}
+
 bool direct_wins(int K, int N, int M, int r, bool backward, bool f16) {
     const size_t elements = (size_t)K * N;
     const int C = backward ? N : K, Cout = backward ? K : N;
-    const bool small = elements < ((size_t)1 << 23);
-    if (M > 1024 || elements > ((size_t)1 << 32) || (small && Cout % direct::CT != 0)) return false;
-    double us;
-    const DirectPlan p = direct_plan(M, C, Cout, backward, &us);
-    double tiles = gemm_tile_us(M, C, Cout, false) + (r > 0 ? 9.0 : 0.0);
-    const long rounds = ((long)p.tiles_m * p.tiles_c * p.split + 255) / 256;
-    double margin = rounds == 1 ? 1.1 : (M <= 128 ? 1.2 : 1.3);
-    if (rounds >= 3 && M > 256 && us > 110.0 && big_plan(M, C, Cout).mt == 256) margin = 1.5;
-    // turns of the projection of 16 rows that the busiest workgroup takes (8 steps of 32 to a chunk, 32 to a turn)
-    const int steps = ((p.chunks + p.split - 1) / p.split * 8 + p.proj_parts - 1) / p.proj_parts;
-    const int turns = (2 * p.rt * p.proj_parts + p.tiles_c - 1) / p.tiles_c * ((steps + 31) / 32);
-    if (small && r > 0) us += 3.2 * (turns - 1);
-    if (r > 16 && !f16) {
-        const auto trips = [M](int rank) { return ((M < 32 ? M : 32) * rank + 255) / 256; };
-        const double more = (double)((r - 1) / 16), outputs = (double)((M + 31) / 32) * ((Cout + 63) / 64);
-        us += 3.2 * more * turns + 0.5 * (trips(r) - trips(16)) * ((p.split * p.proj_parts + 7) / 8) + 1.6e-4 * (r - 16) * outputs;
-        tiles += more * (2.0 + 4.0 * (C < 8192 ? C : 8192) / 8192) + (backward ? 4.5e-8 : 1e-8) * (r - 16) * (double)C * M;
-    }
-    return us * margin < tiles;
+    if (M > 1024 || elements > ((size_t)1 << 32)) return false;
+    if (elements < ((size_t)1 << 23) && Cout % (backward ? direct::CT : 16) != 0) return false;
+    const DirectPlan p = direct_plan(M, C, Cout, backward);
+    double margin = r <= 16 || f16 ? 1.0 : (backward && M <= 512 ? 1.13 : 1.02);
+    if (M > 128 && big_half_rows(M) && (long)p.tiles_m * p.tiles_c * p.split > 256) margin = 1.15;
+    return direct_us(p, M, Cout, r, backward, f16) * margin < gemm_tile_us(M, C, Cout, r, f16) + lora_down_us(M, C, r, backward);
 }
 
 hipError_t launch_direct(const SmallArgs &a, bool backward, hipStream_t stream) {

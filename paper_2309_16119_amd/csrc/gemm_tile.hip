@@ -653,46 +653,50 @@ static TilePick forced_pick() {
     return (TilePick)cached;
 }
 
-// Estimated time of the whole grid in microseconds, from measured times of one 64-deep
-// contraction step of each variant: alone on a CU (t1) and sharing it with a second
-// workgroup (t2), times how often the 256 CUs (x occupancy) are refilled.  The 256 x 256
-// kernel cuts the tiles of its last, partial round into slices of the contraction
-// (BigPlan); that round then costs 1/split of a round plus the traffic of the partial
-// tiles (written once, read once) and one more launch.
+// Estimated time of the whole grid in microseconds.  Every kernel takes `fixed` for its start and end; for each full
+// round of 256 x occ workgroups `step` per 64 elements of the contraction and `round`; for the last, partial round
+// `last`, and a step of `last_step`, `last_shared` more where some unit holds two workgroups, and `last_load` times the
+// share of the chip that is busy (the clock and the memory are shared).  The adapter's segments lengthen the
+// contraction.  Least-squares fits (6 to 10 % rms) to some 2000 to 3200 timed launches of each kernel, of the sweep
+// that big_plan_us() describes; over 700 other layers the pick is on average 0.9 % slower than the quickest tile
+// kernel, and 4 % with a table of steps alone, us with that table / now: 320 x 5312, 1212 tokens, r = 8 backward
+// 42 / 30; 256 x 10176 binary16, 270 tokens 20 / 15; 7168 x 1664, 821 tokens backward 51 / 42; 15744 x 256, 3625 tokens
+// 56 / 46.
 // (any token count: a 32-row tile kernel for M <= 32 measured 1.2 us per step, more than any of these)
 // `tuned_only`: of the 256 x 256 and the 128 x 64 kernel, the two that exist for binary16.
-static TilePick cheapest_pick(int M, int C, int Cout, bool tuned_only, double *us) {
-    struct Variant { TilePick pick; int mt, ct, occ; double t1, t2; };
-    const Variant vs[5] = {{PICK_MID, 256, 128, 2, 1.46, 1.95},
-                           {PICK_M128, 128, 128, 2, 0.97, 1.40},
-                           {PICK_M64, 64, 128, 2, 0.75, 1.10},
-                           {PICK_M64K, 64, 128, 1, 0.62, 0.62},
-                           {PICK_T128S, 128, 64, 1, 0.48, 0.48}};   // gemm_mid.hip
-    const double steps = (double)C / 64.0;
+static TilePick cheapest_pick(int M, int C, int Cout, int extension, bool tuned_only, double *us) {
+    struct Variant { TilePick pick; int mt, ct, occ; double fixed, step, round, last, last_step, last_shared, last_load; };
+    const Variant vs[5] = {{PICK_MID, 256, 128, 2, 3.27, 2.03, 5.68, 1.90, 1.305, 0.402, 0.365},
+                           {PICK_M128, 128, 128, 2, 3.68, 1.19, 3.32, 0.0, 0.855, 0.307, 0.209},
+                           {PICK_M64, 64, 128, 2, 3.17, 0.877, 2.48, 0.0, 0.680, 0.251, 0.134},
+                           {PICK_M64K, 64, 128, 1, 1.85, 0.512, 2.97, 1.96, 0.489, 0.0, 0.0734},
+                           {PICK_T128S, 128, 64, 1, 1.70, 0.372, 4.11, 3.61, 0.300, 0.0, 0.0825}};   // gemm_mid.hip
+    const int more = (extension + 63) / 64, steps = (C + 63) / 64 + more;
     const BigPlan bp = big_plan(M, C, Cout);
-    double best = ((double)(bp.full / 256) + (bp.tail ? 1.0 / bp.split : 0.0)) * (bp.mt == 128 ? 1.0 : 1.83) * steps;
-    if (bp.split > 1) best += (bp.mt == 128 ? 12.0 : 9.0) + (double)bp.partial_bytes() / 4.0e6;
+    double best = big_plan_us(bp, C, more) * (bp.mt == 128 ? big_128_margin(M) : 1.0);
     TilePick pick = PICK_BIG;
     for (const Variant &v : vs) {
         if (tuned_only && v.pick != PICK_T128S) continue;
-        const long tiles = (long)((M + v.mt - 1) / v.mt) * ((Cout + v.ct - 1) / v.ct);
-        const double cost = steps * (tiles <= 256 ? v.t1 : (double)((tiles + 256 * v.occ - 1) / (256 * v.occ)) * v.t2);
+        const long tiles = (long)((M + v.mt - 1) / v.mt) * ((Cout + v.ct - 1) / v.ct), per_round = 256L * v.occ;
+        const long rest = tiles % per_round;
+        double cost = v.fixed + (double)(tiles / per_round) * (v.step * steps + v.round);
+        if (rest > 0) cost += v.last + steps * (v.last_step + (rest > 256 ? v.last_shared : 0.0) + v.last_load * ((double)rest / (double)per_round));
         if (cost < best) { best = cost; pick = v.pick; }
     }
     if (us) *us = best;
     return pick;
 }
-double gemm_tile_us(int M, int C, int Cout, bool f16) {
+double gemm_tile_us(int M, int C, int Cout, int r, bool f16) {
     if (forced_pick() != PICK_AUTO) return 0.0;      // a forced tile kernel is always the cheapest way
     double us;
-    cheapest_pick(M, C, Cout, f16, &us);
+    cheapest_pick(M, C, Cout, r > 0 ? lora_ext_len(r, f16) : 0, f16, &us);
     return us;
 }
 
 template <int BITS, bool BWD>
 static hipError_t launch_bits_dir(const GemmArgs &a, hipStream_t stream) {
     TilePick pick = forced_pick();
-    if (pick == PICK_AUTO) pick = cheapest_pick(a.M, BWD ? a.w.N : a.w.K, BWD ? a.w.K : a.w.N, false, nullptr);
+    if (pick == PICK_AUTO) pick = cheapest_pick(a.M, BWD ? a.w.N : a.w.K, BWD ? a.w.K : a.w.N, a.RE, false, nullptr);
     switch (pick) {
         case PICK_MID:
             return launch_variant<BITS, BWD, 256, 256, 128, 128, 64, 2, 0>(
@@ -715,7 +719,7 @@ static hipError_t launch_bits_dir(const GemmArgs &a, hipStream_t stream) {
 
 hipError_t launch_gemm_f16(const GemmArgs &a, hipStream_t stream) {
     const int C = a.backward ? a.w.N : a.w.K, Cout = a.backward ? a.w.K : a.w.N;
-    return cheapest_pick(a.M, C, Cout, true, nullptr) == PICK_T128S ? launch_gemm_mid_f16(a, stream) : launch_gemm_big_f16(a, stream);
+    return cheapest_pick(a.M, C, Cout, a.RE, true, nullptr) == PICK_T128S ? launch_gemm_mid_f16(a, stream) : launch_gemm_big_f16(a, stream);
 }
 
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t stream) {

@@ -97,18 +97,48 @@ inline BigPlan big_plan_rows(int M, int C, int Cout, int mt) {
     }
     return p;
 }
-// 128-row tiles where the last block of 256 rows would be at most half full and the row blocks
-// are few: a step of the 128-row kernel takes 0.55 of a 256-row step, so an odd number n of
-// 128-row blocks costs 0.55 n against (n + 1) / 2.
-inline BigPlan big_plan(int M, int C, int Cout) {
-    const int n128 = (M + 127) / 128;
-    const bool half_rows = (n128 & 1) != 0 && n128 <= 5;
-    return big_plan_rows(M, C, Cout, half_rows ? 128 : 256);
+// Estimated time of a plan in microseconds, fix-up launch included: `fixed`, for each round of 256 whole tiles
+// `step` per 64 elements of the contraction (extension_steps: those of the adapter's segments) and `round`, for the
+// last round `last` and a step that grows with the workgroups in flight, then the fix-up and its partial tiles.
+// Least-squares fit (7 % rms) to 9900 timed launches of both row heights, sliced and whole: 1650 layers of 256 to
+// 22016 wide, 2 ... 4096 tokens, r = 0 to 64, all bit widths, both directions and conventions.
+inline double big_plan_us(const BigPlan &p, int C, int extension_steps) {
+    struct Cost { double fixed, step, round, last, last_step, last_load, fixup, fixup_mb; };
+    const Cost k = p.mt == 128 ? Cost{2.46, 0.988, 5.58, 3.34, 0.779, 0.225, 3.86, 0.229}
+                               : Cost{8.44, 1.60, 7.29, 0.0, 1.04, 0.489, 3.08, 0.195};
+    const int steps = (C + 63) / 64;
+    double us = k.fixed + (double)(p.full / 256) * (k.step * (steps + extension_steps) + k.round);
+    if (p.tail > 0) us += k.last + (k.last_step + k.last_load * (p.tail * p.split / 256.0)) * ((steps + p.split - 1) / p.split + extension_steps);
+    if (p.split > 1) us += k.fixup + k.fixup_mb * 1e-6 * (double)p.partial_bytes();
+    return us;
 }
-// Scratch for the partial tiles of either direction.
+// Rows of a tile: 128 where the last block of 256 rows would be at most half full and the row blocks are few (a
+// step of the 128-row kernel takes 0.55 of a 256-row step, so an odd number n of 128-row blocks costs 0.55 n against
+// (n + 1) / 2); beyond that where 128 rows are estimated to take less than 1 / 1.1 of the time (the estimates
+// spread that much).  Measured with 256 / 128 rows, us: 11648 x 256 binary16, 1061 tokens 56 / 49; 7168 x 1664, 821 tokens
+// backward 51 / 42; 5376 x 640, 1535 tokens 24 / 22; on the other side 4096 x 11008, 2048 tokens 168 / 191, 6656 x
+// 6656, 1024 tokens 93 / 96.
+inline bool big_half_rows(int M) {
+    const int n128 = (M + 127) / 128;
+    return (n128 & 1) != 0 && n128 <= 5;
+}
+inline double big_128_margin(int M) { return big_half_rows(M) ? 1.0 : 1.1; }
+inline BigPlan big_plan(int M, int C, int Cout) {
+    const BigPlan low = big_plan_rows(M, C, Cout, 128);
+    if (big_half_rows(M)) return low;
+    const BigPlan high = big_plan_rows(M, C, Cout, 256);
+    return big_128_margin(M) * big_plan_us(low, C, 0) < big_plan_us(high, C, 0) ? low : high;
+}
+// Scratch for the partial tiles of either direction and either row height: what a caller provides for a number
+// of tokens does not hang on the estimate.
 inline size_t gemm_partial_bytes(int M, int K, int N) {
-    const size_t f = big_plan(M, K, N).partial_bytes(), b = big_plan(M, N, K).partial_bytes();
-    return f > b ? f : b;
+    size_t most = 0;
+    for (int rows = 128; rows <= (M <= 128 ? 128 : 256); rows += 128) {
+        const size_t f = big_plan_rows(M, K, N, rows).partial_bytes(), b = big_plan_rows(M, N, K, rows).partial_bytes();
+        if (f > most) most = f;
+        if (b > most) most = b;
+    }
+    return most;
 }
 
 // ---- lora_kernels.hip ----------------------------------------------------------
@@ -207,6 +237,16 @@ inline DownPlan lora_down_plan(int M, int C, int r) {
     const int longest = (chunks + most - 1) / most;
     p.split = (chunks + longest - 1) / longest;
     return p;
+}
+// Estimated time of the projection's launches in microseconds (17 % rms over 3200 timed calls): a launch, a second
+// one behind a split, the activations read, and the steps of 32 that a wave of the row kernel takes in turn.
+inline double lora_down_us(int M, int C, int r, bool backward) {
+    if (r <= 0) return 0.0;
+    const DownPlan p = lora_down_plan(M, C, r);
+    const double more = (double)((r + 15) / 16 - 1), million = 1e-6 * M * C;
+    const double steps = p.tiles ? 0.0 : C / 32.0 / (p.split * p.nwaves);
+    return 4.76 + (p.split > 1 ? 3.78 : 0.0) + million * (0.385 + 0.345 * more) + steps * (0.285 + 0.316 * more + (backward ? 0.138 : 0.0)) +
+           0.409 * more;
 }
 inline size_t down_plan_bytes(const DownPlan &p, int M, int r) {
     if (r <= 0 || p.split <= 1) return 0;
@@ -350,14 +390,15 @@ struct DirectPlan {
     static int part_stride(int M, int r) { return (M * r + 3) & ~3; }
     size_t ws_bytes(int M, int Cout, int r) const { return partial_bytes(M, Cout) + (((size_t)split * proj_parts * part_stride(M, r) * 4 + 255) & ~(size_t)255); }
 };
-// The split of the contraction with the smallest estimated time, in microseconds (`us`).  The model and
+// The split of the contraction with the smallest estimated time, in microseconds.  The model and
 // its constants are a least-squares fit (6 % rms) to 1080 timed calls: six layers of 4096 x 4096 to
 // 8192 x 22016, 12 ... 768 tokens, both directions, 1 ... 16 slices; over them the slice count it picks
 // is on average 0.5 % and at most 10 % slower than the best one.  A round of 256 workgroups costs
 // `chunk` per chunk of 256 elements of the longest slice (by row tiles and direction: issue-bound up to
 // 64 rows, matrix cores and issue beyond; backward also transposes) plus its start; the slices' fp32
-// results are written and read once at 4 TB/s; 9.5 is both launches and the sum.
-inline DirectPlan direct_plan(int M, int C, int Cout, bool backward, double *us = nullptr) {
+// results are written and read once at 4 TB/s; 9.5 is both launches and the sum.  (direct_us() is the estimate of a
+// whole call by a later fit to smaller layers too; it is not split differently for them.)
+inline DirectPlan direct_plan(int M, int C, int Cout, bool backward) {
     DirectPlan p;
     p.tiles_m = (M + 127) / 128;
     p.rt = ((M + p.tiles_m - 1) / p.tiles_m + 31) / 32;
@@ -374,40 +415,29 @@ inline DirectPlan direct_plan(int M, int C, int Cout, bool backward, double *us 
                             (double)s * M * Cout * (8.0 / 4.0e6);
         if (cost < best) { best = cost; p.split = s; }
     }
-    if (us) *us = best;
     p.proj_parts = p.tiles_c / (2 * p.rt);
     if (p.proj_parts > 32 / p.split) p.proj_parts = 32 / p.split;
     if (p.proj_parts < 1) p.proj_parts = 1;
     return p;
 }
-// Whether gemm_direct.hip is the quicker way for this shape and direction, by its own estimate against
-// that of the tile kernels (gemm_tile_us()) plus 9 us for their projection launches, where there is an
-// adapter.  The margins are 1.1 where every workgroup runs at once and 1.2 or 1.3 beyond, because many
-// rounds lower the clock.  They are 1.5 for long calls of three rounds and more against whole 256-row tiles,
-// whose steps then take 1.5 us and not the 1.83 of their estimate (6656 x 17920, r = 8: 392 tokens 137 us with
-// tiles, 156 direct; binary16, 407 tokens 147 and 170).
-// In bfloat16 a rank beyond 16 costs the direct kernel more than the tiles.  For each further 16 columns a turn of
-// the projection takes 3.2 us in the product kernel.  The second launch adds the projection's parts in trips of
-// eight loads, 0.5 us each, and multiplies.  The tiles pay 2 ... 6 us per 16 columns, and with the rank's share of the
-// projection, which reads B^T slowly (1024 x 8832 forward, 38 tokens: r = 8 18.2 us with tiles, 16.3 direct, r = 32
-// 18.4 and 21.9, r = 64 23.7 and 31.6).  In binary16 the tiles' epilogue pays for a rank as well: no such term.
-// Over 2295 timed pairs (33 ... 1024 tokens, 2^23 to 2^28 weights, r = 0 to 64, both conventions, wherever the
-// margins 1.1 to 1.3 alone take the direct kernel) the choice is on average 0.5 % (bfloat16) and 0.1 % (binary16)
-// slower than the quicker way.  It is over 3 % slower with the direct kernel in 1.2 % of them (at most 13 %); without the
-// last two rules it was in 7 % (at most 41 %).  Measured, us a call forward /
-// backward, r = 8: 8192 x 8192, 48 tokens 42 / 43 -> 23 / 26, 128 tokens 42 / 42 -> 30 / 33; 4096 x 4096,
-// 512 tokens 37 / 36 -> 30 / 33; beyond the line 8192 x 22016, 512 tokens: 193 with tiles, 225 direct.
-// Layers under 2^23 weights take it by the same estimate where their output is a whole number of its column blocks
-// of 128 (other sizes below that line stay with the tile kernels, for whose tests such sizes were chosen, though the
-// times do not cross there: 1056 x 4104 backward, 100 tokens 31 us with tiles, 18 direct).  A narrow output leaves
-// the projection to few workgroups: 3.2 us for each turn after the first (1024 x 256 backward, 464 tokens, r = 16:
-// 16 us with tiles, 24 direct).  Over 276 timed pairs (17 ... 1024 tokens, 256 to 22016 wide, both conventions, r = 0 to 64)
-// the choice is 0.7 % slower than the quicker way on average and 17 % quicker than tiles alone, us a call with tiles / direct:
-// 3840 x 1024, 30 tokens 29 / 13; 2560 x 2176 binary16, 35 tokens 31 / 15; 2304 x 2304, 58 tokens 30 / 15; 512 x 11136
-// backward, 143 tokens 47 / 23; 21248 x 256, 230 tokens, r = 0 55 / 20; 1024 x 1024, 64 tokens 17.3 / 15.0.
+// Whether gemm_direct.hip is the quicker way for this shape and direction: direct_us() against the cheapest tile
+// kernel's estimate (gemm_tile_us()) and its projection's (lora_down_us()).  All are fits to the same sweep of
+// every kernel over 1600 random layers (256 to 22016 wide, 2 ... 4096 tokens, r = 0 to 64, both conventions); on 400
+// others the choice among all kernels is on average 1.7 % slower than the quickest one (part of it the noise of taking
+// the quickest of eight timings), 4.6 % with the estimates of single steps that it replaces.  Doubtful cases stay
+// with the tiles, by 13 % backward to 512 tokens and 2 % elsewhere for bfloat16 ranks over 16, and by 15 % for
+// several rounds against several 128-row tiles, where the estimates spread by 8 % (9728 x 1536 backward, 288 tokens,
+// r = 32 34 with tiles, 32 direct; 8192 x 22016 backward, 300 tokens 174 and 172).  Measured, us a call with tiles /
+// direct: 8192 x 8192, r = 8, 48 tokens 42 / 23, 128 tokens 42 / 30; 4096 x 4096, 512 tokens 41 / 32; 3328 x 928, 458
+// tokens 32 / 20; 3840 x 1024, 30 tokens 29 / 13; 448 x 3456 binary16 backward, 239 tokens 30 / 21; beyond the line
+// 8192 x 22016, 512 tokens 193 / 225, 768 x 384 binary16, r = 64, 132 tokens 22 / 35, 640 x 3200 backward, 43 tokens 14 / 19.
+// Layers under 2^23 weights take it forward from whole 16-column tiles and backward from whole column blocks of 128
+// (other sizes below that line stay with the tile kernels, for whose tests such sizes were chosen, though the
+// times do not cross there: 1056 x 4104 backward, 100 tokens 31 us with tiles, 18 direct).
 // Over 2^32 weights the kernel's 32-bit offsets would overflow.
+double direct_us(const DirectPlan &p, int M, int Cout, int r, bool backward, bool f16);      // estimated time of a call
 bool direct_wins(int K, int N, int M, int r, bool backward, bool f16);
-double gemm_tile_us(int M, int C, int Cout, bool f16);      // gemm_tile.hip: estimated time of the cheapest tile kernel
+double gemm_tile_us(int M, int C, int Cout, int r, bool f16);      // gemm_tile.hip: estimated time of the cheapest tile kernel
 hipError_t launch_direct(const SmallArgs &a, bool backward, hipStream_t stream);
 
 }  // namespace mlr
