@@ -654,7 +654,7 @@ static TilePick forced_pick() {
 }
 
 // Estimated time of the whole grid in microseconds.  Every kernel takes `fixed` for its start and end; for each full
-// round of 256 x occ workgroups `step` per 64 elements of the contraction and `round`; for the last, partial round
+// round of 256 (or, two to a unit, 512) workgroups `step` per 64 elements of the contraction and `round`; for the last, partial round
 // `last`, and a step of `last_step`, `last_shared` more where some unit holds two workgroups, and `last_load` times the
 // share of the chip that is busy (the clock and the memory are shared).  The adapter's segments lengthen the
 // contraction.  Least-squares fits (6 to 10 % rms) to some 2000 to 3200 timed launches of each kernel, of the sweep
@@ -665,22 +665,23 @@ static TilePick forced_pick() {
 // (any token count: a 32-row tile kernel for M <= 32 measured 1.2 us per step, more than any of these)
 // `tuned_only`: of the 256 x 256 and the 128 x 64 kernel, the two that exist for binary16.
 static TilePick cheapest_pick(int M, int C, int Cout, int extension, bool tuned_only, double *us) {
-    struct Variant { TilePick pick; int mt, ct, occ; double fixed, step, round, last, last_step, last_shared, last_load; };
-    const Variant vs[5] = {{PICK_MID, 256, 128, 2, 3.27, 2.03, 5.68, 1.90, 1.305, 0.402, 0.365},
-                           {PICK_M128, 128, 128, 2, 3.68, 1.19, 3.32, 0.0, 0.855, 0.307, 0.209},
-                           {PICK_M64, 64, 128, 2, 3.17, 0.877, 2.48, 0.0, 0.680, 0.251, 0.134},
-                           {PICK_M64K, 64, 128, 1, 1.85, 0.512, 2.97, 1.96, 0.489, 0.0, 0.0734},
-                           {PICK_T128S, 128, 64, 1, 1.70, 0.372, 4.11, 3.61, 0.300, 0.0, 0.0825}};   // gemm_mid.hip
+    // rows and columns of a tile and workgroups of a round as powers of two: a call makes this choice, so no divisions
+    struct Variant { TilePick pick; int mt, ct, round_of; double fixed, step, round, last, last_step, last_shared, last_load; };
+    static constexpr Variant vs[5] = {{PICK_MID, 8, 7, 9, 3.27, 2.03, 5.68, 1.90, 1.305, 0.402, 0.365},
+                                      {PICK_M128, 7, 7, 9, 3.68, 1.19, 3.32, 0.0, 0.855, 0.307, 0.209},
+                                      {PICK_M64, 6, 7, 9, 3.17, 0.877, 2.48, 0.0, 0.680, 0.251, 0.134},
+                                      {PICK_M64K, 6, 7, 8, 1.85, 0.512, 2.97, 1.96, 0.489, 0.0, 0.0734},
+                                      {PICK_T128S, 7, 6, 8, 1.70, 0.372, 4.11, 3.61, 0.300, 0.0, 0.0825}};   // gemm_mid.hip
     const int more = (extension + 63) / 64, steps = (C + 63) / 64 + more;
     const BigPlan bp = big_plan(M, C, Cout);
     double best = big_plan_us(bp, C, more) * (bp.mt == 128 ? big_128_margin(M) : 1.0);
     TilePick pick = PICK_BIG;
     for (const Variant &v : vs) {
         if (tuned_only && v.pick != PICK_T128S) continue;
-        const long tiles = (long)((M + v.mt - 1) / v.mt) * ((Cout + v.ct - 1) / v.ct), per_round = 256L * v.occ;
-        const long rest = tiles % per_round;
-        double cost = v.fixed + (double)(tiles / per_round) * (v.step * steps + v.round);
-        if (rest > 0) cost += v.last + steps * (v.last_step + (rest > 256 ? v.last_shared : 0.0) + v.last_load * ((double)rest / (double)per_round));
+        const uint64_t tiles = (uint64_t)((M + (1 << v.mt) - 1) >> v.mt) * (uint64_t)((Cout + (1 << v.ct) - 1) >> v.ct);
+        const uint32_t rest = (uint32_t)tiles & ((1u << v.round_of) - 1u);
+        double cost = v.fixed + (double)(tiles >> v.round_of) * (v.step * steps + v.round);
+        if (rest > 0) cost += v.last + steps * (v.last_step + (rest > 256 ? v.last_shared : 0.0) + v.last_load * (rest * (v.round_of == 9 ? 1.0 / 512 : 1.0 / 256)));
         if (cost < best) { best = cost; pick = v.pick; }
     }
     if (us) *us = best;

@@ -84,8 +84,8 @@ struct BigPlan {
 inline BigPlan big_plan_rows(int M, int C, int Cout, int mt) {
     BigPlan p;
     p.mt = mt;
-    const long tiles = (long)((M + mt - 1) / mt) * ((Cout + 255) / 256);
-    p.full = (int)(tiles / 256 * 256);
+    const long tiles = (long)((M + mt - 1) >> (mt == 128 ? 7 : 8)) * ((Cout + 255) >> 8);
+    p.full = (int)(tiles & ~255L);
     p.tail = (int)(tiles - p.full);
     p.split = 1;
     if (p.tail > 0) {
@@ -409,8 +409,10 @@ inline DirectPlan direct_plan(int M, int C, int Cout, bool backward) {
     const long tiles = (long)p.tiles_m * p.tiles_c;
     p.split = 1;
     double best = 1e30;
-    for (int s = 1; s <= 16 && (s == 1 || p.chunks / s >= 2); ++s) {
-        const double rounds = (double)((tiles * s + 255) / 256);
+#pragma clang loop unroll(full)      // divisions by constants: a call makes this choice
+    for (int s = 1; s <= 16; ++s) {
+        if (s > 1 && p.chunks < 2 * s) break;
+        const double rounds = (double)((tiles * s + 255) >> 8);
         const double cost = 9.5 + rounds * ((p.chunks + s - 1) / s * chunk[backward][p.rt - 1] + start[p.rt - 1]) +
                             (double)s * M * Cout * (8.0 / 4.0e6);
         if (cost < best) { best = cost; p.split = s; }
