@@ -66,14 +66,21 @@ struct WsLayout {
     size_t act_ext, w_ext, p0, p1, gpart, gemm_part, dpart, total;
     size_t gemm_part_bytes;      // size of the region at gemm_part
     size_t dpart_bytes;          // size of the region at dpart
-    bool direct_fwd, direct_bwd; // gemm_direct.hip takes this direction unless a streaming kernel does
+    mlr::Route fwd, bwd;         // what takes this direction unless a streaming kernel does
 };
 
-// Bytes that gemm_direct.hip needs at the start of the workspace for the directions it takes.
-size_t direct_bytes(int32_t K, int32_t N, int32_t M, int32_t r, bool fwd, bool bwd) {
-    const size_t f = fwd ? mlr::direct_plan(M, K, N, false).ws_bytes(M, N, r) : 0;
-    const size_t b = bwd ? mlr::direct_plan(M, N, K, true).ws_bytes(M, K, r) : 0;
+// Bytes at the start of the workspace for the directions that leave their slices' results to a second launch.
+size_t route_bytes(mlr::Route route, int32_t K, int32_t N, int32_t M, int32_t r, bool backward, bool f16) {
+    const int32_t C = backward ? N : K, Cout = backward ? K : N;
+    if (route == mlr::ROUTE_DIRECT) return mlr::direct_plan(M, C, Cout, backward).ws_bytes(M, Cout, r);
+    return route == mlr::ROUTE_SLICED ? mlr::sliced_plan(M, C, Cout, r, f16).ws_bytes(M, Cout, r) : 0;
+}
+size_t routes_bytes(mlr::Route fwd, mlr::Route bwd, int32_t K, int32_t N, int32_t M, int32_t r, bool f16) {
+    const size_t f = route_bytes(fwd, K, N, M, r, false, f16), b = route_bytes(bwd, K, N, M, r, true, f16);
     return f > b ? f : b;
+}
+hipError_t launch_route(mlr::Route route, const mlr::SmallArgs &sa, bool backward, hipStream_t st) {
+    return route == mlr::ROUTE_DIRECT ? mlr::launch_direct(sa, backward, st) : mlr::launch_sliced(sa, backward, st);
 }
 WsLayout ws_layout(int32_t K, int32_t N, int32_t M, int32_t r) {
     WsLayout l{};
@@ -83,9 +90,9 @@ WsLayout ws_layout(int32_t K, int32_t N, int32_t M, int32_t r) {
     // fp32 partial tiles of the split contraction of the 256 x 256 kernel (also when r == 0)
     const size_t part = align256(mlr::gemm_partial_bytes(M, K, N));
     l.gemm_part_bytes = part;
-    l.direct_fwd = mlr::direct_wins(K, N, M, r, false, false);
-    l.direct_bwd = mlr::direct_wins(K, N, M, r, true, false);
-    const size_t dir = direct_bytes(K, N, M, r, l.direct_fwd, l.direct_bwd);
+    l.fwd = mlr::product_route(K, N, M, r, false, false);
+    l.bwd = mlr::product_route(K, N, M, r, true, false);
+    const size_t dir = routes_bytes(l.fwd, l.bwd, K, N, M, r, false);
     if (r <= 0) {
         l.gemm_part = 0;
         l.total = small > part ? small : part;
@@ -119,10 +126,11 @@ WsLayout ws_layout_fwd(const mlr::LayerView &v, int32_t M, int32_t r, size_t ava
         l.total = mlr::smallm_fwd_ws_bytes(v, r);
         return l;
     }
-    if (mlr::direct_wins(v.K, v.N, M, r, false, false)) {
-        l.total = direct_bytes(v.K, v.N, M, r, true, false);
-        l.direct_fwd = l.total <= avail_direct;
-        if (l.direct_fwd) return l;
+    l.fwd = mlr::product_route(v.K, v.N, M, r, false, false);
+    if (l.fwd != mlr::ROUTE_TILES) {
+        l.total = route_bytes(l.fwd, v.K, v.N, M, r, false, false);
+        if (l.total <= avail_direct) return l;
+        l.fwd = mlr::ROUTE_TILES;
     }
     size_t off = 0;
     const size_t part = align256(mlr::big_plan(M, v.K, v.N).partial_bytes());
@@ -167,13 +175,13 @@ int check_fwd_args(const modulora_qweight *w, const uint16_t *X, int32_t M, cons
 int run_fwd(const modulora_qweight *w, const uint16_t *X, int32_t M, const float *A, const float *B, int32_t r,
             float lora_scale, uint16_t *Y, float *XA, char *ws, const WsLayout &l, hipStream_t st) {
     const bool streams = mlr::smallm_fwd_supported(view_of(w), M);
-    if (streams || l.direct_fwd) {
+    if (streams || l.fwd != mlr::ROUTE_TILES) {
         mlr::SmallArgs sa{};
         sa.w = view_of(w);
         sa.act = X; sa.M = M; sa.out = Y;
         sa.A = A; sa.B = B; sa.r = r; sa.lora_scale = lora_scale;
         sa.P_out = XA; sa.ws = ws;
-        return hip_status(streams ? mlr::launch_smallm_fwd(sa, st) : mlr::launch_direct(sa, false, st));
+        return hip_status(streams ? mlr::launch_smallm_fwd(sa, st) : launch_route(l.fwd, sa, false, st));
     }
     mlr::GemmArgs g{};
     g.w = view_of(w);
@@ -314,7 +322,7 @@ int modulora_fwd_static(const modulora_qweight *w, const uint16_t *X, int32_t M,
     int s = check_fwd_args(w, X, M, A, B, r, Y, XA);
     if (s != MODULORA_OK) return s;
     const WsLayout l = ws_layout_fwd(view_of(w), M, r, kStaticScratchBytes, kStaticDirectBytes);
-    if (!l.direct_fwd && l.total > kStaticScratchBytes) return MODULORA_ERR_WORKSPACE;     // beyond the library's scratch
+    if (l.fwd == mlr::ROUTE_TILES && l.total > kStaticScratchBytes) return MODULORA_ERR_WORKSPACE;     // beyond the library's scratch
     char *ws = nullptr;
     if ((s = static_scratch(&ws)) != MODULORA_OK) return s;
     return run_fwd(w, X, M, A, B, r, lora_scale, Y, XA, ws, l, static_cast<hipStream_t>(stream));
@@ -335,13 +343,13 @@ int modulora_bwd_input(const modulora_qweight *w, const uint16_t *dY, int32_t M,
     hipStream_t st = static_cast<hipStream_t>(stream);
     char *ws = static_cast<char *>(workspace);
     const bool streams = mlr::smallm_bwd_supported(view_of(w), M);
-    if (streams || l.direct_bwd) {
+    if (streams || l.bwd != mlr::ROUTE_TILES) {
         mlr::SmallArgs sa{};
         sa.w = view_of(w);
         sa.act = dY; sa.M = M; sa.out = dX;
         sa.A = A; sa.B = B; sa.r = r; sa.lora_scale = lora_scale;
         sa.P_out = dYBt; sa.ws = ws;
-        return hip_status(streams ? mlr::launch_smallm_bwd(sa, st) : mlr::launch_direct(sa, true, st));
+        return hip_status(streams ? mlr::launch_smallm_bwd(sa, st) : launch_route(l.bwd, sa, true, st));
     }
     mlr::GemmArgs g{};
     g.w = view_of(w);
@@ -435,7 +443,7 @@ mlr::F16Layer view_of(const modulora_qweight_f16 *w) {
 }
 struct F16Ws {
     size_t act_ext, w_ext, p0, p1, gpart, dpart, dpart_bytes, gemm_part, total;
-    bool direct_fwd, direct_bwd;
+    mlr::Route fwd, bwd;
 };
 F16Ws f16_ws(int32_t K, int32_t N, int32_t M, int32_t r) {
     F16Ws l{};
@@ -457,9 +465,9 @@ F16Ws f16_ws(int32_t K, int32_t N, int32_t M, int32_t r) {
         const size_t small = mlr::smallm_ws_bytes(K, N, r);
         if (small > l.total) l.total = small;
     }
-    l.direct_fwd = !mlr::f16_plain_forced() && mlr::direct_wins(K, N, M, r, false, true);
-    l.direct_bwd = !mlr::f16_plain_forced() && mlr::direct_wins(K, N, M, r, true, true);
-    const size_t dir = direct_bytes(K, N, M, r, l.direct_fwd, l.direct_bwd);
+    l.fwd = mlr::f16_plain_forced() ? mlr::ROUTE_TILES : mlr::product_route(K, N, M, r, false, true);
+    l.bwd = mlr::f16_plain_forced() ? mlr::ROUTE_TILES : mlr::product_route(K, N, M, r, true, true);
+    const size_t dir = routes_bytes(l.fwd, l.bwd, K, N, M, r, true);
     if (dir > l.total) l.total = dir;
     return l;
 }
@@ -544,7 +552,7 @@ int modulora_f16_fwd(const modulora_qweight_f16 *w, const uint16_t *X, int32_t M
     if ((s = check_ws_f16(l, workspace, workspace_bytes)) != MODULORA_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool streams = mlr::smallm_fwd_supported(stream_view_of(w), M);
-    if (streams || l.direct_fwd) {
+    if (streams || l.fwd != mlr::ROUTE_TILES) {
         // a handful of tokens: the direct product with the quantized matrix (Section 3.1.2)
         mlr::SmallArgs sa{};
         sa.w = stream_view_of(w);
@@ -552,7 +560,7 @@ int modulora_f16_fwd(const modulora_qweight_f16 *w, const uint16_t *X, int32_t M
         sa.A = A; sa.B = B; sa.r = r; sa.lora_scale = lora_scale;
         sa.P_out = XA; sa.ws = workspace;
         sa.f16 = true; sa.zeros16 = w->zeros; sa.bias16 = w->bias;
-        return hip_status(streams ? mlr::launch_smallm_fwd(sa, st) : mlr::launch_direct(sa, false, st));
+        return hip_status(streams ? mlr::launch_smallm_fwd(sa, st) : launch_route(l.fwd, sa, false, st));
     }
     return f16_tiles(w, false, X, M, A, B, r, lora_scale, Y, XA, static_cast<char *>(workspace), l, st);
 }
@@ -570,14 +578,14 @@ int modulora_f16_bwd_input(const modulora_qweight_f16 *w, const uint16_t *dY, in
     if ((s = check_ws_f16(l, workspace, workspace_bytes)) != MODULORA_OK) return s;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool streams = mlr::smallm_bwd_supported(stream_view_of(w), M);
-    if (streams || l.direct_bwd) {
+    if (streams || l.bwd != mlr::ROUTE_TILES) {
         mlr::SmallArgs sa{};
         sa.w = stream_view_of(w);
         sa.act = dY; sa.M = M; sa.out = dX;
         sa.A = A; sa.B = B; sa.r = r; sa.lora_scale = lora_scale;
         sa.P_out = dYBt; sa.ws = workspace;
         sa.f16 = true; sa.zeros16 = w->zeros; sa.bias16 = nullptr;
-        return hip_status(streams ? mlr::launch_smallm_bwd(sa, st) : mlr::launch_direct(sa, true, st));
+        return hip_status(streams ? mlr::launch_smallm_bwd(sa, st) : launch_route(l.bwd, sa, true, st));
     }
     return f16_tiles(w, true, dY, M, A, B, r, lora_scale, dX, dYBt, static_cast<char *>(workspace), l, st);
 }

@@ -36,6 +36,7 @@
 #include <type_traits>
 
 #include "gemm_common.h"
+#include "project.h"
 
 namespace mlr {
 
@@ -155,14 +156,34 @@ __device__ __forceinline__ float4 *big_partial_of(float *partials, int tail_tile
     return reinterpret_cast<float4 *>(partials) + ((size_t)tail_tile * split + slice) * (size_t)big::Geo<MT>::PART_F4;
 }
 
+// What a launch of launch_sliced() does beside the product (parts == 0: nothing).
+struct BigSide {
+    const float *F;             // the projection's factor
+    float *ppart;               // [parts], part_stride apart: [M][r]
+    int r, parts, part_stride;
+    int first, stride;          // workgroup first + x takes items x, x + stride, ...
+    bool only;                  // ... and nothing else
+    uint32_t row_tiles_magic;   // item / row tiles by one multiply-high
+};
+
 template <int BITS, bool BWD, bool F16, int MT>
-__global__ __launch_bounds__(big::THREADS, 2) void gemm_big_kernel(GemmDev d, BigPlan plan) {
+__global__ __launch_bounds__(big::THREADS, 2) void gemm_big_kernel(GemmDev d, BigPlan plan, BigSide side) {
     using namespace big;
     using G = Geo<MT>;
     constexpr int WM = G::WM, TI = G::TI, A_BYTES = G::A_BYTES, W_BASE = G::W_BASE, A_CH = G::A_CH;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
     const GemmArgs &a = d.a;
+    if (side.parts > 0 && (int)blockIdx.x >= side.first) {
+        const int C = BWD ? a.w.N : a.w.K, row_tiles = (a.M + 15) >> 4, steps = (C + 31) >> 5;
+        for (int x = (int)blockIdx.x - side.first; x < row_tiles * side.parts; x += side.stride) {
+            const int part = row_tiles > 1 ? (int)__umulhi((uint32_t)x, side.row_tiles_magic) : x, tile = x - part * row_tiles;
+            const int k0 = steps * part / side.parts * 32, k1 = steps * (part + 1) / side.parts * 32;
+            project_rows<!BWD, F16, NWAVES>(ProjectArgs{a.act, side.F, a.M, C, side.r}, 16 * tile, k0, k1 < C ? k1 : C,
+                                            side.ppart + (size_t)part * side.part_stride, reinterpret_cast<float *>(smem));
+        }
+        if (side.only) return;
+    }
     const BigItem item = big_item_of_block(blockIdx.x, plan);
     if (item.tile < 0) return;   // grid padded to a multiple of 8
     const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
@@ -526,6 +547,21 @@ __global__ __launch_bounds__(big::THREADS, 2) void gemm_big_kernel(GemmDev d, Bi
         for (int t = n_main; t < n_tiles; ++t) tail_tile(t, std::true_type());
     }
 
+    if (side.parts > 0) {
+        // [slice][M][Cout] for finish.hip: 32 adjacent columns of two rows per store
+        const int lane_col = c0 + (wave & 3) * WN + (lane & 31);
+        float *part = a.partials + (size_t)item.slice * a.M * Cout;
+#pragma unroll
+        for (int i = 0; i < TI; ++i)
+#pragma unroll
+            for (int j = 0; j < TJ; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int row = m0 + (wave >> 2) * WM + i * 32 + 8 * (v / 4) + 4 * (lane >> 5) + (v % 4), col = lane_col + j * 32;
+                    if (row < a.M && col < Cout) __builtin_nontemporal_store(acc[i][j][v], part + (size_t)row * Cout + col);
+                }
+        return;
+    }
     if (item.slice >= 0) {
         // a slice: leave the raw accumulators for gemm_big_fixup_kernel
         float4 *part = big_partial_of<MT>(a.partials, item.tile - plan.full, item.slice, plan.split) + tid;
@@ -590,13 +626,19 @@ __global__ __launch_bounds__(64) void gemm_big_fixup_kernel(GemmDev d, BigPlan p
 }
 
 template <int BITS, bool BWD, bool F16, int MT>
-static hipError_t launch_big_mt(const GemmArgs &a, BigPlan plan, hipStream_t stream) {
+static hipError_t launch_big_mt(const GemmArgs &a, BigPlan plan, hipStream_t stream, const SlicedPlan *sliced = nullptr, BigSide side = {}) {
     const GemmDev d = make_gemm_dev(a, MT, big::CT);
     // no (or too little) scratch for partial tiles: whole tiles only
-    if (a.partials == nullptr || a.partials_bytes < plan.partial_bytes()) plan.split = 1;
+    if (!sliced && (a.partials == nullptr || a.partials_bytes < plan.partial_bytes())) plan.split = 1;
     const int whole = plan.split > 1 ? plan.full : plan.full + plan.tail;
     const int slices = plan.split > 1 ? plan.tail * plan.split : 0;
-    const int blocks = ((whole + 7) / 8 + (slices + 7) / 8) * 8;
+    int blocks = ((whole + 7) / 8 + (slices + 7) / 8) * 8;
+    if (sliced) {
+        side.only = sliced->idle > 0;
+        side.first = side.only ? blocks : 0;
+        blocks += sliced->idle;
+        side.stride = blocks - side.first;
+    }
     const size_t lds_bytes = big::Geo<MT>::LDS_BYTES;
     auto kern = gemm_big_kernel<BITS, BWD, F16, MT>;
     static bool configured[64] = {};
@@ -604,9 +646,9 @@ static hipError_t launch_big_mt(const GemmArgs &a, BigPlan plan, hipStream_t str
     if (e != hipSuccess) return e;
     const char *name = F16 ? (BWD ? "f16_gemm_bwd" : "f16_gemm_fwd")
                            : MT == 256 ? (BWD ? "gemm_bwd_256x256" : "gemm_fwd_256x256") : (BWD ? "gemm_bwd_128x256" : "gemm_fwd_128x256");
-    launch_kernel(name, kern, blocks, big::THREADS, lds_bytes, stream, d, plan);
+    launch_kernel(name, kern, blocks, big::THREADS, lds_bytes, stream, d, plan, side);
     hipError_t err = hipGetLastError();
-    if (err != hipSuccess || plan.split <= 1) return err;
+    if (err != hipSuccess || plan.split <= 1 || sliced) return err;
     constexpr size_t FIXUP_LDS = 32 * big::PATCH_ROW * 2;      // one wave's patch
     auto fix = gemm_big_fixup_kernel<F16, MT>;
     const char *fix_name = F16 ? (BWD ? "f16_gemm_bwd_fixup" : "f16_gemm_fwd_fixup")
@@ -638,6 +680,48 @@ hipError_t launch_gemm_big_f16(const GemmArgs &a, hipStream_t stream) {
         case 3: return a.backward ? launch_big<3, true, true>(a, stream) : launch_big<3, false, true>(a, stream);
         default: return a.backward ? launch_big<4, true, true>(a, stream) : launch_big<4, false, true>(a, stream);
     }
+}
+
+template <int BITS, bool BWD, bool F16>
+static hipError_t launch_sliced_bits(const GemmArgs &a, const SlicedPlan &p, const BigSide &side, hipStream_t stream) {
+    if (p.big.mt == 128) return launch_big_mt<BITS, BWD, F16, 128>(a, p.big, stream, &p, side);
+    return launch_big_mt<BITS, BWD, F16, 256>(a, p.big, stream, &p, side);
+}
+template <bool BWD, bool F16>
+static hipError_t launch_sliced_any(const GemmArgs &a, const SlicedPlan &p, const BigSide &side, hipStream_t stream) {
+    switch (a.w.bits) {
+        case 2: return launch_sliced_bits<2, BWD, F16>(a, p, side, stream);
+        case 3: return launch_sliced_bits<3, BWD, F16>(a, p, side, stream);
+        default: return launch_sliced_bits<4, BWD, F16>(a, p, side, stream);
+    }
+}
+
+hipError_t launch_sliced(const SmallArgs &s, bool backward, hipStream_t stream) {
+    const int C = backward ? s.w.N : s.w.K, Cout = backward ? s.w.K : s.w.N;
+    const SlicedPlan p = sliced_plan(s.M, C, Cout, s.r, s.f16);
+    if (p.parts < 1) return hipErrorInvalidValue;     // callers asked product_route() first
+    GemmArgs g{};
+    g.w = s.w; g.backward = backward; g.act = s.act; g.M = s.M; g.out = s.out;
+    g.zeros16 = s.zeros16; g.bias16 = s.bias16;
+    g.partials = static_cast<float *>(s.ws);
+    BigSide side{};
+    side.F = backward ? s.B : s.A;
+    side.ppart = reinterpret_cast<float *>(static_cast<char *>(s.ws) + p.slices_bytes(s.M, Cout));
+    side.r = s.r; side.parts = p.parts; side.part_stride = SlicedPlan::part_stride(s.M, s.r);
+    const int row_tiles = (s.M + 15) / 16;
+    side.row_tiles_magic = row_tiles > 1 ? (uint32_t)((1ull << 32) / row_tiles) + 1u : 0u;      // items < 2^16
+    hipError_t e;
+    if (s.f16) e = backward ? launch_sliced_any<true, true>(g, p, side, stream) : launch_sliced_any<false, true>(g, p, side, stream);
+    else e = backward ? launch_sliced_any<true, false>(g, p, side, stream) : launch_sliced_any<false, false>(g, p, side, stream);
+    if (e != hipSuccess) return e;
+    FinishArgs f{};
+    f.slices = g.partials; f.slice_stride = (size_t)s.M * Cout; f.split = p.big.split; f.M = s.M; f.Cout = Cout;
+    f.ppart = side.ppart; f.part_stride = side.part_stride; f.parts = p.parts; f.r = s.r;
+    f.F = backward ? s.A : s.B; f.bias16 = s.bias16; f.lora_scale = s.lora_scale; f.out = s.out; f.P_out = s.P_out;
+    const char *name = s.f16 ? (backward ? "f16_gemm_bwd_fixup" : "f16_gemm_fwd_fixup")
+                     : p.big.mt == 256 ? (backward ? "gemm_bwd_256x256_fixup" : "gemm_fwd_256x256_fixup")
+                                       : (backward ? "gemm_bwd_128x256_fixup" : "gemm_fwd_128x256_fixup");
+    return launch_finish(name, f, backward, s.f16, stream);
 }
 
 }  // namespace mlr

@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "gemm_common.h"
+#include "project.h"
 
 namespace mlr {
 
@@ -67,80 +68,6 @@ struct DirectDev {
     uint32_t group_plus, group_magic;
     __device__ __forceinline__ uint32_t group_of_block(uint32_t blk) const { return __umulhi(blk + group_plus, group_magic); }
 };
-
-// The projection of 16 activation rows over contraction elements [k0, k1) (multiples of 8), all waves
-// of the workgroup together: P[row][j] = sum act[row][c] F(c, j) on the matrix cores, the fp32 factor
-// split exactly into three bfloat16 terms (binary16 activations into two).  `red`: NWAVES * RG * 256
-// floats of LDS.  Ends with every thread past its reads of `red`.
-template <bool F_IS_A, bool F16>
-__device__ __forceinline__ void direct_project(const DirectDev &d, int row0, int k0, int k1, float *dst, float *red) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
-    const int i = lane & 15, cs = lane >> 4, r = d.r;
-    const int row = row0 + i < d.M ? row0 + i : d.M - 1;
-    const uint16_t *arow = d.act + (size_t)row * d.C;
-    const int steps = (k1 - k0 + 31) / 32;
-    const int s0 = steps * wave / direct::NWAVES, s1 = steps * (wave + 1) / direct::NWAVES;
-    const int RG = (r + 15) >> 4;
-    for (int g = 0; g < RG; ++g) {
-        const int j = g * 16 + i;
-        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-        constexpr int UNR = 4;
-        for (int st = s0; st < s1; st += UNR) {
-            uint4 av[UNR];
-            float f[UNR][8];
-#pragma unroll
-            for (int q = 0; q < UNR; ++q) {
-                const int c = k0 + (st + q) * 32 + cs * 8;
-                const bool ok = st + q < s1 && c < k1;
-                av[q] = make_uint4(0, 0, 0, 0);
-                if (ok) av[q] = *reinterpret_cast<const uint4 *>(arow + c);
-#pragma unroll
-                for (int e = 0; e < 8; ++e) f[q][e] = 0.f;
-                if (ok && j < r) {
-                    if (F_IS_A) {
-#pragma unroll
-                        for (int e = 0; e < 8; ++e) f[q][e] = d.Fp[(size_t)(c + e) * r + j];
-                    } else {
-                        const float4 q0 = *reinterpret_cast<const float4 *>(d.Fp + (size_t)j * d.C + c);
-                        const float4 q1 = *reinterpret_cast<const float4 *>(d.Fp + (size_t)j * d.C + c + 4);
-                        f[q][0] = q0.x; f[q][1] = q0.y; f[q][2] = q0.z; f[q][3] = q0.w;
-                        f[q][4] = q1.x; f[q][5] = q1.y; f[q][6] = q1.z; f[q][7] = q1.w;
-                    }
-                }
-            }
-#pragma unroll
-            for (int q = 0; q < UNR; ++q) {
-                uint32_t p[3][4];
-                split3(f[q], p[0], p[1], p[2]);
-                const uint32_t ar[4] = {av[q].x, av[q].y, av[q].z, av[q].w};
-                uint32_t a2[2][4];
-                if (F16) split_f16x8(ar, a2[0], a2[1]);
-#pragma unroll
-                for (int h = 0; h < (F16 ? 2 : 1); ++h) {
-                    bf16x8 x, y;
-                    __builtin_memcpy(&x, F16 ? a2[h] : ar, 16);
-#pragma unroll
-                    for (int t = 0; t < 3; ++t) {
-                        __builtin_memcpy(&y, p[t], 16);
-                        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, acc, 0, 0, 0);
-                    }
-                }
-            }
-        }
-#pragma unroll
-        for (int v = 0; v < 4; ++v) red[((wave * RG + g) * 4 + v) * 64 + lane] = acc[v];
-    }
-    __syncthreads();
-    for (int x = tid; x < RG * 256; x += direct::THREADS) {
-        const int g = x >> 8, v = (x >> 6) & 3, l = x & 63;
-        float sum = 0.f;
-#pragma unroll
-        for (int w = 0; w < direct::NWAVES; ++w) sum += red[((w * RG + g) * 4 + v) * 64 + l];
-        const int prow = row0 + 4 * (l >> 4) + v, j = g * 16 + (l & 15);
-        if (prow < d.M && j < r) dst[(size_t)prow * r + j] = sum;
-    }
-    __syncthreads();
-}
 
 template <int BITS, bool BWD, bool F16, int RT>
 __global__ __launch_bounds__(direct::THREADS, 2) void gemm_direct_kernel(DirectDev d) {
@@ -348,7 +275,7 @@ __global__ __launch_bounds__(direct::THREADS, 2) void gemm_direct_kernel(DirectD
             if (row0 >= M) continue;
             const int ks = ch0 * CHUNK + 32 * (steps * x / d.proj_parts);
             const int ke = x + 1 == d.proj_parts ? k1 : ch0 * CHUNK + 32 * (steps * (x + 1) / d.proj_parts);
-            direct_project<!BWD, F16>(d, row0, ks, ke, d.ppart + (size_t)(slice * d.proj_parts + x) * d.part_stride,
+            project_rows<!BWD, F16, NWAVES>(ProjectArgs{d.act, d.Fp, d.M, d.C, d.r}, row0, ks, ke, d.ppart + (size_t)(slice * d.proj_parts + x) * d.part_stride,
                                       reinterpret_cast<float *>(smem + SLOTS * SLOT));
         }
     }
@@ -552,15 +479,20 @@ double direct_us(const DirectPlan &p, int M, int Cout, int r, bool backward, boo
     return us;
 }
 
-bool direct_wins(int K, int N, int M, int r, bool backward, bool f16) {
+Route product_route(int K, int N, int M, int r, bool backward, bool f16) {
     const size_t elements = (size_t)K * N;
     const int C = backward ? N : K, Cout = backward ? K : N;
-    if (M > 1024 || elements > ((size_t)1 << 32)) return false;
-    if (elements < ((size_t)1 << 23) && Cout % (backward ? direct::CT : 16) != 0) return false;
-    const DirectPlan p = direct_plan(M, C, Cout, backward);
-    double margin = r <= 16 || f16 ? 1.0 : (backward && M <= 512 ? 1.13 : 1.02);
-    if (M > 128 && big_half_rows(M) && (long)p.tiles_m * p.tiles_c * p.split > 256) margin = 1.15;
-    return direct_us(p, M, Cout, r, backward, f16) * margin < gemm_tile_us(M, C, Cout, r, f16) + lora_down_us(M, C, r, backward);
+    if (elements < ((size_t)1 << 23) && Cout % (backward ? direct::CT : 16) != 0) return ROUTE_TILES;
+    const double tiles = gemm_tile_us(M, C, Cout, r, f16) + lora_down_us(M, C, r, backward);
+    const SlicedPlan sliced = sliced_plan(M, C, Cout, r, f16);
+    if (M <= 1024 && elements <= ((size_t)1 << 32)) {
+        const DirectPlan p = direct_plan(M, C, Cout, backward);
+        double margin = r <= 16 || f16 ? 1.0 : (backward && M <= 512 ? 1.13 : 1.02);
+        if (M > 128 && big_half_rows(M) && (long)p.tiles_m * p.tiles_c * p.split > 256) margin = 1.15;
+        const double us = direct_us(p, M, Cout, r, backward, f16) * margin;
+        if (us < tiles) return sliced.parts > 0 && r <= 16 && 1.2 * sliced.us < us ? ROUTE_SLICED : ROUTE_DIRECT;
+    }
+    return sliced.parts > 0 && 1.05 * sliced.us < tiles ? ROUTE_SLICED : ROUTE_TILES;
 }
 
 hipError_t launch_direct(const SmallArgs &a, bool backward, hipStream_t stream) {

@@ -102,15 +102,17 @@ inline BigPlan big_plan_rows(int M, int C, int Cout, int mt) {
 // last round `last` and a step that grows with the workgroups in flight, then the fix-up and its partial tiles.
 // Least-squares fit (7 % rms) to 9900 timed launches of both row heights, sliced and whole: 1650 layers of 256 to
 // 22016 wide, 2 ... 4096 tokens, r = 0 to 64, all bit widths, both directions and conventions.
+inline double big_fixup_us(const BigPlan &p) {
+    if (p.split <= 1) return 0.0;
+    return p.mt == 128 ? 3.86 + 0.229e-6 * (double)p.partial_bytes() : 3.08 + 0.195e-6 * (double)p.partial_bytes();
+}
 inline double big_plan_us(const BigPlan &p, int C, int extension_steps) {
-    struct Cost { double fixed, step, round, last, last_step, last_load, fixup, fixup_mb; };
-    const Cost k = p.mt == 128 ? Cost{2.46, 0.988, 5.58, 3.34, 0.779, 0.225, 3.86, 0.229}
-                               : Cost{8.44, 1.60, 7.29, 0.0, 1.04, 0.489, 3.08, 0.195};
+    struct Cost { double fixed, step, round, last, last_step, last_load; };
+    const Cost k = p.mt == 128 ? Cost{2.46, 0.988, 5.58, 3.34, 0.779, 0.225} : Cost{8.44, 1.60, 7.29, 0.0, 1.04, 0.489};
     const int steps = (C + 63) / 64;
     double us = k.fixed + (double)(p.full / 256) * (k.step * (steps + extension_steps) + k.round);
     if (p.tail > 0) us += k.last + (k.last_step + k.last_load * (p.tail * p.split / 256.0)) * ((steps + p.split - 1) / p.split + extension_steps);
-    if (p.split > 1) us += k.fixup + k.fixup_mb * 1e-6 * (double)p.partial_bytes();
-    return us;
+    return us + big_fixup_us(p);
 }
 // Rows of a tile: 128 where the last block of 256 rows would be at most half full and the row blocks are few (a
 // step of the 128-row kernel takes 0.55 of a 256-row step, so an odd number n of 128-row blocks costs 0.55 n against
@@ -139,6 +141,53 @@ inline size_t gemm_partial_bytes(int M, int K, int N) {
         if (b > most) most = b;
     }
     return most;
+}
+
+// The 256-column kernel with the contraction of every tile cut into slices, the rank-r projection as a side job and
+// the adapter term in the second launch (launch_finish()): no launch ahead of the product.  The compute units that
+// the slices leave idle take the projection if they get through it meanwhile, else every workgroup does its share first.
+struct SlicedPlan {
+    BigPlan big;
+    int parts;           // of the contraction, in the projection of 16 rows; 0: no such plan
+    int idle;            // workgroups beside the product's that do the projection; 0: all of the product's do
+    double us;
+    size_t slices_bytes(int M, int Cout) const { return ((size_t)big.split * M * Cout * 4 + 255) & ~(size_t)255; }
+    static int part_stride(int M, int r) { return (M * r + 3) & ~3; }
+    size_t ws_bytes(int M, int Cout, int r) const { return slices_bytes(M, Cout) + (((size_t)parts * part_stride(M, r) * 4 + 255) & ~(size_t)255); }
+};
+// The estimate is a fit to 2800 timed calls (24 ... 4096 tokens, r = 4 to 64): the product launch 8 % rms where idle units
+// project and 13 % where all do, the second launch 11 %.
+inline SlicedPlan sliced_plan(int M, int C, int Cout, int r, bool f16) {
+    SlicedPlan best{};
+    if (r <= 0) return best;
+    const int row_tiles = (M + 15) >> 4, steps = (C + 31) >> 5, more = (r - 1) >> 4, deepest = steps < 64 ? 1 : steps < 256 ? steps >> 5 : 8;
+    const double turn = 2.2 + 1.69 * more + (f16 ? 0.64 + 0.53 * more : 0.0);      // 16 rows x 32 steps of 32 (direct_us())
+    const double outputs = 1e-3 * ((M + 31) >> 5) * ((Cout + 63) >> 6);
+    for (int rows = big_half_rows(M) ? 128 : 256; rows >= 128; rows -= 128) {
+        SlicedPlan p;
+        p.big = big_plan_rows(M, C, Cout, rows);
+        if (p.big.full > 0 || p.big.split <= 1) continue;
+        const int slices = p.big.tail * p.big.split;
+        const double second = 3.9 + 0.125e-6 * (double)((size_t)p.big.split * M * Cout * 4) + 0.18 * outputs +
+                              (r > 16 ? 0.9 + 0.075 * (r - 16) * outputs : 0.0);
+        const double product_us = big_plan_us(p.big, C, 0) - big_fixup_us(p.big);
+        auto job_us = [&](int parts, int workgroups) {
+            return (double)((row_tiles * parts + workgroups - 1) / workgroups) * (((steps + parts - 1) / parts + 31) >> 5) * turn;
+        };
+        auto at_least_one = [&](int parts) { return parts < 1 ? 1 : parts > deepest ? deepest : parts; };
+        p.idle = 0;
+        p.parts = at_least_one(slices / row_tiles);
+        p.us = 0.46 + 1.05 * product_us + 0.92 * job_us(p.parts, slices) + second + 0.012 * outputs * r * p.parts;
+        const int idle = 256 - ((slices + 7) & ~7);
+        if (idle > 0) {
+            const int parts = at_least_one((2 * idle + row_tiles - 1) / row_tiles);
+            const double alone = 1.03 + 0.978 * product_us, job = 1.96 + 1.29 * job_us(parts, idle);
+            const double us = (alone > job ? alone : job) + second + 0.012 * outputs * r * parts;
+            if (us < p.us) { p.idle = idle; p.parts = parts; p.us = us; }
+        }
+        if (best.parts == 0 || p.us < best.us) best = p;
+    }
+    return best;
 }
 
 // ---- lora_kernels.hip ----------------------------------------------------------
@@ -438,7 +487,9 @@ inline DirectPlan direct_plan(int M, int C, int Cout, bool backward) {
 // times do not cross there: 1056 x 4104 backward, 100 tokens 31 us with tiles, 18 direct).
 // Over 2^32 weights the kernel's 32-bit offsets would overflow.
 double direct_us(const DirectPlan &p, int M, int Cout, int r, bool backward, bool f16);      // estimated time of a call
-bool direct_wins(int K, int N, int M, int r, bool backward, bool f16);
+enum Route { ROUTE_TILES, ROUTE_DIRECT, ROUTE_SLICED };
+Route product_route(int K, int N, int M, int r, bool backward, bool f16);
+hipError_t launch_sliced(const SmallArgs &a, bool backward, hipStream_t stream);      // gemm_big.hip
 double gemm_tile_us(int M, int C, int Cout, int r, bool f16);      // gemm_tile.hip: estimated time of the cheapest tile kernel
 hipError_t launch_direct(const SmallArgs &a, bool backward, hipStream_t stream);
 
