@@ -158,12 +158,13 @@ __device__ __forceinline__ void codes_to_operand(const uint32_t *w, int c, const
 // The rank-r projection of the (at most 16) activation rows, XA = X A or dYBt = dY B^T, for
 // the adapter term: done by the first `nblk` workgroups of a stream kernel beside the
 // streaming ones, on the matrix cores (16x16x32 bf16 MFMA; the fp32 factor split exactly
-// into three bfloat16 terms).  The waves of those workgroups split the contraction; each
+// into three bfloat16 terms, binary16 activations into two: in plain fp32 on the vector ALUs, eight ranks a pass,
+// a rank of 64 took 25 us of a 1024 x 2816 forward call's first launch and takes 7).  The waves of those workgroups split the contraction; each
 // workgroup leaves one partial [16][r] and the finish kernel adds the nblk of them.
 // Lane l = 16 cs + i: activation row i (rows >= M repeat row M - 1; their results are never
 // used), factor column 16 g + i, contraction elements 8 cs .. 8 cs + 7 of a step of 32.
 // ---------------------------------------------------------------------------------
-template <bool F_IS_A, int NWAVES>
+template <bool F_IS_A, bool F16, int NWAVES>
 __device__ __forceinline__ void smallm_project(const uint16_t *act, int M, int C, const float *F, int r, int blk,
                                                int nblk, float *parts, float *red /* LDS, NWAVES * 4 * 256 floats */) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -209,12 +210,15 @@ __device__ __forceinline__ void smallm_project(const uint16_t *act, int M, int C
             }
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
-                uint32_t hi[4], mid[4], lo[4];
-                split3(f[q], hi, mid, lo);
-                const bf16x8 a = sm::as_bf16x8(av[q]);
-                acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, sm::as_bf16x8(hi), acc[g], 0, 0, 0);
-                acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, sm::as_bf16x8(mid), acc[g], 0, 0, 0);
-                acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, sm::as_bf16x8(lo), acc[g], 0, 0, 0);
+                uint32_t p[3][4], h[2][4];
+                split3(f[q], p[0], p[1], p[2]);
+                const uint32_t aw[4] = {av[q].x, av[q].y, av[q].z, av[q].w};
+                if (F16) split_f16x8(aw, h[0], h[1]);
+#pragma unroll
+                for (int x = 0; x < (F16 ? 2 : 1); ++x)
+#pragma unroll
+                    for (int t = 0; t < 3; ++t)
+                        acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sm::as_bf16x8(F16 ? h[x] : aw), sm::as_bf16x8(p[t]), acc[g], 0, 0, 0);
             }
         }
     }
@@ -232,64 +236,6 @@ __device__ __forceinline__ void smallm_project(const uint16_t *act, int M, int C
         for (int w = 0; w < NWAVES; ++w) sum += red[((w * 4 + g) * 4 + v) * 64 + l];
         const int prow = 4 * (l >> 4) + v, j = g * 16 + (l & 15);
         if (j < r) mine[prow * r + j] = sum;
-    }
-}
-
-// The same projection for binary16 activations (the layer in the paper's own storage convention),
-// in plain fp32 on the vector ALUs: a binary16 activation does not fit a bfloat16 operand, and at
-// most 16 rows by a few thousand contraction elements per workgroup are too little work to matter.
-// Thread t: row t % 16, chunks of 8 contraction elements (t / 16) + k * (threads / 16) of the
-// workgroup's range (one 16-byte activation load per chunk, and every factor load of the chunk in
-// flight with it); eight rank columns per pass; the threads' sums meet in LDS.  Same partial layout
-// as above: one [16][r] per workgroup.
-template <bool F_IS_A, int NWAVES>
-__device__ __forceinline__ void smallm_project_f16(const uint16_t *act, int M, int C, const float *F, int r, int blk,
-                                                   int nblk, float *parts, float *red /* LDS, NWAVES * 64 * 8 floats */) {
-    constexpr int NT = NWAVES * 64, KL = NT / 16;
-    const int tid = threadIdx.x, m = tid & 15, kl = tid >> 4;
-    const int chunks = C >> 3;
-    const int ch0 = (int)((long)chunks * blk / nblk), ch1 = (int)((long)chunks * (blk + 1) / nblk);
-    const uint16_t *arow = act + (size_t)(m < M ? m : M - 1) * C;
-    float *mine = parts + (size_t)blk * 16 * r;
-    for (int j0 = 0; j0 < r; j0 += 8) {
-        float acc[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] = 0.f;
-        for (int ch = ch0 + kl; ch < ch1; ch += KL) {
-            const int c = ch << 3;
-            const uint4 xv = *reinterpret_cast<const uint4 *>(arow + c);
-            const uint32_t xw[4] = {xv.x, xv.y, xv.z, xv.w};
-            float x[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] = half_bits_to_float((uint16_t)(xw[e >> 1] >> (16 * (e & 1))));
-            float f[8][8];       // [rank column][contraction element]
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const bool ok = j0 + j < r;
-                if (F_IS_A) {
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) f[j][e] = ok ? F[(size_t)(c + e) * r + j0 + j] : 0.f;
-                } else {
-                    const float *src = F + (size_t)(ok ? j0 + j : 0) * C + c;     // 32-byte aligned: C is a multiple of 8
-                    const float4 q0 = *reinterpret_cast<const float4 *>(src), q1 = *reinterpret_cast<const float4 *>(src + 4);
-                    f[j][0] = q0.x; f[j][1] = q0.y; f[j][2] = q0.z; f[j][3] = q0.w;
-                    f[j][4] = q1.x; f[j][5] = q1.y; f[j][6] = q1.z; f[j][7] = q1.w;
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc[j] = __builtin_fmaf(x[e], f[j][e], acc[j]);
-        }
-        __syncthreads();                         // the previous pass has been read
-#pragma unroll
-        for (int j = 0; j < 8; ++j) red[(kl * 16 + m) * 8 + j] = acc[j];
-        __syncthreads();
-        if (tid < 128) {                         // (row, column) = (tid / 8, tid % 8)
-            float sum = 0.f;
-            for (int q = 0; q < KL; ++q) sum += red[(q * 16 + (tid >> 3)) * 8 + (tid & 7)];
-            if (j0 + (tid & 7) < r) mine[(tid >> 3) * r + j0 + (tid & 7)] = sum;
-        }
     }
 }
 
@@ -502,8 +448,7 @@ __global__ __launch_bounds__(sm::FWD_THREADS, 4) void smallm_fwd_kernel(SmallFwd
     if ((int)blockIdx.x < d.n_proj) {
         // projection workgroups: partials of XA = X A for the finish kernel; they run beside the
         // streaming ones and are done long before them
-        if (F16) smallm_project_f16<true, sm::FWD_WAVES>(d.X, d.M, d.w.K, d.A, d.r, blockIdx.x, d.n_proj, d.Upart, reinterpret_cast<float *>(xs));
-        else smallm_project<true, sm::FWD_WAVES>(d.X, d.M, d.w.K, d.A, d.r, blockIdx.x, d.n_proj, d.Upart, reinterpret_cast<float *>(xs));
+        smallm_project<true, F16, sm::FWD_WAVES>(d.X, d.M, d.w.K, d.A, d.r, blockIdx.x, d.n_proj, d.Upart, reinterpret_cast<float *>(xs));
         return;
     }
     const int bid = blockIdx.x - d.n_proj;
@@ -945,8 +890,7 @@ __global__ __launch_bounds__(sm::WG_THREADS, 2) void smallm_bwd_kernel(SmallBwdD
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if ((int)blockIdx.x < d.n_proj) {
         // projection workgroups: partials of dYBt = dY B^T (see the forward kernel)
-        if (F16) smallm_project_f16<false, sm::WG_WAVES>(d.dY, d.M, d.w.N, d.B, d.r, blockIdx.x, d.n_proj, d.Tpart, reinterpret_cast<float *>(ys));
-        else smallm_project<false, sm::WG_WAVES>(d.dY, d.M, d.w.N, d.B, d.r, blockIdx.x, d.n_proj, d.Tpart, reinterpret_cast<float *>(ys));
+        smallm_project<false, F16, sm::WG_WAVES>(d.dY, d.M, d.w.N, d.B, d.r, blockIdx.x, d.n_proj, d.Tpart, reinterpret_cast<float *>(ys));
         return;
     }
     const int bid = blockIdx.x - d.n_proj;
@@ -1362,15 +1306,14 @@ namespace {
 struct SmallWs {
     size_t upart, yacc, total;
 };
-// workgroups that do the rank-r projection beside the streaming ones: one per 512 contraction
-// elements (four steps of 32 per wave), at most 16 -- or, for the binary16 layer, whose projection
-// runs on the vector ALUs with one 8-element chunk per thread and pass, at most 32
-constexpr int MAX_PROJ_BLOCKS = 32;
-int n_proj_blocks(int C, int r, bool f16) {
+// workgroups that do the rank-r projection beside the streaming ones: one per 256 contraction elements,
+// at most 16 (8 tokens, r = 64 backward, us of the product launch with one per 512 / 256: 14720 x 512 6.7 / 5.4,
+// 1024 x 2048 6.9 / 4.9; with at most 32 the second launch takes longer to add them than the first gains)
+constexpr int MAX_PROJ_BLOCKS = 16;
+int n_proj_blocks(int C, int r) {
     if (r <= 0) return 0;
-    const int cap = f16 ? MAX_PROJ_BLOCKS : 16;
-    int n = C / 512;
-    return n < 1 ? 1 : (n > cap ? cap : n);
+    const int n = C / 256;
+    return n < 1 ? 1 : (n > MAX_PROJ_BLOCKS ? MAX_PROJ_BLOCKS : n);
 }
 SmallWs small_ws(int K, int N, int r) {
     const size_t kmax = (size_t)(K > N ? K : N);
@@ -1451,7 +1394,7 @@ hipError_t launch_smallm_fwd(const SmallArgs &a, hipStream_t stream) {
     d.B = a.B;
     d.M = a.M;
     d.r = a.r;
-    d.n_proj = n_proj_blocks(K, a.r, a.f16);
+    d.n_proj = n_proj_blocks(K, a.r);
     d.ksplit = ksplit;
     d.lora_scale = a.lora_scale;
     d.Y = a.out;
@@ -1527,7 +1470,7 @@ hipError_t launch_smallm_bwd(const SmallArgs &a, hipStream_t stream) {
     d.A = a.A;
     d.M = a.M;
     d.r = a.r;
-    d.n_proj = n_proj_blocks(N, a.r, a.f16);
+    d.n_proj = n_proj_blocks(N, a.r);
     d.nsplit = nsplit;
     d.lora_scale = a.lora_scale;
     d.dX = a.out;
