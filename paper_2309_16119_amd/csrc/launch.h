@@ -410,6 +410,9 @@ bool smallm_fwd_supported(const LayerView &w, int M);
 bool smallm_bwd_supported(const LayerView &w, int M);
 size_t smallm_ws_bytes(int K, int N, int r);              // enough for both passes of any layer of this shape
 size_t smallm_fwd_ws_bytes(const LayerView &w, int r);    // what launch_smallm_fwd touches for this layer
+// single.hip: the forward call in one launch, for small layers that the streaming kernels take
+bool single_wins(const LayerView &w, int M, int r, bool f16);
+hipError_t launch_single(const SmallArgs &a, hipStream_t stream);
 hipError_t launch_smallm_fwd(const SmallArgs &a, hipStream_t stream);
 hipError_t launch_smallm_bwd(const SmallArgs &a, hipStream_t stream);
 

@@ -1,0 +1,65 @@
+"""The forward call of up to 15 tokens through a small layer in one launch (single.hip): either width of its
+workgroups, ranks that fill a group of 16 or not, ragged outputs, contractions of fewer units than waves and of
+several rounds.  Against the product with the unrounded weight in 64 bits, and against the two launches that larger
+token counts take."""
+import pytest
+import torch
+
+from paper_2309_16119_amd import binding as b, synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("conv", ["bf16", "f16"])
+@pytest.mark.parametrize("bits,K,N,M,r,group", [
+    (4, 256, 256, 15, 8, 64),          # eight units: one per wave
+    (3, 256, 488, 1, 0, 128),          # no adapter, a last workgroup of eight columns
+    (2, 384, 264, 3, 9, 64),           # twelve units
+    (4, 896, 2104, 7, 16, 32),         # a rank that fills its group, one step per quantization group
+    (3, 896, 1032, 5, 17, 896),        # one group per row
+    (2, 1024, 272, 13, 32, 128),       # two rounds of units in flight
+    (4, 1920, 520, 2, 1, 384),         # a last round of half the waves
+    (3, 256, 17032, 9, 8, 128),        # workgroups of 64 columns, the last of eight
+    (2, 512, 12040, 4, 24, 64),
+    (4, 256, 9608, 15, 47, 64),
+])
+def test_one_launch(bits, K, N, M, r, group, conv):
+    cfg = synth.LayerConfig("t", K, N, bits, group, M, max(r, 1))
+    L = synth.make_layer_torch(cfg, device="cuda", seed=29)
+    f16 = conv == "f16"
+    dtype, call = (torch.float16, b.modulora_f16_fwd) if f16 else (torch.bfloat16, b.modulora_fwd)
+    words = (L["qweight"].long() & 0xFFFFFFFF).view(K // 32, bits, N)
+    code = []
+    for pos in range(0, 32 * bits, bits):               # the 32 codes of a block, two of which may straddle words
+        v = words[:, pos // 32] >> (pos % 32)
+        if pos % 32 + bits > 32:
+            v = v | (words[:, pos // 32 + 1] << (32 - pos % 32))
+        code.append(v & ((1 << bits) - 1))
+    codes, s = torch.stack(code, dim=1).reshape(K, N).double(), L["scales"].double().repeat_interleave(group, dim=0)
+    if f16:
+        zeros = (L["zeros"].float() * -L["scales"].float()).half()
+        bias = torch.randn(N, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1)).half()
+        w, W = b.QWeightF16(L["qweight"], L["scales"], zeros, bias, K, N, bits, group), codes * s + zeros.double().repeat_interleave(group, dim=0)
+    else:
+        w, W = b.QWeight(L["qweight"], L["scales"], L["zeros"], K, N, bits, group), (codes - L["zeros"].double().repeat_interleave(group, dim=0)) * s
+    A, B = (L["A"] * 3, L["B"] * 30) if r else (None, None)      # an adapter term as large as the product
+    X = torch.randn((16, K), device="cuda", generator=torch.Generator(device="cuda").manual_seed(2)).to(dtype)
+    out = torch.full((M, N), float("nan"), dtype=dtype, device="cuda")
+    b.modulora_profile_begin()
+    Y, XA = call(w, X[:M].contiguous(), A, B, 2.0, out)
+    torch.cuda.synchronize()
+    assert set(b.modulora_profile_end()) == {("f16_" if f16 else "") + "stream_fwd_single"}
+    X64 = X[:M].double()
+    ref, mag = X64 @ W, X64.abs() @ (codes.abs() + (1088 if f16 else 136 + L["zeros"].double().repeat_interleave(group, dim=0))).mul(s)
+    if r:
+        down = X64 @ A.double()
+        assert bool(((XA.double() - down).abs() <= 2.0 ** -24 * (64 + K ** 0.5) * (X64.abs() @ A.double().abs())).all())
+        ref, mag = ref + 2 * down @ B.double(), mag + 2 * (X64.abs() @ A.double().abs()) @ B.double().abs()
+    if f16:
+        ref = ref + bias.double()
+    # one rounding of the output; fp32 sums of products with the offset codes
+    tol = (2.0 ** -11 if f16 else 2.0 ** -8) * ref.abs() + 2.0 ** -24 * (64 + K ** 0.5) * mag
+    assert bool(((Y.double() - ref).abs() <= tol).all()), float(((Y.double() - ref).abs() / tol).max())
+    # sixteen tokens take two launches: the same rows to the same accuracy
+    both = call(w, X, A, B, 2.0)[0][:M].double()
+    assert bool(((both - ref).abs() <= tol).all())
