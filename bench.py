@@ -557,7 +557,9 @@ def rocprof_kernel_pattern(lib_name: str) -> str:
     if lib_name.startswith("gemm_bwd_128x64s"):
         return "gemm_mid_kernel<%d, true"
     if "_direct" in lib_name:
-        return "gemm_direct_finish_kernel" if "fixup" in lib_name else "gemm_direct_kernel<%d, " + ("true" if "bwd" in lib_name else "false")
+        return "finish_kernel" if "fixup" in lib_name else "gemm_direct_kernel<%d, " + ("true" if "bwd" in lib_name else "false")
+    if lib_name.endswith("_single"):
+        return "single_kernel<%d"
     if lib_name.startswith("gemm_fwd"):
         return "gemm_tile_kernel<%d, false"
     if lib_name.startswith("gemm_bwd"):

@@ -80,7 +80,11 @@ size_t routes_bytes(mlr::Route fwd, mlr::Route bwd, int32_t K, int32_t N, int32_
     return f > b ? f : b;
 }
 hipError_t launch_route(mlr::Route route, const mlr::SmallArgs &sa, bool backward, hipStream_t st) {
-    return route == mlr::ROUTE_DIRECT ? mlr::launch_direct(sa, backward, st) : mlr::launch_sliced(sa, backward, st);
+    switch (route) {
+        case mlr::ROUTE_DIRECT: return mlr::launch_direct(sa, backward, st);
+        case mlr::ROUTE_SINGLE: return mlr::launch_single(sa, true, st);
+        default: return mlr::launch_sliced(sa, backward, st);
+    }
 }
 WsLayout ws_layout(int32_t K, int32_t N, int32_t M, int32_t r) {
     WsLayout l{};

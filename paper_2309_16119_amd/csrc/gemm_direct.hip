@@ -490,9 +490,14 @@ Route product_route(int K, int N, int M, int r, bool backward, bool f16) {
         double margin = r <= 16 || f16 ? 1.0 : (backward && M <= 512 ? 1.13 : 1.02);
         if (M > 128 && big_half_rows(M) && (long)p.tiles_m * p.tiles_c * p.split > 256) margin = 1.15;
         const double us = direct_us(p, M, Cout, r, backward, f16) * margin;
-        if (us < tiles) return sliced.parts > 0 && r <= 16 && 1.2 * sliced.us < us ? ROUTE_SLICED : ROUTE_DIRECT;
+        if (us < tiles) {
+            if (!backward && single_beats(K, N, M, r, f16, us)) return ROUTE_SINGLE;
+            return sliced.parts > 0 && r <= 16 && 1.2 * sliced.us < us ? ROUTE_SLICED : ROUTE_DIRECT;
+        }
     }
-    return sliced.parts > 0 && 1.05 * sliced.us < tiles ? ROUTE_SLICED : ROUTE_TILES;
+    const bool slices = sliced.parts > 0 && 1.05 * sliced.us < tiles;
+    if (!backward && single_beats(K, N, M, r, f16, slices ? sliced.us : tiles)) return ROUTE_SINGLE;
+    return slices ? ROUTE_SLICED : ROUTE_TILES;
 }
 
 hipError_t launch_direct(const SmallArgs &a, bool backward, hipStream_t stream) {

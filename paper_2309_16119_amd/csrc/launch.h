@@ -410,9 +410,11 @@ bool smallm_fwd_supported(const LayerView &w, int M);
 bool smallm_bwd_supported(const LayerView &w, int M);
 size_t smallm_ws_bytes(int K, int N, int r);              // enough for both passes of any layer of this shape
 size_t smallm_fwd_ws_bytes(const LayerView &w, int r);    // what launch_smallm_fwd touches for this layer
-// single.hip: the forward call in one launch, for small layers that the streaming kernels take
+// single.hip: the forward call of a small layer in one launch, instead of the streaming kernels (single_wins()) or, with the
+// weight rounded as in every other kernel (`round`), of what is estimated to take `us`
 bool single_wins(const LayerView &w, int M, int r, bool f16);
-hipError_t launch_single(const SmallArgs &a, hipStream_t stream);
+bool single_beats(int K, int N, int M, int r, bool f16, double us);
+hipError_t launch_single(const SmallArgs &a, bool round, hipStream_t stream);
 hipError_t launch_smallm_fwd(const SmallArgs &a, hipStream_t stream);
 hipError_t launch_smallm_bwd(const SmallArgs &a, hipStream_t stream);
 
@@ -490,7 +492,7 @@ inline DirectPlan direct_plan(int M, int C, int Cout, bool backward) {
 // times do not cross there: 1056 x 4104 backward, 100 tokens 31 us with tiles, 18 direct).
 // Over 2^32 weights the kernel's 32-bit offsets would overflow.
 double direct_us(const DirectPlan &p, int M, int Cout, int r, bool backward, bool f16);      // estimated time of a call
-enum Route { ROUTE_TILES, ROUTE_DIRECT, ROUTE_SLICED };
+enum Route { ROUTE_TILES, ROUTE_DIRECT, ROUTE_SLICED, ROUTE_SINGLE };
 Route product_route(int K, int N, int M, int r, bool backward, bool f16);
 hipError_t launch_sliced(const SmallArgs &a, bool backward, hipStream_t stream);      // gemm_big.hip
 double gemm_tile_us(int M, int C, int Cout, int r, bool f16);      // gemm_tile.hip: estimated time of the cheapest tile kernel

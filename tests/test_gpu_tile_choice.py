@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
     ("bf16", "bwd", 3, 256, 4864, 1716, 0, 64, "gemm_bwd_128x256"),          # one column block, 52 rows in the last block
     ("f16", "fwd", 4, 768, 18304, 794, 0, 128, "f16_gemm_fwd"),              # more than 256 whole tiles, no adapter
     ("f16", "fwd", 3, 11648, 256, 1061, 0, 128, "f16_gemm_fwd"),             # 37 rows in the last block
-    ("bf16", "fwd", 4, 2304, 1040, 40, 16, 32, "gemm_fwd_direct"),           # 16 columns in the last block
+    ("bf16", "fwd", 4, 2560, 1040, 40, 16, 32, "gemm_fwd_direct"),           # 16 columns in the last block
     ("f16", "fwd", 3, 6912, 608, 25, 4, 64, "f16_gemm_fwd_direct"),
     ("bf16", "fwd", 2, 3328, 912, 458, 8, 128, "gemm_fwd_direct"),
     # sliced contractions with the projection as a side job: in idle units

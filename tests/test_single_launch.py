@@ -1,7 +1,7 @@
-"""The forward call of up to 15 tokens through a small layer in one launch (single.hip): either width of its
-workgroups, ranks that fill a group of 16 or not, ragged outputs, contractions of fewer units than waves and of
-several rounds.  Against the product with the unrounded weight in 64 bits, and against the two launches that larger
-token counts take."""
+"""The forward call of a small layer in one launch (single.hip): either width of its workgroups, ranks that fill a
+group of 16 or not, ragged rows and outputs, contractions of fewer units than waves and of several rounds.  Up to 15
+tokens against the product with the unrounded weight in 64 bits, and against the two launches that sixteen take;
+more tokens against the product with the rounded weight."""
 import pytest
 import torch
 
@@ -63,3 +63,55 @@ def test_one_launch(bits, K, N, M, r, group, conv):
     # sixteen tokens take two launches: the same rows to the same accuracy
     both = call(w, X, A, B, 2.0)[0][:M].double()
     assert bool(((both - ref).abs() <= tol).all())
+
+
+@pytest.mark.parametrize("conv", ["bf16", "f16"])
+@pytest.mark.parametrize("bits,K,N,M,r,group", [
+    (4, 256, 256, 17, 8, 64),          # two workgroups' rows, the second of one
+    (3, 256, 496, 252, 4, 32),         # groups of one block, a last row block of 28
+    (2, 384, 272, 33, 9, 64),
+    (4, 896, 2064, 48, 16, 32),        # a rank that fills its group
+    (3, 416, 1040, 100, 17, 416),      # one group per row, thirteen units
+    (2, 768, 272, 131, 64, 128),
+    (4, 1152, 528, 31, 1, 384),
+    (3, 1088, 272, 20, 0, 64),         # no adapter, 34 units
+    (3, 256, 5136, 70, 8, 128),        # workgroups of 64 columns, the last of 16
+    (2, 512, 4112, 64, 32, 64),
+    (4, 256, 7696, 40, 47, 64),
+])
+def test_one_launch_with_the_rounded_weight(bits, K, N, M, r, group, conv):
+    cfg = synth.LayerConfig("t", K, N, bits, group, M, max(r, 1))
+    L = synth.make_layer_torch(cfg, device="cuda", seed=31)
+    f16 = conv == "f16"
+    dtype, call = (torch.float16, b.modulora_f16_fwd) if f16 else (torch.bfloat16, b.modulora_fwd)
+    if f16:
+        bias = torch.randn(N, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1)).half()
+        w = b.QWeightF16(L["qweight"], L["scales"], -2 * L["scales"], bias, K, N, bits, group)
+        W = b.modulora_f16_dequant(w).double().t()
+    else:
+        w = b.QWeight(L["qweight"], L["scales"], L["zeros"], K, N, bits, group)
+        W = b.modulora_dequant(w).double().t()
+    A, B = (L["A"] * 3, L["B"] * 30) if r else (None, None)
+    X = torch.randn((M, K), device="cuda", generator=torch.Generator(device="cuda").manual_seed(2)).to(dtype)
+    out = torch.full((M, N), float("nan"), dtype=dtype, device="cuda")
+    b.modulora_profile_begin()
+    Y, XA = call(w, X, A, B, 2.0, out)
+    torch.cuda.synchronize()
+    assert set(b.modulora_profile_end()) == {("f16_" if f16 else "") + "gemm_fwd_single"}
+    X64 = X.double()
+    ref, mag = X64 @ W, X64.abs() @ W.abs()
+    if r:
+        down = X64 @ A.double()
+        assert bool(((XA.double() - down).abs() <= 2.0 ** -24 * (64 + K ** 0.5) * (X64.abs() @ A.double().abs())).all())
+        ref, mag = ref + 2 * down @ B.double(), mag + 2 * (X64.abs() @ A.double().abs()) @ B.double().abs()
+    if f16:
+        ref = ref + bias.double()
+    tol = (2.0 ** -11 if f16 else 2.0 ** -8) * ref.abs() + 2.0 ** -24 * (64 + K ** 0.5) * mag      # one rounding, fp32 sums
+    assert bool(((Y.double() - ref).abs() <= tol).all()), float(((Y.double() - ref).abs() / tol).max())
+    # a one-hot row picks a row of the weight, bit for bit
+    hot = torch.zeros((M, K), dtype=dtype, device="cuda")
+    hot[torch.arange(M), (torch.arange(M) * 37 + 5) % K] = 1.0
+    picked = W[(torch.arange(M, device="cuda") * 37 + 5) % K].to(dtype)
+    if f16:
+        picked = (picked.float() + bias.float()).half()
+    assert torch.equal(call(w, hot, None, None, 1.0)[0], picked)
