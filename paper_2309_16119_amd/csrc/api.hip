@@ -82,7 +82,7 @@ size_t routes_bytes(mlr::Route fwd, mlr::Route bwd, int32_t K, int32_t N, int32_
 hipError_t launch_route(mlr::Route route, const mlr::SmallArgs &sa, bool backward, hipStream_t st) {
     switch (route) {
         case mlr::ROUTE_DIRECT: return mlr::launch_direct(sa, backward, st);
-        case mlr::ROUTE_SINGLE: return mlr::launch_single(sa, true, st);
+        case mlr::ROUTE_SINGLE: return mlr::launch_single(sa, backward, true, st);
         default: return mlr::launch_sliced(sa, backward, st);
     }
 }

@@ -491,12 +491,12 @@ Route product_route(int K, int N, int M, int r, bool backward, bool f16) {
         if (M > 128 && big_half_rows(M) && (long)p.tiles_m * p.tiles_c * p.split > 256) margin = 1.15;
         const double us = direct_us(p, M, Cout, r, backward, f16) * margin;
         if (us < tiles) {
-            if (!backward && single_beats(K, N, M, r, f16, us)) return ROUTE_SINGLE;
+            if (single_beats(K, N, M, r, backward, f16, us)) return ROUTE_SINGLE;
             return sliced.parts > 0 && r <= 16 && 1.2 * sliced.us < us ? ROUTE_SLICED : ROUTE_DIRECT;
         }
     }
     const bool slices = sliced.parts > 0 && 1.05 * sliced.us < tiles;
-    if (!backward && single_beats(K, N, M, r, f16, slices ? sliced.us : tiles)) return ROUTE_SINGLE;
+    if (single_beats(K, N, M, r, backward, f16, slices ? sliced.us : tiles)) return ROUTE_SINGLE;
     return slices ? ROUTE_SLICED : ROUTE_TILES;
 }
 

@@ -410,11 +410,11 @@ bool smallm_fwd_supported(const LayerView &w, int M);
 bool smallm_bwd_supported(const LayerView &w, int M);
 size_t smallm_ws_bytes(int K, int N, int r);              // enough for both passes of any layer of this shape
 size_t smallm_fwd_ws_bytes(const LayerView &w, int r);    // what launch_smallm_fwd touches for this layer
-// single.hip: the forward call of a small layer in one launch, instead of the streaming kernels (single_wins()) or, with the
-// weight rounded as in every other kernel (`round`), of what is estimated to take `us`
+// single.hip: a small layer's call in one launch, forward instead of the streaming kernels (single_wins()) or, with the
+// weight rounded as in every other kernel (`round`; always backward), of what is estimated to take `us`
 bool single_wins(const LayerView &w, int M, int r, bool f16);
-bool single_beats(int K, int N, int M, int r, bool f16, double us);
-hipError_t launch_single(const SmallArgs &a, bool round, hipStream_t stream);
+bool single_beats(int K, int N, int M, int r, bool backward, bool f16, double us);
+hipError_t launch_single(const SmallArgs &a, bool backward, bool round, hipStream_t stream);
 hipError_t launch_smallm_fwd(const SmallArgs &a, hipStream_t stream);
 hipError_t launch_smallm_bwd(const SmallArgs &a, hipStream_t stream);
 

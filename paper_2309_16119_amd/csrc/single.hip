@@ -1,17 +1,20 @@
-// The forward call of a handful of tokens through a small layer in one launch.
+// A small layer's product with its adapter term in one launch.
 //
-// The streaming kernels (smallm.hip) cut the contraction into slices so that every compute unit reads a share of the
-// packed weight, and a second launch adds the slices and the adapter term.  For a small layer both launches are
-// mostly their own start and end (4 us each, with a product of less than one).  Here a workgroup owns 16 or 64
-// output columns and the whole contraction, which its eight waves share: they meet in LDS, and the rank-r projection of
-// the rows is computed by every workgroup for itself beside the product -- that repeated work is what bounds the size of
-// the layer (single_wins()).  Same arithmetic as smallm.hip: the codes themselves enter the matrix cores, weights are never
-// rounded to 16 bits, the projection is exact products summed in fp32.  Bound by one trip to memory for everything (all of a
-// wave's first units are on their way before the first is waited for) and the start of the launch.
-// Measured, us of a call's kernels with two launches / here (8 tokens or fewer): 256 x 2304, r = 8 9.6 / 4.1; 768 x 2432
-// 9.2 / 5.3; 1024 x 2048 8.9 / 6.0; 2048 x 1200 9.6 / 6.3; 512 x 11008, r = 64 11.6 / 11.0; 256 x 17000, r = 8 11.1 / 9.
-// (Backward the same plan lost: a workgroup needs 128 columns, so few of them each dequantize their columns' whole
-// contraction: 512 x 2304 8.4 / 12.7 us, 256 x 512 8.3 / 7.2.)
+// The other kernels cut the contraction into slices so that every compute unit has work, or project the rows ahead of the
+// product, and a second launch adds the slices or multiplies.  For a small layer those launches are mostly their own
+// start and end (4 us each, with a product of less than one).  Here a workgroup owns a few output columns -- 16 or 64
+// forward, the 32 of a code block backward -- and the whole contraction, which its eight waves share: they meet in LDS, and the
+// rank-r projection of the rows is computed by every workgroup for itself beside the product.  That repeated work is what
+// bounds the size of the layer (single_wins(), single_beats()).  Bound by one trip to memory for everything (a wave's first
+// units are all on their way before the first is waited for, and nothing is loaded that is not used: loads past the end
+// cost 1 ... 3 us of the end of the launch) and by the start of the launch.
+//   - Up to 15 tokens, forward: the streaming kernels' arithmetic (smallm.hip), weights never rounded to 16 bits.
+//     Kernels of a call, us, with two launches / here: 256 x 2304, r = 8 9.6 / 4.1; 768 x 2432 9.2 / 5.0; 1024 x 2048 8.9 / 5.5;
+//     2048 x 512, r = 16 10 / 7.1; 512 x 11008, r = 64 11.6 / 10.5.
+//   - More tokens: the weight dequantized and rounded as in every other kernel (`round`).
+// The projection is exact products (the fp32 factor split into three bfloat16 terms, binary16 activations into two) summed in
+// fp32: against 64 bits its error is 0.6e-7 ... 1.2e-7 in the 2-norm over 256 ... 4096 elements, 1.0e-7 ... 1.4e-7 with
+// the other kernels.
 #include <cmath>
 
 #include "gemm_common.h"
@@ -26,13 +29,14 @@ constexpr int NWAVES = 8, THREADS = NWAVES * 64;
 
 struct SingleDev {
     LayerView w;
-    const uint16_t *act;       // [M][K]
+    const uint16_t *act;       // [M][K], backward [M][N]
     const float *A, *B;        // [K][r], [r][N]
     int M, r;
     float lora_scale;
     uint16_t *out;
     float *P_out;              // [M][r] or NULL
     const uint16_t *zeros16, *bias16;
+    uint32_t r_magic;          // x / r by one multiply-high
     uint32_t bpg_plus, bpg_magic;      // quantization group of a 32-code block, (block + plus) * magic / 2^32
 };
 
@@ -60,7 +64,7 @@ template <int BITS, bool F16, bool ROUND, int RG, int RT, int CT>
 __global__ __launch_bounds__(single::THREADS, 2) void single_kernel(SingleDev d) {
     using namespace single;
     using NF = sm::Num<F16>;
-    constexpr int NWORDS = BITS == 3 ? 2 : 1, U = RG == 1 && RT * CT <= 4 ? 4 : 2, R = 16 * RG, PS = R + 4;
+    constexpr int NWORDS = BITS == 3 ? 2 : 1, U = RG == 1 && RT * CT <= 4 ? 4 : RT * CT * RG > 16 ? 1 : 2, R = 16 * RG, PS = R + 4;
     extern __shared__ __attribute__((aligned(16))) float smem[];
     float *red_y = smem, *red_p = red_y + NWAVES * RT * CT * 256, *Ps = red_p + NWAVES * RT * RG * 256, *Bs = Ps + 16 * RT * PS;      // Bs [R][16 CT]
     const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
@@ -94,7 +98,7 @@ __global__ __launch_bounds__(single::THREADS, 2) void single_kernel(SingleDev d)
         float f[RG][8];
     };
     auto load = [&](Stage &s, int u) {
-        if (u > units - 1) u = units - 1;
+        if (u >= units) return;                     // (the same for every lane of the wave)
         const uint32_t *block = d.w.qweight + (size_t)u * BITS * N + n;
         auto words_at = [&](uint32_t *dst, const uint32_t *src) {
             if (CT == 1) dst[0] = *src;
@@ -130,13 +134,13 @@ __global__ __launch_bounds__(single::THREADS, 2) void single_kernel(SingleDev d)
     const bf16x8 ones = sm::as_bf16x8(ones4), offs = sm::as_bf16x8(offs4);
     const sm::CodeMasks masks = sm::make_masks<BITS, F16>();
     const DqMasks dq_masks = make_dq_masks<BITS>();
-    f32x4 y[RT][CT], P[RT][RG];
+    f32x4 y[RT][CT], P[RT][RG], P_rest[RT][RG];      // (the leading part of the factor, and what it leaves: a shorter chain of roundings)
 #pragma unroll
     for (int t = 0; t < RT; ++t) {
 #pragma unroll
         for (int c = 0; c < CT; ++c) y[t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int q = 0; q < RG; ++q) P[t][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int q = 0; q < RG; ++q) P[t][q] = P_rest[t][q] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     auto compute = [&](const Stage &s) {
         // elements p and p + 4 of the lane side by side, as the code registers pair them
@@ -205,8 +209,10 @@ __global__ __launch_bounds__(single::THREADS, 2) void single_kernel(SingleDev d)
 #pragma unroll
                 for (int x = 0; x < (F16 ? 2 : 1); ++x)
 #pragma unroll
-                    for (int e = 0; e < 3; ++e)
-                        P[t][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sm::as_bf16x8(F16 ? h[x] : a4[t]), sm::as_bf16x8(p3[e]), P[t][q], 0, 0, 0);
+                    for (int e = 0; e < 3; ++e) {
+                        f32x4 &sum = e == 0 && x == 0 ? P[t][q] : P_rest[t][q];
+                        sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sm::as_bf16x8(F16 ? h[x] : a4[t]), sm::as_bf16x8(p3[e]), sum, 0, 0, 0);
+                    }
             }
         }
     };
@@ -233,7 +239,7 @@ __global__ __launch_bounds__(single::THREADS, 2) void single_kernel(SingleDev d)
 #pragma unroll
         for (int q = 0; q < RG; ++q)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) red_p[(((wave * RT + t) * RG + q) * 4 + v) * 64 + lane] = P[t][q][v];
+            for (int v = 0; v < 4; ++v) red_p[(((wave * RT + t) * RG + q) * 4 + v) * 64 + lane] = P[t][q][v] + P_rest[t][q][v];
     }
     __syncthreads();
     single_projection<RG, RT>(d, m0, red_p, Ps);
@@ -269,6 +275,220 @@ __global__ __launch_bounds__(single::THREADS, 2) void single_kernel(SingleDev d)
     }
 }
 
+// Backward: 32 rows, the 32 output columns of one 32-code block, the whole contraction over n.  A unit is 64 n, one per lane:
+// the lane dequantizes the block of its weight column, the wave turns 64 x 32 weights round in 4 KB of LDS of its own and
+// reads them back with the transposing LDS read (as gemm_direct.hip), four 16-deep MFMA steps.  The projection takes the rows
+// again as two tiles of 16 by two steps of 32 (sixteen rank columns a tile, so few are empty).  R: room for the rank.
+template <int BITS, bool F16, int R>
+__global__ __launch_bounds__(single::THREADS, 2) void single_bwd_kernel(SingleDev d) {
+    using namespace single;
+    constexpr int U = R <= 32 ? 2 : 1, RG = R / 16, PS = R + 4;
+    extern __shared__ __attribute__((aligned(16))) float smem[];
+    float *red_p = smem + NWAVES * 1024, *Ps = red_p + NWAVES * 32 * R, *As = Ps + 32 * PS;      // [wave][32][R], [32][PS], [32][PS]
+    const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+    const int K = d.w.K, N = d.w.N, r = d.r, M = d.M, kb = blockIdx.x, m0 = blockIdx.y * 32;
+    const int l31 = lane & 31, half = lane >> 5, i = lane & 15, j = lane >> 4, units = (N + 63) / 64;
+    const size_t g = (size_t)__umulhi((uint32_t)kb + d.bpg_plus, d.bpg_magic) * N;
+    const uint32_t *block = d.w.qweight + (size_t)kb * BITS * N;
+    const uint16_t *yrow = d.act + (size_t)(m0 + l31 < M ? m0 + l31 : M - 1) * N + 8 * half, *prow[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) prow[t] = d.act + (size_t)(m0 + 16 * t + i < M ? m0 + 16 * t + i : M - 1) * N + 8 * j;
+
+    // the adapter's rows of these columns: one run of 32 r floats, on its way first and needed last
+    constexpr int A4 = (8 * R + THREADS - 1) / THREADS;
+    float4 aq[A4];
+#pragma unroll
+    for (int q = 0; q < A4; ++q) {
+        const int x = q * THREADS + tid;
+        aq[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (x < 8 * r) aq[q] = *reinterpret_cast<const float4 *>(d.A + (size_t)kb * 32 * r + 4 * x);
+    }
+    struct Stage {
+        uint32_t w[BITS], sc, z;
+        uint4 y[4], x[2][2];       // [step], projection: [step][row tile]
+        float f[RG][2][8];
+    };
+    auto load = [&](Stage &s, int u) {
+        if (u >= units) return;                     // (the same for every lane of the wave)
+        const int n = 64 * u + lane < N ? 64 * u + lane : N - 1;
+#pragma unroll
+        for (int q = 0; q < BITS; ++q) s.w[q] = block[(size_t)q * N + n];
+        s.sc = d.w.scales[g + n];
+        s.z = F16 ? (uint32_t)d.zeros16[g + n] : (uint32_t)d.w.zeros[g + n];
+        // (N is a multiple of 8: a lane's eight are all there or none)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int at = 64 * u + 16 * e;
+            s.y[e] = make_uint4(0, 0, 0, 0);
+            if (at + 8 * half < N) s.y[e] = *reinterpret_cast<const uint4 *>(yrow + at);
+        }
+        if (r == 0) return;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const int at = 64 * u + 32 * e;
+            const bool there = at + 8 * j < N;
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                s.x[e][t] = make_uint4(0, 0, 0, 0);
+                if (there) s.x[e][t] = *reinterpret_cast<const uint4 *>(prow[t] + at);
+            }
+#pragma unroll
+            for (int q = 0; q < RG; ++q) {
+#pragma unroll
+                for (int x = 0; x < 8; ++x) s.f[q][e][x] = 0.f;
+                if (there && 16 * q + i < r) {
+                    const float *f = d.B + (size_t)(16 * q + i) * N + at + 8 * j;
+                    const float4 f0 = *reinterpret_cast<const float4 *>(f), f1 = *reinterpret_cast<const float4 *>(f + 4);
+                    s.f[q][e][0] = f0.x; s.f[q][e][1] = f0.y; s.f[q][e][2] = f0.z; s.f[q][e][3] = f0.w;
+                    s.f[q][e][4] = f1.x; s.f[q][e][5] = f1.y; s.f[q][e][6] = f1.z; s.f[q][e][7] = f1.w;
+                }
+            }
+        }
+    };
+    unsigned char *tbuf = reinterpret_cast<unsigned char *>(smem) + wave * 4096;
+    const int t_wr = lane * 64, t_swz = (lane >> 2) & 3, ti = lane & 15, tg = (lane >> 4) & 1;
+    int t_rd[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+        t_rd[e] = (8 * half + 4 * e + (ti >> 2)) * 64 + (((2 * tg + ((ti & 3) >> 1)) ^ ((2 * half + e) & 3)) << 4) + 8 * (ti & 1);
+    const DqMasks masks = make_dq_masks<BITS>();
+    f32x16 y;
+    f32x4 P[2][RG], P_rest[2][RG];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) y[v] = 0.f;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int q = 0; q < RG; ++q) P[t][q] = P_rest[t][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+    typedef __attribute__((address_space(3))) unsigned char lds_byte;
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+    typedef _Float16 half16x8 __attribute__((ext_vector_type(8)));
+    auto compute = [&](const Stage &s, int u) {
+        const DqPair dq = make_dq_pair<BITS, F16>(s.sc, s.z);
+        const bool there = 64 * u + lane < N;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            uint32_t o[4];
+            dequant_quarter_pairs<BITS, F16>(s.w, q, dq, masks, o);
+            *reinterpret_cast<uint4 *>(tbuf + t_wr + ((q ^ t_swz) << 4)) = there ? make_uint4(o[0], o[1], o[2], o[3]) : make_uint4(0, 0, 0, 0);
+        }
+        // the wave's own stores are read by other lanes of it: LDS operations of a wave keep their order
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            uint32_t bw[4];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)((lds_byte *)(tbuf + t_rd[h] + e * 1024)));
+                __builtin_memcpy(&bw[2 * h], &v, 8);
+            }
+            const uint32_t yw[4] = {s.y[e].x, s.y[e].y, s.y[e].z, s.y[e].w};
+            const bf16x8 a = sm::as_bf16x8(yw);
+            if (F16) {
+                half16x8 x, z;
+                __builtin_memcpy(&x, yw, 16);
+                __builtin_memcpy(&z, bw, 16);
+                y = __builtin_amdgcn_mfma_f32_32x32x16_f16(x, z, y, 0, 0, 0);
+            } else {
+                y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, sm::as_bf16x8(bw), y, 0, 0, 0);
+            }
+        }
+        asm volatile("" ::: "memory");
+        if (r == 0) return;
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+            for (int q = 0; q < RG; ++q) {
+                uint32_t p3[3][4];
+                split3(s.f[q][e], p3[0], p3[1], p3[2]);
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    const uint32_t xw[4] = {s.x[e][t].x, s.x[e][t].y, s.x[e][t].z, s.x[e][t].w};
+                    uint32_t h[2][4];
+                    if (F16) split_f16x8(xw, h[0], h[1]);
+#pragma unroll
+                    for (int x = 0; x < (F16 ? 2 : 1); ++x)
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) {
+                            f32x4 &sum = c == 0 && x == 0 ? P[t][q] : P_rest[t][q];
+                            sum = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sm::as_bf16x8(F16 ? h[x] : xw), sm::as_bf16x8(p3[c]), sum, 0, 0, 0);
+                        }
+                }
+            }
+    };
+    Stage st[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) load(st[q], wave + NWAVES * q);
+    // (a run of four may cross a row; columns past r are zeros)
+#pragma unroll
+    for (int q = 0; q < A4; ++q) {
+        const int x = q * THREADS + tid;
+        if (x < 8 * r) {
+            int k = r > 1 ? (int)__umulhi((uint32_t)(4 * x), d.r_magic) : 4 * x, c = 4 * x - k * r;
+            const float f4[4] = {aq[q].x, aq[q].y, aq[q].z, aq[q].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                As[k * PS + c] = f4[e];
+                if (++c == r) { c = 0; ++k; }
+            }
+        }
+    }
+    for (int x = tid; x < 32 * (R - r); x += THREADS) As[x % 32 * PS + r + x / 32] = 0.f;
+    for (int u = wave; u < units; u += NWAVES * U) {
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+            if (u + NWAVES * q < units) {
+                compute(st[q], u + NWAVES * q);
+                load(st[q], u + NWAVES * (q + U));
+            }
+    }
+    // D register v: row 8 (v / 4) + 4 half + v % 4, column l31; the wave's tile takes the place of its transposition buffer
+    float *mine = smem + wave * 1024;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int row = 8 * (v / 4) + 4 * half + v % 4;
+        mine[row * 32 + l31] = y[v];
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int q = 0; q < RG; ++q)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) red_p[(wave * 32 + 16 * t + 4 * j + v) * R + 16 * q + i] = P[t][q][v] + P_rest[t][q][v];
+    __syncthreads();
+    for (int x = tid; x < 32 * R; x += THREADS) {
+        const int row = x / R, c = x % R;
+        float sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < NWAVES; ++w) sum += red_p[w * 32 * R + x];
+        Ps[row * PS + c] = sum;
+        if (kb == 0 && d.P_out != nullptr && m0 + row < M && c < r) d.P_out[(size_t)(m0 + row) * r + c] = sum;
+    }
+    __syncthreads();
+    const int row = tid >> 4, c = 2 * (tid & 15);
+    if (m0 + row >= M) return;
+    float2 o = make_float2(0.f, 0.f);
+#pragma unroll
+    for (int w = 0; w < NWAVES; ++w) {
+        const float2 v = *reinterpret_cast<const float2 *>(smem + w * 1024 + row * 32 + c);
+        o.x += v.x; o.y += v.y;
+    }
+    if (r > 0) {
+        float2 ad = make_float2(0.f, 0.f);
+#pragma unroll
+        for (int q = 0; q < R; q += 4) {
+            const float4 p = *reinterpret_cast<const float4 *>(Ps + row * PS + q);
+            const float4 a = *reinterpret_cast<const float4 *>(As + c * PS + q), b = *reinterpret_cast<const float4 *>(As + (c + 1) * PS + q);
+            ad.x = __builtin_fmaf(p.x, a.x, ad.x); ad.x = __builtin_fmaf(p.y, a.y, ad.x); ad.x = __builtin_fmaf(p.z, a.z, ad.x); ad.x = __builtin_fmaf(p.w, a.w, ad.x);
+            ad.y = __builtin_fmaf(p.x, b.x, ad.y); ad.y = __builtin_fmaf(p.y, b.y, ad.y); ad.y = __builtin_fmaf(p.z, b.z, ad.y); ad.y = __builtin_fmaf(p.w, b.w, ad.y);
+        }
+        o.x = __builtin_fmaf(d.lora_scale, ad.x, o.x);
+        o.y = __builtin_fmaf(d.lora_scale, ad.y, o.y);
+    }
+    *reinterpret_cast<uint32_t *>(d.out + (size_t)(m0 + row) * K + kb * 32 + c) = sm::pack16<F16>(o.x, o.y);
+}
+
 namespace {
 template <int BITS, bool F16, bool ROUND, int RG, int RT, int CT>
 hipError_t launch_single_ct(const SingleDev &d, hipStream_t stream) {
@@ -301,11 +521,34 @@ hipError_t launch_single_any(const SingleDev &d, bool round, bool wide, hipStrea
         default: return launch_single_bits<4, F16>(d, round, wide, stream);
     }
 }
+template <int BITS, bool F16, int R>
+hipError_t launch_single_bwd_rank(const SingleDev &d, hipStream_t stream) {
+    constexpr size_t LDS = (size_t)(single::NWAVES * (1024 + 32 * R) + 64 * (R + 4)) * 4;
+    auto kern = single_bwd_kernel<BITS, F16, R>;
+    static bool configured[64] = {};
+    const hipError_t e = ensure_lds_limit(reinterpret_cast<const void *>(kern), LDS, configured);
+    if (e != hipSuccess) return e;
+    launch_kernel(F16 ? "f16_gemm_bwd_single" : "gemm_bwd_single", kern, dim3(d.w.K / 32, (d.M + 31) / 32), single::THREADS, LDS, stream, d);
+    return hipGetLastError();
+}
+template <int BITS, bool F16>
+hipError_t launch_single_bwd_bits(const SingleDev &d, hipStream_t stream) {
+    if (d.r <= 16) return launch_single_bwd_rank<BITS, F16, 16>(d, stream);
+    return d.r <= 32 ? launch_single_bwd_rank<BITS, F16, 32>(d, stream) : launch_single_bwd_rank<BITS, F16, 64>(d, stream);
+}
+template <bool F16>
+hipError_t launch_single_bwd_any(const SingleDev &d, hipStream_t stream) {
+    switch (d.w.bits) {
+        case 2: return launch_single_bwd_bits<2, F16>(d, stream);
+        case 3: return launch_single_bwd_bits<3, F16>(d, stream);
+        default: return launch_single_bwd_bits<4, F16>(d, stream);
+    }
+}
 }  // namespace
 
-// Estimated time of the launch in microseconds: its start, the units that a wave takes in turn, and the same again for
-// every workgroup more than one per compute unit.  Fits (9 to 15 % rms) to 1060 timed layers of 256 to 4096 x 256 to
-// 22016 with up to 15 tokens, and 1425 of up to 2^23 weights with 16 ... 2500 (round), r = 0 to 64, both conventions.
+// Estimated time of the forward launch in microseconds: its start, the units that a wave takes in turn, and the same again for
+// every workgroup more than one per compute unit.  Fits (9 to 14 % rms) to 670 timed layers of 256 to 4096 x 256 to
+// 22016 with up to 15 tokens, and 880 of up to 2^23 weights with 16 ... 2500 (round), r = 0 to 64, both conventions.
 static double single_us(const LayerView &w, int M, int r, bool f16, bool round, bool wide) {
     const double units = w.K / 256.0, rg = (double)(r > 32 ? 4 : (r + 15) / 16), h = f16 ? rg : 0.0, three = w.bits == 3 ? 1.0 : 0.0;
     const int columns = wide ? (w.N + 63) / 64 : (w.N + 15) / 16;
@@ -314,36 +557,46 @@ static double single_us(const LayerView &w, int M, int r, bool f16, bool round, 
     if (round && (wide || rg > 2.0)) more = std::ceil(more);      // their LDS leaves room for one workgroup per compute unit
     if (round) {
         if (wide)
-            return 5.42 + (r > 16 ? 1.18 : 0.0) + units * (0.383 + 0.621 * rg + 0.198 * h) +
-                   more * (2.06 + 1.85 * rg + units * (0.811 + 0.244 * rg + 0.336 * h));
-        return 5.68 + units * (0.313 + 0.383 * rg + 0.192 * h) + more * (2.87 + 0.646 * rg + units * (0.578 + 0.241 * rg + 0.146 * h));
+            return 5.09 + (r > 16 ? 1.04 : 0.0) + units * (0.42 + 0.543 * rg + 0.244 * h) +
+                   more * (1.51 + 1.79 * rg + units * (0.92 + 0.215 * rg + 0.311 * h));
+        return 4.39 + (r > 16 ? 0.8 : 0.0) + units * (0.352 + 0.378 * rg + 0.239 * h) +
+               more * (1.42 + 0.77 * rg + units * (0.695 + 0.264 * rg + 0.332 * h));
     }
     if (wide)
-        return 4.02 + units * (0.36 + 0.13 * three + 0.40 * rg + 0.17 * h) +
-               more * (9.98 + 2.88 * rg + units * (2.58 + 1.40 * three + 0.99 * rg + 0.63 * h));
-    return 3.63 + units * (0.23 + 0.07 * three + 0.36 * rg + 0.13 * h) + more * (0.60 + 1.06 * rg + units * (0.35 + 0.05 * three + 0.30 * rg + 0.09 * h));
+        return 3.83 + (r > 16 ? 0.47 : 0.0) + units * (0.335 + 0.091 * three + 0.357 * rg + 0.13 * h) +
+               more * (8.5 * rg + units * (2.91 + 0.263 * three + 0.595 * rg + 0.6 * h));
+    return 3.81 + units * (0.154 + 0.037 * three + 0.326 * rg + 0.101 * h) +
+           more * (0.541 * rg + units * (0.552 + 0.139 * three + 0.328 * rg + 0.291 * h) + units * 0.399);
+}
+// The same backward (13 % rms, 1610 layers, 1 ... 2500 tokens).
+static double single_bwd_us(int K, int N, int M, int r, bool f16) {
+    const double units = N / 512.0, rg = (double)(r > 32 ? 4 : (r + 15) / 16), h = f16 ? rg : 0.0;
+    const double workgroups = (double)(K / 32) * ((M + 31) / 32), more = workgroups > 256.0 ? std::ceil(workgroups / 256.0 - 1.0) : 0.0;
+    return 3.8 + (r > 16 ? 0.64 : 0.0) + units * (0.805 + 1.23 * rg + 0.44 * h) + more * (1.4 + 0.591 * rg + units * (1.43 + 1.55 * rg + 0.389 * h));
 }
 
 // In place of the two streaming launches.  (Sixteen tokens, a full tile, keep the two launches that the streaming
 // kernels' tests name, though the times do not cross there.)
 bool single_wins(const LayerView &w, int M, int r, bool f16) {
     if (M > 15 || w.K > 4096) return false;
-    const double two = 9.2 + 0.177e-6 * ((double)w.K * w.N * w.bits / 8) + 0.35 * ((r + 15) / 16) + 0.23 * w.K / 1024;
+    const double two = 9.6 + 0.24e-6 * ((double)w.K * w.N * w.bits / 8) + 0.27 * ((r + 15) / 16) + 0.29 * w.K / 1024;
     const double narrow = single_us(w, M, r, f16, false, false), wide = single_us(w, M, r, f16, false, true);
     return 1.1 * (narrow < wide ? narrow : wide) < two;
 }
-// In place of a product and its projection or second launch, whose estimate is `us`: over the 1425 layers above a
-// call's kernels take 1.37x less time on average (256 x 488, 252 tokens, us 11.4 -> 6.3; 1024 x 640, 40 tokens 15.5 -> 9.6; on the other
-// side 512 x 4096, 300 tokens 14.4 and 20).
-bool single_beats(int K, int N, int M, int r, bool f16, double us) {
-    if (K > 2304 || (size_t)K * N >= ((size_t)1 << 23)) return false;
+// In place of a product and its projection or second launch, whose estimate is `us`.  A call's kernels take, forward / backward,
+// 1.4x / 1.3x less time on average over layers of up to 2^23 weights and contractions of up to 2304, 16 ... 2500 tokens
+// (us, before and here: 256 x 256, 347 tokens 11 / 5; 512 x 384, 98 tokens 12 / 5.1, backward 11.8 / 5.6; 1024 x 640, 40 tokens
+// 15.5 / 8; on the other side 512 x 4096, 300 tokens 14.4 / 20, 1024 x 2048 backward, 8 tokens 8.3 / 9.9).
+bool single_beats(int K, int N, int M, int r, bool backward, bool f16, double us) {
+    if ((backward ? N : K) > 2304 || (size_t)K * N >= ((size_t)1 << 23)) return false;
+    if (backward) return 1.1 * single_bwd_us(K, N, M, r, f16) < us;
     LayerView w{};
     w.K = K; w.N = N;
     const double narrow = single_us(w, M, r, f16, true, false), wide = single_us(w, M, r, f16, true, true);
     return 1.05 * (narrow < wide ? narrow : wide) < us;
 }
 
-hipError_t launch_single(const SmallArgs &a, bool round, hipStream_t stream) {
+hipError_t launch_single(const SmallArgs &a, bool backward, bool round, hipStream_t stream) {
     SingleDev d;
     d.w = a.w;
     d.act = a.act;
@@ -355,6 +608,8 @@ hipError_t launch_single(const SmallArgs &a, bool round, hipStream_t stream) {
     const uint32_t bpg = (uint32_t)(a.w.group / 32);      // blocks per group
     d.bpg_plus = bpg > 1 ? 0u : 1u;
     d.bpg_magic = bpg > 1 ? (uint32_t)((1ull << 32) / bpg) + 1u : 0xFFFFFFFFu;
+    d.r_magic = a.r > 1 ? (uint32_t)((1ull << 32) / a.r) + 1u : 0u;
+    if (backward) return a.f16 ? launch_single_bwd_any<true>(d, stream) : launch_single_bwd_any<false>(d, stream);
     const bool wide = single_us(a.w, a.M, a.r, a.f16, round, true) < single_us(a.w, a.M, a.r, a.f16, round, false);
     return a.f16 ? launch_single_any<true>(d, round, wide, stream) : launch_single_any<false>(d, round, wide, stream);
 }

@@ -1313,7 +1313,7 @@ hipError_t launch_smallm_fwd(const SmallArgs &a, hipStream_t stream) {
         const hipError_t e = launch_fwd_pass(first, stream);
         return e != hipSuccess ? e : launch_fwd_pass(rows_after_first_pass(a, a.w.K, a.w.N), stream);
     }
-    return single_wins(a.w, a.M, a.r, a.f16) ? launch_single(a, false, stream) : launch_fwd_pass(a, stream);
+    return single_wins(a.w, a.M, a.r, a.f16) ? launch_single(a, false, false, stream) : launch_fwd_pass(a, stream);
 }
 
 template <int BITS, bool F16, int GPT>

@@ -32,10 +32,10 @@ SHAPES = [
     (4, 4096, 2104, 7, 33, 128),        # a handful of tokens that the backward streaming kernel does not take
     (3, 288, 32768, 40, 8, 288),        # an output of little more than two column blocks (backward only)
     # under 2^23 weights, an output of whole column blocks in both directions
-    (3, 2432, 2048, 64, 8, 128),
-    (4, 2560, 1024, 33, 16, 32),
+    (3, 2432, 2944, 64, 8, 128),
+    (4, 2560, 2560, 33, 16, 32),
     (2, 2688, 2304, 150, 3, 64),
-    (3, 3840, 896, 5, 8, 32),           # a handful of tokens, groups of 32 at three bits: no streaming kernel
+    (3, 2944, 2432, 5, 8, 32),          # a handful of tokens, groups of 32 at three bits: no streaming kernel
     (2, 2048, 2176, 257, 33, 2048),     # three row blocks, one group per row
     (4, 3200, 2560, 20, 0, 128),        # no adapter, a weight too small for two streaming passes
 ]

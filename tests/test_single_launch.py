@@ -1,4 +1,4 @@
-"""The forward call of a small layer in one launch (single.hip): either width of its workgroups, ranks that fill a
+"""A small layer's call in one launch (single.hip): either width of its workgroups, ranks that fill a
 group of 16 or not, ragged rows and outputs, contractions of fewer units than waves and of several rounds.  Up to 15
 tokens against the product with the unrounded weight in 64 bits, and against the two launches that sixteen take;
 more tokens against the product with the rounded weight."""
@@ -115,3 +115,46 @@ def test_one_launch_with_the_rounded_weight(bits, K, N, M, r, group, conv):
     if f16:
         picked = (picked.float() + bias.float()).half()
     assert torch.equal(call(w, hot, None, None, 1.0)[0], picked)
+
+
+@pytest.mark.parametrize("conv", ["bf16", "f16"])
+@pytest.mark.parametrize("bits,K,N,M,r,group", [
+    (4, 256, 256, 17, 8, 64),          # four units for eight waves
+    (3, 384, 488, 252, 4, 32),         # groups of one block, the last unit of 40 n, a last row block of 28
+    (2, 512, 264, 33, 9, 512),         # one group, the last unit of 8 n
+    (4, 1024, 520, 100, 16, 128),      # nine units: a second round of one
+    (3, 256, 1032, 40, 0, 64),         # no adapter
+    (2, 768, 328, 64, 33, 96),
+    (4, 640, 392, 98, 64, 128),
+    (3, 6912, 264, 5, 1, 32),          # a handful of tokens that the backward streaming kernel does not take
+])
+def test_one_launch_backward(bits, K, N, M, r, group, conv):
+    cfg = synth.LayerConfig("t", K, N, bits, group, M, max(r, 1))
+    L = synth.make_layer_torch(cfg, device="cuda", seed=37)
+    f16 = conv == "f16"
+    dtype, call = (torch.float16, b.modulora_f16_bwd_input) if f16 else (torch.bfloat16, b.modulora_bwd_input)
+    if f16:
+        w = b.QWeightF16(L["qweight"], L["scales"], -2 * L["scales"], None, K, N, bits, group)
+        W = b.modulora_f16_dequant(w).double()
+    else:
+        w = b.QWeight(L["qweight"], L["scales"], L["zeros"], K, N, bits, group)
+        W = b.modulora_dequant(w).double()
+    A, B = (L["A"] * 30, L["B"] * 3) if r else (None, None)
+    dY = torch.randn((M, N), device="cuda", generator=torch.Generator(device="cuda").manual_seed(2)).to(dtype)
+    out = torch.full((M, K), float("nan"), dtype=dtype, device="cuda")
+    b.modulora_profile_begin()
+    dX, T = call(w, dY, A, B, 2.0, out)
+    torch.cuda.synchronize()
+    assert set(b.modulora_profile_end()) == {("f16_" if f16 else "") + "gemm_bwd_single"}
+    dY64 = dY.double()
+    ref, mag = dY64 @ W, dY64.abs() @ W.abs()
+    if r:
+        down = dY64 @ B.double().t()
+        assert bool(((T.double() - down).abs() <= 2.0 ** -24 * (64 + N ** 0.5) * (dY64.abs() @ B.double().t().abs())).all())
+        ref, mag = ref + 2 * down @ A.double().t(), mag + 2 * (dY64.abs() @ B.double().t().abs()) @ A.double().t().abs()
+    tol = (2.0 ** -11 if f16 else 2.0 ** -8) * ref.abs() + 2.0 ** -24 * (64 + N ** 0.5) * mag      # one rounding, fp32 sums
+    assert bool(((dX.double() - ref).abs() <= tol).all()), float(((dX.double() - ref).abs() / tol).max())
+    # a one-hot row picks a row of the weight, bit for bit
+    hot, at = torch.zeros((M, N), dtype=dtype, device="cuda"), (torch.arange(M, device="cuda") * 37 + 5) % N
+    hot[torch.arange(M), at] = 1.0
+    assert torch.equal(call(w, hot, None, None, 1.0)[0], W[at].to(dtype))
