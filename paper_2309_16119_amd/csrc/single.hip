@@ -548,13 +548,17 @@ hipError_t launch_single_bwd_any(const SingleDev &d, hipStream_t stream) {
 
 // Estimated time of the forward launch in microseconds: its start, the units that a wave takes in turn, and the same again for
 // every workgroup more than one per compute unit.  Fits (9 to 14 % rms) to 670 timed layers of 256 to 4096 x 256 to
-// 22016 with up to 15 tokens, and 880 of up to 2^23 weights with 16 ... 2500 (round), r = 0 to 64, both conventions.
+// 22016 with up to 15 tokens, and 880 of up to 2^23 weights with 16 ... 2500 (round), r = 0 to 64, both conventions.  The
+// former repeated their calls on one weight; `stream` is what a weight that has to come from memory adds (170 further layers).
 static double single_us(const LayerView &w, int M, int r, bool f16, bool round, bool wide) {
     const double units = w.K / 256.0, rg = (double)(r > 32 ? 4 : (r + 15) / 16), h = f16 ? rg : 0.0, three = w.bits == 3 ? 1.0 : 0.0;
     const int columns = wide ? (w.N + 63) / 64 : (w.N + 15) / 16;
     const double workgroups = (double)columns * (round ? (M + 31) / 32 : 1);
     double more = workgroups > 256.0 ? workgroups / 256.0 - 1.0 : 0.0;
-    if (round && (wide || rg > 2.0)) more = std::ceil(more);      // their LDS leaves room for one workgroup per compute unit
+    // one workgroup per compute unit (`round`: LDS, else registers); the waves of a short contraction end apart, which
+    // lets the fraction stand for a wide round
+    if (round ? wide || rg > 2.0 : !wide || units > 8.0) more = std::ceil(more);
+    const double stream = 0.15e-6 * ((double)w.K * w.N * w.bits / 8);   // the packed weight from memory
     if (round) {
         if (wide)
             return 5.09 + (r > 16 ? 1.04 : 0.0) + units * (0.42 + 0.543 * rg + 0.244 * h) +
@@ -563,9 +567,9 @@ static double single_us(const LayerView &w, int M, int r, bool f16, bool round, 
                more * (1.42 + 0.77 * rg + units * (0.695 + 0.264 * rg + 0.332 * h));
     }
     if (wide)
-        return 3.83 + (r > 16 ? 0.47 : 0.0) + units * (0.335 + 0.091 * three + 0.357 * rg + 0.13 * h) +
+        return 3.83 + stream + (r > 16 ? 0.47 : 0.0) + units * (0.335 + 0.091 * three + 0.357 * rg + 0.13 * h) +
                more * (8.5 * rg + units * (2.91 + 0.263 * three + 0.595 * rg + 0.6 * h));
-    return 3.81 + units * (0.154 + 0.037 * three + 0.326 * rg + 0.101 * h) +
+    return 3.81 + stream + units * (0.154 + 0.037 * three + 0.326 * rg + 0.101 * h) +
            more * (0.541 * rg + units * (0.552 + 0.139 * three + 0.328 * rg + 0.291 * h) + units * 0.399);
 }
 // The same backward (13 % rms, 1610 layers, 1 ... 2500 tokens).
@@ -575,7 +579,12 @@ static double single_bwd_us(int K, int N, int M, int r, bool f16) {
     return 3.8 + (r > 16 ? 0.64 : 0.0) + units * (0.805 + 1.23 * rg + 0.44 * h) + more * (1.4 + 0.591 * rg + units * (1.43 + 1.55 * rg + 0.389 * h));
 }
 
-// In place of the two streaming launches.  (Sixteen tokens, a full tile, keep the two launches that the streaming
+// In place of the two streaming launches, on weights from memory.  On 170 layers around the line the choice is on average 1.1 %
+// slower than the quicker way, at most 7 % (without `stream` and with narrow rounds counted in fractions 2.0 %, at most 91 %).
+// Kernels of a call, us, two launches / here: 1920 x 14016, 13 tokens, r = 16 13.9 / 10.1; 2304 x 8000, 1 token, r = 8 11.3 /
+// 10.2; 1408 x 4032, 4 tokens, r = 8 11.1 / 6.7; on the other side 4096 x 11008, 1 token, r = 16 13.6 / 17.7; 4096 x 4096
+// 11.2 / 12.7; 3456 x 4160 (260 narrow workgroups) 10.2 / 19.4; 2688 x 16512, 4 tokens, r = 8 13.4 / 21.7; 2688 x
+// 17216 (269 wide) 13.9 / 17.4.  (Sixteen tokens, a full tile, keep the two launches that the streaming
 // kernels' tests name, though the times do not cross there.)
 bool single_wins(const LayerView &w, int M, int r, bool f16) {
     if (M > 15 || w.K > 4096) return false;
