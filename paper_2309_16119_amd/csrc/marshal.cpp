@@ -276,8 +276,14 @@ struct Layer : torch::autograd::Function<Layer> {
         dy = dy.detach().reshape({-1, w.d_out}).to(act_type(f16)).contiguous();
         Tensor dx, t, dA, dB;
         at::NoGradGuard no_grad;
+        // (saved-tensor hooks may have brought back other tensors than were saved, and the weight may be another one)
+        const bool factors = A.defined() && (ctx->needs_input_grad(1) || ctx->needs_input_grad(2));
+        TORCH_CHECK(plain(dy) && factors_fit(A, B, w.d_in, w.d_out), "the adapter or the weight is no longer what the forward pass saw");
+        TORCH_CHECK(!factors || (plain(x2) && x2.scalar_type() == act_type(f16) && x2.dim() == 2 && x2.size(0) == dy.size(0) && x2.size(1) == w.d_in &&
+                                 (!xa.defined() || (plain(xa) && xa.scalar_type() == at::kFloat && xa.numel() == dy.size(0) * A.size(1)))),
+                    "the saved activations are no longer what the forward pass saw");
         int status = product(w, true, dy, A, B, (float)scale, true, dx, t);
-        if (status == MODULORA_OK && A.defined() && (ctx->needs_input_grad(1) || ctx->needs_input_grad(2)))
+        if (status == MODULORA_OK && factors)
             status = gradients(f16, x2, dy, A, B, (float)scale, xa, t, dA, dB);
         TORCH_CHECK(status == MODULORA_OK, "the backward pass of a ModuLoRA layer failed with status ", status);
         return {dx.view(shape), dA, dB, Tensor(), Tensor(), Tensor()};

@@ -254,3 +254,23 @@ def test_scratch_memory_per_stream_and_thread():
         grown = b._workspace("cuda", a.numel() + 1)
         assert grown.data_ptr() != a.data_ptr() and b._workspace("cuda", 10).data_ptr() == grown.data_ptr()
     assert b._workspace(torch.device("cuda", device), 0) is None
+
+
+@gpu
+@pytest.mark.parametrize("which", [0, 1, 2, 3])
+@pytest.mark.parametrize("changed", [lambda t: t.t().contiguous().t(), lambda t: t.double(), lambda t: t[:-1].clone(), lambda t: t.cpu()])
+def test_backward_refuses_other_tensors_from_hooks(which, changed):
+    """What a saved-tensor hook brings back (activations, A, B, XA) is checked before anything is launched."""
+    w, X, dY, A, B = _layer(False)
+    module = ModuLoRALinear(w, r=8, alpha=16.0)
+    x = X.detach().requires_grad_(True)
+    count = []
+
+    def pack(t):
+        count.append(0)
+        return len(count) - 1, t
+    with torch.autograd.graph.saved_tensors_hooks(pack, lambda p: changed(p[1]) if p[0] == which else p[1]):
+        y = module(x)
+    assert len(count) == 4
+    with pytest.raises(RuntimeError, match="no longer what the forward pass saw"):
+        torch.autograd.grad(y, (x, module.A, module.B), dY)
