@@ -579,18 +579,19 @@ static double single_bwd_us(int K, int N, int M, int r, bool f16) {
     return 3.8 + (r > 16 ? 0.64 : 0.0) + units * (0.805 + 1.23 * rg + 0.44 * h) + more * (1.4 + 0.591 * rg + units * (1.43 + 1.55 * rg + 0.389 * h));
 }
 
-// In place of the two streaming launches, on weights from memory.  On 170 layers around the line the choice is on average 1.1 %
-// slower than the quicker way, at most 7 % (without `stream` and with narrow rounds counted in fractions 2.0 %, at most 91 %).
-// Kernels of a call, us, two launches / here: 1920 x 14016, 13 tokens, r = 16 13.9 / 10.1; 2304 x 8000, 1 token, r = 8 11.3 /
-// 10.2; 1408 x 4032, 4 tokens, r = 8 11.1 / 6.7; on the other side 4096 x 11008, 1 token, r = 16 13.6 / 17.7; 4096 x 4096
+// In place of the two streaming launches, on weights from memory.  On 434 layers around the line the choice is on average 0.2 %
+// slower than the quicker way, at most 8 % (without `stream` and with narrow rounds counted in fractions 2.0 %, at most 91 %).
+// Kernels of a call, us, two launches / here: 1920 x 14016, 13 tokens, r = 16 13.9 / 10.1; 2432 x 7552, 15 tokens, r = 8 13.5 /
+// 10.9; 1408 x 4032, 4 tokens, r = 8 11.1 / 6.7; on the other side 4096 x 11008, 1 token, r = 16 13.6 / 17.7; 4096 x 4096
 // 11.2 / 12.7; 3456 x 4160 (260 narrow workgroups) 10.2 / 19.4; 2688 x 16512, 4 tokens, r = 8 13.4 / 21.7; 2688 x
-// 17216 (269 wide) 13.9 / 17.4.  (Sixteen tokens, a full tile, keep the two launches that the streaming
-// kernels' tests name, though the times do not cross there.)
+// 17216 (269 wide) 13.9 / 17.4.  (Narrow workgroups held to 128 registers, so that two share a compute unit, are no quicker there than
+// the wide ones: 1536 x 6272, r = 0 5.4 / 5.4, 2304 x 6912, r = 4 11.9 / 9.9.)  (Sixteen tokens, a full tile, keep the two launches
+// that the streaming kernels' tests name, though the times do not cross there.)
 bool single_wins(const LayerView &w, int M, int r, bool f16) {
     if (M > 15 || w.K > 4096) return false;
-    const double two = 9.6 + 0.24e-6 * ((double)w.K * w.N * w.bits / 8) + 0.27 * ((r + 15) / 16) + 0.29 * w.K / 1024;
+    const double two = 9.6 + 0.24e-6 * ((double)w.K * w.N * w.bits / 8) + 0.27 * ((r + 15) / 16) + 0.29 * w.K / 1024 + 0.07 * M;
     const double narrow = single_us(w, M, r, f16, false, false), wide = single_us(w, M, r, f16, false, true);
-    return 1.1 * (narrow < wide ? narrow : wide) < two;
+    return 1.05 * (narrow < wide ? narrow : wide) < two;
 }
 // In place of a product and its projection or second launch, whose estimate is `us`.  A call's kernels take, forward / backward,
 // 1.4x / 1.3x less time on average over layers of up to 2^23 weights and contractions of up to 2304, 16 ... 2500 tokens
