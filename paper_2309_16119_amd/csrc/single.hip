@@ -41,7 +41,8 @@ struct SingleDev {
 };
 
 // Sum of the waves' parts of the projection: P[row][16 RG], row stride 16 RG + 4, and its hand-off by the first column of workgroups.
-template <int RG, int RT>
+// AGAIN: see project_f16_again().
+template <int RG, int RT, bool AGAIN>
 __device__ __forceinline__ void single_projection(const SingleDev &d, int m0, const float *red, float *Ps) {
     using namespace single;
     constexpr int PS = 16 * RG + 4;
@@ -51,6 +52,8 @@ __device__ __forceinline__ void single_projection(const SingleDev &d, int m0, co
 #pragma unroll
         for (int w = 0; w < NWAVES; ++w) sum += red[((w * RT * RG + g) * 4 + v) * 64 + l];
         const int row = 16 * (g / RG) + 4 * (l >> 4) + v, j = g % RG * 16 + (l & 15);
+        if (AGAIN && __builtin_expect(sum != sum, 0))
+            sum = m0 + row < d.M && j < d.r ? project_f16_again<true>(d.act + (size_t)(m0 + row) * d.w.K, d.A, d.w.K, d.r, j, 0, d.w.K) : 0.f;
         Ps[row * PS + j] = sum;
         if (blockIdx.x == 0 && d.P_out != nullptr && m0 + row < d.M && j < d.r) d.P_out[(size_t)(m0 + row) * d.r + j] = sum;
     }
@@ -242,7 +245,7 @@ __global__ __launch_bounds__(single::THREADS, 2) void single_kernel(SingleDev d)
             for (int v = 0; v < 4; ++v) red_p[(((wave * RT + t) * RG + q) * 4 + v) * 64 + lane] = P[t][q][v] + P_rest[t][q][v];
     }
     __syncthreads();
-    single_projection<RG, RT>(d, m0, red_p, Ps);
+    single_projection<RG, RT, F16 && !ROUND>(d, m0, red_p, Ps);
     __syncthreads();
     // two adjacent columns of a row: T threads side by side share the waves' sums and the rank
     constexpr int T = 4 / CT;

@@ -121,4 +121,22 @@ __device__ __forceinline__ void codes_to_operand(const uint32_t *w, int c, const
 
 }  // namespace sm
 
+// One element of the projection of binary16 activations over contraction elements [k0, k1) (multiples of 8), in plain
+// fp32.  An infinity has no exact split (inf - inf is NaN) and meets the zero parts of the other operand (inf * 0): where
+// the matrix cores' sum of a row and a factor column is NaN, it is added again by this, which gives what the definition
+// does.  (An infinite activation is no rarity in binary16.)
+template <bool F_IS_A>
+__device__ __forceinline__ float project_f16_again(const uint16_t *row, const float *F, int C, int r, int j, int k0, int k1) {
+    float sum = 0.f;
+#pragma unroll 1
+    for (int c = k0; c < k1; c += 8) {
+        const uint4 x = *reinterpret_cast<const uint4 *>(row + c);
+        const uint32_t xw[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            sum = __builtin_fmaf(half_bits_to_float((uint16_t)(xw[e >> 1] >> (16 * (e & 1)))), F_IS_A ? F[(size_t)(c + e) * r + j] : F[(size_t)j * C + c + e], sum);
+    }
+    return sum;
+}
+
 }  // namespace mlr

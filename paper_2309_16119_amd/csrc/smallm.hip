@@ -123,7 +123,12 @@ __device__ __forceinline__ void smallm_project(const uint16_t *act, int M, int C
 #pragma unroll
         for (int w = 0; w < NWAVES; ++w) sum += red[((w * 4 + g) * 4 + v) * 64 + l];
         const int prow = 4 * (l >> 4) + v, j = g * 16 + (l & 15);
-        if (j < r) mine[prow * r + j] = sum;
+        if (j >= r) continue;
+        if (F16 && __builtin_expect(sum != sum && prow < M, 0)) {
+            const long p0 = (long)blk * NWAVES;
+            sum = project_f16_again<F_IS_A>(act + (size_t)prow * C, F, C, r, j, 32 * (int)(steps * p0 / nparts), 32 * (int)(steps * (p0 + NWAVES) / nparts));
+        }
+        mine[prow * r + j] = sum;
     }
 }
 

@@ -399,3 +399,39 @@ def test_adapter_term_through_the_extended_contraction(K, N, M, r, bits):
         assert bool(torch.isinf(got[:, col]).all())
         keep = torch.arange(got.shape[1], device="cuda") != col
         assert torch.equal(got[:, keep].view(torch.int16), was[:, keep].view(torch.int16))
+
+
+@pytest.mark.parametrize("bits,K,N,M,r,fwd", [
+    (4, 256, 384, 9, 8, "single"),           # the projection beside the one-launch product
+    (2, 896, 2176, 15, 33, "single"),        # ... with three groups of rank columns, the last of one
+    (4, 4096, 4096, 16, 8, "stream"),        # sixteen projecting workgroups, the streaming kernels' own second launch
+    (3, 4096, 4224, 27, 5, "stream"),        # two passes, the second of eleven rows
+    (3, 512, 1152, 16, 64, "stream"),        # the shared second launch
+])
+def test_infinite_activations_in_the_projection_of_few_tokens(bits, K, N, M, r, fwd):
+    """X A and dY B^T of an infinite activation (an overflow, no rarity in binary16) or factor: the infinities that the
+    definition gives, NaN only where one meets zero or its opposite, every other element as without them."""
+    D = layer(bits, K, N, M, r, 128 if K % 256 == 0 and bits == 3 else 64, seed=13)
+    inf, nan = float("inf"), float("nan")
+    for backward, act, F in ((False, D["Xd"].clone(), D["Ad"].clone()), (True, D["dYd"].clone(), D["Bd"].t().contiguous())):
+        C = act.shape[1]
+        act[0, 5], act[1, 3], act[1, 9] = inf, inf, -inf
+        act[M - 1, C - 1], act[2, C // 2] = -inf, nan
+        act[M - 2, 17] = 0.0
+        F[5, r // 2] = 0.0                                   # meets the infinity of row 0
+        F[17, r - 1] = -inf                                  # meets the zero of row M - 2
+        A, B = (F, D["Bd"]) if not backward else (D["Ad"], F.t().contiguous())
+        call = b.modulora_f16_bwd_input if backward else b.modulora_f16_fwd
+        b.modulora_profile_begin()
+        _, P = call(D["w"], act, A, B, 2.0)
+        torch.cuda.synchronize()
+        names = set(b.modulora_profile_end())
+        want = {"f16_stream_bwd", "f16_stream_bwd_finish"} if backward else \
+               {"f16_stream_fwd_single"} if fwd == "single" else {"f16_stream_fwd", "f16_stream_fwd_finish"}
+        assert names == want
+        for j in range(r):
+            terms = act.double() * F[:, j].double()
+            ref, mag, got = terms.sum(1), terms.abs().sum(1), P[:, j].double()
+            assert torch.equal(got.isnan(), ref.isnan()) and torch.equal(got.isposinf(), ref.isposinf()) and torch.equal(got.isneginf(), ref.isneginf())
+            ok = ref.isfinite()
+            assert bool(((got - ref).abs()[ok] <= (2.0 ** -24 * (64 + C ** 0.5) * mag)[ok]).all())
