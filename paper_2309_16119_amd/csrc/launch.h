@@ -18,7 +18,7 @@ struct LayerView {
 // Length of the extended contraction that carries the rank-r adapter through the
 // MFMA pipeline: bfloat16 segments of r, padded to the MFMA K-step of 16.  Three
 // (hi*hi, hi*lo, lo*hi: 2^-16 relative) where the output is bfloat16; six of a
-// three-way split (what is dropped is below 2^-23) where it is binary16.
+// three-way split (what is dropped is at most 2^-24) where it is binary16.
 inline int lora_ext_segments(bool f16) { return f16 ? 6 : 3; }
 inline int lora_ext_len(int r, bool f16 = false) { return r > 0 ? ((lora_ext_segments(f16) * r + 15) / 16) * 16 : 0; }
 

@@ -15,8 +15,10 @@ namespace mlr {
 // activation side and (hi,lo,hi) on the weight side of a two-way split, so that the dot product is
 // hi*hi + hi*lo + lo*hi ~= (hi+lo)*(hi+lo) to about 2^-16 relative.  Six segments (binary16 outputs):
 // the products of a three-way split down to 2^-16 of the first, (0,0,1,1,0,2) against (0,1,0,1,2,0); the
-// three parts carry all 24 bits and what is left out is below 2^-23.  There the parts are truncations
-// and an infinity or NaN stands in the first segment only: an infinite factor or projection then gives
+// three parts, each rounded to nearest, carry all 24 bits, and what is left out is at most 2^-24 of a product and of
+// either sign: an fp32 multiply's own rounding (over 4 M pairs near a power of two, where it is largest: at most
+// 2^-24.1, 2^-26.5 rms; 2^-24.0 and 2^-24.8 rounded to fp32; with truncated parts 2^-21.1 and all of one sign).
+// There an infinity or NaN stands in the first segment only: an infinite factor or projection then gives
 // the infinity that the definition gives, not the NaN of inf - inf or inf * 0.
 __device__ __forceinline__ uint16_t ext_part(float v, int segment, int segments, bool weight_side) {
     if (segments == 3) {
@@ -25,12 +27,16 @@ __device__ __forceinline__ uint16_t ext_part(float v, int segment, int segments,
         return float_to_bf16_bits(v - bf16_bits_to_float(hi));
     }
     const int part = ((weight_side ? 0x021010 : 0x201100) >> (4 * segment)) & 15;
-    const uint32_t b0 = __float_as_uint(v) & 0xFFFF0000u;
-    if ((b0 & 0x7F800000u) == 0x7F800000u) return segment ? (uint16_t)0 : (uint16_t)((b0 >> 16) | ((__float_as_uint(v) & 0xFFFFu) ? 1u : 0u));
-    const float r1 = v - __uint_as_float(b0);
-    const uint32_t b1 = __float_as_uint(r1) & 0xFFFF0000u;
-    const float r2 = r1 - __uint_as_float(b1);
-    return (uint16_t)((part == 0 ? b0 : part == 1 ? b1 : __float_as_uint(r2)) >> 16);
+    uint16_t hi = float_to_bf16_bits(v);
+    if ((hi & 0x7F80u) == 0x7F80u) {
+        const uint32_t bits = __float_as_uint(v);
+        if ((bits & 0x7F800000u) == 0x7F800000u) return segment ? (uint16_t)0 : hi;
+        hi = (uint16_t)(bits >> 16);             // finite, and rounded past the largest bfloat16
+    }
+    if (part == 0) return hi;
+    const float r1 = v - bf16_bits_to_float(hi);
+    const uint16_t mid = float_to_bf16_bits(r1);
+    return part == 1 ? mid : float_to_bf16_bits(r1 - bf16_bits_to_float(mid));
 }
 
 // ---------------------------------------------------------------------------

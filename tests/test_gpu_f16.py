@@ -435,3 +435,34 @@ def test_infinite_activations_in_the_projection_of_few_tokens(bits, K, N, M, r, 
             assert torch.equal(got.isnan(), ref.isnan()) and torch.equal(got.isposinf(), ref.isposinf()) and torch.equal(got.isneginf(), ref.isneginf())
             ok = ref.isfinite()
             assert bool(((got - ref).abs()[ok] <= (2.0 ** -24 * (64 + C ** 0.5) * mag)[ok]).all())
+
+
+@pytest.mark.parametrize("backward", [False, True])
+def test_extended_contraction_is_as_exact_as_fp32(backward):
+    """One product p f per output (rank 1, one-hot rows, a weight of zeros), carried as six segments: the output is the
+    product's own binary16 rounding wherever the product lies further than 2^-22 of itself from a rounding boundary
+    (2^-24 that the segments leave out, 2^-23 for the matrix cores' sum of the six).  The operands stand just above a power of
+    two with long runs of ones, where a split is at its worst: a split by truncation misses by up to 2^-21 there,
+    and a hundred outputs and more land on the wrong side of the boundary."""
+    K, N = 1056, 4104
+    rng = np.random.default_rng(4)
+
+    def factor(n):               # 1.0000000 11xxxxxx 1xxxxxxx
+        low = 0xC080 | (rng.integers(0, 64, n, dtype=np.uint32) << 8) | rng.integers(0, 128, n, dtype=np.uint32)
+        return (np.uint32(0x3F800000) | low.astype(np.uint32)).view(np.float32)
+    A, B = factor(K).reshape(K, 1), factor(N).reshape(1, N)
+    w = b.QWeightF16(torch.zeros((K // 8, N), dtype=torch.int32, device="cuda"), torch.zeros((K // 32, N), dtype=torch.float16, device="cuda"),
+                     torch.zeros((K // 32, N), dtype=torch.float16, device="cuda"), None, K, N, 4, 32)
+    act = torch.eye(K, N if backward else K, dtype=torch.float16, device="cuda")
+    call = b.modulora_f16_bwd_input if backward else b.modulora_f16_fwd
+    b.modulora_profile_begin()
+    out, P = call(w, act, torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(), 1.0)
+    torch.cuda.synchronize()
+    assert "lora_down" in b.modulora_profile_end()           # the tile kernels, which take the segments
+    p, f = (B[0, :K], A[:, 0]) if backward else (A[:, 0], B[0])
+    assert np.array_equal(P[:, 0].cpu().numpy(), p)
+    exact = np.multiply.outer(p.astype(np.float64), f.astype(np.float64))
+    half = exact.astype(np.float16)
+    boundary = np.abs(np.abs(exact - half.astype(np.float64)) - np.spacing(half).astype(np.float64) / 2)
+    got = out.cpu().numpy()
+    assert int(((got != half) & (boundary > 2.0 ** -22 * exact)).sum()) == 0
