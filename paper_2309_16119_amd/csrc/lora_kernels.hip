@@ -18,15 +18,11 @@ namespace mlr {
 // three parts, each rounded to nearest, carry all 24 bits, and what is left out is at most 2^-24 of a product and of
 // either sign: an fp32 multiply's own rounding (over 4 M pairs near a power of two, where it is largest: at most
 // 2^-24.1, 2^-26.5 rms; 2^-24.0 and 2^-24.8 rounded to fp32; with truncated parts 2^-21.1 and all of one sign).
-// There an infinity or NaN stands in the first segment only: an infinite factor or projection then gives
-// the infinity that the definition gives, not the NaN of inf - inf or inf * 0.
+// An infinity or NaN stands in the first segment only: an infinite factor or projection then gives
+// the infinity that the definition gives, as in the kernels that add the term in fp32 (finish.hip), not the
+// NaN of inf - inf or inf * 0.
 __device__ __forceinline__ uint16_t ext_part(float v, int segment, int segments, bool weight_side) {
-    if (segments == 3) {
-        const uint16_t hi = float_to_bf16_bits(v);
-        if (segment != (weight_side ? 1 : 2)) return hi;
-        return float_to_bf16_bits(v - bf16_bits_to_float(hi));
-    }
-    const int part = ((weight_side ? 0x021010 : 0x201100) >> (4 * segment)) & 15;
+    const int part = ((segments == 3 ? (weight_side ? 0x010 : 0x100) : weight_side ? 0x021010 : 0x201100) >> (4 * segment)) & 15;
     uint16_t hi = float_to_bf16_bits(v);
     if ((hi & 0x7F80u) == 0x7F80u) {
         const uint32_t bits = __float_as_uint(v);

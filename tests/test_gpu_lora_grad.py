@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from paper_2309_16119_amd import binding as b
+from paper_2309_16119_amd import binding as b, synth
 
 pytestmark = pytest.mark.gpu
 
@@ -137,3 +137,33 @@ def test_projections_by_tiles(M, K, N, r, f16):
         ref = 2.0 * proj @ F
         bound = rounding * ref.abs() + 2.0 * (err + (2.0 ** -20 if f16 else 2.0 ** -15) * proj.abs()) @ F.abs() + 2.0 ** -25
         assert bool(((got.double() - ref).abs() <= bound).all()), float((got.double() - ref).abs().max())
+
+
+@pytest.mark.parametrize("K,N,M,r,backward", [
+    (4128, 4440, 303, 64, True),      # by tiles since the estimates choose, in fp32 before
+    (1056, 4104, 130, 3, False),
+    (1056, 4104, 2200, 17, False),
+])
+def test_infinite_factor_through_the_extended_contraction(K, N, M, r, backward):
+    """bfloat16 tile kernels: an infinite adapter factor gives infinities in its output column, NaN where it meets zeros
+    only, and leaves every other column as it was."""
+    cfg = synth.LayerConfig("t", K, N, 3, 32, M, r)
+    L = synth.make_layer_torch(cfg, device="cuda", seed=17)
+    w = b.QWeight(L["qweight"], L["scales"], L["zeros"], K, N, 3, 32)
+    A, B = L["A"].clone(), L["B"].clone()
+    act, call = (L["dY"], b.modulora_bwd_input) if backward else (L["X"], b.modulora_fwd)
+    act[3] = 0.0                                              # projects to zeros
+    was, P = call(w, act, A, B, 2.0)
+    F = A if backward else B.t()
+    F[5, r - 1], F[9, 0] = float("inf"), -float("inf")
+    b.modulora_profile_begin()
+    got, P2 = call(w, act, A, B, 2.0)
+    torch.cuda.synchronize()
+    assert "lora_down" in b.modulora_profile_end()            # the tile kernels
+    assert torch.equal(P, P2)
+    for col, j, sign in ((5, r - 1, 1.0), (9, 0, -1.0)):
+        assert torch.equal(got[:, col].double().nan_to_num(0.0, 1.0, -1.0), torch.sign(P[:, j].double()) * sign)
+        assert bool(got[3, col].isnan()) and not bool(got[:3, col].isnan().any())
+    keep = torch.ones(got.shape[1], dtype=torch.bool, device="cuda")
+    keep[5] = keep[9] = False
+    assert torch.equal(got[:, keep].view(torch.int16), was[:, keep].view(torch.int16))
