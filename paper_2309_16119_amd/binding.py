@@ -11,6 +11,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import threading
 from typing import Optional
 
 import torch
@@ -178,6 +179,14 @@ class _Held(dict):
 _workspaces = _Held()        # without _marshal, which keeps its own
 
 
+def _scratch_key(device) -> tuple:
+    device = torch.device(device)
+    index = device.index
+    if device.type != "cuda" or index is None:
+        index = torch.cuda.current_stream(device).device_index      # refuses what is not a GPU
+    return index, _raw_stream(index)
+
+
 def _workspace(device, nbytes: int) -> Optional[torch.Tensor]:
     """Scratch memory for one call: a cached tensor per (device, current stream), so that calls
     sharing a buffer are ordered on one stream as the library requires.  A request larger than
@@ -186,19 +195,45 @@ def _workspace(device, nbytes: int) -> Optional[torch.Tensor]:
     Callers that capture graphs can size the buffer first with reserve_workspace()."""
     if nbytes == 0:
         return None
-    device = torch.device(device)
-    index = device.index
-    if device.type != "cuda" or index is None:
-        index = torch.cuda.current_stream(device).device_index      # refuses what is not a GPU
-    key = (index, _raw_stream(index))
+    key = _scratch_key(device)
     if _marshal is not None:
-        return _marshal.workspace(index, key[1], nbytes)
+        return _marshal.workspace(*key, nbytes)
     held = _workspaces.get(key)
     if held is None:
         held = _workspaces.setdefault(key, [])
     if not held or held[-1].numel() < nbytes:
-        held.append(torch.empty(nbytes, dtype=torch.uint8, device=device))
+        ws = torch.empty(nbytes, dtype=torch.uint8, device=torch.device(device))
+        held.append(ws)
+        return ws                        # not held[-1]: another thread may have added a smaller one since
     return held[-1]
+
+
+_orders: dict = {}           # (device, stream) -> lock; without _marshal, which keeps its own
+
+
+class _scratch:
+    """`with _scratch(device, nbytes) as ws:` around one library call.  The call is several launches that hand
+    data over through the scratch memory of their stream, and Python's lock is released meanwhile: no other
+    thread's call on the same stream may come between them."""
+
+    def __init__(self, device, nbytes: int):
+        self.ws = _workspace(device, nbytes)
+        self.key = None if self.ws is None else _scratch_key(device)
+
+    def __enter__(self):
+        if self.key is not None:
+            if _marshal is not None:
+                self.unlock = _marshal.unlock
+                _marshal.lock(*self.key)
+            else:
+                order = _orders.setdefault(self.key, threading.RLock())
+                self.unlock = lambda *key: order.release()
+                order.acquire()
+        return self.ws
+
+    def __exit__(self, *exc):
+        if self.key is not None:
+            self.unlock(*self.key)
 
 
 def reserve_workspace(device, nbytes: int) -> None:
@@ -258,9 +293,9 @@ def modulora_fwd(w: QWeight, X: torch.Tensor, A: Optional[torch.Tensor], B: Opti
         XA = torch.empty((M, r), dtype=torch.float32, device=X.device)
     st = ctypes.byref(w.c_struct())
     nbytes = lib.modulora_workspace_bytes(st, M, r)
-    ws = _workspace(X.device, nbytes)
-    _check(lib.modulora_fwd(st, _ptr(X), M, _ptr(A), _ptr(B), r, float(lora_scale),
-                            _ptr(Y), _ptr(XA), _ptr(ws), nbytes, _stream()), "modulora_fwd")
+    with _scratch(X.device, nbytes) as ws:
+        _check(lib.modulora_fwd(st, _ptr(X), M, _ptr(A), _ptr(B), r, float(lora_scale),
+                                _ptr(Y), _ptr(XA), _ptr(ws), nbytes, _stream()), "modulora_fwd")
     return Y, XA
 
 
@@ -301,9 +336,9 @@ def modulora_bwd_input(w: QWeight, dY: torch.Tensor, A: Optional[torch.Tensor], 
         dYBt = torch.empty((M, r), dtype=torch.float32, device=dY.device)
     st = ctypes.byref(w.c_struct())
     nbytes = lib.modulora_workspace_bytes(st, M, r)
-    ws = _workspace(dY.device, nbytes)
-    _check(lib.modulora_bwd_input(st, _ptr(dY), M, _ptr(A), _ptr(B), r, float(lora_scale),
-                                  _ptr(dX), _ptr(dYBt), _ptr(ws), nbytes, _stream()), "modulora_bwd_input")
+    with _scratch(dY.device, nbytes) as ws:
+        _check(lib.modulora_bwd_input(st, _ptr(dY), M, _ptr(A), _ptr(B), r, float(lora_scale),
+                                      _ptr(dX), _ptr(dYBt), _ptr(ws), nbytes, _stream()), "modulora_bwd_input")
     return dX, dYBt
 
 
@@ -329,10 +364,10 @@ def modulora_bwd_lora(X: torch.Tensor, dY: torch.Tensor, A: torch.Tensor, B: tor
         dB = torch.empty((r, d_out), dtype=torch.float32, device=X.device)
     shape = modulora_qweight(d_in, d_out, 4, 32, 0, 0, 0)
     nbytes = int(lib.modulora_workspace_bytes(ctypes.byref(shape), M, r))
-    ws = _workspace(X.device, nbytes)
-    _check(lib.modulora_bwd_lora(d_in, d_out, M, r, float(lora_scale), _ptr(X), _ptr(dY), _ptr(A), _ptr(B),
-                                 _ptr(XA), _ptr(dYBt), _ptr(dA), _ptr(dB), 1 if accumulate else 0,
-                                 _ptr(ws), nbytes, _stream()), "modulora_bwd_lora")
+    with _scratch(X.device, nbytes) as ws:
+        _check(lib.modulora_bwd_lora(d_in, d_out, M, r, float(lora_scale), _ptr(X), _ptr(dY), _ptr(A), _ptr(B),
+                                     _ptr(XA), _ptr(dYBt), _ptr(dA), _ptr(dB), 1 if accumulate else 0,
+                                     _ptr(ws), nbytes, _stream()), "modulora_bwd_lora")
     return dA, dB
 
 
@@ -398,9 +433,9 @@ def _f16_call(fn, name, w: QWeightF16, act: torch.Tensor, width_in: int, width_o
         P = torch.empty((M, r), dtype=torch.float32, device=act.device)
     st = ctypes.byref(w.c_struct())
     nbytes = lib.modulora_f16_workspace_bytes(st, M, r)
-    ws = _workspace(act.device, nbytes)
-    _check(fn(st, _ptr(act), M, _ptr(A), _ptr(B), r, float(lora_scale), _ptr(out), _ptr(P), _ptr(ws), nbytes,
-              _stream()), name)
+    with _scratch(act.device, nbytes) as ws:
+        _check(fn(st, _ptr(act), M, _ptr(A), _ptr(B), r, float(lora_scale), _ptr(out), _ptr(P), _ptr(ws), nbytes,
+                  _stream()), name)
     return out, P
 
 
@@ -436,10 +471,10 @@ def modulora_f16_bwd_lora(X: torch.Tensor, dY: torch.Tensor, A: torch.Tensor, B:
         dB = torch.empty((r, d_out), dtype=torch.float32, device=X.device)
     shape = modulora_qweight_f16(d_in, d_out, 4, 32, 0, 0, 0, 0)
     nbytes = int(lib.modulora_f16_workspace_bytes(ctypes.byref(shape), M, r))
-    ws = _workspace(X.device, nbytes)
-    _check(lib.modulora_f16_bwd_lora(d_in, d_out, M, r, float(lora_scale), _ptr(X), _ptr(dY), _ptr(A), _ptr(B),
-                                     _ptr(XA), _ptr(dYBt), _ptr(dA), _ptr(dB), 1 if accumulate else 0,
-                                     _ptr(ws), nbytes, _stream()), "modulora_f16_bwd_lora")
+    with _scratch(X.device, nbytes) as ws:
+        _check(lib.modulora_f16_bwd_lora(d_in, d_out, M, r, float(lora_scale), _ptr(X), _ptr(dY), _ptr(A), _ptr(B),
+                                         _ptr(XA), _ptr(dYBt), _ptr(dA), _ptr(dB), 1 if accumulate else 0,
+                                         _ptr(ws), nbytes, _stream()), "modulora_f16_bwd_lora")
     return dA, dB
 
 

@@ -42,29 +42,41 @@ struct Library {
 } lib{};
 
 // ---- scratch memory: one buffer per (device, stream), see binding._workspace() --------------------
-struct Workspaces {
-    std::mutex mutex;
-    std::map<std::pair<int, int64_t>, std::vector<Tensor>> held;
+// A call is several launches that hand data over through the scratch memory of their stream, so a call has to be on its
+// stream whole before another host thread's on the same stream begins: `order` is held from before the library call
+// until it returns.  (Recursive: what Python runs on its own account, a finalizer say, may call in between.)
+struct Scratch {
+    std::recursive_mutex order;
+    std::vector<Tensor> held;
 };
-Workspaces &workspaces() {
-    static auto *w = new Workspaces;       // never destroyed: the buffers outlive the GPU runtime's own end otherwise
-    return *w;
+struct Scratches {
+    std::mutex mutex;                                       // of the map and of every `held`
+    std::map<std::pair<int, int64_t>, Scratch> of;          // entries stay where they are
+    Scratch &at(int device, int64_t stream) {
+        std::lock_guard<std::mutex> lock(mutex);
+        return of[{device, stream}];
+    }
+};
+Scratches &scratches() {
+    static auto *s = new Scratches;        // never destroyed: the buffers outlive the GPU runtime's own end otherwise
+    return *s;
 }
 // A request larger than the held buffer gets a new one; the old ones stay, because a HIP graph captured
 // earlier may still hold their addresses.  Undefined for no bytes.
-Tensor workspace(int device, int64_t stream, size_t nbytes) {
+Tensor workspace(int device, int64_t stream, size_t nbytes, Scratch **of = nullptr) {
     if (nbytes == 0) return {};
-    Workspaces &w = workspaces();
+    Scratches &all = scratches();
+    Scratch *s;
     {
-        std::lock_guard<std::mutex> lock(w.mutex);
-        auto it = w.held.find({device, stream});
-        if (it != w.held.end() && !it->second.empty() && (size_t)it->second.back().numel() >= nbytes) return it->second.back();
+        std::lock_guard<std::mutex> lock(all.mutex);
+        s = &all.of[{device, stream}];
+        if (of) *of = s;
+        if (!s->held.empty() && (size_t)s->held.back().numel() >= nbytes) return s->held.back();
     }
     // (the allocator may run Python of its own: not under the lock)
     Tensor t = at::empty({(int64_t)nbytes}, at::TensorOptions().dtype(at::kByte).device(at::kCUDA, device));
-    std::lock_guard<std::mutex> lock(w.mutex);
-    auto &v = w.held[{device, stream}];
-    if (v.empty() || v.back().numel() < t.numel()) v.push_back(t);
+    std::lock_guard<std::mutex> lock(all.mutex);
+    if (s->held.empty() || s->held.back().numel() < t.numel()) s->held.push_back(t);
     return t;
 }
 
@@ -140,11 +152,17 @@ bool factors_fit(const Tensor &A, const Tensor &B, int64_t d_in, int64_t d_out) 
 struct Where {                 // what a call is launched on, and where its scratch memory lives
     void *stream;
     Tensor ws;
+    Scratch *scratch = nullptr;
     Where(int device, size_t nbytes) {
         const auto current = c10::hip::current_device();
         const auto s = c10::hip::getCurrentHIPStream(current);
         stream = s.stream();
-        ws = workspace(device, (int64_t)(intptr_t)(device == current ? s : c10::hip::getCurrentHIPStream(device)).stream(), nbytes);
+        const int64_t key = (int64_t)(intptr_t)(device == current ? s : c10::hip::getCurrentHIPStream(device)).stream();
+        ws = workspace(device, key, nbytes, &scratch);
+    }
+    // taken without Python's lock, which another thread may need to let this one go
+    std::unique_lock<std::recursive_mutex> order() const {
+        return scratch ? std::unique_lock<std::recursive_mutex>(scratch->order) : std::unique_lock<std::recursive_mutex>();
     }
 };
 
@@ -159,6 +177,7 @@ int product(const Weight &w, bool backward, const Tensor &act, const Tensor &A, 
     const size_t nbytes = lib.bytes[w.f16](layer, (int32_t)M, (int32_t)r);
     const Where at(act.get_device(), nbytes);
     ReleaseGil release;
+    const auto in_order = at.order();
     return lib.product[w.f16][backward](layer, ptr<uint16_t>(act), (int32_t)M, ptr<float>(A), ptr<float>(B), (int32_t)r, scale, ptr<uint16_t>(out),
                                         ptr<float>(P), ptr<void>(at.ws), nbytes, at.stream);
 }
@@ -173,6 +192,7 @@ int gradients(bool f16, const Tensor &X, const Tensor &dY, const Tensor &A, cons
     const size_t nbytes = lib.bytes[f16](f16 ? static_cast<const void *>(&h) : static_cast<const void *>(&q), (int32_t)M, (int32_t)r);
     const Where at(X.get_device(), nbytes);
     ReleaseGil release;
+    const auto in_order = at.order();
     return lib.grad[f16](d_in, d_out, (int32_t)M, (int32_t)r, scale, ptr<uint16_t>(X), ptr<uint16_t>(dY), ptr<float>(A), ptr<float>(B), ptr<float>(XA), ptr<float>(T),
                          ptr<float>(dA), ptr<float>(dB), 0, ptr<void>(at.ws), nbytes, at.stream);
 }
@@ -329,11 +349,36 @@ PyObject *py_workspace(PyObject *, PyObject *args) {
 }
 PyObject *py_forget(PyObject *, PyObject *) {
     HANDLE_TH_ERRORS
-    std::map<std::pair<int, int64_t>, std::vector<Tensor>> gone;
+    std::vector<Tensor> gone;
     {
-        std::lock_guard<std::mutex> lock(workspaces().mutex);
-        gone.swap(workspaces().held);
+        std::lock_guard<std::mutex> lock(scratches().mutex);
+        for (auto &entry : scratches().of) {
+            gone.insert(gone.end(), entry.second.held.begin(), entry.second.held.end());
+            entry.second.held.clear();
+        }
     }
+    Py_RETURN_NONE;
+    END_HANDLE_TH_ERRORS
+}
+// lock(device index, stream), unlock(device index, stream): Scratch::order for a call that Python makes
+PyObject *py_lock(PyObject *, PyObject *args) {
+    HANDLE_TH_ERRORS
+    int device;
+    long long stream;
+    if (!PyArg_ParseTuple(args, "iL", &device, &stream)) return nullptr;
+    Scratch &s = scratches().at(device, stream);
+    Py_BEGIN_ALLOW_THREADS
+    s.order.lock();
+    Py_END_ALLOW_THREADS
+    Py_RETURN_NONE;
+    END_HANDLE_TH_ERRORS
+}
+PyObject *py_unlock(PyObject *, PyObject *args) {
+    HANDLE_TH_ERRORS
+    int device;
+    long long stream;
+    if (!PyArg_ParseTuple(args, "iL", &device, &stream)) return nullptr;
+    scratches().at(device, stream).order.unlock();
     Py_RETURN_NONE;
     END_HANDLE_TH_ERRORS
 }
@@ -356,6 +401,8 @@ PyMethodDef methods[] = {
     {"layer", reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(py_layer)), METH_FASTCALL, nullptr},
     {"workspace", py_workspace, METH_VARARGS, nullptr},
     {"forget_workspaces", py_forget, METH_NOARGS, nullptr},
+    {"lock", py_lock, METH_VARARGS, nullptr},
+    {"unlock", py_unlock, METH_VARARGS, nullptr},
     {"use", py_use, METH_VARARGS, nullptr},
     {nullptr, nullptr, 0, nullptr},
 };

@@ -31,6 +31,42 @@ def test_leaves_what_is_not_on_the_gpu_to_python():
         b.modulora_bwd_lora(X, dY, A.t(), B, 1.0)
 
 
+@pytest.mark.parametrize("marshal", [True, False])
+def test_calls_of_two_threads_on_one_stream_do_not_overlap(monkeypatch, marshal):
+    """A library call is several launches that share the stream's scratch memory, and Python's lock is released
+    meanwhile: the next thread's call on that stream waits until the first has launched them all."""
+    import threading
+    import time
+
+    log = []
+
+    class Library:
+        modulora_workspace_bytes = staticmethod(lambda *a: 64)
+
+        @staticmethod
+        def modulora_fwd(*a):
+            log.append((threading.get_ident(), "first launch"))
+            time.sleep(0.05)
+            log.append((threading.get_ident(), "last launch"))
+            return 0
+    monkeypatch.setattr(b, "lib", Library)
+    if not marshal:
+        monkeypatch.setattr(b, "_marshal", None)
+    monkeypatch.setattr(b, "_scratch_key", lambda device: (0, 12345), raising=False)
+    monkeypatch.setattr(b, "_workspace", lambda device, nbytes: torch.empty(nbytes, dtype=torch.uint8))
+    monkeypatch.setattr(b, "_stream", lambda: 0)
+    w = b.QWeight(torch.zeros(48, 256, dtype=torch.int32), torch.ones(4, 256, dtype=torch.float16),
+                  torch.zeros(4, 256, dtype=torch.uint8), 512, 256, 3, 128)
+    X = torch.zeros(4, 512, dtype=torch.bfloat16)
+    threads = [threading.Thread(target=lambda: [b.modulora_fwd(w, X, None, None, 1.0) for _ in range(2)]) for _ in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert len(log) == 12
+    for first, last in zip(log[::2], log[1::2]):
+        assert first == (last[0], "first launch") and last[1] == "last launch"
+
 def _layer(f16, K=512, N=384, M=20, r=8, bits=3, group=128, seed=3):
     cfg = synth.LayerConfig("t", K, N, bits, group, M, max(r, 1), seed=seed)
     L = synth.make_layer_torch(cfg, device="cuda", seed=seed)
@@ -274,3 +310,36 @@ def test_backward_refuses_other_tensors_from_hooks(which, changed):
     assert len(count) == 4
     with pytest.raises(RuntimeError, match="no longer what the forward pass saw"):
         torch.autograd.grad(y, (x, module.A, module.B), dY)
+
+
+@gpu
+@pytest.mark.parametrize("mixed", [False, True])
+def test_scratch_memory_of_two_threads_on_one_stream(monkeypatch, mixed):
+    """Calls of two threads on the same stream at once, of several launches each: every result is that of the call
+    alone.  `mixed`: one of them with outputs given, which Python marshals."""
+    import threading
+
+    jobs = []
+    for i, (K, N, M) in enumerate(((2048, 4096, 60), (4096, 2048, 300))):
+        w, X, dY, A, B = _layer(False, K=K, N=N, M=M, seed=i)
+        out = torch.empty((M, N), dtype=torch.bfloat16, device="cuda") if mixed and i else None
+        jobs.append((w, X, dY, A, B, b.modulora_fwd(w, X, A, B, 2.0)[0], b.modulora_bwd_input(w, dY, A, B, 2.0)[0], out))
+    b.modulora_profile_begin()
+    b.modulora_fwd(*jobs[0][:2], *jobs[0][3:5], 2.0)
+    assert len(b.modulora_profile_end()) > 1
+    torch.cuda.synchronize()
+    failed = []
+
+    def work(job):
+        w, X, dY, A, B, Y, dX, out = job
+        for _ in range(40):
+            got = [(b.modulora_fwd(w, X, A, B, 2.0, out)[0].clone(), b.modulora_bwd_input(w, dY, A, B, 2.0)[0]) for _ in range(8)]
+            torch.cuda.current_stream().synchronize()
+            if not all(torch.equal(y, Y) and torch.equal(dx, dX) for y, dx in got):
+                failed.append(X.shape)
+    threads = [threading.Thread(target=work, args=(job,)) for job in jobs]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not failed
