@@ -122,7 +122,7 @@ except ImportError:
     _marshal = None
 if _marshal is not None:
     _marshal.use(*(ctypes.cast(getattr(lib, "modulora_" + kind + name), ctypes.c_void_p).value
-                   for kind in ("", "f16_") for name in ("fwd", "bwd_input", "bwd_lora", "workspace_bytes")))
+                   for kind in ("", "f16_") for name in ("fwd", "bwd_input", "bwd_lora", "workspace_bytes")), ModuloraError)
 
 
 def _ptr(t: Optional[torch.Tensor]) -> Optional[int]:

@@ -260,6 +260,19 @@ struct WeightObject : torch::CustomClassHolder {      // the Python weight, read
         PyGILState_Release(g);
     }
 };
+// A backward call that the library refused before it launched anything: binding.ModuloraError, as Python raises it.
+PyObject *refusal;
+[[noreturn]] void raise_refusal(int status, const char *where) {
+    python_error raised;
+    {
+        pybind11::gil_scoped_acquire gil;
+        PyObject *error = PyObject_CallFunction(refusal, "is", status, where);
+        if (error) PyErr_SetObject(refusal, error);
+        Py_XDECREF(error);
+        raised.persist();
+    }
+    throw std::move(raised);
+}
 struct Refused {};             // the library refused a forward call before it launched anything: Python names the error
 
 struct Layer : torch::autograd::Function<Layer> {
@@ -303,9 +316,9 @@ struct Layer : torch::autograd::Function<Layer> {
                                  (!xa.defined() || (plain(xa) && xa.scalar_type() == at::kFloat && xa.numel() == dy.size(0) * A.size(1)))),
                     "the saved activations are no longer what the forward pass saw");
         int status = product(w, true, dy, A, B, (float)scale, true, dx, t);
-        if (status == MODULORA_OK && factors)
-            status = gradients(f16, x2, dy, A, B, (float)scale, xa, t, dA, dB);
-        TORCH_CHECK(status == MODULORA_OK, "the backward pass of a ModuLoRA layer failed with status ", status);
+        if (status != MODULORA_OK) raise_refusal(status, f16 ? "modulora_f16_bwd_input" : "modulora_bwd_input");
+        if (factors) status = gradients(f16, x2, dy, A, B, (float)scale, xa, t, dA, dB);
+        if (status != MODULORA_OK) raise_refusal(status, f16 ? "modulora_f16_bwd_lora" : "modulora_bwd_lora");
         return {dx.view(shape), dA, dB, Tensor(), Tensor(), Tensor()};
     }
 };
@@ -382,10 +395,14 @@ PyObject *py_unlock(PyObject *, PyObject *args) {
     Py_RETURN_NONE;
     END_HANDLE_TH_ERRORS
 }
-// use(addresses of fwd, bwd_input, bwd_lora, workspace_bytes, and of the four f16 ones)
+// use(addresses of fwd, bwd_input, bwd_lora, workspace_bytes, and of the four f16 ones, ModuloraError)
 PyObject *py_use(PyObject *, PyObject *args) {
     unsigned long long p[8];
-    if (!PyArg_ParseTuple(args, "KKKKKKKK", &p[0], &p[1], &p[2], &p[3], &p[4], &p[5], &p[6], &p[7])) return nullptr;
+    PyObject *error;
+    if (!PyArg_ParseTuple(args, "KKKKKKKKO", &p[0], &p[1], &p[2], &p[3], &p[4], &p[5], &p[6], &p[7], &error)) return nullptr;
+    Py_INCREF(error);
+    Py_XDECREF(refusal);
+    refusal = error;
     for (int f = 0; f < 2; ++f) {
         lib.product[f][0] = reinterpret_cast<fwd_fn>(p[4 * f]);
         lib.product[f][1] = reinterpret_cast<fwd_fn>(p[4 * f + 1]);

@@ -140,6 +140,22 @@ def test_refusals_are_pythons(monkeypatch):
         assert errors[0] == errors[1]
 
 
+@gpu
+@pytest.mark.parametrize("f16", [False, True])
+def test_refused_backward_calls_are_pythons(monkeypatch, f16):
+    """A gradient that is contiguous but eight bytes off: the same class, message and status from the backward pass."""
+    w, X, dY, A, B = _layer(f16)
+    module = ModuLoRALinear(w, r=8, alpha=16.0)
+    odd = torch.zeros(20 * 384 + 4, dtype=dY.dtype, device="cuda")[4:].view(20, 384)
+    errors = []
+    for marshal in (b._marshal, None):
+        with monkeypatch.context() as m, pytest.raises(b.ModuloraError) as e:
+            m.setattr(b, "_marshal", marshal)
+            module(X.detach().requires_grad_(True)).backward(odd)
+        errors.append((type(e.value), str(e.value), e.value.status))
+    assert errors[0] == errors[1]
+
+
 def _step(module, x, dy, inputs):
     y = module(x)
     return (y, *torch.autograd.grad(y, inputs, dy, allow_unused=True))
