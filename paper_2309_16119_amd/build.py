@@ -48,9 +48,20 @@ def _compile(src: str, extra: list[str]) -> str:
     return obj
 
 
-def _build_marshal() -> None:
-    """The module that hands tensors to the library: host code against torch's headers."""
-    torch_dir = os.path.dirname(importlib.util.find_spec("torch").origin)
+def _torch_dir() -> str | None:
+    """Where torch is installed, if its headers and libraries for AMD GPUs are there too."""
+    spec = importlib.util.find_spec("torch")
+    root = os.path.dirname(spec.origin) if spec and spec.origin else None
+    needed = (("include", "c10", "hip", "HIPStream.h"), ("lib", "libc10_hip.so"))
+    return root if root and all(os.path.exists(os.path.join(root, *path)) for path in needed) else None
+
+
+def _build_marshal() -> bool:
+    """The module that hands tensors to the library: host code against torch's headers.  False without them: the
+    library itself needs no torch, and binding.py does its calls without the module."""
+    torch_dir = _torch_dir()
+    if torch_dir is None:
+        return False
     inc = [os.path.join(ROOT, "include"), "/opt/rocm/include", os.path.join(torch_dir, "include"),
            os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"]]
     libs = os.path.join(torch_dir, "lib")
@@ -62,22 +73,27 @@ def _build_marshal() -> None:
     if res.returncode != 0:
         raise RuntimeError("hipcc failed for marshal.cpp:\n%s\n%s" % (res.stdout, res.stderr))
     os.replace(tmp, MARSHAL)
+    return True
 
 
 def build_library(extra_flags: list[str] | None = None, verbose: bool = False) -> str:
-    """Compile every HIP source for gfx950, link the shared library and build the host module.  Always rebuilds."""
+    """Compile every HIP source for gfx950, link the shared library and build the host module (where torch's headers are
+    there; whatever becomes of it, the library is linked).  Always rebuilds."""
     os.makedirs(OBJ, exist_ok=True)
     extra = list(extra_flags or [])
     with ThreadPoolExecutor(max_workers=8) as ex:
         marshal = ex.submit(_build_marshal)
         objs = list(ex.map(lambda s: _compile(s, extra), SOURCES))
-        marshal.result()
     tmp = LIB + ".tmp.%d" % os.getpid()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("link failed:\n%s\n%s" % (res.stdout, res.stderr))
     os.replace(tmp, LIB)
+    if not marshal.result():
+        if os.path.exists(MARSHAL):
+            os.remove(MARSHAL)           # of another torch
+        print("no torch headers for AMD GPUs: built without", os.path.basename(MARSHAL), file=sys.stderr)
     if verbose:
         print("built", LIB)
     return LIB

@@ -1,11 +1,13 @@
 """The calls that csrc/marshal.cpp takes over from Python: the same results bit for bit, the same refusals with
 the same errors, and Python's own way wherever a tensor or a mode is not plain."""
+import types
+
 import numpy as np
 import pytest
 import torch
 
 from paper_2309_16119_amd import binding as b
-from paper_2309_16119_amd import synth
+from paper_2309_16119_amd import build, synth
 from paper_2309_16119_amd.nn import ModuLoRALinear
 
 gpu = pytest.mark.gpu
@@ -13,6 +15,30 @@ gpu = pytest.mark.gpu
 
 def test_the_module_is_built_for_this_torch():
     assert b._marshal is not None
+
+
+@pytest.mark.parametrize("without", ["torch", "headers", "a_good_compile"])
+def test_the_library_builds_without_the_module(monkeypatch, tmp_path, without):
+    """libmodulora.so needs no torch: it is linked whether the module can be built or not, and no module of an earlier
+    build stays behind where it cannot."""
+    monkeypatch.setattr(build, "LIB", str(tmp_path / "lib.so"))
+    monkeypatch.setattr(build, "MARSHAL", str(tmp_path / "_marshal.so"))
+    monkeypatch.setattr(build, "OBJ", str(tmp_path / "obj"))
+    monkeypatch.setattr(build, "SOURCES", ["optim.hip"])
+    (tmp_path / "_marshal.so").write_text("stale")
+    if without == "a_good_compile":
+        def fails():
+            raise RuntimeError("marshal.cpp does not compile")
+        monkeypatch.setattr(build, "_build_marshal", fails)
+        with pytest.raises(RuntimeError, match="marshal.cpp"):
+            build.build_library()
+    else:
+        (tmp_path / "torch").mkdir()
+        spec = None if without == "torch" else types.SimpleNamespace(origin=str(tmp_path / "torch" / "__init__.py"))
+        monkeypatch.setattr(build.importlib.util, "find_spec", lambda name: spec)
+        build.build_library()
+        assert not (tmp_path / "_marshal.so").exists()
+    assert (tmp_path / "lib.so").exists()
 
 
 def test_leaves_what_is_not_on_the_gpu_to_python():
