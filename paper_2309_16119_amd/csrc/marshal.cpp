@@ -400,9 +400,7 @@ PyObject *py_use(PyObject *, PyObject *args) {
     unsigned long long p[8];
     PyObject *error;
     if (!PyArg_ParseTuple(args, "KKKKKKKKO", &p[0], &p[1], &p[2], &p[3], &p[4], &p[5], &p[6], &p[7], &error)) return nullptr;
-    Py_INCREF(error);
-    Py_XDECREF(refusal);
-    refusal = error;
+    if (!refusal) refusal = Py_NewRef(error);      // of the first binding: another copy of the module changes nothing
     for (int f = 0; f < 2; ++f) {
         lib.product[f][0] = reinterpret_cast<fwd_fn>(p[4 * f]);
         lib.product[f][1] = reinterpret_cast<fwd_fn>(p[4 * f + 1]);
