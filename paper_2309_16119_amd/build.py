@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import importlib.util
 import os
+import runpy
 import subprocess
 import sys
 import sysconfig
@@ -65,9 +66,10 @@ def _build_marshal() -> bool:
     inc = [os.path.join(ROOT, "include"), "/opt/rocm/include", os.path.join(torch_dir, "include"),
            os.path.join(torch_dir, "include", "torch", "csrc", "api", "include"), sysconfig.get_paths()["include"]]
     libs = os.path.join(torch_dir, "lib")
+    version = runpy.run_path(os.path.join(torch_dir, "version.py"))
     tmp = MARSHAL + ".tmp.%d" % os.getpid()
     cmd = [_hipcc(), "-x", "c++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-           *("-I" + d for d in inc), os.path.join(CSRC, "marshal.cpp"), "-o", tmp, "-L" + libs, "-ltorch_python", "-ltorch", "-ltorch_cpu",
+           '-DMARSHAL_TORCH="%s %s"' % (version["__version__"], version["git_version"]), *("-I" + d for d in inc), os.path.join(CSRC, "marshal.cpp"), "-o", tmp, "-L" + libs, "-ltorch_python", "-ltorch", "-ltorch_cpu",
            "-lc10", "-lc10_hip"]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:

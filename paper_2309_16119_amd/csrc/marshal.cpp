@@ -425,7 +425,27 @@ PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, method
 
 }  // namespace
 
+// Tensors are read through torch's C++ classes, whose layout is that of one build of torch: no other one loads this
+// module (MARSHAL_TORCH: the version and commit it was compiled for), not even one with the same symbols.
+static bool is_this_torch() {
+    PyObject *module = PyImport_ImportModule("torch.version");
+    PyObject *version = module ? PyObject_GetAttrString(module, "__version__") : nullptr;
+    PyObject *commit = version ? PyObject_GetAttrString(module, "git_version") : nullptr;
+    PyObject *found = commit ? PyUnicode_FromFormat("%S %S", version, commit) : nullptr;
+    const bool same = found && PyUnicode_CompareWithASCIIString(found, MARSHAL_TORCH) == 0;
+    if (!same) {
+        PyErr_Clear();
+        PyErr_Format(PyExc_ImportError, "compiled for torch %s, not %V", MARSHAL_TORCH, found, "this one");
+    }
+    Py_XDECREF(found);
+    Py_XDECREF(commit);
+    Py_XDECREF(version);
+    Py_XDECREF(module);
+    return same;
+}
+
 PyMODINIT_FUNC PyInit__marshal() {
+    if (!is_this_torch()) return nullptr;
     const char *attr[8] = {"d_in", "d_out", "bits", "group_size", "qweight", "scales", "zeros", "bias"};
     for (int i = 0; i < 8; ++i)
         if (!(names[i] = PyUnicode_InternFromString(attr[i]))) return nullptr;

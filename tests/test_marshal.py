@@ -1,6 +1,8 @@
 """The calls that csrc/marshal.cpp takes over from Python: the same results bit for bit, the same refusals with
 the same errors, and Python's own way wherever a tensor or a mode is not plain."""
 import importlib.util
+import subprocess
+import sys
 import types
 
 import numpy as np
@@ -16,6 +18,17 @@ gpu = pytest.mark.gpu
 
 def test_the_module_is_built_for_this_torch():
     assert b._marshal is not None
+
+
+@pytest.mark.parametrize("attribute", ["__version__", "git_version"])
+def test_the_module_does_not_load_into_another_torch(attribute):
+    """Another build of torch may have the same symbols and other class layouts: the import fails, and the binding does
+    every call in Python."""
+    code = ("import torch, torch.version; torch.version.%s = 'another'\n"
+            "from paper_2309_16119_amd import binding as b; assert b._marshal is None\n"
+            "import paper_2309_16119_amd._marshal") % attribute
+    res = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, cwd=build.ROOT)
+    assert res.returncode != 0 and "ImportError: compiled for torch" in res.stderr, res.stderr[-500:]
 
 
 @pytest.mark.parametrize("without", ["torch", "headers", "a_good_compile"])
