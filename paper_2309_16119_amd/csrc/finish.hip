@@ -11,6 +11,26 @@
 
 namespace mlr {
 
+// Bias, adapter term (l; already in y where ADDED) and rounding of eight adjacent outputs.
+template <bool BWD, bool F16, bool ADDED = false>
+__device__ __forceinline__ void finish_store(const FinishArgs &d, int m, int col, float (&y)[8], const float (&l)[8]) {
+    if (F16 && !BWD && d.bias16 != nullptr) {               // the frozen layer's bias: forward only
+        const uint4 bw = *reinterpret_cast<const uint4 *>(d.bias16 + col);
+        const uint32_t w4[4] = {bw.x, bw.y, bw.z, bw.w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            y[2 * q] += half_bits_to_float((uint16_t)(w4[q] & 0xFFFFu));
+            y[2 * q + 1] += half_bits_to_float((uint16_t)(w4[q] >> 16));
+        }
+    }
+    if (!ADDED) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) y[c] = __builtin_fmaf(d.lora_scale, l[c], y[c]);
+    }
+    const uint4 o = make_uint4(pack_pair<F16>(y[0], y[1]), pack_pair<F16>(y[2], y[3]), pack_pair<F16>(y[4], y[5]), pack_pair<F16>(y[6], y[7]));
+    *reinterpret_cast<uint4 *>(d.out + (size_t)m * d.Cout + col) = o;
+}
+
 // R: columns of rank that there is room for (0, 8, 16, 32, 64).  ROWS x COLS outputs, eight of a row per thread, in SG
 // groups of threads that share the slices and the rank and meet in LDS.
 // DEEP: everything in flight at once, at two waves a SIMD.
@@ -204,21 +224,92 @@ __global__ __launch_bounds__(256, DEEP ? 2 : (R <= 16 ? 6 : 4)) void finish_kern
         }
     }
     if (!mine) return;
-    if (F16 && !BWD && d.bias16 != nullptr) {               // the frozen layer's bias: forward only
-        const uint4 bw = *reinterpret_cast<const uint4 *>(d.bias16 + col);
-        const uint32_t w4[4] = {bw.x, bw.y, bw.z, bw.w};
+    finish_store<BWD, F16, (SG > 1)>(d, m, col, y, l);
+}
+
+// The same for a rank of 1 to 8 where many workgroups fill the chip: 32 rows x 64 columns, eight of a row per thread, one element of
+// the projection and two of the factor's tile per thread, so that registers leave eight waves a SIMD and the first
+// slices, the factor and eight parts are all on their way at once.  Bound by that trip and the slices' bytes.
+// us in finish_kernel (R = 8) / here, forward and backward: 512 x 4096, r = 8 6.1 / 5.6 and 6.0 / 5.6, binary16 6.2 / 5.7 and
+// 5.9 / 5.5; 200 x 8192 5.4 / 5.0 and 5.4 / 5.0; 1000 x 4096, r = 5 7.2 / 5.9 and 8.3 / 6.0; 1024 x 6656, r = 8 13.7 /
+// 13.7 and 14.4 / 13.6.
+template <bool BWD, bool F16>
+__global__ __launch_bounds__(256) void finish_low_rank_kernel(FinishArgs d) {
+    constexpr int R = 8, PARTS = 8, SB = 4, FS = BWD ? 68 : 64;      // 68: a column's r values, written at once, meet different banks
+    __shared__ __attribute__((aligned(16))) float Ps[32 * R], Fs[R * FS];      // [32][r], [r][64]
+    const int tid = threadIdx.x, r = d.r, M = d.M, Cout = d.Cout;
+    const int m0 = blockIdx.y * 32, c0 = blockIdx.x * 64;
+    const int m = m0 + (tid >> 3), cl = (tid & 7) * 8, col = c0 + cl;
+    const int rows = M - m0 < 32 ? M - m0 : 32, cols = Cout - c0 < 64 ? Cout - c0 : 64;
+    const bool mine = m < M && col < Cout;                // Cout is a multiple of 8: all eight or none
+    const float *src = d.slices + (mine ? (size_t)m * Cout + col : (size_t)0);
+    float4 v0[SB], v1[SB];
+    auto load_slices = [&](int q0) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            y[2 * q] += half_bits_to_float((uint16_t)(w4[q] & 0xFFFFu));
-            y[2 * q + 1] += half_bits_to_float((uint16_t)(w4[q] >> 16));
+        for (int u = 0; u < SB; ++u)
+            if (q0 + u < d.split) {
+                v0[u] = *reinterpret_cast<const float4 *>(src + (size_t)(q0 + u) * d.slice_stride);
+                v1[u] = *reinterpret_cast<const float4 *>(src + (size_t)(q0 + u) * d.slice_stride + 4);
+            }
+    };
+    float y[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    auto add_slices = [&](int q0) {
+#pragma unroll
+        for (int u = 0; u < SB; ++u)
+            if (q0 + u < d.split) {
+                y[0] += v0[u].x; y[1] += v0[u].y; y[2] += v0[u].z; y[3] += v0[u].w;
+                y[4] += v1[u].x; y[5] += v1[u].y; y[6] += v1[u].z; y[7] += v1[u].w;
+            }
+    };
+    load_slices(0);
+    float f[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int x = tid + 256 * h;
+        f[h] = 0.f;
+        if (!BWD) {
+            if ((x >> 6) < r && (x & 63) < cols) f[h] = d.F[(size_t)(x >> 6) * Cout + c0 + (x & 63)];
+        } else if (x < cols * r) {                        // one run of floats
+            f[h] = d.F[(size_t)c0 * r + x];
         }
     }
-    if (SG == 1) {
+    const bool has_p = tid < rows * r;
+    const float *psrc = d.ppart + (size_t)m0 * r + (has_p ? tid : 0);
+    float p[PARTS], sum = 0.f;
 #pragma unroll
-        for (int c = 0; c < 8; ++c) y[c] = __builtin_fmaf(d.lora_scale, l[c], y[c]);
+    for (int s = 0; s < PARTS; ++s) p[s] = s < d.parts ? psrc[(size_t)s * d.part_stride] : 0.f;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int x = tid + 256 * h;
+        if (!BWD) {
+            Fs[(x >> 6) * FS + (x & 63)] = f[h];
+        } else if (x < cols * r) {
+            const int c = r > 1 ? (int)__umulhi((uint32_t)x, d.r_magic) : x;
+            Fs[(x - c * r) * FS + c] = f[h];
+        }
     }
-    const uint4 o = make_uint4(pack_pair<F16>(y[0], y[1]), pack_pair<F16>(y[2], y[3]), pack_pair<F16>(y[4], y[5]), pack_pair<F16>(y[6], y[7]));
-    *reinterpret_cast<uint4 *>(d.out + (size_t)m * Cout + col) = o;
+#pragma unroll
+    for (int s = 0; s < PARTS; ++s) sum += p[s];
+#pragma unroll 8
+    for (int s = PARTS; s < d.parts; ++s) sum += psrc[(size_t)s * d.part_stride];
+    if (has_p) {
+        Ps[tid] = sum;
+        if (blockIdx.x == 0 && d.P_out != nullptr) d.P_out[(size_t)m0 * r + tid] = sum;
+    }
+    __syncthreads();
+    add_slices(0);
+    for (int q0 = SB; q0 < d.split; q0 += SB) { load_slices(q0); add_slices(q0); }
+    if (!mine) return;
+    float l[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < r; ++j) {
+        const float pj = Ps[(tid >> 3) * r + j];
+        const float4 a = *reinterpret_cast<const float4 *>(Fs + j * FS + cl), b = *reinterpret_cast<const float4 *>(Fs + j * FS + cl + 4);
+        l[0] = __builtin_fmaf(pj, a.x, l[0]); l[1] = __builtin_fmaf(pj, a.y, l[1]);
+        l[2] = __builtin_fmaf(pj, a.z, l[2]); l[3] = __builtin_fmaf(pj, a.w, l[3]);
+        l[4] = __builtin_fmaf(pj, b.x, l[4]); l[5] = __builtin_fmaf(pj, b.y, l[5]);
+        l[6] = __builtin_fmaf(pj, b.z, l[6]); l[7] = __builtin_fmaf(pj, b.w, l[7]);
+    }
+    finish_store<BWD, F16>(d, m, col, y, l);
 }
 
 namespace {
@@ -227,7 +318,10 @@ hipError_t launch_finish_rows(const char *name, const FinishArgs &d, hipStream_t
     constexpr int COLS = 2048 / ROWS / SG;
     const dim3 grid((d.Cout + COLS - 1) / COLS, (d.M + ROWS - 1) / ROWS);
     if (d.r == 0) launch_kernel(name, finish_kernel<BWD, F16, 0, ROWS, SG, DEEP>, grid, 256, 0, stream, d);
-    else if (d.r <= 8) launch_kernel(name, finish_kernel<BWD, F16, 8, ROWS, SG, DEEP>, grid, 256, 0, stream, d);
+    else if (d.r <= 8) {
+        if constexpr (DEEP) launch_kernel(name, finish_kernel<BWD, F16, 8, ROWS, SG, DEEP>, grid, 256, 0, stream, d);
+        else launch_kernel(name, finish_low_rank_kernel<BWD, F16>, grid, 256, 0, stream, d);      // ROWS is 32, COLS 64
+    }
     else if (d.r <= 16) launch_kernel(name, finish_kernel<BWD, F16, 16, ROWS, SG, DEEP>, grid, 256, 0, stream, d);
     else if (d.r <= 32) launch_kernel(name, finish_kernel<BWD, F16, 32, ROWS, SG, DEEP>, grid, 256, 0, stream, d);
     else launch_kernel(name, finish_kernel<BWD, F16, 64, ROWS, SG, DEEP>, grid, 256, 0, stream, d);
@@ -244,7 +338,7 @@ hipError_t launch_finish_any(const char *name, const FinishArgs &d, bool backwar
 // r = 16 / 64, us with 32, 64 and 128 columns: 4096 wide 5.9, 7.6, 10.5 / 6.8, 8.9, 13.3; 11008 wide 5.0, 5.3, 7.2 / 6.1,
 // 6.6, 9.8; 22016 wide 7.2, 5.1, 5.5 / 9.1, 6.8, 8.9; 40960 wide 9.5, 7.6, 5.7 / 11.6, 10.3, 9.1).
 // More: many workgroups need registers for four to six waves a SIMD more than they need every load in flight
-// (512 x 4096, r = 8: 8.4 us deep, 6.2 not); few wait for their trips (24 x 2048, r = 16: 7.8 us deep, 12.2 not).
+// (512 x 4096, r = 8: 8.4 us deep, 6.2 not, 5.6 in the kernel for low ranks); few wait for their trips (24 x 2048, r = 16: 7.8 us deep, 12.2 not).
 hipError_t launch_finish(const char *name, FinishArgs d, bool backward, bool f16, hipStream_t stream) {
     d.r_magic = d.r > 1 ? (uint32_t)((1ull << 32) / d.r) + 1u : 0u;      // x / r by one multiply-high, x < 2^13, r <= 64
     if (d.M <= 16) {

@@ -112,6 +112,12 @@ def test_against_the_oracle(bits, K, N, M, r, group, conv):
     (4, 4128, 2304, 63, 47, 96),
     (3, 4096, 4096, 700, 64, 128),
     (3, 4096, 4096, 545, 15, 128),
+    # many workgroups and a rank of up to eight: a last row, last columns of eight, a rank that is no multiple of four,
+    # one column of rank with seven slices (forward) and sixteen parts (backward), nine parts
+    (3, 4096, 4104, 545, 8, 128),
+    (4, 4128, 4096, 600, 3, 96),
+    (2, 8192, 8200, 200, 1, 64),
+    (3, 17920, 3336, 330, 5, 128),
 ])
 def test_second_launch_adds_slices_and_adapter(bits, K, N, M, r, group, conv):
     """An adapter term that is most of the output (factors times thirty), so that a part, a slice or a column of
