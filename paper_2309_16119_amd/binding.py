@@ -483,12 +483,10 @@ def modulora_quantize_rtn(W: torch.Tensor, bits: int, group_size: int) -> "QWeig
     assert W.dtype == torch.float32 and W.dim() == 2
     d_out, d_in = W.shape
     W = W.contiguous()
-    # an invalid shape: let the library name the error (it validates on the host before touching
-    # any pointer), instead of sizing allocations by it
-    probe = modulora_qweight(d_in, d_out, bits, group_size, 0, 0, 0)
-    if lib.modulora_workspace_bytes(ctypes.byref(probe), 1, 1) == 0:
-        _check(lib.modulora_quantize_rtn(_ptr(W), d_in, d_out, bits, group_size, 0, 0, 0, _stream()),
-               "modulora_quantize_rtn")
+    # The library names the errors (it validates on the host, the shape before any pointer); nothing is sized by a bit
+    # width or a group that it would refuse.
+    if bits not in (2, 3, 4) or group_size < 32:
+        _check(lib.modulora_quantize_rtn(_ptr(W), d_in, d_out, bits, group_size, 0, 0, 0, _stream()), "modulora_quantize_rtn")
         raise AssertionError("unreachable: invalid shape accepted")
     G = d_in // group_size
     q = torch.empty((d_in * bits // 32, d_out), dtype=torch.int32, device=W.device)

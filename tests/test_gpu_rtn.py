@@ -99,3 +99,18 @@ def test_one_pass_kernel_at_tile_edges_and_ties(bits, K, N, group):
     assert np.array_equal(qw.scales.cpu().numpy().view(np.uint16), s_ref)
     assert np.array_equal(qw.zeros.cpu().numpy(), z_ref)
     assert np.array_equal(qw.qweight.cpu().numpy().view(np.uint32), q_ref)
+
+
+@pytest.mark.parametrize("d_out,d_in,bits,group,status", [
+    (64, 256, 5, 64, 3), (64, 256, 0, 64, 3), (64, 256, 4, 0, 4), (64, 256, 4, -32, 4), (64, 256, 4, 48, 4), (64, 256, 4, 512, 4),
+    (64, 250, 4, 32, 2), (12, 256, 4, 64, 2), (0, 256, 4, 64, 2), (64, 0, 4, 64, 2),
+])
+def test_refused_shapes(monkeypatch, d_out, d_in, bits, group, status):
+    """The library's own status, without a size query ahead of the call."""
+    class Library:
+        modulora_quantize_rtn, modulora_status_string = b.lib.modulora_quantize_rtn, b.lib.modulora_status_string
+    monkeypatch.setattr(b, "lib", Library)
+    with pytest.raises(b.ModuloraError) as e:
+        b.modulora_quantize_rtn(torch.zeros((d_out, d_in), device="cuda"), bits, group)
+    assert e.value.status == status
+    b.modulora_quantize_rtn(torch.zeros((64, 256), device="cuda"), 4, 64)
