@@ -23,16 +23,14 @@ namespace mlr {
 // NaN of inf - inf or inf * 0.
 __device__ __forceinline__ uint16_t ext_part(float v, int segment, int segments, bool weight_side) {
     const int part = ((segments == 3 ? (weight_side ? 0x010 : 0x100) : weight_side ? 0x021010 : 0x201100) >> (4 * segment)) & 15;
+    const uint32_t bits = __float_as_uint(v);
+    const bool finite = (bits & 0x7F800000u) != 0x7F800000u;
     uint16_t hi = float_to_bf16_bits(v);
-    if ((hi & 0x7F80u) == 0x7F80u) {
-        const uint32_t bits = __float_as_uint(v);
-        if ((bits & 0x7F800000u) == 0x7F800000u) return segment ? (uint16_t)0 : hi;
-        hi = (uint16_t)(bits >> 16);             // finite, and rounded past the largest bfloat16
-    }
-    if (part == 0) return hi;
+    if (finite && (hi & 0x7FFFu) == 0x7F80u) hi = (uint16_t)(bits >> 16);      // rounded past the largest bfloat16
     const float r1 = v - bf16_bits_to_float(hi);
-    const uint16_t mid = float_to_bf16_bits(r1);
-    return part == 1 ? mid : float_to_bf16_bits(r1 - bf16_bits_to_float(mid));
+    const uint16_t mid = float_to_bf16_bits(r1), lo = float_to_bf16_bits(r1 - bf16_bits_to_float(mid));
+    const uint16_t value = part == 0 ? hi : part == 1 ? mid : lo;
+    return finite || segment == 0 ? value : (uint16_t)0;
 }
 
 // ---------------------------------------------------------------------------
