@@ -602,6 +602,7 @@ bool single_wins(const LayerView &w, int M, int r, bool f16) {
 // 15.5 / 8; on the other side 512 x 4096, 300 tokens 14.4 / 20, 1024 x 2048 backward, 8 tokens 8.3 / 9.9).
 bool single_beats(int K, int N, int M, int r, bool backward, bool f16, double us) {
     if ((backward ? N : K) > 2304 || (size_t)K * N >= ((size_t)1 << 23)) return false;
+    if (M > 32 * 65535) return false;      // row blocks are the grid's second dimension, which ends there
     if (backward) return 1.1 * single_bwd_us(K, N, M, r, f16) < us;
     LayerView w{};
     w.K = K; w.N = N;

@@ -234,3 +234,15 @@ def test_binding_without_the_private_torch_functions(monkeypatch):
     monkeypatch.setattr(again, "_current_device", lambda: 3)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda index: types.SimpleNamespace(cuda_stream=4096 + index))
     assert again._stream() == 4099 and again._raw_stream(1) == 4097
+
+
+def test_one_launch_route_ends_where_the_grid_does():
+    """single.hip counts row blocks of 32 in the grid's second dimension (at most 65535): beyond it the tile kernels,
+    whose grids have one dimension, take the call.  (Layers that the one launch wins at any number of tokens.)"""
+    route = b.lib._ZN3mlr13product_routeEiiiibb
+    route.restype, route.argtypes = ctypes.c_int, [ctypes.c_int] * 4 + [ctypes.c_bool] * 2
+    TILES, SINGLE = 0, 3
+    for K, N, r in ((2304, 16, 8), (2048, 64, 64), (2304, 48, 64)):
+        assert route(K, N, 32 * 65535, r, False, False) == SINGLE
+        for M in (32 * 65535 + 1, 1 << 22):
+            assert route(K, N, M, r, False, False) == TILES
