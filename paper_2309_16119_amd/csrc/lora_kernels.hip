@@ -380,7 +380,11 @@ static hipError_t launch_down_rg(const DownArgs &a, const DownPlan &plan, hipStr
     const int w_blocks = a.w_ext ? (int)(((size_t)a.Cw * (a.RE / 8) + nthreads - 1) / nthreads) : 0;
     const size_t lds = (size_t)(nwaves * RG * ROWT * 256) * sizeof(float);
     const dim3 grid(row_blocks + w_blocks, split);
-    if (a.act_f16) {
+    if constexpr (RG == 2 && ROWT == 4) {
+        // long calls of such a rank go by tiles, but for a bfloat16 forward call with little scratch (lora_down_row_bytes())
+        if (a.act_f16 || !a.f_is_A) return hipErrorInvalidValue;
+        launch_kernel("lora_down", lora_down_kernel<RG, ROWT, true, false>, grid, nthreads, lds, stream, a, row_blocks, split);
+    } else if (a.act_f16) {
         if (a.f_is_A)
             launch_kernel("lora_down", lora_down_kernel<RG, ROWT, true, true>, grid, nthreads, lds, stream, a, row_blocks, split);
         else

@@ -101,3 +101,20 @@ def test_partial_tiles_that_do_not_fit_are_done_without(shape, static, workspace
     if static == workspace:
         assert torch.equal(Y.view(torch.int16), Y_ref.view(torch.int16))
     assert float((Y.float() - Y_ref.float()).abs().max()) <= 2.0 ** -7 * float(Y_ref.float().abs().max())
+
+
+@pytest.mark.parametrize("K,N,M,r", [(6144, 72, 1494, 20), (6144, 72, 1494, 32), (6144, 72, 1882, 9)])
+def test_projection_by_rows_where_its_slices_do_not_fit(K, N, M, r):
+    """3 to 5 MB of projection slices beside 12 and 15 MB of partial tiles: the static entry point projects by rows of the
+    activations instead of by tiles.  Both against float64 (fp32 products and sums), the outputs at the oracle's bar."""
+    L = _layer(3, K, N, M, r, 128, seed=53)
+    D, s = to_device(L), L["lora_scale"]
+    Y, XA = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device="cuda"), torch.full((M, r), float("nan"), device="cuda")
+    b.modulora_fwd_static(D["w"], D["Xd"], D["Ad"], D["Bd"], s, Y, XA)
+    Y_ref, XA_ref = b.modulora_fwd(D["w"], D["Xd"], D["Ad"], D["Bd"], s)
+    X64, A64 = D["Xd"].double(), D["Ad"].double()
+    bound = 2.0 ** -24 * (64 + K ** 0.5) * (X64.abs() @ A64.abs())
+    for got in (XA, XA_ref):
+        assert bool(((got.double() - X64 @ A64).abs() <= bound).all())
+    assert not torch.equal(XA, XA_ref)                       # another order of the sums
+    assert float((Y.float() - Y_ref.float()).abs().max()) <= 2.0 ** -7 * float(Y_ref.float().abs().max())
