@@ -106,6 +106,10 @@ def test_against_the_oracle(bits, K, N, M, r, group, conv):
     (2, 768, 16512, 5, 17, 64),
     (4, 512, 32896, 3, 33, 128),
     (3, 4096, 4096, 29, 16, 128),
+    # sixteen tokens, which the one-launch kernel leaves to two launches: 32 columns a workgroup, 64 forward, 64 backward
+    (4, 512, 640, 16, 9, 128),
+    (2, 768, 16512, 16, 17, 64),
+    (3, 16640, 512, 16, 17, 128),
     # and of 32 rows behind the direct kernel, deep and not: one row past a tile, a rank of 1, 2, 47 and 64
     (3, 4096, 2056, 33, 1, 128),
     (2, 4096, 4104, 65, 2, 32),
@@ -138,8 +142,13 @@ def test_second_launch_adds_slices_and_adapter(bits, K, N, M, r, group, conv):
     X, dY, W = act(L["X"]), act(L["dY"]), What.double()
     A, B = torch.from_numpy(L["A"]).cuda() * 30, torch.from_numpy(L["B"]).cuda() * 30
     nan = lambda cols, t: torch.full((M, cols), float("nan"), dtype=t, device="cuda")
+    b.modulora_profile_begin()
     Y, XA = fwd(w, X, A, B, s, nan(N, dtype), nan(r, torch.float32))
     dX, T = bwd(w, dY, A, B, s, nan(K, dtype), nan(r, torch.float32))
+    torch.cuda.synchronize()
+    names = set(b.modulora_profile_end())
+    if M == 16:
+        assert names == {("f16_" if f16 else "") + "stream_" + which for which in ("fwd", "fwd_finish", "bwd", "bwd_finish")}
     XAr, Tr = X.double() @ A.double(), dY.double() @ B.double().t()
     Yr = X.double() @ W.t() + s * XAr @ B.double()
     if f16:

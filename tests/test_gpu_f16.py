@@ -1,6 +1,10 @@
 """GPU parity of the paper-literal variant (float zero point, binary16, bias) against its
 oracle: bit-exact materialization, forward / input-gradient / adapter-gradient outputs at
 the stated bar and at a tight bound derived from the arithmetic."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 import torch
@@ -466,3 +470,35 @@ def test_extended_contraction_is_as_exact_as_fp32(backward):
     boundary = np.abs(np.abs(exact - half.astype(np.float64)) - np.spacing(half).astype(np.float64) / 2)
     got = out.cpu().numpy()
     assert int(((got != half) & (boundary > 2.0 ** -22 * exact)).sum()) == 0
+
+
+PLAIN = """
+import torch
+from paper_2309_16119_amd import binding as b, synth
+for bits, K, N, M, r in ((3, 544, 264, 33, 3), (4, 1024, 2056, 300, 64), (2, 256, 512, 20, 0)):
+    L = synth.make_layer_torch(synth.LayerConfig("t", K, N, bits, 32, M, max(r, 1)), device="cuda", seed=3)
+    bias = torch.randn(N, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1)).half()
+    w = b.QWeightF16(L["qweight"], L["scales"], -2 * L["scales"], bias, K, N, bits, 32)
+    W = b.modulora_f16_dequant(w).double()
+    X, dY, A, B = L["X"].half(), L["dY"].half(), *((L["A"] * 3, L["B"] * 30) if r else (None, None))
+    b.modulora_profile_begin()
+    Y, _ = b.modulora_f16_fwd(w, X, A, B, 2.0)
+    dX, _ = b.modulora_f16_bwd_input(w, dY, A, B, 2.0)
+    torch.cuda.synchronize()
+    assert {k for k in b.modulora_profile_end() if not k.startswith("lora_")} == {"f16_gemm_fwd", "f16_gemm_bwd"}
+    Yr, dXr, mY, mX = X.double() @ W.t() + bias.double(), dY.double() @ W, X.double().abs() @ W.abs().t(), dY.double().abs() @ W.abs()
+    if r:
+        A, B = A.double(), B.double()
+        Yr, dXr = Yr + 2 * (X.double() @ A) @ B, dXr + 2 * (dY.double() @ B.t()) @ A.t()
+        mY, mX = mY + 2 * (X.double().abs() @ A.abs()) @ B.abs(), mX + 2 * (dY.double().abs() @ B.abs().t()) @ A.abs().t()
+    for got, ref, mag, n in ((Y, Yr, mY, K), (dX, dXr, mX, N)):      # one rounding, fp32 sums
+        assert bool(((got.double() - ref).abs() <= 2.0 ** -11 * ref.abs() + 2.0 ** -24 * (64 + n ** 0.5) * mag + 2.0 ** -25).all())
+print("plain kernel agrees")
+"""
+
+
+def test_plain_kernel_for_comparisons():
+    """MODULORA_F16_PLAIN, read once per process: every shape that no streaming kernel takes on the plain kernel."""
+    res = subprocess.run([sys.executable, "-c", PLAIN], capture_output=True, text=True, timeout=100,
+                         cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), env={**os.environ, "MODULORA_F16_PLAIN": "1"})
+    assert res.returncode == 0 and "plain kernel agrees" in res.stdout, res.stdout + res.stderr[-2000:]

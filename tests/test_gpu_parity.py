@@ -222,6 +222,22 @@ def test_streaming_kernels_pick_out_single_weights(bits, group):
         assert np.all(np.abs(f64(dX) - Wf[lo:lo + 16]) <= 2.0 ** -7 * np.abs(Wf[lo:lo + 16]))
 
 
+@pytest.mark.parametrize("bits,group", [(2, 128), (2, 64), (3, 128), (4, 128), (4, 64)])
+def test_streaming_forward_picks_out_single_weights_of_sixteen_rows(bits, group):
+    """Sixteen one-hot rows, which the forward streaming kernel takes (fewer go through the one-launch kernel)."""
+    K, N = 512, 384
+    L = layer(bits, K, N, 1, 0, group, seed=6)
+    D = to_device(L)
+    What = oracle.dequant_bf16(*oracle_args(L))
+    eyeK = torch.eye(K, dtype=torch.bfloat16, device="cuda")
+    for lo in (0, 100, 496):
+        b.modulora_profile_begin()
+        Y, _ = b.modulora_fwd(D["w"], eyeK[lo:lo + 16].contiguous(), None, None, 1.0)
+        torch.cuda.synchronize()
+        assert set(b.modulora_profile_end()) == {"stream_fwd", "stream_fwd_finish"}
+        assert np.array_equal(bits16(Y), What.T[lo:lo + 16])
+
+
 def test_second_streaming_pass_picks_out_the_right_rows():
     """One-hot rows 0 .. 31 through the two-pass form (17 .. 32 tokens): row m of the output is
     column / row hot[m] of the weight, so a second pass that read or wrote at the wrong row offset

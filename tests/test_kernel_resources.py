@@ -94,3 +94,25 @@ def test_producer_consumer_tile_kernel_does_not_spill(tmp_path):
     for name, v in zip(names, spills):
         assert int(v) == 0, "%s spills %s vector registers" % (name, v)
     assert "scratch_load" not in text and "scratch_store" not in text
+
+
+@pytest.mark.skipif(_hipcc() is None, reason="hipcc not available")
+@pytest.mark.parametrize("source,kernel,count", [
+    ("single.hip", "single_", 72 + 18),               # 3 bit widths x conventions x 3 rank groups x (rounded or not x 2 widths; backward)
+    ("finish.hip", "finish", 96 + 4),                 # 4 shapes of up to 5 ranks x directions x conventions, and the low-rank one
+    ("lora_kernels.hip", "lora_down", 21 + 16 + 4),   # by rows, by tiles, second launches
+])
+def test_one_launch_second_launch_and_projection_kernels_do_not_spill(tmp_path, source, kernel, count):
+    """Every load of these is on its way before the first is waited for, up to the register file's size: a spill would
+    wait for it in the middle."""
+    out = tmp_path / "out.s"
+    cmd = [_hipcc(), *build.HIPCC_FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, source), "-o", str(out)]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    text = out.read_text()
+    names = re.findall(r"^\s*\.name:\s+(\S+)", text, flags=re.M)
+    spills = re.findall(r"^\s*\.vgpr_spill_count:\s+(\d+)", text, flags=re.M)
+    assert sum(kernel in n for n in names) == count
+    for name, v in zip(names, spills):
+        assert int(v) == 0, "%s spills %s vector registers" % (name, v)
+    assert "scratch_load" not in text and "scratch_store" not in text
