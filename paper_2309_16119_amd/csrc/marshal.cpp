@@ -41,48 +41,65 @@ struct Library {
     bytes_fn bytes[2];
 } lib{};
 
+struct ReleaseGil {            // as ctypes does around a library call
+    PyThreadState *state = PyGILState_Check() ? PyEval_SaveThread() : nullptr;
+    ~ReleaseGil() { if (state) PyEval_RestoreThread(state); }
+};
+
 // ---- scratch memory: one buffer per (device, stream), see binding._workspace() --------------------
 // A call is several launches that hand data over through the scratch memory of their stream, so a call has to be on its
 // stream whole before another host thread's on the same stream begins: `order` is held from before the library call
-// until it returns.  (Recursive: what Python runs on its own account, a finalizer say, may call in between.)
+// until it has returned.  (Recursive: what Python runs on its own account, a finalizer say, may call in between.)
 struct Scratch {
-    std::recursive_mutex order;
+    std::recursive_mutex order;                             // of `held` too
     std::vector<Tensor> held;
 };
 struct Scratches {
-    std::mutex mutex;                                       // of the map and of every `held`
+    std::mutex mutex;
     std::map<std::pair<int, int64_t>, Scratch> of;          // entries stay where they are
-    Scratch &at(int device, int64_t stream) {
-        std::lock_guard<std::mutex> lock(mutex);
-        return of[{device, stream}];
-    }
 };
 Scratches &scratches() {
     static auto *s = new Scratches;        // never destroyed: the buffers outlive the GPU runtime's own end otherwise
     return *s;
 }
-// A request larger than the held buffer gets a new one; the old ones stay, because a HIP graph captured
-// earlier may still hold their addresses.  Undefined for no bytes.
-Tensor workspace(int device, int64_t stream, size_t nbytes, Scratch **of = nullptr) {
-    if (nbytes == 0) return {};
-    Scratches &all = scratches();
-    Scratch *s;
-    {
-        std::lock_guard<std::mutex> lock(all.mutex);
-        s = &all.of[{device, stream}];
-        if (of) *of = s;
-        if (!s->held.empty() && (size_t)s->held.back().numel() >= nbytes) return s->held.back();
+Scratch &scratch_of(int device, int64_t stream) {
+    static thread_local std::pair<int, int64_t> last_key;
+    static thread_local Scratch *last = nullptr;
+    const std::pair<int, int64_t> key(device, stream);
+    if (!last || last_key != key) {
+        std::lock_guard<std::mutex> lock(scratches().mutex);
+        last = &scratches().of[key];
+        last_key = key;
     }
-    // (the allocator may run Python of its own: not under the lock)
-    Tensor t = at::empty({(int64_t)nbytes}, at::TensorOptions().dtype(at::kByte).device(at::kCUDA, device));
-    std::lock_guard<std::mutex> lock(all.mutex);
-    if (s->held.empty() || s->held.back().numel() < t.numel()) s->held.push_back(t);
-    return t;
+    return *last;
 }
+// A call's turn on its stream: holds `order`, and a buffer of at least `nbytes`.  No thread waits for `order` with
+// Python's lock in hand.  A request larger than the held buffer gets a new one; the old ones stay, because a HIP graph
+// captured earlier may still hold their addresses.
+struct Turn {
+    Scratch *scratch = nullptr;            // none for no bytes
+    Turn(int device, int64_t stream, size_t nbytes) {
+        if (nbytes == 0) return;
+        Scratch *s = &scratch_of(device, stream);
+        take(s);
+        if (s->held.empty() || (size_t)s->held.back().numel() < nbytes) {
+            s->order.unlock();             // (the allocator may run Python of its own)
+            Tensor t = at::empty({(int64_t)nbytes}, at::TensorOptions().dtype(at::kByte).device(at::kCUDA, device));
+            take(s);
+            if (s->held.empty() || s->held.back().numel() < t.numel()) s->held.push_back(t);
+        }
+        scratch = s;
+    }
+    ~Turn() { if (scratch) scratch->order.unlock(); }
+    Turn(const Turn &) = delete;
+    void *memory() const { return scratch ? scratch->held.back().data_ptr() : nullptr; }
 
-struct ReleaseGil {            // as ctypes does around a library call
-    PyThreadState *state = PyGILState_Check() ? PyEval_SaveThread() : nullptr;
-    ~ReleaseGil() { if (state) PyEval_RestoreThread(state); }
+private:
+    static void take(Scratch *s) {
+        if (s->order.try_lock()) return;
+        ReleaseGil release;
+        s->order.lock();
+    }
 };
 
 // ---- the weight, as the attributes of a QWeight / QWeightF16 say at the time of the call -----------------
@@ -149,21 +166,15 @@ bool factors_fit(const Tensor &A, const Tensor &B, int64_t d_in, int64_t d_out) 
            A.size(0) == d_in && B.size(1) == d_out && A.size(1) == B.size(0) && A.size(1) > 0;
 }
 
-struct Where {                 // what a call is launched on, and where its scratch memory lives
+struct Where {                 // what a call is launched on, and its turn there
     void *stream;
-    Tensor ws;
-    Scratch *scratch = nullptr;
-    Where(int device, size_t nbytes) {
-        const auto current = c10::hip::current_device();
-        const auto s = c10::hip::getCurrentHIPStream(current);
-        stream = s.stream();
-        const int64_t key = (int64_t)(intptr_t)(device == current ? s : c10::hip::getCurrentHIPStream(device)).stream();
-        ws = workspace(device, key, nbytes, &scratch);
-    }
-    // taken without Python's lock, which another thread may need to let this one go
-    std::unique_lock<std::recursive_mutex> order() const {
-        return scratch ? std::unique_lock<std::recursive_mutex>(scratch->order) : std::unique_lock<std::recursive_mutex>();
-    }
+    Turn turn;
+    Where(int device, size_t nbytes) : Where(device, nbytes, c10::hip::current_device()) {}
+
+private:
+    Where(int device, size_t nbytes, int current) : Where(device, nbytes, current, c10::hip::getCurrentHIPStream(current)) {}
+    Where(int device, size_t nbytes, int current, c10::hip::HIPStream s)
+        : stream(s.stream()), turn(device, (int64_t)(intptr_t)(device == current ? s : c10::hip::getCurrentHIPStream(device)).stream(), nbytes) {}
 };
 
 // One forward or input-gradient call; returns the library's status.
@@ -177,9 +188,8 @@ int product(const Weight &w, bool backward, const Tensor &act, const Tensor &A, 
     const size_t nbytes = lib.bytes[w.f16](layer, (int32_t)M, (int32_t)r);
     const Where at(act.get_device(), nbytes);
     ReleaseGil release;
-    const auto in_order = at.order();
     return lib.product[w.f16][backward](layer, ptr<uint16_t>(act), (int32_t)M, ptr<float>(A), ptr<float>(B), (int32_t)r, scale, ptr<uint16_t>(out),
-                                        ptr<float>(P), ptr<void>(at.ws), nbytes, at.stream);
+                                        ptr<float>(P), at.turn.memory(), nbytes, at.stream);
 }
 int gradients(bool f16, const Tensor &X, const Tensor &dY, const Tensor &A, const Tensor &B, float scale, const Tensor &XA, const Tensor &T, Tensor &dA, Tensor &dB) {
     const int64_t M = X.size(0), r = A.size(1);
@@ -192,9 +202,8 @@ int gradients(bool f16, const Tensor &X, const Tensor &dY, const Tensor &A, cons
     const size_t nbytes = lib.bytes[f16](f16 ? static_cast<const void *>(&h) : static_cast<const void *>(&q), (int32_t)M, (int32_t)r);
     const Where at(X.get_device(), nbytes);
     ReleaseGil release;
-    const auto in_order = at.order();
     return lib.grad[f16](d_in, d_out, (int32_t)M, (int32_t)r, scale, ptr<uint16_t>(X), ptr<uint16_t>(dY), ptr<float>(A), ptr<float>(B), ptr<float>(XA), ptr<float>(T),
-                         ptr<float>(dA), ptr<float>(dB), 0, ptr<void>(at.ws), nbytes, at.stream);
+                         ptr<float>(dA), ptr<float>(dB), 0, at.turn.memory(), nbytes, at.stream);
 }
 at::ScalarType act_type(bool f16) { return f16 ? at::kHalf : at::kBFloat16; }
 
@@ -355,21 +364,26 @@ PyObject *py_workspace(PyObject *, PyObject *args) {
     long long stream, nbytes;
     if (!PyArg_ParseTuple(args, "iLL", &device, &stream, &nbytes)) return nullptr;
     at::NoGradGuard no_grad;
-    const Tensor t = workspace(device, stream, (size_t)nbytes);
-    if (!t.defined()) Py_RETURN_NONE;
-    return THPVariable_Wrap(t);
+    const Turn turn(device, stream, (size_t)nbytes);
+    if (!turn.scratch) Py_RETURN_NONE;
+    return THPVariable_Wrap(turn.scratch->held.back());
     END_HANDLE_TH_ERRORS
 }
 PyObject *py_forget(PyObject *, PyObject *) {
     HANDLE_TH_ERRORS
     std::vector<Tensor> gone;
+    std::vector<Scratch *> all;
     {
         std::lock_guard<std::mutex> lock(scratches().mutex);
-        for (auto &entry : scratches().of) {
-            gone.insert(gone.end(), entry.second.held.begin(), entry.second.held.end());
-            entry.second.held.clear();
-        }
+        for (auto &entry : scratches().of) all.push_back(&entry.second);
     }
+    Py_BEGIN_ALLOW_THREADS
+    for (Scratch *s : all) {
+        std::lock_guard<std::recursive_mutex> lock(s->order);
+        gone.insert(gone.end(), s->held.begin(), s->held.end());
+        s->held.clear();
+    }
+    Py_END_ALLOW_THREADS
     Py_RETURN_NONE;
     END_HANDLE_TH_ERRORS
 }
@@ -379,7 +393,7 @@ PyObject *py_lock(PyObject *, PyObject *args) {
     int device;
     long long stream;
     if (!PyArg_ParseTuple(args, "iL", &device, &stream)) return nullptr;
-    Scratch &s = scratches().at(device, stream);
+    Scratch &s = scratch_of(device, stream);
     Py_BEGIN_ALLOW_THREADS
     s.order.lock();
     Py_END_ALLOW_THREADS
@@ -391,7 +405,7 @@ PyObject *py_unlock(PyObject *, PyObject *args) {
     int device;
     long long stream;
     if (!PyArg_ParseTuple(args, "iL", &device, &stream)) return nullptr;
-    scratches().at(device, stream).order.unlock();
+    scratch_of(device, stream).order.unlock();
     Py_RETURN_NONE;
     END_HANDLE_TH_ERRORS
 }
