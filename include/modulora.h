@@ -140,7 +140,8 @@ int modulora_fwd(const modulora_qweight *w, const uint16_t *X, int32_t M,
  * tile kernels need about 2 (M + d_out) (3 r + 16) bytes).
  * Results are those of modulora_fwd bit for bit, except where that call adds up more fp32 partial
  * results of a split contraction than the array holds.  Partial tiles of a split last round of
- * 256 x 256 tiles that do not fit are done without (those tiles run whole); where the kernel for up to 1024
+ * 256 x 256 tiles that do not fit are done without (those tiles run whole); a projection of many tokens whose slices do not fit
+ * beside the rest is cut into fewer; where the kernel for up to 1024
  * tokens needs more than the array and the 4 MiB (never while its at most sixteen slices of
  * 4 M d_out bytes fit the array) the tile kernels run instead.  The fp32 sums then have another
  * order; everything stated at modulora_fwd holds.

@@ -145,7 +145,7 @@ __global__ __launch_bounds__(direct::THREADS, 2) void gemm_direct_kernel(DirectD
     };
     // Addresses are a uniform base per word row (kept) plus one 32-bit offset per lane, so that a unit
     // costs a handful of scalar operations: in a loop bound by issue those count too.  (Offsets stay
-    // below 2^32 bytes: direct_wins().)
+    // below 2^32 bytes: product_route().)
     const uint32_t *wrow[BITS];
 #pragma unroll
     for (int q = 0; q < BITS; ++q) wrow[q] = d.w.qweight + (size_t)(BWD ? kb * BITS + q : q) * N;
@@ -479,6 +479,15 @@ double direct_us(const DirectPlan &p, int M, int Cout, int r, bool backward, boo
     return us;
 }
 
+// The margins, by a sweep of 1137 random calls with every kernel forced in turn (256 to 22016 wide, 17 ... 4096 tokens, r = 4 to 64; each
+// estimate within 7 to 10 % rms; the choice is on average 1.3 % slower than the quickest kernel):
+//   - sliced for direct from an estimate a sixth lower (1.2) and a rank of at most 16.  Measured, where the estimates' ratio is under 0.83:
+//     sliced is the quicker one in 44 of 45 calls, by 17 % on average; 0.83 ... 1: in 63 of 120, by 1 %; above: in 10 of 194.  (8704 x 5504
+//     backward, 421 tokens 92 us direct, 58 sliced; 3328 x 1152 backward binary16, 205 tokens 19.1 and 19.2; 9088 x 2432, 241 tokens
+//     27 and 31.)  Larger ranks were left out without being measured: there it is the quicker one in 71 of 81 calls under 1 too, by 17 %.
+//   - sliced for tiles at 1.05: the whole choice is 2.2 % off the quickest at 1 and 1.05, 2.4 at 1.1, 2.7 at 0.9, 3.0 at 1.2.
+//   - the single launch at 1.05 forward, 1.1 backward (single_beats()): 0.8 % off up to 1.05 and 1.9 from 1.1 on; 0.4 to 0.5 % from 1 to 1.1, 0.8 at
+//     0.9 and 1.0 at 1.2.
 Route product_route(int K, int N, int M, int r, bool backward, bool f16) {
     const size_t elements = (size_t)K * N;
     const int C = backward ? N : K, Cout = backward ? K : N;

@@ -200,7 +200,7 @@ inline SlicedPlan sliced_plan(int M, int C, int Cout, int r, bool f16) {
 //   else    : w_ext[c][.] from Wsrc[j * Cw + c] (B, for the forward pass)
 struct DownArgs {
     const uint16_t *act;  // bf16 [M][C] (binary16 when act_f16)
-    bool act_f16;         // the layer in the paper's own storage convention: binary16 activations, P only
+    bool act_f16;         // the layer in the paper's own storage convention: binary16 activations
     int M, C, r;
     const float *Fm;
     bool f_is_A;
