@@ -124,7 +124,8 @@ __device__ __forceinline__ void codes_to_operand(const uint32_t *w, int c, const
 // One element of the projection of binary16 activations over contraction elements [k0, k1) (multiples of 8), in plain
 // fp32.  An infinity has no exact split (inf - inf is NaN) and meets the zero parts of the other operand (inf * 0): where
 // the matrix cores' sum of a row and a factor column is NaN, it is added again by this, which gives what the definition
-// does.  (An infinite activation is no rarity in binary16.)
+// does.  (An infinite activation is no rarity in binary16.)  Only such calls pay: us of the launch without / with every
+// activation NaN 16 x 22016, r = 64 27 / 81; 16 x 8192, r = 8 19.5 / 18.4; 2048 x 2048, 15 tokens, r = 8 in one launch 9 / 49.
 template <bool F_IS_A>
 __device__ __forceinline__ float project_f16_again(const uint16_t *row, const float *F, int C, int r, int j, int k0, int k1) {
     float sum = 0.f;
