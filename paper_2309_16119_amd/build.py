@@ -22,7 +22,7 @@ OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libmodulora.so")
 MARSHAL = os.path.join(PKG, "_marshal.so")
 
-SOURCES = ["api.hip", "dequant_kernel.hip", "gemm_tile.hip", "gemm_big.hip", "gemm_mid.hip", "gemm_direct.hip", "finish.hip", "lora_kernels.hip", "smallm.hip", "single.hip", "optim.hip", "quantize.hip", "f16_path.hip", "bench_hooks.hip"]
+SOURCES = ["api.hip", "dequant_kernel.hip", "gemm_tile.hip", "gemm_big.hip", "gemm_big_192.hip", "gemm_mid.hip", "gemm_direct.hip", "finish.hip", "lora_kernels.hip", "smallm.hip", "single.hip", "optim.hip", "quantize.hip", "f16_path.hip", "bench_hooks.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",

@@ -674,7 +674,7 @@ static TilePick cheapest_pick(int M, int C, int Cout, int extension, bool tuned_
                                       {PICK_T128S, 7, 6, 8, 1.70, 0.372, 4.11, 3.61, 0.300, 0.0, 0.0825}};   // gemm_mid.hip
     const int more = (extension + 63) / 64, steps = (C + 63) / 64 + more;
     const BigPlan bp = big_plan(M, C, Cout);
-    double best = big_plan_us(bp, C, more) * (bp.mt == 128 ? big_128_margin(M) : 1.0);
+    double best = big_plan_us(bp, C, more) * (bp.mt == 128 ? big_128_margin(M) : bp.mt == 192 ? BIG_192_MARGIN : 1.0);
     TilePick pick = PICK_BIG;
     for (const Variant &v : vs) {
         if (tuned_only && v.pick != PICK_T128S) continue;

@@ -76,7 +76,7 @@ hipError_t launch_gemm_big_f16(const GemmArgs &a, hipStream_t stream);
 // 256: the first `full` tiles run whole; each of the `tail` remaining ones is cut into
 // `split` slices of the contraction, one workgroup each, which leave fp32 partial tiles
 // that a second small kernel adds up.  split == 1: nothing is cut.  `mt`: rows of a tile,
-// 256 or (the kernel's second instantiation) 128.
+// 256 or (the kernel's other instantiations) 192, whole tiles only, or 128.
 struct BigPlan {
     int full, tail, split, mt;
     size_t partial_bytes() const { return split > 1 ? (size_t)tail * split * ((size_t)mt * 256u * 4u) : 0; }
@@ -84,7 +84,8 @@ struct BigPlan {
 inline BigPlan big_plan_rows(int M, int C, int Cout, int mt) {
     BigPlan p;
     p.mt = mt;
-    const long tiles = (long)((M + mt - 1) >> (mt == 128 ? 7 : 8)) * ((Cout + 255) >> 8);
+    const long blocks = mt == 192 ? (M + 191) / 192 : (M + mt - 1) >> (mt == 128 ? 7 : 8);
+    const long tiles = blocks * ((Cout + 255) >> 8);
     p.full = (int)(tiles & ~255L);
     p.tail = (int)(tiles - p.full);
     p.split = 1;
@@ -101,14 +102,15 @@ inline BigPlan big_plan_rows(int M, int C, int Cout, int mt) {
 // `step` per 64 elements of the contraction (extension_steps: those of the adapter's segments) and `round`, for the
 // last round `last` and a step that grows with the workgroups in flight, then the fix-up and its partial tiles.
 // Least-squares fit (7 % rms) to 9900 timed launches of both row heights, sliced and whole: 1650 layers of 256 to
-// 22016 wide, 2 ... 4096 tokens, r = 0 to 64, all bit widths, both directions and conventions.
+// 22016 wide, 2 ... 4096 tokens, r = 0 to 64, all bit widths, both directions and conventions.  (192 rows: between the
+// other two, set to their mean error over 37 launches, 13 % rms.)
 inline double big_fixup_us(const BigPlan &p) {
     if (p.split <= 1) return 0.0;
     return p.mt == 128 ? 3.86 + 0.229e-6 * (double)p.partial_bytes() : 3.08 + 0.195e-6 * (double)p.partial_bytes();
 }
 inline double big_plan_us(const BigPlan &p, int C, int extension_steps) {
     struct Cost { double fixed, step, round, last, last_step, last_load; };
-    const Cost k = p.mt == 128 ? Cost{2.46, 0.988, 5.58, 3.34, 0.779, 0.225} : Cost{8.44, 1.60, 7.29, 0.0, 1.04, 0.489};
+    const Cost k = p.mt == 128 ? Cost{2.46, 0.988, 5.58, 3.34, 0.779, 0.225} : p.mt == 192 ? Cost{6.0, 1.31, 6.4, 1.0, 0.93, 0.38} : Cost{8.44, 1.60, 7.29, 0.0, 1.04, 0.489};
     const int steps = (C + 63) / 64;
     double us = k.fixed + (double)(p.full / 256) * (k.step * (steps + extension_steps) + k.round);
     if (p.tail > 0) us += k.last + (k.last_step + k.last_load * (p.tail * p.split / 256.0)) * ((steps + p.split - 1) / p.split + extension_steps);
@@ -125,11 +127,24 @@ inline bool big_half_rows(int M) {
     return (n128 & 1) != 0 && n128 <= 5;
 }
 inline double big_128_margin(int M) { return big_half_rows(M) ? 1.0 : 1.1; }
+// 192 rows where their tiles run whole and are estimated to take less than 1 / 1.02 of the time of 256: their step takes 0.9 of a
+// 256-row one when all compute units are busy (the clock is shared), so they pay where fewer rows are padding or a last round disappears.
+// Measured with 256 / 192 rows, us a call: 11008 x 4096 backward, 777 tokens (five blocks in place of four, and 215
+// busy units in place of 172) 113 / 107; 12032 x 9472 backward, 700 tokens 218 / 199; 4608 x 9600, 925 tokens 101 / 95; 1664 x
+// 11008, 1547 tokens 90 / 84; 8192 x 8192, 1500 tokens 219 / 216; on the other side 4096 x 11008, 2048 tokens 205 / 209, 5248 x
+// 8320, 2530 tokens 228 / 241.  (Cut into slices they are not chosen: 2 % on average either way.)
+constexpr double BIG_192_MARGIN = 1.02;
 inline BigPlan big_plan(int M, int C, int Cout) {
     const BigPlan low = big_plan_rows(M, C, Cout, 128);
     if (big_half_rows(M)) return low;
-    const BigPlan high = big_plan_rows(M, C, Cout, 256);
-    return big_128_margin(M) * big_plan_us(low, C, 0) < big_plan_us(high, C, 0) ? low : high;
+    const BigPlan high = big_plan_rows(M, C, Cout, 256), mid = big_plan_rows(M, C, Cout, 192);
+    BigPlan best = high;
+    double us = big_plan_us(high, C, 0);
+    if (mid.split == 1) {
+        const double whole = BIG_192_MARGIN * big_plan_us(mid, C, 0);
+        if (whole < us) { best = mid; us = whole; }
+    }
+    return big_128_margin(M) * big_plan_us(low, C, 0) < us ? low : best;
 }
 // Scratch for the partial tiles of either direction and either row height: what a caller provides for a number
 // of tokens does not hang on the estimate.

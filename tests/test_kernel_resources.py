@@ -116,3 +116,18 @@ def test_one_launch_second_launch_and_projection_kernels_do_not_spill(tmp_path, 
     for name, v in zip(names, spills):
         assert int(v) == 0, "%s spills %s vector registers" % (name, v)
     assert "scratch_load" not in text and "scratch_store" not in text
+
+
+@pytest.mark.skipif(_hipcc() is None, reason="hipcc not available")
+def test_large_m_tile_kernel_of_192_rows_does_not_spill(tmp_path):
+    out = tmp_path / "gemm_big_192.s"
+    cmd = [_hipcc(), *build.HIPCC_FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, "gemm_big_192.hip"), "-o", str(out)]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    text = out.read_text()
+    names = re.findall(r"^\s*\.name:\s+(\S+)", text, flags=re.M)
+    spills = re.findall(r"^\s*\.vgpr_spill_count:\s+(\d+)", text, flags=re.M)
+    assert sum("gemm_big_kernel" in n for n in names) == 12       # 3 bit widths x forward / backward x bfloat16 / binary16
+    for name, v in zip(names, spills):
+        assert int(v) == 0, "%s spills %s vector registers" % (name, v)
+    assert "scratch_load" not in text and "scratch_store" not in text
