@@ -170,7 +170,7 @@ struct BigSide {
 };
 
 template <int BITS, bool BWD, bool F16, int MT>
-__global__ __launch_bounds__(big::THREADS, 2) void gemm_big_kernel(GemmDev d, BigPlan plan, BigSide side) {
+__global__ __launch_bounds__(big::THREADS, 2) void gemm_big_kernel(GemmDev d, BigPlan plan, BigSide side, Cut slices /* of the full main tiles */) {
     using namespace big;
     using G = Geo<MT>;
     constexpr int WM = G::WM, TI = G::TI, A_BYTES = G::A_BYTES, W_BASE = G::W_BASE, A_CH = G::A_CH;
@@ -201,8 +201,8 @@ __global__ __launch_bounds__(big::THREADS, 2) void gemm_big_kernel(GemmDev d, Bi
     const int n_tiles = n_main + n_ext;
     // this workgroup's share of the full main tiles; the last slice also takes the ragged
     // tile and the adapter extension
-    const int t0 = item.slice < 0 ? 0 : (int)((long)n_full * item.slice / plan.split);
-    const int t1 = item.slice < 0 ? n_full : (int)((long)n_full * (item.slice + 1) / plan.split);
+    const int t0 = item.slice < 0 ? 0 : (int)slices.begin(item.slice);
+    const int t1 = item.slice < 0 ? n_full : (int)slices.begin(item.slice + 1);
     const bool takes_tail = item.slice < 0 || item.slice == plan.split - 1;
     // LDS byte address of the dynamic segment (what M0 wants)
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
@@ -662,7 +662,7 @@ static hipError_t launch_big_mt(const GemmArgs &a, BigPlan plan, hipStream_t str
     const hipError_t e = ensure_lds_limit(reinterpret_cast<const void *>(kern), lds_bytes, configured);
     if (e != hipSuccess) return e;
     const char *name = big_name(MT, BWD, F16, false);
-    launch_kernel(name, kern, blocks, big::THREADS, lds_bytes, stream, d, plan, side);
+    launch_kernel(name, kern, blocks, big::THREADS, lds_bytes, stream, d, plan, side, make_cut((BWD ? a.w.N : a.w.K) / big::RT, plan.split));
     hipError_t err = hipGetLastError();
     if (err != hipSuccess || plan.split <= 1 || sliced) return err;
     if constexpr (big::Geo<MT>::SLICES) {

@@ -56,7 +56,9 @@ struct DirectDev {
     const uint16_t *act;          // [M][C]
     const uint16_t *zeros16;      // F16: binary16 zero points
     int M, C, Cout;
-    int tiles_m, tiles_c, split, nch;
+    int tiles_m, tiles_c, split;
+    FastDiv by_tiles_m, by_tiles_c;
+    Cut slices;                   // of the contraction's chunks of 256
     float *part;                  // [split][M][Cout]
     int proj_parts;               // workgroups that share one row tile's projection over one slice
     float *ppart;                 // [split * proj_parts], part_stride apart: [M][r]
@@ -83,10 +85,11 @@ __global__ __launch_bounds__(direct::THREADS, 2) void gemm_direct_kernel(DirectD
     const int total = d.tiles_m * d.tiles_c * d.split, per_xcd = (total + 7) / 8;
     const int item = (blockIdx.x % 8) * per_xcd + blockIdx.x / 8;
     if (item >= total) return;                 // grid padded to a multiple of 8
-    const int tm = item % d.tiles_m, rest = item / d.tiles_m;
-    const int tc = rest % d.tiles_c, slice = rest / d.tiles_c;
+    uint32_t tm_u, tc_u;
+    const int slice = (int)d.by_tiles_c.div(d.by_tiles_m.div((uint32_t)item, tm_u), tc_u);
+    const int tm = (int)tm_u, tc = (int)tc_u;
     const int m0 = tm * MT, c0 = tc * CT;
-    const int ch0 = (int)((long)d.nch * slice / d.split), ch1 = (int)((long)d.nch * (slice + 1) / d.split);
+    const int ch0 = (int)d.slices.begin(slice), ch1 = (int)d.slices.begin(slice + 1);
     const int ch1_full = ch1 < C / CHUNK ? ch1 : C / CHUNK;        // the last chunk of the contraction may be ragged
     const int n_ch = ch1_full - ch0;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)smem;
@@ -517,7 +520,8 @@ hipError_t launch_direct(const SmallArgs &a, bool backward, hipStream_t stream) 
     d.act = a.act;
     d.zeros16 = a.zeros16;
     d.M = a.M; d.C = C; d.Cout = Cout;
-    d.tiles_m = p.tiles_m; d.tiles_c = p.tiles_c; d.split = p.split; d.nch = p.chunks; d.proj_parts = p.proj_parts;
+    d.tiles_m = p.tiles_m; d.tiles_c = p.tiles_c; d.split = p.split; d.proj_parts = p.proj_parts;
+    d.by_tiles_m = fast_div(p.tiles_m); d.by_tiles_c = fast_div(p.tiles_c); d.slices = make_cut(p.chunks, p.split);
     d.part = static_cast<float *>(a.ws);
     d.ppart = reinterpret_cast<float *>(static_cast<char *>(a.ws) + p.partial_bytes(a.M, Cout));
     d.Fp = backward ? a.B : a.A;

@@ -93,7 +93,7 @@ __device__ __forceinline__ void store_projection(const DownArgs &a, int m, int j
 // are issued together before any of them is used.
 // ACT_F16: the activations are binary16; each operand is split exactly into two bfloat16 ones.
 template <int RG, int ROWT, bool F_IS_A, bool ACT_F16>
-__global__ __launch_bounds__(1024) void lora_down_kernel(DownArgs a, int row_blocks, int split) {
+__global__ __launch_bounds__(1024) void lora_down_kernel(DownArgs a, int row_blocks, int split, Cut cut /* of the steps of 32 over slices and waves */) {
     extern __shared__ __attribute__((aligned(16))) float lds_f[];   // [waves][ROWT][RG][256] partial tiles
     constexpr int UNR = ROWT > 1 ? 2 : (RG == 1 ? 4 : (RG == 2 ? 2 : 1));
     constexpr int ROWS = 16 * ROWT;
@@ -119,9 +119,7 @@ __global__ __launch_bounds__(1024) void lora_down_kernel(DownArgs a, int row_blo
         arow[t] = a.act + (size_t)row * a.C;
     }
     // the contraction is cut over (blockIdx.y, wave)
-    const int steps = (a.C + 31) / 32;
-    const long part = (long)blockIdx.y * nwaves + wave, parts = (long)split * nwaves;
-    const int s_begin = (int)(steps * part / parts), s_end = (int)(steps * (part + 1) / parts);
+    const int s_begin = (int)cut.begin(blockIdx.y * nwaves + wave), s_end = (int)cut.begin(blockIdx.y * nwaves + wave + 1);
 
     f32x4 acc[ROWT][RG];
 #pragma unroll
@@ -219,10 +217,11 @@ __global__ __launch_bounds__(1024) void lora_down_kernel(DownArgs a, int row_blo
 // unit at r <= 16, 1.6 at 32, 2.3 at 64 -- into which the unit's other workgroups fall; workgroups of eight
 // waves were no quicker anywhere.
 constexpr int DOWN_WAVES = 4;
+constexpr int DOWN_CHUNK = 128;      // contraction elements of one chunk
 template <int RG, bool F_IS_A, bool ACT_F16>
-__global__ __launch_bounds__(DOWN_WAVES * 64) void lora_down_tile_kernel(DownArgs a, int row_blocks, int split) {
+__global__ __launch_bounds__(DOWN_WAVES * 64) void lora_down_tile_kernel(DownArgs a, int row_blocks, int split, Cut cut /* of the chunks over the slices */) {
     constexpr int NW = DOWN_WAVES;
-    constexpr int KC = 128, ROW = KC * 2 + 16;           // bytes of an LDS row: 16 lanes of a 16-byte read meet 64 banks
+    constexpr int KC = DOWN_CHUNK, ROW = KC * 2 + 16;           // bytes of an LDS row: 16 lanes of a 16-byte read meet 64 banks
     constexpr int COLS = 16 * RG, PLANE = COLS * ROW;
     constexpr int UNITS = (COLS * (KC / 8) + NW * 64 - 1) / (NW * 64);   // (column, eight elements) units per thread
     __shared__ __attribute__((aligned(16))) unsigned char planes[3 * PLANE];
@@ -237,8 +236,7 @@ __global__ __launch_bounds__(DOWN_WAVES * 64) void lora_down_tile_kernel(DownArg
     const int lane = tid & 63, wave = uniform(tid >> 6), i = lane & 15, cs = lane >> 4;
     const int m0 = (blockIdx.x * NW + wave) * 16;
     const uint16_t *arow = a.act + (size_t)(m0 + i < a.M ? m0 + i : a.M - 1) * C + 8 * cs;
-    const int chunks = (C + KC - 1) / KC;
-    const int ch0 = (int)((long)chunks * blockIdx.y / split), ch1 = (int)((long)chunks * (blockIdx.y + 1) / split);
+    const int ch0 = (int)cut.begin(blockIdx.y), ch1 = (int)cut.begin(blockIdx.y + 1);
 
     struct Chunk {
         uint4 x[KC / 32];
@@ -380,19 +378,20 @@ static hipError_t launch_down_rg(const DownArgs &a, const DownPlan &plan, hipStr
     const int w_blocks = a.w_ext ? (int)(((size_t)a.Cw * (a.RE / 8) + nthreads - 1) / nthreads) : 0;
     const size_t lds = (size_t)(nwaves * RG * ROWT * 256) * sizeof(float);
     const dim3 grid(row_blocks + w_blocks, split);
+    const Cut cut = make_cut((a.C + 31) / 32, split * nwaves);
     if constexpr (RG == 2 && ROWT == 4) {
         // long calls of such a rank go by tiles, but for a bfloat16 forward call with little scratch (lora_down_row_bytes())
         if (a.act_f16 || !a.f_is_A) return hipErrorInvalidValue;
-        launch_kernel("lora_down", lora_down_kernel<RG, ROWT, true, false>, grid, nthreads, lds, stream, a, row_blocks, split);
+        launch_kernel("lora_down", lora_down_kernel<RG, ROWT, true, false>, grid, nthreads, lds, stream, a, row_blocks, split, cut);
     } else if (a.act_f16) {
         if (a.f_is_A)
-            launch_kernel("lora_down", lora_down_kernel<RG, ROWT, true, true>, grid, nthreads, lds, stream, a, row_blocks, split);
+            launch_kernel("lora_down", lora_down_kernel<RG, ROWT, true, true>, grid, nthreads, lds, stream, a, row_blocks, split, cut);
         else
-            launch_kernel("lora_down", lora_down_kernel<RG, ROWT, false, true>, grid, nthreads, lds, stream, a, row_blocks, split);
+            launch_kernel("lora_down", lora_down_kernel<RG, ROWT, false, true>, grid, nthreads, lds, stream, a, row_blocks, split, cut);
     } else if (a.f_is_A) {
-        launch_kernel("lora_down", lora_down_kernel<RG, ROWT, true, false>, grid, nthreads, lds, stream, a, row_blocks, split);
+        launch_kernel("lora_down", lora_down_kernel<RG, ROWT, true, false>, grid, nthreads, lds, stream, a, row_blocks, split, cut);
     } else {
-        launch_kernel("lora_down", lora_down_kernel<RG, ROWT, false, false>, grid, nthreads, lds, stream, a, row_blocks, split);
+        launch_kernel("lora_down", lora_down_kernel<RG, ROWT, false, false>, grid, nthreads, lds, stream, a, row_blocks, split, cut);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || split <= 1) return e;
@@ -405,13 +404,14 @@ static hipError_t launch_down_tiles(const DownArgs &a, const DownPlan &plan, hip
     const int row_blocks = (a.M + 16 * DOWN_WAVES - 1) / (16 * DOWN_WAVES), split = plan.split;
     const int w_blocks = a.w_ext ? (int)(((size_t)a.Cw * (a.RE / 8) + DOWN_WAVES * 64 - 1) / (DOWN_WAVES * 64)) : 0;
     const dim3 grid(row_blocks, split + (w_blocks + row_blocks - 1) / row_blocks);
+    const Cut cut = make_cut((a.C + DOWN_CHUNK - 1) / DOWN_CHUNK, split);
     if (a.act_f16) {
-        if (a.f_is_A) launch_kernel("lora_down", lora_down_tile_kernel<RG, true, true>, grid, DOWN_WAVES * 64, 0, stream, a, row_blocks, split);
-        else launch_kernel("lora_down", lora_down_tile_kernel<RG, false, true>, grid, DOWN_WAVES * 64, 0, stream, a, row_blocks, split);
+        if (a.f_is_A) launch_kernel("lora_down", lora_down_tile_kernel<RG, true, true>, grid, DOWN_WAVES * 64, 0, stream, a, row_blocks, split, cut);
+        else launch_kernel("lora_down", lora_down_tile_kernel<RG, false, true>, grid, DOWN_WAVES * 64, 0, stream, a, row_blocks, split, cut);
     } else if (a.f_is_A) {
-        launch_kernel("lora_down", lora_down_tile_kernel<RG, true, false>, grid, DOWN_WAVES * 64, 0, stream, a, row_blocks, split);
+        launch_kernel("lora_down", lora_down_tile_kernel<RG, true, false>, grid, DOWN_WAVES * 64, 0, stream, a, row_blocks, split, cut);
     } else {
-        launch_kernel("lora_down", lora_down_tile_kernel<RG, false, false>, grid, DOWN_WAVES * 64, 0, stream, a, row_blocks, split);
+        launch_kernel("lora_down", lora_down_tile_kernel<RG, false, false>, grid, DOWN_WAVES * 64, 0, stream, a, row_blocks, split, cut);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || split <= 1) return e;

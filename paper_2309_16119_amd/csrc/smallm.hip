@@ -54,13 +54,11 @@ constexpr int MAX_KSPLIT = 32;         // workgroups that may share a column blo
 // ---------------------------------------------------------------------------------
 template <bool F_IS_A, bool F16, int NWAVES>
 __device__ __forceinline__ void smallm_project(const uint16_t *act, int M, int C, const float *F, int r, int blk,
-                                               int nblk, float *parts, float *red /* LDS, NWAVES * 4 * 256 floats */) {
+                                               const Cut &cut /* of the steps of 32 over all waves */, float *parts, float *red /* LDS, NWAVES * 4 * 256 floats */) {
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int i = lane & 15, cs = lane >> 4;
     const uint16_t *arow = act + (size_t)(i < M ? i : M - 1) * C;
-    const int steps = C / 32;
-    const long part = (long)blk * NWAVES + wave, nparts = (long)nblk * NWAVES;
-    const int s0 = (int)(steps * part / nparts), s1 = (int)(steps * (part + 1) / nparts);
+    const int s0 = (int)cut.begin(blk * NWAVES + wave), s1 = (int)cut.begin(blk * NWAVES + wave + 1);
     const int RG = (r + 15) >> 4;
     f32x4 acc[4];
 #pragma unroll
@@ -125,8 +123,7 @@ __device__ __forceinline__ void smallm_project(const uint16_t *act, int M, int C
         const int prow = 4 * (l >> 4) + v, j = g * 16 + (l & 15);
         if (j >= r) continue;
         if (F16 && __builtin_expect(sum != sum && prow < M, 0)) {
-            const long p0 = (long)blk * NWAVES;
-            sum = project_f16_again<F_IS_A>(act + (size_t)prow * C, F, C, r, j, 32 * (int)(steps * p0 / nparts), 32 * (int)(steps * (p0 + NWAVES) / nparts));
+            sum = project_f16_again<F_IS_A>(act + (size_t)prow * C, F, C, r, j, 32 * (int)cut.begin(blk * NWAVES), 32 * (int)cut.begin((blk + 1) * NWAVES));
         }
         mine[prow * r + j] = sum;
     }
@@ -186,6 +183,8 @@ struct SmallFwdDev {
     const float *B;         // [r][N]
     int M, r, n_proj;       // n_proj: workgroups of the stream kernel that do the projection
     int ksplit;             // workgroups that share one column block (split of the groups along K)
+    Cut slices, proj;       // of the groups over those workgroups, of the projection's steps of 32 over its waves
+    FastDiv by_spg;         // steps per group
     float lora_scale;
     uint16_t *Y;            // [M][N]
     float *XA;              // [M][r] or NULL
@@ -341,23 +340,22 @@ __global__ __launch_bounds__(sm::FWD_THREADS, 4) void smallm_fwd_kernel(SmallFwd
     if ((int)blockIdx.x < d.n_proj) {
         // projection workgroups: partials of XA = X A for the finish kernel; they run beside the
         // streaming ones and are done long before them
-        smallm_project<true, F16, sm::FWD_WAVES>(d.X, d.M, d.w.K, d.A, d.r, blockIdx.x, d.n_proj, d.Upart, reinterpret_cast<float *>(xs));
+        smallm_project<true, F16, sm::FWD_WAVES>(d.X, d.M, d.w.K, d.A, d.r, blockIdx.x, d.proj, d.Upart, reinterpret_cast<float *>(xs));
         return;
     }
     const int bid = blockIdx.x - d.n_proj;
     const int i = lane & 15, j = lane >> 4;
     const int N = d.w.N, group = d.w.group;
-    const int cb = bid / d.ksplit, ks = bid % d.ksplit;   // column block, K slice
+    uint32_t ks;                                    // K slice
+    const int cb = (int)d.slices.parts.div((uint32_t)bid, ks);     // column block
     const int nw = cb * sm::BCOLS + wave * sm::WCOLS;   // first column of the wave
     int n = nw + 4 * i;
     const bool col_ok = n < N;                      // N is a multiple of 8: all four columns or none
     if (n > N - 4) n = N - 4;                       // clamped loads, masked at the store
 
     // this workgroup's run of quantization groups, as a run of steps (KSTEP codes each)
-    const int n_groups = d.w.K / group;
-    const int g_begin = (int)((long)n_groups * ks / d.ksplit);
-    const int g_end = (int)((long)n_groups * (ks + 1) / d.ksplit);
-    const int spg = group / G::KSTEP;               // steps per group
+    const int g_begin = (int)d.slices.begin(ks), g_end = (int)d.slices.begin(ks + 1);
+    const int spg = SPG1 ? 1 : group / G::KSTEP;    // steps per group
     const int s_begin = g_begin * spg, s_end = g_end * spg;
 
     // stages in flight (the binary16 zero points take one more register per stage: one stage fewer,
@@ -378,7 +376,8 @@ __global__ __launch_bounds__(sm::FWD_THREADS, 4) void smallm_fwd_kernel(SmallFwd
         const uint32_t *wbase = d.w.qweight + (size_t)s * (4 * G::WORDS) * N;
 #pragma unroll
         for (int q = 0; q < G::WORDS; ++q) sm::ald(sd.w[q], wbase + (size_t)q * N, w_voff);
-        const int g = s / spg;
+        uint32_t rest;
+        const int g = SPG1 ? s : (int)d.by_spg.div((uint32_t)s, rest);
         sm::ald(sd.sc, d.w.scales + (size_t)g * N, s_voff);
         if (F16) sm::ald(sd.z16, d.zeros16 + (size_t)g * N, s_voff);
         else sm::ald(sd.z, d.w.zeros + (size_t)g * N, z_voff);
@@ -674,6 +673,8 @@ struct SmallBwdDev {
     const float *A;         // [K][r]
     int M, r, n_proj;       // n_proj: workgroups of the stream kernel that do the projection
     int nsplit;             // workgroups that share one 128-column tile (split of N)
+    Cut slices, proj;       // of the steps over those workgroups, of the projection's steps over its waves
+    FastDiv by_group;
     float lora_scale;
     uint16_t *dX;           // [M][K]
     float *T_out;           // dYBt [M][r] or NULL
@@ -783,19 +784,19 @@ __global__ __launch_bounds__(sm::WG_THREADS, 2) void smallm_bwd_kernel(SmallBwdD
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     if ((int)blockIdx.x < d.n_proj) {
         // projection workgroups: partials of dYBt = dY B^T (see the forward kernel)
-        smallm_project<false, F16, sm::WG_WAVES>(d.dY, d.M, d.w.N, d.B, d.r, blockIdx.x, d.n_proj, d.Tpart, reinterpret_cast<float *>(ys));
+        smallm_project<false, F16, sm::WG_WAVES>(d.dY, d.M, d.w.N, d.B, d.r, blockIdx.x, d.proj, d.Tpart, reinterpret_cast<float *>(ys));
         return;
     }
     const int bid = blockIdx.x - d.n_proj;
     const int i = lane & 15, j = lane >> 4, b = i & 3, u = i >> 2;
     const int N = d.w.N, K = d.w.K;
-    const int kb = bid / d.nsplit, ns = bid % d.nsplit;
+    uint32_t ns, in_group;
+    const int kb = (int)d.slices.parts.div((uint32_t)bid, ns);
     const int kt = kb * smb::KT;
-    const int n_steps = N / smb::NSTEP;
-    const int S0 = (int)((long)n_steps * ns / d.nsplit), S1 = (int)((long)n_steps * (ns + 1) / d.nsplit);
+    const int S0 = (int)d.slices.begin(ns), S1 = (int)d.slices.begin(ns + 1);
     // this wave's steps: S0 + wave + 4 t, t = 0 .. nw - 1
     const int nw = S1 - S0 > wave ? (S1 - S0 - wave + sm::WG_WAVES - 1) / sm::WG_WAVES : 0;
-    const int g = kt / d.w.group;        // first of the tile's GPT quantization groups
+    const int g = (int)d.by_group.div((uint32_t)kt, in_group);        // first of the tile's GPT quantization groups
 
     // word rows of this lane, relative to the first word row of the tile
     constexpr int NROWS = BITS == 3 ? 2 : 1;
@@ -1282,6 +1283,8 @@ static hipError_t launch_fwd_pass(const SmallArgs &a, hipStream_t stream) {
     d.r = a.r;
     d.n_proj = n_proj_blocks(K, a.r);
     d.ksplit = ksplit;
+    d.slices = make_cut(K / a.w.group, ksplit);
+    d.proj = make_cut(K / 32, (d.n_proj > 0 ? d.n_proj : 1) * sm::FWD_WAVES);
     d.lora_scale = a.lora_scale;
     d.Y = a.out;
     d.XA = a.P_out;
@@ -1296,6 +1299,7 @@ static hipError_t launch_fwd_pass(const SmallArgs &a, hipStream_t stream) {
     if (lds_bytes < 32 * 1024) lds_bytes = 32 * 1024;      // the projection workgroups' wave reduction
     const int kstep = a.w.bits == 4 ? 32 : (a.w.bits == 2 ? 64 : 128);
     const bool spg1 = a.w.group == kstep;             // one step per quantization group
+    d.by_spg = fast_div(a.w.group / kstep);
     e = a.f16 ? launch_fwd_any<true>(d, a.w.bits, spg1, col_blocks, lds_bytes, stream)
               : launch_fwd_any<false>(d, a.w.bits, spg1, col_blocks, lds_bytes, stream);
     if (e != hipSuccess) return e;
@@ -1368,6 +1372,9 @@ hipError_t launch_smallm_bwd(const SmallArgs &a, hipStream_t stream) {
     d.r = a.r;
     d.n_proj = n_proj_blocks(N, a.r);
     d.nsplit = nsplit;
+    d.slices = make_cut(N / smb::NSTEP, nsplit);
+    d.proj = make_cut(N / 32, (d.n_proj > 0 ? d.n_proj : 1) * sm::WG_WAVES);
+    d.by_group = fast_div(a.w.group);
     d.lora_scale = a.lora_scale;
     d.dX = a.out;
     d.T_out = a.P_out;
