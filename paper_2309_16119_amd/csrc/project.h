@@ -52,6 +52,7 @@ __device__ __forceinline__ void project_rows(const ProjectArgs &d, int row0, int
             }
 #pragma unroll
             for (int q = 0; q < UNR; ++q) {
+                if (st + q >= s1) break;      // wave-uniform
                 uint32_t p[3][4];
                 split3(f[q], p[0], p[1], p[2]);
                 const uint32_t ar[4] = {av[q].x, av[q].y, av[q].z, av[q].w};
