@@ -268,18 +268,32 @@ __global__ __launch_bounds__(direct::THREADS, 2) void gemm_direct_kernel(DirectD
 #pragma unroll
         for (int sl = 0; sl < SLOTS - 1; ++sl) issue_a(ch0 + sl < last_ch ? ch0 + sl : last_ch, sl);
     }
+    // This slice's share of the projection while the first chunks are on their way: 16-row tile
+    // q of the row block and part x of the slice by the workgroup of column block q + 2 RT x.  Where that is one
+    // item of one group of ranks a workgroup, its waves' sums stay in four registers until the results meet in LDS too: no
+    // barrier and no trip through LDS before the first chunk.
+    const ProjectArgs pa{d.act, d.Fp, d.M, d.C, d.r};
+    float *const p_red = reinterpret_cast<float *>(smem + SLOTS * SLOT);
+    f32x4 p_acc = {0.f, 0.f, 0.f, 0.f};
+    float *p_dst = nullptr;                    // where they go; NULL: nothing kept
+    int p_row0 = 0;
     if (d.r > 0) {
-        // this slice's share of the projection while the first chunks are on their way: 16-row tile
-        // q of the row block and part x of the slice by the workgroup of column block q + 2 RT x
         const int k1 = ch1 * CHUNK < C ? ch1 * CHUNK : C;
-        const int steps = (k1 - ch0 * CHUNK + 31) / 32;
-        for (int q = tc; q < 2 * RT * d.proj_parts; q += d.tiles_c) {
+        const int steps = (k1 - ch0 * CHUNK + 31) / 32, items = 2 * RT * d.proj_parts;
+        const bool keep = d.r <= 16 && items <= d.tiles_c;
+        for (int q = tc; q < items; q += d.tiles_c) {
             const int row0 = m0 + 16 * (q % (2 * RT)), x = q / (2 * RT);
             if (row0 >= M) continue;
             const int ks = ch0 * CHUNK + 32 * (steps * x / d.proj_parts);
             const int ke = x + 1 == d.proj_parts ? k1 : ch0 * CHUNK + 32 * (steps * (x + 1) / d.proj_parts);
-            project_rows<!BWD, F16, NWAVES>(ProjectArgs{d.act, d.Fp, d.M, d.C, d.r}, row0, ks, ke, d.ppart + (size_t)(slice * d.proj_parts + x) * d.part_stride,
-                                      reinterpret_cast<float *>(smem + SLOTS * SLOT));
+            float *dst = d.ppart + (size_t)(slice * d.proj_parts + x) * d.part_stride;
+            if (keep) {
+                p_acc = project_wave<!BWD, F16, NWAVES>(pa, row0, ks, ke, 0);
+                p_dst = dst;
+                p_row0 = row0;
+            } else {
+                project_rows<!BWD, F16, NWAVES>(pa, row0, ks, ke, dst, p_red);
+            }
         }
     }
     if (n_ch > 0) {
@@ -404,6 +418,7 @@ __global__ __launch_bounds__(direct::THREADS, 2) void gemm_direct_kernel(DirectD
     // [0, KEEP0) or [KEEP0, RT) and hand the others to their partner
     constexpr int KEEP0 = G::KEEP0;
     float4 *red = reinterpret_cast<float4 *>(smem);
+    if (p_dst != nullptr) project_leave(p_acc, 0, 1, p_red);
 #pragma unroll
     for (int i = 0; i < RT; ++i) {
         if ((i >= KEEP0) == (kg == 1)) continue;
@@ -413,6 +428,7 @@ __global__ __launch_bounds__(direct::THREADS, 2) void gemm_direct_kernel(DirectD
             red[((dstw * KEEP0 + x) * 4 + q) * 64 + lane] = make_float4(acc[i][4 * q], acc[i][4 * q + 1], acc[i][4 * q + 2], acc[i][4 * q + 3]);
     }
     __syncthreads();
+    if (p_dst != nullptr) project_sum<NWAVES>(pa, p_row0, 1, p_dst, p_red);
     const int col = c0 + cg * 32 + (lane & 31);
     float *part = d.part + (size_t)slice * M * Cout + col;
 #pragma unroll
