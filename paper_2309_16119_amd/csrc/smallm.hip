@@ -1120,12 +1120,30 @@ __global__ __launch_bounds__(64) void smallm_bwd_finish_kernel(SmallBwdDev d) {
 }
 
 namespace {
+// Workgroups that do the rank-r projection beside the streaming ones: one per 256 contraction elements,
+// at most 16 (8 tokens, r = 64 backward, us of the product launch with one per 512 / 256: 14720 x 512 6.7 / 5.4,
+// 1024 x 2048 6.9 / 4.9; with at most 32 the second launch takes longer to add them than the first gains)
+constexpr int MAX_PROJ_BLOCKS = 16;
+int n_proj_blocks(int C, int r) {
+    if (r <= 0) return 0;
+    const int n = C / 256;
+    return n < 1 ? 1 : (n > MAX_PROJ_BLOCKS ? MAX_PROJ_BLOCKS : n);
+}
+// How many of `n_proj` have a compute unit of their own beside a forward grid of `wgs`: all, at least half, or none that counts (0).
+// A streaming workgroup that shares its unit with a projecting one sends its first loads 3 us later and ends as much
+// later (stamps, 22016 x 8192 with 256 + 16: ends 13 us after the first start, 16.4 on those units).
+int proj_room(int wgs, int n_proj) {
+    if (wgs > 256 || wgs + n_proj <= 256) return n_proj;
+    const int room = 256 - wgs;
+    return 2 * room >= n_proj ? room : 0;
+}
 // K slices for a product with contraction length Kc (groups of `group`) and Nout outputs:
 // slices of whole groups that fit the LDS, at most MAX_KSPLIT, about one (8-wave) workgroup
 // per compute unit.  The stream is bound by instruction issue, so the time is set by the
 // fullest unit: workgroups per unit x groups per slice; a grid a little over 256 workgroups
-// (43 column blocks x 6 = 258) would leave a few units with two.  Returns 0 when no split exists.
-int pick_ksplit(int Kc, int Nout, int group) {
+// (43 column blocks x 6 = 258) would leave a few units with two, and one that leaves no room for the projecting ones
+// (proj_room()) costs about five steps of 128.  Returns 0 when no split exists.
+int pick_ksplit(int Kc, int Nout, int group, int n_proj) {
     if (group > sm::MAX_RANGE) return 0;
     const int n_groups = Kc / group;
     const int gmax = sm::MAX_RANGE / group;                    // groups per slice that fit the LDS
@@ -1142,7 +1160,7 @@ int pick_ksplit(int Kc, int Nout, int group) {
         const int gps = (n_groups + ks - 1) / ks;              // groups of the longest slice
         if ((long)gps * group > sm::MAX_RANGE) continue;
         const int wgs = col_blocks * ks, per_cu = (wgs + 255) / 256;
-        const double cost = (double)per_cu * gps + (wgs > 256 ? 3.0 : 0.0) + 0.1 * ks;
+        const double cost = (double)per_cu * gps + (wgs > 256 ? 3.0 : 0.0) + 0.1 * ks + (proj_room(wgs, n_proj) < 1 && n_proj > 0 ? 5.0 * 128 / group : 0.0);
         if (cost < best_cost) { best_cost = cost; best = ks; }
     }
     return best;
@@ -1193,22 +1211,13 @@ bool smallm_bwd_supported(const LayerView &w, int M) {
 bool smallm_fwd_supported(const LayerView &w, int M) {
     if (!smallm_rows_ok(w, M)) return false;
     const int kstep = w.bits == 4 ? 32 : (w.bits == 2 ? 64 : 128);
-    return w.group % kstep == 0 && w.K % sm::PREP_K == 0 && pick_ksplit(w.K, w.N, w.group) > 0;
+    return w.group % kstep == 0 && w.K % sm::PREP_K == 0 && pick_ksplit(w.K, w.N, w.group, 0) > 0;
 }
 
 namespace {
 struct SmallWs {
     size_t upart, yacc, total;
 };
-// workgroups that do the rank-r projection beside the streaming ones: one per 256 contraction elements,
-// at most 16 (8 tokens, r = 64 backward, us of the product launch with one per 512 / 256: 14720 x 512 6.7 / 5.4,
-// 1024 x 2048 6.9 / 4.9; with at most 32 the second launch takes longer to add them than the first gains)
-constexpr int MAX_PROJ_BLOCKS = 16;
-int n_proj_blocks(int C, int r) {
-    if (r <= 0) return 0;
-    const int n = C / 256;
-    return n < 1 ? 1 : (n > MAX_PROJ_BLOCKS ? MAX_PROJ_BLOCKS : n);
-}
 SmallWs small_ws(int K, int N, int r) {
     const size_t kmax = (size_t)(K > N ? K : N);
     auto al = [](size_t v) { return (v + 255) & ~(size_t)255; };
@@ -1226,7 +1235,7 @@ SmallWs small_ws(int K, int N, int r) {
 size_t smallm_ws_bytes(int K, int N, int r) { return small_ws(K, N, r).total; }
 
 size_t smallm_fwd_ws_bytes(const LayerView &w, int r) {
-    const int ksplit = pick_ksplit(w.K, w.N, w.group);
+    const int ksplit = pick_ksplit(w.K, w.N, w.group, n_proj_blocks(w.K, r));
     if (ksplit < 1) return 0;
     // the projection partials, then ksplit partial tiles [16][N]
     return small_ws(w.K, w.N, r).yacc + (((size_t)ksplit * 16 * w.N * 4 + 255) & ~(size_t)255);
@@ -1269,7 +1278,7 @@ static hipError_t launch_fwd_pass(const SmallArgs &a, hipStream_t stream) {
     float *Upart = reinterpret_cast<float *>(ws + l.upart);
     float *Yacc = reinterpret_cast<float *>(ws + l.yacc);
     const int col_blocks = (N + sm::BCOLS - 1) / sm::BCOLS;
-    const int ksplit = pick_ksplit(K, N, a.w.group);
+    const int ksplit = pick_ksplit(K, N, a.w.group, n_proj_blocks(K, a.r));
     if (ksplit < 1) return hipErrorInvalidValue;     // callers check smallm_fwd_supported first
 
     hipError_t e;
@@ -1282,6 +1291,8 @@ static hipError_t launch_fwd_pass(const SmallArgs &a, hipStream_t stream) {
     d.M = a.M;
     d.r = a.r;
     d.n_proj = n_proj_blocks(K, a.r);
+    const int own = proj_room(col_blocks * ksplit, d.n_proj);
+    if (own > 0) d.n_proj = own;
     d.ksplit = ksplit;
     d.slices = make_cut(K / a.w.group, ksplit);
     d.proj = make_cut(K / 32, (d.n_proj > 0 ? d.n_proj : 1) * sm::FWD_WAVES);
