@@ -756,8 +756,12 @@ struct BwdGeo {
     static constexpr int W_PIECES = WR * 8, S_PIECE0 = W_PIECES, Z_PIECE0 = S_PIECE0 + 4 * GPT, Y_PIECE0 = Z_PIECE0 + Z_PER_GROUP * GPT;
     static constexpr int N_PIECES = Y_PIECE0 + 64;
     static constexpr int NI = (N_PIECES + 63) / 64;    // loads per stage
-    static constexpr int STAGE_BYTES = NI * 1024;
     static constexpr int DEPTH = 4;                    // stages per wave (even: two register sets alternate)
+    // The idle lanes of a stage's last load take no room in the LDS where three workgroups do not fit a compute unit
+    // otherwise (4 bits: 65536 bytes each, so 50688): the projecting workgroups no longer wait for a streaming one to end
+    // beside a grid of 512.  us of this launch, 16 tokens, r = 8, whole loads / so: 8192 x 22016 27.7 / 26.9,
+    // 4096 x 11008 11.7 / 10.6, 4096 x 4096 7.8 / 7.0.  With 2 and 3 bits both ways are equal.
+    static constexpr int STAGE_BYTES = 3 * sm::WG_WAVES * DEPTH * NI * 1024 > 160 * 1024 ? N_PIECES * 16 : NI * 1024;
     static constexpr int LDS_BYTES = sm::WG_WAVES * DEPTH * STAGE_BYTES;
     static_assert(LDS_BYTES >= smb::RED_BYTES, "the wave reduction re-uses the stages");
     static_assert(DEPTH * NI < 64, "vmcnt is a 6-bit counter");
@@ -1168,7 +1172,7 @@ int pick_ksplit(int Kc, int Nout, int group, int n_proj) {
 // upper bound of pick_ksplit over all group sizes (for the workspace query)
 int ksplit_bound(int, int) { return sm::MAX_KSPLIT; }
 // N slices of the backward product (contraction length N, K outputs in tiles of 128).  Every
-// workgroup of the grid is resident at once (up to 3 per compute unit); the time is set by the
+// workgroup of the grid is resident at once (up to 3 per compute unit; 2 with two groups to a tile); the time is set by the
 // fullest unit, rounds x slice length, so take the split that makes that product smallest, and
 // among equals the smallest one (fewer partial tiles).  A wave keeps at least two steps.
 int pick_nsplit(int N, int K) {

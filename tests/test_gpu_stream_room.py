@@ -1,0 +1,73 @@
+"""Up to 16 tokens, where the workgroups that project share the chip with the streaming ones: forward grids that leave the
+projection no unit (another split), too few (14 and 13 of 16, 9 of 13), enough; backward grids of 512 and more, with 4-bit stages
+that end inside their last load, one and two groups to a tile.  Against the product with the unrounded weight in 64 bits."""
+import pytest
+import torch
+
+from paper_2309_16119_amd import binding as b, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def codes_of(words, K, N, bits):
+    """[N][K] codes of the packed words: 32 codes of a block in `bits` words, two of which a code may straddle."""
+    words = (words.long() & 0xFFFFFFFF).view(K // 32, bits, N)
+    out = []
+    for pos in range(0, 32 * bits, bits):
+        v = words[:, pos // 32] >> (pos % 32)
+        if pos % 32 + bits > 32:
+            v = v | (words[:, pos // 32 + 1] << (32 - pos % 32))
+        out.append(v & ((1 << bits) - 1))
+    return torch.stack(out, dim=1).reshape(K, N).t().double()
+
+
+@pytest.mark.parametrize("conv", ["bf16", "f16"])
+@pytest.mark.parametrize("direction,bits,K,N,M,r,group", [
+    ("fwd", 4, 4096, 4096, 16, 8, 128),     # 24 slices beside 16 projecting workgroups, not 32
+    ("fwd", 3, 4096, 8192, 3, 16, 128),
+    ("fwd", 4, 4096, 5632, 16, 8, 64),      # 242 + 14
+    ("fwd", 2, 3328, 9472, 15, 64, 64),     # 247 + 9 of 13, the last columns of a block missing
+    ("fwd", 4, 5120, 4352, 1, 1, 64),       # 243 + 13
+    ("fwd", 4, 4096, 4096, 16, 0, 128),     # nothing to project: 32 slices
+    ("bwd", 4, 4096, 4096, 16, 8, 128),
+    ("bwd", 4, 4096, 4096, 1, 33, 64),
+    ("bwd", 4, 6656, 2048, 16, 8, 128),
+    ("bwd", 3, 4096, 4096, 9, 8, 128),
+])
+def test_projecting_workgroups(conv, direction, bits, K, N, M, r, group):
+    L = synth.make_layer_torch(synth.LayerConfig("t", K, N, bits, group, M, r), device="cuda", seed=23)
+    f16, fwd = conv == "f16", direction == "fwd"
+    dtype = torch.float16 if f16 else torch.bfloat16
+    scale = L["scales"].double().t().repeat_interleave(group, dim=1)                 # [N][K]
+    W = codes_of(L["qweight"], K, N, bits)
+    if f16:
+        w = b.QWeightF16(L["qweight"], L["scales"], -2 * L["scales"], None, K, N, bits, group)
+        W, call = (W - 2) * scale, b.modulora_f16_fwd if fwd else b.modulora_f16_bwd_input
+    else:
+        w = b.QWeight(L["qweight"], L["scales"], L["zeros"], K, N, bits, group)
+        W, call = (W - L["zeros"].double().t().repeat_interleave(group, dim=1)) * scale, b.modulora_fwd if fwd else b.modulora_bwd_input
+    if fwd:
+        W, scale = W.t(), scale.t()
+    A, B = (L["A"], L["B"]) if r else (None, None)
+    act = (L["X"] if fwd else L["dY"]).to(dtype)
+    out = torch.full((M, N if fwd else K), float("nan"), dtype=dtype, device="cuda")
+    b.modulora_profile_begin()
+    got, P = call(w, act, A, B, 2.0, out)
+    torch.cuda.synchronize()
+    assert ("f16_" if f16 else "") + "stream_" + direction in b.modulora_profile_end()
+    a64 = act.double()
+    ref, mag, terms = a64 @ W, a64.abs() @ W.abs(), (K if fwd else N) ** 0.5
+    if r:
+        down, up = (A.double(), B.double()) if fwd else (B.double().t(), A.double().t())
+        Pr, Pm = a64 @ down, a64.abs() @ down.abs()
+        # fp32 sums of exact products, of as many terms as the contraction has
+        assert bool(((P.double() - Pr).abs() <= 2.0 ** -24 * (64 + terms) * Pm).all())
+        ref, mag = ref + 2 * Pr @ up, mag + 2 * Pm @ up.abs()
+    # one rounding of the output, the fp32 accumulation, and its roundings where the products are of 1024 + code: at
+    # most 16 of a running sum before the 1024 is taken out again
+    half = 2.0 ** -12 if f16 else 2.0 ** -9
+    tol = 2 * half * ref.abs() + 2.0 ** -24 * ((64 + terms) * mag + 16 * 1040 * (a64.abs() @ scale))
+    if not fwd:
+        # each activation times the scale is rounded to 16 bits: six standard deviations of the sum of those errors times codes
+        tol = tol + 6 / 3 ** 0.5 * half * ((1 << bits) - 1) * ((a64 ** 2) @ (scale ** 2)).sqrt()
+    assert bool(((got.double() - ref).abs() <= tol).all()), float(((got.double() - ref).abs() / tol).max())
