@@ -1145,15 +1145,16 @@ int proj_room(int wgs, int n_proj) {
 // slices of whole groups that fit the LDS, at most MAX_KSPLIT, about one (8-wave) workgroup
 // per compute unit.  The stream is bound by instruction issue, so the time is set by the
 // fullest unit: workgroups per unit x groups per slice; a grid a little over 256 workgroups
-// (43 column blocks x 6 = 258) would leave a few units with two, and one that leaves no room for the projecting ones
-// (proj_room()) costs about five steps of 128.  Returns 0 when no split exists.
-int pick_ksplit(int Kc, int Nout, int group, int n_proj) {
+// (43 column blocks x 6 = 258) would leave a few units with two.  Returns 0 when no split exists.
+// `estimate(ks, groups per slice, workgroups)` has the cost.
+template <typename Estimate>
+int least_ksplit(int Kc, int Nout, int group, int most, Estimate estimate) {
     if (group > sm::MAX_RANGE) return 0;
     const int n_groups = Kc / group;
     const int gmax = sm::MAX_RANGE / group;                    // groups per slice that fit the LDS
     const int need = (n_groups + gmax - 1) / gmax;
     const int col_blocks = (Nout + sm::BCOLS - 1) / sm::BCOLS;
-    const int cap = n_groups < sm::MAX_KSPLIT ? n_groups : sm::MAX_KSPLIT;
+    const int cap = n_groups < most ? n_groups : most;
     if (need > cap) return 0;
     int lo = (192 + col_blocks - 1) / col_blocks;
     if (lo < need) lo = need;
@@ -1163,13 +1164,34 @@ int pick_ksplit(int Kc, int Nout, int group, int n_proj) {
     for (int ks = lo; ks <= cap; ++ks) {
         const int gps = (n_groups + ks - 1) / ks;              // groups of the longest slice
         if ((long)gps * group > sm::MAX_RANGE) continue;
-        const int wgs = col_blocks * ks, per_cu = (wgs + 255) / 256;
-        const double cost = (double)per_cu * gps + (wgs > 256 ? 3.0 : 0.0) + 0.1 * ks + (proj_room(wgs, n_proj) < 1 && n_proj > 0 ? 5.0 * 128 / group : 0.0);
+        const double cost = estimate(ks, gps, col_blocks * ks);
         if (cost < best_cost) { best_cost = cost; best = ks; }
     }
     return best;
 }
-// upper bound of pick_ksplit over all group sizes (for the workspace query)
+// The most slices that any call takes: what the scratch has to hold.
+int most_ksplit(int Kc, int Nout, int group) {
+    return least_ksplit(Kc, Nout, group, sm::MAX_KSPLIT, [](int ks, int gps, int wgs) {
+        return (double)((wgs + 255) / 256) * gps + (wgs > 256 ? 3.0 : 0.0) + 0.1 * ks;
+    });
+}
+// ... and those of a call, in microseconds: 0.55 a group of 128 codes, 0.30 one of 64; a slice's partial tile, written and
+// read again (12 ... 16 per 0.1 at 16 tokens), and half a microsecond more behind the 24th; and a projection that shares its units, for
+// as long as its part of the contraction takes.  us a call, 16 tokens, r = 8, most_ksplit() / this (39 shapes by every split):
+// 4096 x 4096 4 bits 14.5 / 13.4 (32 / 24 slices), 8192 x 8192 g = 64 17.7 / 16.9 (16 / 15), 22016 x 8192 3 bits 23.3 / 22.6,
+// 16384 x 8192 g = 64 23.6 / 22.4; the most stay where the slices are short or the tokens few: 4096 x 16384 16.4
+// (7 slices 16.9), 8192 x 8192 2 bits, one token 13.3 (13 slices 13.8).
+int pick_ksplit(int Kc, int Nout, int group, int M, int r) {
+    const int most = most_ksplit(Kc, Nout, group), n_proj = n_proj_blocks(Kc, r);
+    const double step = 0.05 + 0.5 / 128 * group, slice = 0.12 / 16 * M;
+    const double shared = n_proj > 0 ? 0.0007 * (Kc / n_proj) * ((r + 15) / 16) : 0.0;
+    return least_ksplit(Kc, Nout, group, most, [=](int ks, int gps, int wgs) {
+        double us = (wgs + 255) / 256 * gps * step + (wgs > 256 ? 1.65 : 0.0) + slice * ks + (ks > 24 ? 0.5 : 0.0);
+        if (n_proj > 0 && proj_room(wgs, n_proj) < 1) us += shared * (n_proj - (256 - wgs)) / n_proj;
+        return us;
+    });
+}
+// upper bound of most_ksplit over all group sizes (for the workspace query)
 int ksplit_bound(int, int) { return sm::MAX_KSPLIT; }
 // N slices of the backward product (contraction length N, K outputs in tiles of 128).  Every
 // workgroup of the grid is resident at once (up to 3 per compute unit; 2 with two groups to a tile); the time is set by the
@@ -1215,7 +1237,7 @@ bool smallm_bwd_supported(const LayerView &w, int M) {
 bool smallm_fwd_supported(const LayerView &w, int M) {
     if (!smallm_rows_ok(w, M)) return false;
     const int kstep = w.bits == 4 ? 32 : (w.bits == 2 ? 64 : 128);
-    return w.group % kstep == 0 && w.K % sm::PREP_K == 0 && pick_ksplit(w.K, w.N, w.group, 0) > 0;
+    return w.group % kstep == 0 && w.K % sm::PREP_K == 0 && most_ksplit(w.K, w.N, w.group) > 0;
 }
 
 namespace {
@@ -1239,7 +1261,7 @@ SmallWs small_ws(int K, int N, int r) {
 size_t smallm_ws_bytes(int K, int N, int r) { return small_ws(K, N, r).total; }
 
 size_t smallm_fwd_ws_bytes(const LayerView &w, int r) {
-    const int ksplit = pick_ksplit(w.K, w.N, w.group, n_proj_blocks(w.K, r));
+    const int ksplit = most_ksplit(w.K, w.N, w.group);
     if (ksplit < 1) return 0;
     // the projection partials, then ksplit partial tiles [16][N]
     return small_ws(w.K, w.N, r).yacc + (((size_t)ksplit * 16 * w.N * 4 + 255) & ~(size_t)255);
@@ -1282,7 +1304,7 @@ static hipError_t launch_fwd_pass(const SmallArgs &a, hipStream_t stream) {
     float *Upart = reinterpret_cast<float *>(ws + l.upart);
     float *Yacc = reinterpret_cast<float *>(ws + l.yacc);
     const int col_blocks = (N + sm::BCOLS - 1) / sm::BCOLS;
-    const int ksplit = pick_ksplit(K, N, a.w.group, n_proj_blocks(K, a.r));
+    const int ksplit = pick_ksplit(K, N, a.w.group, a.M, a.r);
     if (ksplit < 1) return hipErrorInvalidValue;     // callers check smallm_fwd_supported first
 
     hipError_t e;
