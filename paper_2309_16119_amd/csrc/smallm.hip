@@ -759,7 +759,7 @@ struct BwdGeo {
     static constexpr int DEPTH = 4;                    // stages per wave (even: two register sets alternate)
     // The idle lanes of a stage's last load take no room in the LDS where three workgroups do not fit a compute unit
     // otherwise (4 bits: 65536 bytes each, so 50688): the projecting workgroups no longer wait for a streaming one to end
-    // beside a grid of 512.  us of this launch, 16 tokens, r = 8, whole loads / so: 8192 x 22016 27.7 / 26.9,
+    // beside a grid of 512.  us of this launch, 16 tokens, r = 8, such grids, whole loads / so: 8192 x 22016 27.7 / 26.9,
     // 4096 x 11008 11.7 / 10.6, 4096 x 4096 7.8 / 7.0.  With 2 and 3 bits both ways are equal.
     static constexpr int STAGE_BYTES = 3 * sm::WG_WAVES * DEPTH * NI * 1024 > 160 * 1024 ? N_PIECES * 16 : NI * 1024;
     static constexpr int LDS_BYTES = sm::WG_WAVES * DEPTH * STAGE_BYTES;
@@ -1193,28 +1193,31 @@ int pick_ksplit(int Kc, int Nout, int group, int M, int r) {
 }
 // upper bound of most_ksplit over all group sizes (for the workspace query)
 int ksplit_bound(int, int) { return sm::MAX_KSPLIT; }
-// N slices of the backward product (contraction length N, K outputs in tiles of 128).  Every
-// workgroup of the grid is resident at once (up to 3 per compute unit; 2 with two groups to a tile); the time is set by the
-// fullest unit, rounds x slice length, so take the split that makes that product smallest, and
-// among equals the smallest one (fewer partial tiles).  A wave keeps at least two steps.
-int pick_nsplit(int N, int K) {
-    const int n_steps = N / smb::NSTEP;
-    const int k_blocks = K / smb::KT;
-    if (n_steps < 1 || k_blocks < 1) return 0;
+// N slices of the backward product (contraction length N, K outputs in tiles of 128), for M tokens of one pass.  Up to 3
+// workgroups of the grid share a compute unit (2 with two groups to a tile), and the fullest unit sets the time: a start that
+// grows with its workgroups and their steps, of which two workgroups hide part of each other's waits; besides, the slices' partial
+// tiles, written and read again, and the projecting workgroups that find no place beside the streaming ones, for as long as
+// their part of the contraction takes.  Microseconds of a call, fitted to 46 layers with every split (5 % rms; the pick is 1.1 %
+// slower than the quickest split).  us a call, 16 tokens, r = 8, with at least 512 workgroups, as it was / with this: 4096 x 4096 4
+// bits 11.1 / 10.1 (16 / 7 slices), 8192 x 22016 3 bits 25.6 / 23.9 (8 / 7), 5120 x 13824 4 bits 20.9 / 15.3 (19 / 6), 3072 x
+// 9216 17.4 / 11.4 (32 / 10); none of the 46 lost more than 1 %.  A wave keeps at least two steps.
+int pick_nsplit(const LayerView &w, int M, int r) {
+    const int n_steps = w.N / smb::NSTEP, k_blocks = w.K / smb::KT, n_proj = n_proj_blocks(w.N, r);
     // largest admissible split: two steps per wave, at most 768 workgroups
     int cap = 1;
     while (cap < sm::MAX_KSPLIT && n_steps / (cap + 1) >= 2 * sm::WG_WAVES && (long)k_blocks * (cap + 1) <= 768) ++cap;
-    // two workgroups per compute unit where the shape allows (a second wave per SIMD hides the
-    // first one's waits)
-    int lo = (512 + k_blocks - 1) / k_blocks;
+    int lo = (192 + k_blocks - 1) / k_blocks;
     if (lo > cap) lo = cap;
+    const double start[3] = {7.3, 8.4, 9.5}, step[3] = {0.092, 0.068, 0.0725};
+    const double more = 0.0142 * (w.bits - 3) + (w.group < smb::KT ? 0.038 : 0.0), tokens = M / 16.0;
+    const double shared = n_proj > 0 ? 0.0016 * (w.N / n_proj) * ((r + 15) / 16) * (0.5 + 0.5 * tokens) : 0.0;
     int best = lo;
-    double best_cost = 1e30;
+    double best_us = 1e30;
     for (int ns = lo; ns <= cap; ++ns) {
-        const int per_cu = (k_blocks * ns + 255) / 256;
-        // steps the fullest unit runs, a fixed cost per workgroup, the partial tiles
-        const double cost = (double)per_cu * ((n_steps + ns - 1) / ns) + 8.0 * per_cu + 0.5 * ns;
-        if (cost < best_cost) { best_cost = cost; best = ns; }
+        const int wgs = k_blocks * ns, per_cu = (wgs + 255) / 256, c = per_cu < 3 ? per_cu - 1 : 2, room = 256 * per_cu - wgs;
+        const double us = start[c] + (step[c] + more) * per_cu * ((n_steps + ns - 1) / ns) + 0.105 * tokens * ns +
+                          (room < n_proj ? shared * (n_proj - room) / n_proj : 0.0);
+        if (us < best_us) { best_us = us; best = ns; }
     }
     return best;
 }
@@ -1231,7 +1234,7 @@ bool smallm_bwd_supported(const LayerView &w, int M) {
     if (!smallm_rows_ok(w, M)) return false;
     // a 128-column tile lies inside one quantization group, or covers exactly two
     const bool group_ok = w.group % smb::KT == 0 || w.group == smb::KT / 2;
-    return group_ok && w.K % smb::KT == 0 && w.N % sm::PREP_K == 0 && pick_nsplit(w.N, w.K) > 0;
+    return group_ok && w.K % smb::KT == 0 && w.N % sm::PREP_K == 0 && w.N >= smb::NSTEP && w.K >= smb::KT;
 }
 
 bool smallm_fwd_supported(const LayerView &w, int M) {
@@ -1395,8 +1398,7 @@ hipError_t launch_smallm_bwd(const SmallArgs &a, hipStream_t stream) {
     char *ws = static_cast<char *>(a.ws);
     float *Tpart = reinterpret_cast<float *>(ws + l.upart);
     const int k_blocks = K / smb::KT;
-    const int nsplit = pick_nsplit(N, K);
-    if (nsplit < 1) return hipErrorInvalidValue;     // callers check smallm_bwd_supported first
+    const int nsplit = pick_nsplit(a.w, a.M, a.r);   // callers check smallm_bwd_supported first
 
     hipError_t e;
     SmallBwdDev d;

@@ -1,6 +1,6 @@
 """Up to 16 tokens, where the workgroups that project share the chip with the streaming ones: forward grids that leave the
-projection no unit, too few (14 of 16, 9 of 13, 4 of 6), enough; backward grids of 512 and more, with 4-bit stages
-that end inside their last load, one and two groups to a tile.  Against the product with the unrounded weight in 64 bits."""
+projection no unit, too few (14 of 16, 9 of 13, 4 of 6), enough; backward grids of one to three
+workgroups to a unit, with and without room, whose 4-bit stages end inside their last load, one and two groups to a tile.  Against the product with the unrounded weight in 64 bits."""
 import pytest
 import torch
 
@@ -29,10 +29,14 @@ def codes_of(words, K, N, bits):
     ("fwd", 2, 3328, 9464, 15, 64, 64),     # 247 + 9 of 13, the last columns of a block missing
     ("fwd", 4, 1536, 10496, 16, 1, 64),     # 252 + 4 of 6
     ("fwd", 4, 4096, 4096, 16, 0, 128),     # nothing to project
-    ("bwd", 4, 4096, 4096, 16, 8, 128),
+    ("bwd", 4, 4096, 4096, 16, 8, 128),     # 224 + 16
     ("bwd", 4, 4096, 4096, 1, 33, 64),
-    ("bwd", 4, 6656, 2048, 16, 8, 128),
     ("bwd", 3, 4096, 4096, 9, 8, 128),
+    ("bwd", 4, 5120, 13824, 16, 8, 128),    # 240 + 16
+    ("bwd", 2, 6656, 6656, 16, 16, 64),     # two to a unit
+    ("bwd", 4, 22016, 2048, 5, 8, 128),     # a step over in some slices
+    ("bwd", 4, 22016, 8192, 16, 8, 128),    # 688: three to a unit
+    ("bwd", 3, 256, 4096, 16, 8, 128),      # two column tiles, most slices
 ])
 def test_projecting_workgroups(conv, direction, bits, K, N, M, r, group):
     L = synth.make_layer_torch(synth.LayerConfig("t", K, N, bits, group, M, r), device="cuda", seed=23)
