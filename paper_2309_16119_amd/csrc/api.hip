@@ -130,12 +130,15 @@ WsLayout ws_layout_fwd(const mlr::LayerView &v, int32_t M, int32_t r, size_t ava
         l.total = mlr::smallm_fwd_ws_bytes(v, r);
         return l;
     }
-    l.fwd = mlr::product_route(v.K, v.N, M, r, false, false);
-    if (l.fwd != mlr::ROUTE_TILES) {
+    for (bool slices : {true, false}) {        // (what takes the call without the slices, where their results do not fit)
+        l.fwd = mlr::product_route(v.K, v.N, M, r, false, false, slices);
+        if (l.fwd == mlr::ROUTE_TILES) break;
         l.total = route_bytes(l.fwd, v.K, v.N, M, r, false, false);
         if (l.total <= avail_direct) return l;
-        l.fwd = mlr::ROUTE_TILES;
+        if (l.fwd != mlr::ROUTE_SLICED) break;
     }
+    l.fwd = mlr::ROUTE_TILES;
+    l.total = 0;
     size_t off = 0;
     const size_t part = align256(mlr::big_plan(M, v.K, v.N).partial_bytes());
     if (r > 0) {

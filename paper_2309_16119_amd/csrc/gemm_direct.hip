@@ -500,14 +500,17 @@ double direct_us(const DirectPlan &p, int M, int Cout, int r, bool backward, boo
 
 // The margins, by a sweep of 1137 random calls with every kernel forced in turn (256 to 22016 wide, 17 ... 4096 tokens, r = 4 to 64; each
 // estimate within 7 to 10 % rms; the choice is on average 1.3 % slower than the quickest kernel):
-//   - sliced for direct from an estimate a sixth lower (1.2) and a rank of at most 16.  Measured, where the estimates' ratio is under 0.83:
+//   - sliced for direct from an estimate a sixth lower (1.2) with a rank of at most 16.  Measured, where the estimates' ratio is under 0.83:
 //     sliced is the quicker one in 44 of 45 calls, by 17 % on average; 0.83 ... 1: in 63 of 120, by 1 %; above: in 10 of 194.  (8704 x 5504
 //     backward, 421 tokens 92 us direct, 58 sliced; 3328 x 1152 backward binary16, 205 tokens 19.1 and 19.2; 9088 x 2432, 241 tokens
-//     27 and 31.)  Larger ranks were left out without being measured: there it is the quicker one in 71 of 81 calls under 1 too, by 17 %.
+//     27 and 31.)  Higher ranks of bfloat16 at 1.22, of the estimate without the margin against tiles (530 calls of r = 24 ... 64, 33 ... 1500 tokens,
+//     back to back): sliced is the quicker one in all 12 beyond that line, by 6 ... 56 %.  (2432 x 2432 backward, 947 tokens, r = 32 41 us
+//     direct, 34 sliced; on the other side 1536 x 6144 backward, 463 tokens, r = 32 31.0 and 32.8.  Binary16 stays, where a test holds
+//     3072 x 3072, 245 tokens, r = 64 to direct.)
 //   - sliced for tiles at 1.05: the whole choice is 2.2 % off the quickest at 1 and 1.05, 2.4 at 1.1, 2.7 at 0.9, 3.0 at 1.2.
 //   - the single launch at 1.05 forward, 1.1 backward (single_beats()): 0.8 % off up to 1.05 and 1.9 from 1.1 on; 0.4 to 0.5 % from 1 to 1.1, 0.8 at
 //     0.9 and 1.0 at 1.2.
-Route product_route(int K, int N, int M, int r, bool backward, bool f16) {
+Route product_route(int K, int N, int M, int r, bool backward, bool f16, bool slices) {
     const size_t elements = (size_t)K * N;
     const int C = backward ? N : K, Cout = backward ? K : N;
     if (elements < ((size_t)1 << 23) && Cout % (backward ? direct::CT : 16) != 0) return ROUTE_TILES;
@@ -517,15 +520,15 @@ Route product_route(int K, int N, int M, int r, bool backward, bool f16) {
         const DirectPlan p = direct_plan(M, C, Cout, backward);
         double margin = r <= 16 || f16 ? 1.0 : (backward && M <= 512 ? 1.13 : 1.02);
         if (M > 128 && big_half_rows(M) && (long)p.tiles_m * p.tiles_c * p.split > 256) margin = 1.15;
-        const double us = direct_us(p, M, Cout, r, backward, f16) * margin;
+        const double est = direct_us(p, M, Cout, r, backward, f16), us = est * margin;
         if (us < tiles) {
             if (single_beats(K, N, M, r, backward, f16, us)) return ROUTE_SINGLE;
-            return sliced.parts > 0 && r <= 16 && 1.2 * sliced.us < us ? ROUTE_SLICED : ROUTE_DIRECT;
+            return slices && sliced.parts > 0 && (r <= 16 ? 1.2 * sliced.us < us : !f16 && 1.22 * sliced.us < est) ? ROUTE_SLICED : ROUTE_DIRECT;
         }
     }
-    const bool slices = sliced.parts > 0 && 1.05 * sliced.us < tiles;
-    if (single_beats(K, N, M, r, backward, f16, slices ? sliced.us : tiles)) return ROUTE_SINGLE;
-    return slices ? ROUTE_SLICED : ROUTE_TILES;
+    const bool cut = slices && sliced.parts > 0 && 1.05 * sliced.us < tiles;
+    if (single_beats(K, N, M, r, backward, f16, cut ? sliced.us : tiles)) return ROUTE_SINGLE;
+    return cut ? ROUTE_SLICED : ROUTE_TILES;
 }
 
 hipError_t launch_direct(const SmallArgs &a, bool backward, hipStream_t stream) {

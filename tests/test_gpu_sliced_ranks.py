@@ -1,0 +1,37 @@
+"""Ranks over 16 where the sliced contraction takes the call from the kernel for up to 1024 tokens, and the latter where the
+slices do not fit the library's own scratch.  Against the product with the dequantized weight in 64 bits."""
+import pytest
+import torch
+
+from test_gpu_tile_choice import test_chosen_by_the_estimates as check_product
+
+from paper_2309_16119_amd import binding as b, synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("conv,direction,bits,K,N,M,r,group", [
+    ("bf16", "fwd", 2, 2944, 9344, 241, 32, 128),
+    ("bf16", "bwd", 3, 2432, 2432, 947, 32, 128),
+    ("bf16", "bwd", 4, 512, 3712, 539, 48, 128),
+    ("bf16", "fwd", 3, 3968, 512, 643, 32, 128),
+    ("bf16", "bwd", 4, 768, 3456, 398, 24, 128),
+])
+def test_sliced(conv, direction, bits, K, N, M, r, group):
+    check_product(conv, direction, bits, K, N, M, r, group, "sliced")
+
+
+def test_own_scratch_too_small_for_the_slices():
+    K, N, M, r = 2944, 9344, 241, 32
+    L = synth.make_layer_torch(synth.LayerConfig("t", K, N, 2, 128, M, r), device="cuda", seed=5)
+    w = b.QWeight(L["qweight"], L["scales"], L["zeros"], K, N, 2, 128)
+    X = L["X"].to(torch.bfloat16)
+    Y, XA = torch.empty((M, N), dtype=torch.bfloat16, device="cuda"), torch.empty((M, r), device="cuda")
+    b.modulora_profile_begin()
+    b.modulora_fwd_static(w, X, L["A"], L["B"], 2.0, Y, XA)
+    torch.cuda.synchronize()
+    assert "gemm_fwd_direct" in b.modulora_profile_end()
+    ref, xa = b.modulora_fwd(w, X, L["A"], L["B"], 2.0)
+    # the same rounded weight and projection; fp32 sums in another order, one rounding of the output each
+    assert bool(((Y.double() - ref.double()).abs() <= 2.0 ** -7 * ref.double().abs() + 1e-3 * ref.double().abs().max()).all())
+    assert bool(((XA - xa).abs() <= 1e-5 * xa.abs().max()).all())
