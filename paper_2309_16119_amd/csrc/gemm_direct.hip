@@ -530,6 +530,7 @@ Route product_route(int K, int N, int M, int r, bool backward, bool f16, bool sl
     if (single_beats(K, N, M, r, backward, f16, cut ? sliced.us : tiles)) return ROUTE_SINGLE;
     return cut ? ROUTE_SLICED : ROUTE_TILES;
 }
+Route product_route(int K, int N, int M, int r, bool backward, bool f16) { return product_route(K, N, M, r, backward, f16, true); }
 
 hipError_t launch_direct(const SmallArgs &a, bool backward, hipStream_t stream) {
     const int C = backward ? a.w.N : a.w.K, Cout = backward ? a.w.K : a.w.N;

@@ -534,7 +534,8 @@ inline DirectPlan direct_plan(int M, int C, int Cout, bool backward) {
 // Over 2^32 weights the kernel's 32-bit offsets would overflow.
 double direct_us(const DirectPlan &p, int M, int Cout, int r, bool backward, bool f16);      // estimated time of a call
 enum Route { ROUTE_TILES, ROUTE_DIRECT, ROUTE_SLICED, ROUTE_SINGLE };
-Route product_route(int K, int N, int M, int r, bool backward, bool f16, bool slices = true);     // slices: ROUTE_SLICED may be taken
+Route product_route(int K, int N, int M, int r, bool backward, bool f16);
+Route product_route(int K, int N, int M, int r, bool backward, bool f16, bool slices);     // slices: ROUTE_SLICED may be taken
 hipError_t launch_sliced(const SmallArgs &a, bool backward, hipStream_t stream);      // gemm_big.hip
 double gemm_tile_us(int M, int C, int Cout, int r, bool f16);      // gemm_tile.hip: estimated time of the cheapest tile kernel
 hipError_t launch_direct(const SmallArgs &a, bool backward, hipStream_t stream);
