@@ -266,7 +266,7 @@ __device__ __forceinline__ void dequant_quarter_pairs(const uint32_t *w, int j, 
     for (int i = 0; i < 4; ++i) out[i] = pack_pair_cvt<F16>(v[2 * i], v[2 * i + 1]);
 }
 
-// gemm_big.hip: the 256x256 8-wave variant
+// gemm_big.hip, gemm_big_192.hip: the 8-wave variants of 256, 192 and 128 rows by 256 columns
 hipError_t launch_gemm_big(const GemmArgs &a, hipStream_t stream);
 // gemm_mid.hip: 128x64 tiles for grids of about one tile per CU, producer and consumer waves
 hipError_t launch_gemm_mid(const GemmArgs &a, hipStream_t stream);

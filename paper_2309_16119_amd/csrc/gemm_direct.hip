@@ -17,8 +17,8 @@
 //     barrier falls due once per two 64-element steps.
 //   - the contraction is cut into slices to fill 256 compute units (direct_plan()); the slices' fp32
 //     results are added by the second launch, which also adds the projection's partial sums and applies
-//     the adapter term in fp32.  The projection itself is a side job of the product kernel's first
-//     microsecond, spread over its workgroups.  Two launches in all.
+//     the adapter term in fp32.  The projection itself is a side job ahead of the product kernel's
+//     main loop (3 ... 4 us of 24 at 512 tokens, most of it waits), spread over its workgroups.  Two launches in all.
 // What bounds it (stamps of an instrumented build, 8192 x 8192, 3 bits): a chunk takes 1.35 us forward
 // at 64 rows -- 184 of the step's ~250 instructions per wave and step pair are the dequantization's, and
 // two waves a SIMD issue one 4-cycle operation per 2.1 ns -- and 1.9 us at 128 rows, where its 64 MFMAs

@@ -22,7 +22,7 @@
 //
 // Scheduling.  One VALU instruction costs a SIMD about 4 cycles and one 32x32x16 MFMA 32;
 // they overlap when they come from different waves of the same SIMD, or when a wave issues
-// independent VALU work after an MFMA.  The 256x256 variant lives in gemm_big.hip.  The
+// independent VALU work after an MFMA.  The variants of 256 columns live in gemm_big_kernel.h.  The
 // variants of this file are: a single-buffered one (256x128 with two workgroups per CU
 // filling each other's gaps) and pipelined ones for grids of
 // about one tile per CU, where nothing else hides latency: register stages filled several

@@ -95,7 +95,7 @@ hipError_t launch_gemm_f16(const GemmArgs &a, hipStream_t stream);      // the p
 // gemm_mid.hip, binary16 instantiation: the 128 x 64 producer / consumer kernel for the layer in
 // the paper's own storage convention (GemmArgs::zeros16, bias16).
 hipError_t launch_gemm_mid_f16(const GemmArgs &a, hipStream_t stream);
-// gemm_big.hip, binary16 instantiation: the 256 x 256 kernel (whole tiles only when GemmArgs::partials is NULL).
+// gemm_big.hip, binary16 instantiation: the kernels of 256 columns (whole tiles only when GemmArgs::partials is NULL).
 hipError_t launch_gemm_big_f16(const GemmArgs &a, hipStream_t stream);
 
 // How the 256 x 256 kernel fills 256 compute units when the tile count is not a multiple of

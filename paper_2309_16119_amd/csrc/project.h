@@ -1,4 +1,4 @@
-// The rank-r projection as a side job of a product kernel (gemm_direct.hip, gemm_big.hip).
+// The rank-r projection as a side job of a product kernel (gemm_direct.hip, gemm_big_kernel.h).
 #pragma once
 #include "device_common.h"
 
