@@ -1142,13 +1142,13 @@ int proj_room(int wgs, int n_proj) {
     return 2 * room >= n_proj ? room : 0;
 }
 // K slices for a product with contraction length Kc (groups of `group`) and Nout outputs:
-// slices of whole groups that fit the LDS, at most MAX_KSPLIT, about one (8-wave) workgroup
-// per compute unit.  The stream is bound by instruction issue, so the time is set by the
+// slices of whole groups that fit the LDS, at most MAX_KSPLIT and at least `fill` workgroups where that goes,
+// about one (8-wave) workgroup per compute unit.  The stream is bound by instruction issue, so the time is set by the
 // fullest unit: workgroups per unit x groups per slice; a grid a little over 256 workgroups
 // (43 column blocks x 6 = 258) would leave a few units with two.  Returns 0 when no split exists.
 // `estimate(ks, groups per slice, workgroups)` has the cost.
 template <typename Estimate>
-int least_ksplit(int Kc, int Nout, int group, int most, Estimate estimate) {
+int least_ksplit(int Kc, int Nout, int group, int fill, int most, Estimate estimate) {
     if (group > sm::MAX_RANGE) return 0;
     const int n_groups = Kc / group;
     const int gmax = sm::MAX_RANGE / group;                    // groups per slice that fit the LDS
@@ -1156,7 +1156,7 @@ int least_ksplit(int Kc, int Nout, int group, int most, Estimate estimate) {
     const int col_blocks = (Nout + sm::BCOLS - 1) / sm::BCOLS;
     const int cap = n_groups < most ? n_groups : most;
     if (need > cap) return 0;
-    int lo = (192 + col_blocks - 1) / col_blocks;
+    int lo = (fill + col_blocks - 1) / col_blocks;
     if (lo < need) lo = need;
     if (lo > cap) lo = cap;
     int best = 0;
@@ -1171,21 +1171,21 @@ int least_ksplit(int Kc, int Nout, int group, int most, Estimate estimate) {
 }
 // The most slices that any call takes: what the scratch has to hold.
 int most_ksplit(int Kc, int Nout, int group) {
-    return least_ksplit(Kc, Nout, group, sm::MAX_KSPLIT, [](int ks, int gps, int wgs) {
+    return least_ksplit(Kc, Nout, group, 192, sm::MAX_KSPLIT, [](int ks, int gps, int wgs) {
         return (double)((wgs + 255) / 256) * gps + (wgs > 256 ? 3.0 : 0.0) + 0.1 * ks;
     });
 }
 // ... and those of a call, in microseconds: 0.55 a group of 128 codes, 0.30 one of 64; a slice's partial tile, written and
 // read again (12 ... 16 per 0.1 at 16 tokens), and half a microsecond more behind the 24th; and a projection that shares its units, for
 // as long as its part of the contraction takes.  us a call, 16 tokens, r = 8, most_ksplit() / this (39 shapes by every split):
-// 4096 x 4096 4 bits 14.5 / 13.4 (32 / 24 slices), 8192 x 8192 g = 64 17.7 / 16.9 (16 / 15), 22016 x 8192 3 bits 23.3 / 22.6,
+// 4096 x 4096 4 bits 14.5 / 12.6 (32 / 16 slices; 24 13.4, 11 12.9), 2048 x 4096 g = 64 11.5 (16; 24 12.7), 8192 x 8192 g = 64 17.7 / 16.9 (16 / 15), 22016 x 8192 3 bits 23.3 / 22.6,
 // 16384 x 8192 g = 64 23.6 / 22.4; the most stay where the slices are short or the tokens few: 4096 x 16384 16.4
 // (7 slices 16.9), 8192 x 8192 2 bits, one token 13.3 (13 slices 13.8).
 int pick_ksplit(int Kc, int Nout, int group, int M, int r) {
     const int most = most_ksplit(Kc, Nout, group), n_proj = n_proj_blocks(Kc, r);
     const double step = 0.05 + 0.5 / 128 * group, slice = 0.12 / 16 * M;
     const double shared = n_proj > 0 ? 0.0007 * (Kc / n_proj) * ((r + 15) / 16) : 0.0;
-    return least_ksplit(Kc, Nout, group, most, [=](int ks, int gps, int wgs) {
+    return least_ksplit(Kc, Nout, group, 128, most, [=](int ks, int gps, int wgs) {
         double us = (wgs + 255) / 256 * gps * step + (wgs > 256 ? 1.65 : 0.0) + slice * ks + (ks > 24 ? 0.5 : 0.0);
         if (n_proj > 0 && proj_room(wgs, n_proj) < 1) us += shared * (n_proj - (256 - wgs)) / n_proj;
         return us;
@@ -1200,13 +1200,13 @@ int ksplit_bound(int, int) { return sm::MAX_KSPLIT; }
 // their part of the contraction takes.  Microseconds of a call, fitted to 46 layers with every split (5 % rms; the pick is 1.1 %
 // slower than the quickest split).  us a call, 16 tokens, r = 8, with at least 512 workgroups, as it was / with this: 4096 x 4096 4
 // bits 11.1 / 10.1 (16 / 7 slices), 8192 x 22016 3 bits 25.6 / 23.9 (8 / 7), 5120 x 13824 4 bits 20.9 / 15.3 (19 / 6), 3072 x
-// 9216 17.4 / 11.4 (32 / 10); none of the 46 lost more than 1 %.  A wave keeps at least two steps.
+// 9216 17.4 / 11.4 (32 / 10), 1024 x 4096 9.0 (16; at least 192 workgroups 9.9); none of the 46 lost more than 1 %.  A wave keeps at least two steps.
 int pick_nsplit(const LayerView &w, int M, int r) {
     const int n_steps = w.N / smb::NSTEP, k_blocks = w.K / smb::KT, n_proj = n_proj_blocks(w.N, r);
     // largest admissible split: two steps per wave, at most 768 workgroups
     int cap = 1;
     while (cap < sm::MAX_KSPLIT && n_steps / (cap + 1) >= 2 * sm::WG_WAVES && (long)k_blocks * (cap + 1) <= 768) ++cap;
-    int lo = (192 + k_blocks - 1) / k_blocks;
+    int lo = (128 + k_blocks - 1) / k_blocks;
     if (lo > cap) lo = cap;
     const double start[3] = {7.3, 8.4, 9.5}, step[3] = {0.092, 0.068, 0.0725};
     const double more = 0.0142 * (w.bits - 3) + (w.group < smb::KT ? 0.038 : 0.0), tokens = M / 16.0;

@@ -1,5 +1,5 @@
 """Up to 16 tokens, where the workgroups that project share the chip with the streaming ones: forward grids that leave the
-projection no unit, too few (14 of 16, 9 of 13, 4 of 6), enough; backward grids of one to three
+projection no unit, too few (14 of 16, 9 of 13), enough; backward grids of one to three
 workgroups to a unit, with and without room, whose 4-bit stages end inside their last load, one and two groups to a tile.  Against the product with the unrounded weight in 64 bits."""
 import pytest
 import torch
@@ -23,11 +23,10 @@ def codes_of(words, K, N, bits):
 
 @pytest.mark.parametrize("conv", ["bf16", "f16"])
 @pytest.mark.parametrize("direction,bits,K,N,M,r,group", [
-    ("fwd", 4, 4096, 4096, 16, 8, 128),     # 192 + 16
+    ("fwd", 4, 4096, 4096, 16, 8, 128),     # 128 + 16
     ("fwd", 3, 4096, 8192, 3, 16, 128),     # 256 + 16
     ("fwd", 4, 4096, 5376, 1, 8, 64),       # 242 + 14 of 16
     ("fwd", 2, 3328, 9464, 15, 64, 64),     # 247 + 9 of 13, the last columns of a block missing
-    ("fwd", 4, 1536, 10496, 16, 1, 64),     # 252 + 4 of 6
     ("fwd", 4, 4096, 4096, 16, 0, 128),     # nothing to project
     ("bwd", 4, 4096, 4096, 16, 8, 128),     # 224 + 16
     ("bwd", 4, 4096, 4096, 1, 33, 64),
