@@ -1175,7 +1175,7 @@ int most_ksplit(int Kc, int Nout, int group) {
         return (double)((wgs + 255) / 256) * gps + (wgs > 256 ? 3.0 : 0.0) + 0.1 * ks;
     });
 }
-// ... and those of a call, in microseconds: 0.55 a group of 128 codes, 0.30 one of 64; a slice's partial tile, written and
+// ... and those of a call, in microseconds: 0.60 a group of 128 codes, 0.325 one of 64; a slice's partial tile, written and
 // read again (12 ... 16 per 0.1 at 16 tokens), and half a microsecond more behind the 24th; and a projection that shares its units, for
 // as long as its part of the contraction takes.  us a call, 16 tokens, r = 8, most_ksplit() / this (39 shapes by every split):
 // 4096 x 4096 4 bits 14.5 / 12.6 (32 / 16 slices; 24 13.4, 11 12.9), 2048 x 4096 g = 64 11.5 (16; 24 12.7), 8192 x 8192 g = 64 17.7 / 16.9 (16 / 15), 22016 x 8192 3 bits 23.3 / 22.6,
@@ -1183,7 +1183,7 @@ int most_ksplit(int Kc, int Nout, int group) {
 // (7 slices 16.9), 8192 x 8192 2 bits, one token 13.3 (13 slices 13.8).
 int pick_ksplit(int Kc, int Nout, int group, int M, int r) {
     const int most = most_ksplit(Kc, Nout, group), n_proj = n_proj_blocks(Kc, r);
-    const double step = 0.05 + 0.5 / 128 * group, slice = 0.12 / 16 * M;
+    const double step = 0.05 + 0.55 / 128 * group, slice = 0.12 / 16 * M;
     const double shared = n_proj > 0 ? 0.0007 * (Kc / n_proj) * ((r + 15) / 16) : 0.0;
     return least_ksplit(Kc, Nout, group, 128, most, [=](int ks, int gps, int wgs) {
         double us = (wgs + 255) / 256 * gps * step + (wgs > 256 ? 1.65 : 0.0) + slice * ks + (ks > 24 ? 0.5 : 0.0);
